@@ -62,7 +62,7 @@ struct fst_ctx {
   DevBuf aOutPerm, aOutArc, aOutRec, aOutLut, bOutPerm, bOutArc, bOutRec, bOutLut;
   DevBuf aOutLab, aOutW, bOutLab, bOutW, bOutChain, bInChain;
   DevBuf aInOff, aInPerm, aInArc, aInRec, aInLut, bInOff, bInPerm, bInArc, bInRec, bInLut;
-  DevBuf vis, coacc, trim, wbase, fq, bq, heavy, hoff, heavy2, hoff2, cnt, btot;
+  DevBuf vis, coacc, trim, wbase, fq, bq, fcnt, heavy, hoff, heavy2, hoff2, cnt, btot;
   // score workspace
   DevBuf s_pg, s_pidx, s_bcnt, s_bscan, s_btotal;  // grouped scatter
   DevBuf s_sc, s_owner, s_extra, s_inref, s_mbeg, s_mlen, s_mcur, s_marc, s_val, s_acc,
@@ -256,9 +256,22 @@ int add_time(fst_ctx *c, int kernel, int64_t launches) {
   return FST_OK;
 }
 
+// Whether a search whose generations before g have run is over: nothing
+// waits for generation g (a chain search: its counters are in the scalars),
+// or generation g - 1 had no work.
+bool search_over(const fst_ctx *c, bool second, int g) {
+  const Scalars &h = *c->h_sc;
+  const uint32_t gens = second ? h.gens2 : h.gens;
+  if (!c->P.chains) return gens < (uint32_t)g;
+  const GenSlot &nx = (second ? h.G2 : h.G)[g % 3];
+  uint32_t any = (uint32_t)nx.hpack;
+  for (uint32_t i = 0; i < SUBQ; ++i) any |= h.front[second][(g % 3) * SUBQ + i];
+  return any == 0;
+}
+
 // Generations are queued in batches (4, 16, 32, 64, 64, ...) with no host
-// round trip; after each batch the host checks whether the next generation
-// has any work (generations queued after the search has ended do nothing).
+// round trip; after each batch the host checks whether the search is over
+// (generations queued after that do nothing).
 int search(fst_ctx *c, const SearchArgs &S, bool forward, int64_t *levels, hipStream_t s) {
   const int kernel = forward ? FST_KERNEL_SEARCH_FORWARD : FST_KERNEL_SEARCH_BACKWARD;
   const KernelTimer t = timer(c, kernel);
@@ -270,8 +283,7 @@ int search(fst_ctx *c, const SearchArgs &S, bool forward, int64_t *levels, hipSt
     FST_TRY(readback(c, s));
     FST_TRY(add_time(c, kernel, batch));
     if (c->h_sc->overflow) return FST_ERR_TOO_LARGE;
-    const GenSlot &nx = c->h_sc->G[g % 3];
-    if (nx.qcount == 0 && (uint32_t)nx.hpack == 0) break;
+    if (search_over(c, false, g)) break;
     batch = batch == 4 ? 16 : (batch < 64 ? 2 * batch : 64);
   }
   *levels = c->h_sc->gens;
@@ -579,7 +591,9 @@ int search_concurrent(fst_ctx *c, Problem P, const SearchArgs &SF, const SearchA
     // the one search left after the other ends is usually near its end too;
     // the first batch covers as many launches as the last search took
     int batch = fdone || bdone ? 8 : 16;
-    if (first && c->gen_hint > batch) batch = c->gen_hint < 256 ? c->gen_hint : 256;
+    // (a level search: and one that finds nothing)
+    const int hint = c->gen_hint + (P.chains ? 0 : 1);
+    if (first && hint > batch) batch = hint < 256 ? hint : 256;
     first = false;
     t.begin(s);
     for (int b = 0; b < batch; ++b) {
@@ -591,14 +605,13 @@ int search_concurrent(fst_ctx *c, Problem P, const SearchArgs &SF, const SearchA
     FST_TRY(readback(c, s));
     FST_TRY(add_time(c, FST_KERNEL_SEARCH_FORWARD, batch));
     if (c->h_sc->overflow) return FST_ERR_TOO_LARGE;
-    const GenSlot &nf = c->h_sc->G[gf % 3], &nb = c->h_sc->G2[gb % 3];
-    fdone = fdone || (nf.qcount == 0 && (uint32_t)nf.hpack == 0);
-    bdone = bdone || (nb.qcount == 0 && (uint32_t)nb.hpack == 0);
+    fdone = fdone || search_over(c, false, gf);
+    bdone = bdone || search_over(c, true, gb);
     if (fdone) P.restrict_bwd = 1;  // the accessible set is complete
     // an unrestricted backward frontier far wider than the forward one is
     // mostly keys that are not accessible: the backward search waits (its
     // frontier stays in its slot) until the forward search has ended
-    const unsigned long long wf = nf.qcount + (nf.hpack >> 32), wb = nb.qcount + (nb.hpack >> 32);
+    const unsigned long long wf = c->h_sc->note.width, wb = c->h_sc->note2.width;
     pause = pause || (!fdone && wb > 4 * wf + 65536);
     if (fdone && bdone) break;
     // (no growth: a read-back every 16 generations costs less than the
@@ -648,7 +661,8 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   if (VA)
     HIP_TRY(launch_validate(dA, 0, &d_sc->errA, &d_sc->maxLabA, s, &d_sc->naccA, c->validate));
   if (VB)
-    HIP_TRY(launch_validate(dB, 1, &d_sc->errB, &d_sc->maxLabB, s, &d_sc->naccB, c->validate));
+    HIP_TRY(launch_validate(dB, 1, &d_sc->errB, &d_sc->maxLabB, s, &d_sc->naccB, c->validate,
+                            &d_sc->singleB));
   FST_TRY(readback(c, s));
   const uint32_t info_bits = 1u << 16;  // validation's "not in label order" note
   if ((c->h_sc->errA & ~info_bits) || (c->h_sc->errB & ~info_bits)) return FST_ERR_INVALID_GRAPH;
@@ -766,8 +780,12 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     FST_TRY(ensure(c, c->coacc, snwords * 4));
     FST_TRY(ensure(c, c->trim, nwords * 4));
     FST_TRY(ensure(c, c->wbase, nwords * 4));
-    FST_TRY(ensure(c, c->fq, (size_t)cap * 4));
-    FST_TRY(ensure(c, c->bq, (size_t)cap * 4));
+    // two generations of a frontier of cap keys in SUBQ parts, per search
+    const uint32_t rc = (cap + SUBQ - 1) / SUBQ;
+    const size_t fbytes = 2 * (size_t)SUBQ * rc * 4;
+    FST_TRY(ensure(c, c->fq, fbytes));
+    if (c->order == FST_ORDER_CONCURRENT) FST_TRY(ensure(c, c->bq, fbytes));
+    FST_TRY(ensure(c, c->fcnt, 2 * FRONT_WORDS * 4));
     FST_TRY(ensure(c, c->heavy, (size_t)cap * 4));
     FST_TRY(ensure(c, c->hoff, (size_t)cap * 4));
     if (c->order == FST_ORDER_CONCURRENT) {
@@ -792,7 +810,10 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     P.maskB = (1u << shiftB) - 1u;
     P.rowA = (uint32_t)rowA;
     P.chain_max = c->chain_depth;
-    P.mark_accept = 1;
+    // Threads follow keys depth-first where most states of B have a single
+    // out-arc (a lexicon: a word's keys are one thread's walk and jumps);
+    // otherwise a level search spreads the units of every level over lanes.
+    P.chains = c->chain_depth > 0 && 2ull * c->h_sc->singleB > (unsigned long long)VB;
     P.vis = as<uint32_t>(c->vis);
     P.coacc = as<uint32_t>(c->coacc);
     P.trim = as<uint32_t>(c->trim);
@@ -801,16 +822,26 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     // ---- the two searches ----
     int32_t *la = as<int32_t>(c->lists), *lb = la + VA;
     uint32_t *cnts = reinterpret_cast<uint32_t *>(lb + VB);
-    uint32_t *fq = as<uint32_t>(c->fq), *bq = as<uint32_t>(c->bq);
     SearchArgs S;
-    S.Q = fq;
+    S.Q = P.chains ? Frontier{as<uint32_t>(c->fq), rc, 1, d_sc->front[0]}
+                   : Frontier{as<uint32_t>(c->fq), rc, SUBQ_STRIDE, as<uint32_t>(c->fcnt)};
     S.heavy = as<uint32_t>(c->heavy);
     S.hoff = as<uint32_t>(c->hoff);
-    S.acc = bq;
     S.cap = cap;
     S.sc = d_sc;
     S.G = d_sc->G;
     S.gens = &d_sc->gens;
+    S.note = &d_sc->note;
+    // (a chain search's counters were cleared with the scalars)
+    if (!P.chains) HIP_TRY(hipMemsetAsync(c->fcnt.p, 0, 2 * FRONT_WORDS * 4, s));
+    // a second search on the same lists (they hold no keys once the first
+    // has ended, but counters)
+    auto second_search = [&]() -> int {
+      HIP_TRY(hipMemsetAsync(d_sc->G, 0, sizeof(d_sc->G), s));
+      HIP_TRY(hipMemsetAsync(&d_sc->gens, 0, sizeof(d_sc->gens), s));
+      HIP_TRY(hipMemsetAsync(S.Q.cnt, 0, 3 * SUBQ * S.Q.stride * 4, s));
+      return FST_OK;
+    };
     wbase = as<uint32_t>(c->wbase);
     phase_end(c, PH_PRE, s);
     if (c->order == FST_ORDER_CONCURRENT) {
@@ -839,8 +870,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
         FST_TRY(readback(c, s));
         FST_TRY(add_time(c, FST_KERNEL_SEARCH_FORWARD, FIRST));
         if (c->h_sc->overflow) return FST_ERR_TOO_LARGE;
-        const GenSlot &nf = c->h_sc->G[FIRST % 3];
-        fwd_over = nf.qcount == 0 && (uint32_t)nf.hpack == 0;
+        fwd_over = search_over(c, false, FIRST);
       }
       if (fwd_over) {
         c->stats.fwd_levels = c->h_sc->gens;
@@ -849,22 +879,22 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
         phase_end(c, PH_FWD, s);
         phase_begin(c, PH_BWD, s);
         P.restrict_bwd = 1;
-        HIP_TRY(hipMemsetAsync(d_sc->G, 0, sizeof(d_sc->G), s));
-        HIP_TRY(launch_seed_backward(P, S, bq, s));
+        FST_TRY(second_search());
+        HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
+        HIP_TRY(launch_seed_backward(P, S, la, cnts, lb, cnts + 1, s));
         FST_TRY(search(c, S, false, &c->stats.bwd_levels, s));
         HIP_TRY(launch_trim(P, (uint32_t)VA, as<uint32_t>(c->trim), wbase, s));
         phase_end(c, PH_BWD, s);
       } else {
-        P.mark_accept = 0;  // the backward seeds below are every accepting pair
         SearchArgs SB = S;
-        SB.Q = bq;  // the forward search's list of accepting keys is not needed
+        SB.Q = Frontier{as<uint32_t>(c->bq), rc, S.Q.stride, S.Q.cnt + 3 * SUBQ * S.Q.stride};
         SB.heavy = as<uint32_t>(c->heavy2);
         SB.hoff = as<uint32_t>(c->hoff2);
-        SB.acc = nullptr;
         SB.G = d_sc->G2;
         SB.gens = &d_sc->gens2;
+        SB.note = &d_sc->note2;
         HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
-        HIP_TRY(launch_seed_backward_all(P, SB, la, cnts, lb, cnts + 1, s));
+        HIP_TRY(launch_seed_backward(P, SB, la, cnts, lb, cnts + 1, s));
         FST_TRY(search_concurrent(c, P, S, SB, FIRST, s));
         HIP_TRY(launch_popcount(P.vis, snwords, &d_sc->naccessible, s));
         if (c->count_moves) HIP_TRY(launch_count_moves(P, snwords, true, &d_sc->generated, s));
@@ -882,12 +912,12 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       phase_begin(c, PH_BWD, s);
       HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
       HIP_TRY(hipMemsetAsync(d_sc->G, 0, sizeof(d_sc->G), s));
-      HIP_TRY(launch_seed_backward_all(P, S, la, cnts, lb, cnts + 1, s));
+      HIP_TRY(launch_seed_backward(P, S, la, cnts, lb, cnts + 1, s));
       FST_TRY(search(c, S, false, &c->stats.bwd_levels, s));
       phase_end(c, PH_BWD, s);
       phase_begin(c, PH_FWD, s);
       HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
-      HIP_TRY(hipMemsetAsync(d_sc->G, 0, sizeof(d_sc->G), s));
+      FST_TRY(second_search());
       HIP_TRY(launch_seed_forward(P, S, la, cnts, lb, cnts + 1, s));
       FST_TRY(search(c, S, true, &c->stats.fwd_levels, s));
       HIP_TRY(launch_popcount(P.vis, snwords, &d_sc->naccessible, s));
@@ -906,10 +936,11 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       if (c->count_moves) HIP_TRY(launch_count_moves(P, snwords, true, &d_sc->generated, s));
       phase_end(c, PH_FWD, s);
 
-      // backward search, seeded by the accepting keys listed in bq
+      // backward search, seeded by the accepting keys among them
       phase_begin(c, PH_BWD, s);
-      HIP_TRY(hipMemsetAsync(d_sc->G, 0, sizeof(d_sc->G), s));
-      HIP_TRY(launch_seed_backward(P, S, bq, s));
+      FST_TRY(second_search());
+      HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
+      HIP_TRY(launch_seed_backward(P, S, la, cnts, lb, cnts + 1, s));
       FST_TRY(search(c, S, false, &c->stats.bwd_levels, s));
       // the backward search may set co-accessible bits of keys it never
       // expands (not accessible); the trim set is what remains after masking
@@ -925,10 +956,8 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     if (rc == FST_ERR_TOO_LARGE && c->h_sc->overflow && (unsigned long long)cap < cap_full) {
       cap_try = 4ull * cap;
       // the search scalars start again from zero (validation's stay)
-      HIP_TRY(hipMemsetAsync(&d_sc->tail2, 0, sizeof(uint32_t), s));
       HIP_TRY(hipMemsetAsync(&d_sc->heavy, 0,
-                             offsetof(Scalars, gens2) + sizeof(uint32_t) -
-                                 offsetof(Scalars, heavy), s));
+                             sizeof(Scalars) - offsetof(Scalars, heavy), s));
       continue;
     }
     FST_TRY(rc);
@@ -1652,7 +1681,7 @@ void fst_ctx_destroy(fst_ctx *c) {
                     &c->bOutLut,  &c->aInOff,   &c->aInPerm, &c->aInArc,  &c->aInRec,
                     &c->aInLut,   &c->bInOff,   &c->bInPerm, &c->bInArc,  &c->bInRec,
                     &c->bInLut,   &c->vis,      &c->coacc,   &c->trim,    &c->wbase,   &c->heavy2,
-                    &c->hoff2,    &c->fq,
+                    &c->hoff2,    &c->fq,       &c->fcnt,
                     &c->bq,       &c->heavy,    &c->hoff,    &c->cnt,     &c->aOutLab,
                     &c->aOutW,    &c->bOutLab,  &c->bOutW,   &c->btot,    &c->bOutChain,
                     &c->bInChain, &c->s_sc,     &c->s_owner, &c->s_extra, &c->s_inref,

@@ -69,8 +69,9 @@ __device__ __forceinline__ int32_t lb_label(const int2 *a, int32_t lo, int32_t h
 constexpr int VAL_ITEMS = 8;
 
 __global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t *err,
-                                                 uint32_t *maxlab, uint32_t *nacc) {
-  uint32_t bits = 0, mx = 0, na = 0;
+                                                 uint32_t *maxlab, uint32_t *nacc,
+                                                 uint32_t *single) {
+  uint32_t bits = 0, mx = 0, na = 0, n1 = 0;
   const long long V = g.V, E = g.E;
   const long long n = (V + 1 > E) ? V + 1 : E;
   const long long tile = (long long)NT * VAL_ITEMS;
@@ -120,6 +121,7 @@ __global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t 
         if (ob[r] < oa[r]) bits |= ERR_OFFSETS;
         if (st[r] > 1 || ac[r] > 1) bits |= ERR_FLAG;
         na += ac[r] == 1 ? 1u : 0u;
+        n1 += ob[r] - oa[r] == 1 ? 1u : 0u;
       }
       if (i < E) {
         const int32_t sv = sr[r], d = ds[r];
@@ -139,14 +141,16 @@ __global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t 
     }
   }
   // one atomic per workgroup: same-address atomics serialize
-  __shared__ uint32_t s_bits[NWAVES], s_mx[NWAVES], s_na[NWAVES];
+  __shared__ uint32_t s_bits[NWAVES], s_mx[NWAVES], s_na[NWAVES], s_n1[NWAVES];
   bits = wave_or(bits);
   mx = wave_max(mx);
   na = wave_sum(na);
+  n1 = wave_sum(n1);
   if (__lane_id() == 0) {
     s_bits[threadIdx.x / WAVE] = bits;
     s_mx[threadIdx.x / WAVE] = mx;
     s_na[threadIdx.x / WAVE] = na;
+    s_n1[threadIdx.x / WAVE] = n1;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -154,10 +158,12 @@ __global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t 
       bits |= s_bits[w];
       mx = s_mx[w] > mx ? s_mx[w] : mx;
       na += s_na[w];
+      n1 += s_n1[w];
     }
     if (bits) atomicOr(err, bits);
     if (mx) atomicMax(maxlab, mx);
     if (na && nacc) atomicAdd(nacc, na);
+    if (n1 && single) atomicAdd(single, n1);
   }
 }
 
@@ -166,13 +172,15 @@ __global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t 
 // the arcs of every state are in label order (an arc and the one before it
 // with the same source), and the number of accepting states; no checks.
 __global__ __launch_bounds__(NT) void k_label_facts(DevGraph g, int side, uint32_t *err,
-                                                    uint32_t *maxlab, uint32_t *nacc) {
-  uint32_t bits = 0, mx = 0, na = 0;
+                                                    uint32_t *maxlab, uint32_t *nacc,
+                                                    uint32_t *single) {
+  uint32_t bits = 0, mx = 0, na = 0, n1 = 0;
   const long long V = g.V, E = g.E;
   const long long n = V > E ? V : E;
   for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < n;
        i += (long long)gridDim.x * NT) {
     if (i < V && nacc) na += g.accept[i] == 1 ? 1u : 0u;
+    if (i < V && single) n1 += g.off[i + 1] - g.off[i] == 1 ? 1u : 0u;
     if (i < E && side != 2) {
       const int32_t lab = side == 0 ? g.ol[i] : g.il[i];
       if (lab > 0 && (uint32_t)lab > mx) mx = (uint32_t)lab;
@@ -180,14 +188,16 @@ __global__ __launch_bounds__(NT) void k_label_facts(DevGraph g, int side, uint32
         bits |= INFO_UNSORTED;
     }
   }
-  __shared__ uint32_t s_bits[NWAVES], s_mx[NWAVES], s_na[NWAVES];
+  __shared__ uint32_t s_bits[NWAVES], s_mx[NWAVES], s_na[NWAVES], s_n1[NWAVES];
   bits = wave_or(bits);
   mx = wave_max(mx);
   na = wave_sum(na);
+  n1 = wave_sum(n1);
   if (__lane_id() == 0) {
     s_bits[threadIdx.x / WAVE] = bits;
     s_mx[threadIdx.x / WAVE] = mx;
     s_na[threadIdx.x / WAVE] = na;
+    s_n1[threadIdx.x / WAVE] = n1;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -195,10 +205,12 @@ __global__ __launch_bounds__(NT) void k_label_facts(DevGraph g, int side, uint32
       bits |= s_bits[w];
       mx = s_mx[w] > mx ? s_mx[w] : mx;
       na += s_na[w];
+      n1 += s_n1[w];
     }
     if (bits) atomicOr(err, bits);
     if (mx) atomicMax(maxlab, mx);
     if (na && nacc) atomicAdd(nacc, na);
+    if (n1 && single) atomicAdd(single, n1);
   }
 }
 
@@ -502,27 +514,98 @@ __device__ __forceinline__ bool claim(uint32_t *bm, uint32_t k) {
   return (atomicOr(w, bit) & bit) == 0;
 }
 
-// An append-only key list with a device counter.
-struct Pusher {
-  uint32_t *Q;
-  uint32_t cap;
-  uint32_t *count;
+// Keys a wavefront has put aside for the next frontier (LDS).
+constexpr uint32_t PUSH_KEYS = 256;
+struct PushBuf {
+  uint32_t n;       // keys held
+  uint32_t key[PUSH_KEYS];
+};
+
+// The frontier a generation fills: its counters, its keys (parts of rc
+// keys) and the part this wavefront sends its keys to first.
+struct NextFront {
+  uint32_t *cnt, *keys;
+  uint32_t rc, stride, part;
   Scalars *sc;
 };
 
-// Append `key` for every lane with `want`, one atomic per wavefront.
-__device__ __forceinline__ void wave_push(bool want, uint32_t key, const Pusher &pu) {
-  unsigned long long m = __ballot(want);
+__device__ __forceinline__ NextFront next_front(const Frontier &F, int g, uint32_t part,
+                                                Scalars *sc) {
+  NextFront n;
+  n.cnt = F.cnt + (size_t)((g + 1) % 3) * (SUBQ * F.stride);
+  n.keys = F.keys + (size_t)((g + 1) & 1) * SUBQ * F.rc;
+  n.rc = F.rc;
+  n.stride = F.stride;
+  n.part = part % SUBQ;
+  n.sc = sc;
+  return n;
+}
+
+// Sends the wavefront's buffered keys to the list: one atomic on its part's
+// counter (more only where parts are full).  Any subset of the wavefront's
+// lanes may call it (together).
+__device__ __forceinline__ void push_flush(PushBuf &b, const NextFront &q) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const uint32_t n = b.n;
+  if (n == 0) return;
+  const unsigned long long act = __ballot(1);
+  const int leader = __ffsll(act) - 1;
+  const uint32_t lanes = (uint32_t)__popcll(act), rank = (uint32_t)__popcll(act & __lanemask_lt());
+  uint32_t done = 0;
+  for (uint32_t t = 0; t < SUBQ && done < n; ++t) {
+    const uint32_t part = (q.part + t) % SUBQ;
+    uint32_t base = 0;
+    if ((int)__lane_id() == leader) base = atomicAdd(q.cnt + part * q.stride, n - done);
+    base = __shfl(base, leader, WAVE);
+    const uint32_t room = base < q.rc ? q.rc - base : 0u;
+    const uint32_t take = room < n - done ? room : n - done;
+    for (uint32_t i = rank; i < take; i += lanes)
+      q.keys[(size_t)part * q.rc + base + i] = b.key[done + i];
+    done += take;
+  }
+  if (done < n) atomicOr(&q.sc->overflow, 1u);
+  __builtin_amdgcn_wave_barrier();
+  if ((int)__lane_id() == leader) b.n = 0;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Appends `key` for every lane with `want` at once (a search that pushes
+// little), one atomic per wavefront.
+__device__ __forceinline__ void front_push(bool want, uint32_t key, const NextFront &q) {
+  bool left = want;
+  for (uint32_t t = 0; t < SUBQ; ++t) {
+    const unsigned long long m = __ballot(left);
+    if (m == 0) return;
+    const int leader = __ffsll(m) - 1;
+    const uint32_t part = (q.part + t) % SUBQ;
+    uint32_t base = 0;
+    if ((int)__lane_id() == leader)
+      base = atomicAdd(q.cnt + part * q.stride, (uint32_t)__popcll(m));
+    base = __shfl(base, leader, WAVE);
+    const uint32_t pos = base + (uint32_t)__popcll(m & __lanemask_lt());
+    if (left && pos < q.rc) {
+      q.keys[(size_t)part * q.rc + pos] = key;
+      left = false;
+    }
+  }
+  if (left) atomicOr(&q.sc->overflow, 1u);
+}
+
+// Buffers `key` for every lane with `want`; the keys reach the list when
+// the buffer fills up, or with push_flush.
+__device__ __forceinline__ void buf_push(bool want, uint32_t key, PushBuf &b,
+                                         const NextFront &q) {
+  const unsigned long long m = __ballot(want);
   if (m == 0) return;
   const int leader = __ffsll(m) - 1;
+  const uint32_t n = (uint32_t)__popcll(m);
   uint32_t base = 0;
-  if ((int)__lane_id() == leader) base = atomicAdd(pu.count, (uint32_t)__popcll(m));
+  if ((int)__lane_id() == leader) base = atomicAdd(&b.n, n);
   base = __shfl(base, leader, WAVE);
-  if (want) {
-    uint32_t pos = base + (uint32_t)__popcll(m & __lanemask_lt());
-    if (pos < pu.cap) pu.Q[pos] = key;
-    else atomicOr(&pu.sc->overflow, 1u);
-  }
+  if (want) b.key[base + (uint32_t)__popcll(m & __lanemask_lt())] = key;
+  if (base + n > PUSH_KEYS - WAVE) push_flush(b, q);
 }
 
 // A state's two records in one view (see View).
@@ -535,6 +618,15 @@ __device__ __forceinline__ Rec opaque(const Rec &r) {
   Rec o;
   o.r0 = make_int4(opaque(r.r0.x), opaque(r.r0.y), opaque(r.r0.z), opaque(r.r0.w));
   o.r1 = make_int4(opaque(r.r1.x), opaque(r.r1.y), opaque(r.r1.z), opaque(r.r1.w));
+  return o;
+}
+
+__device__ __forceinline__ Rec shfl_rec(const Rec &r, uint32_t from) {
+  Rec o;
+  o.r0 = make_int4(__shfl(r.r0.x, from, WAVE), __shfl(r.r0.y, from, WAVE),
+                   __shfl(r.r0.z, from, WAVE), __shfl(r.r0.w, from, WAVE));
+  o.r1 = make_int4(__shfl(r.r1.x, from, WAVE), __shfl(r.r1.y, from, WAVE),
+                   __shfl(r.r1.z, from, WAVE), 0);
   return o;
 }
 
@@ -847,7 +939,9 @@ __device__ __forceinline__ void for_unit(const Problem &P, const typename Dir<FW
 // Where the next generation's work goes.
 struct NextGen {
   GenSlot *slot;
-  uint32_t qbase, hbase;
+  uint32_t hbase;
+  NextFront q;
+  PushBuf *buf;  // the wavefront's keys for the next frontier
 };
 
 // List a heavy key for the next generation: one packed atomic gives its
@@ -884,22 +978,17 @@ __device__ __forceinline__ void set_bit(uint32_t *bm, uint32_t b) {
   set_bits(bm, b >> 5, 1u << (b & 31u));
 }
 
-// A key reached for the first time (`fresh`).  Forward: if it accepts it is
-// marked co-accessible and listed as a seed of the backward search.  Then:
-// heavy keys go to the next generation's heavy list; a light key becomes this
-// thread's next key (depth-first continuation) if it has none yet and the
-// depth budget allows, else it joins the next frontier.
+// A key reached for the first time (`fresh`): heavy keys go to the next
+// generation's heavy list; a light key becomes this thread's next key
+// (depth-first continuation) if it has none yet and the depth budget allows,
+// else it joins the next frontier.
 template <bool FWD>
 __device__ __forceinline__ void place(const Problem &P, const SearchArgs &S, const NextGen &nx,
                                       bool fresh, uint32_t v, const typename Dir<FWD>::Info &vi,
                                       Next<FWD> &nk, int depth) {
-  bool push = false, seed = false;
+  bool push = false;
   if (fresh) {
     const uint32_t u = Dir<FWD>::units(vi);
-    if constexpr (FWD) {
-      seed = P.mark_accept && vi.accept != 0;
-      if (seed) set_bit(P.coacc, search_bit(P, v));
-    }
     if (u > LIGHT_SEARCH) {
       list_heavy(S, nx, v, u);
     } else if (nk.key == NO_KEY && depth < P.chain_max) {
@@ -909,8 +998,7 @@ __device__ __forceinline__ void place(const Problem &P, const SearchArgs &S, con
       push = true;
     }
   }
-  if (FWD) wave_push(seed, v, Pusher{S.acc, S.cap, &S.sc->tail2, S.sc});
-  wave_push(push, v, Pusher{S.Q + nx.qbase, S.cap - nx.qbase, &nx.slot->qcount, S.sc});
+  front_push(push, v, nx.q);
 }
 
 // Visit a move target (forward) or a predecessor (backward, where only
@@ -1079,6 +1167,44 @@ __device__ __forceinline__ bool chain_jump(const Problem &P, const SearchArgs &S
   return true;
 }
 
+// Exclusive prefix sums of the part counts of generation g's frontier, into
+// LDS (by the first wavefront; a barrier must follow).
+__device__ __forceinline__ void load_front(const Frontier &F, int g, uint32_t *pre) {
+  static_assert(SUBQ == WAVE, "one lane per part");
+  if (threadIdx.x < WAVE) {
+    const uint32_t *c = F.cnt + (size_t)(g % 3) * (SUBQ * F.stride);
+    uint32_t n = c[threadIdx.x * F.stride];
+    n = n < F.rc ? n : F.rc;
+    pre[threadIdx.x + 1] = wave_incl_scan(n);
+    if (threadIdx.x == 0) pre[0] = 0;
+  }
+}
+
+// Key i of generation g's frontier.
+__device__ __forceinline__ uint32_t front_key(const Frontier &F, int g, const uint32_t *pre,
+                                              uint32_t i) {
+  uint32_t a = 0;  // the last part that starts at or before i
+#pragma unroll
+  for (uint32_t h = SUBQ / 2; h; h >>= 1)
+    if (pre[a + h] <= i) a += h;
+  return F.keys[((size_t)(g & 1) * SUBQ + a) * F.rc + (i - pre[a])];
+}
+
+// By one workgroup of generation g: the next generation's heavy list starts
+// at hbase, the slot and the counters of generation g - 1 are free, and the
+// host learns of the n items of this one.
+__device__ __forceinline__ void note_generation(const SearchArgs &S, int g, uint32_t hbase,
+                                                ull n) {
+  if (threadIdx.x == 0) {
+    S.G[(g + 1) % 3].hbase = hbase;  // read by generation g + 1 only
+    S.G[(g + 2) % 3].hpack = 0;
+    S.note->width = n;
+    if (n) *S.gens = (uint32_t)g + 1;
+  }
+  if (threadIdx.x < SUBQ)
+    S.Q.cnt[((size_t)((g + 2) % 3) * SUBQ + threadIdx.x) * S.Q.stride] = 0;
+}
+
 // Generation g (one kernel): one thread per unit slot of the generation's
 // heavy keys, then one thread per light frontier key.  A thread expands its
 // units, then, depth-first, the light keys it reached first (one loop, so
@@ -1100,27 +1226,24 @@ __device__ __forceinline__ void gen_body(const Problem &P, const SearchArgs &S, 
   const ull U = cur.hpack >> 32;
   // a heavy list of at most NT keys is searched in LDS
   __shared__ uint32_t s_ho[NT], s_hk[NT];
+  __shared__ uint32_t s_pre[SUBQ + 1];
+  load_front(S.Q, g, s_pre);
   if (threadIdx.x < hcount) {
     s_ho[threadIdx.x] = S.hoff[cur.hbase + threadIdx.x];
     s_hk[threadIdx.x] = S.heavy[cur.hbase + threadIdx.x];
   }
   __syncthreads();
   if (ovf) return;
+  const uint32_t nq = s_pre[SUBQ];
   NextGen nx;
   nx.slot = &S.G[(g + 1) % 3];
-  nx.qbase = cur.qbase + cur.qcount;
   nx.hbase = cur.hbase + hcount;
-  if (bid == 0 && threadIdx.x == 0) {
-    nx.slot->qbase = nx.qbase;  // read by generation g + 1 only
-    nx.slot->hbase = nx.hbase;
-    GenSlot *done = &S.G[(g + 2) % 3];  // generation g - 1: free
-    done->qcount = 0;
-    done->hpack = 0;
-    if (U + cur.qcount) *S.gens = (uint32_t)g + 1;
-  }
+  nx.q = next_front(S.Q, g, bid * NWAVES + threadIdx.x / WAVE, sc);
+  nx.buf = nullptr;
+  if (bid == 0) note_generation(S, g, nx.hbase, U + nq);
   const uint32_t *hk = S.heavy + cur.hbase;
   const uint32_t *ho = S.hoff + cur.hbase;
-  const ull n = U + cur.qcount;
+  const ull n = U + nq;
   const unsigned xcd = bid & 7u, nl = nb >> 3;
   for (ull j = (ull)(bid >> 3) * NT + threadIdx.x; (bid >> 3) < nl; j += (ull)nl * NT) {
     const ull i = 8 * j + xcd;
@@ -1146,7 +1269,7 @@ __device__ __forceinline__ void gen_body(const Problem &P, const SearchArgs &S, 
       }
       one_unit = true;
     } else {
-      key = S.Q[cur.qbase + (uint32_t)(i - U)];
+      key = front_key(S.Q, g, s_pre, (uint32_t)(i - U));
     }
     Info info = Dir<FWD>::info(P, key);
     if (one_unit && u0 >= Dir<FWD>::units(info)) continue;  // a slot past the key's units
@@ -1184,6 +1307,165 @@ __global__ __launch_bounds__(NT, 4) void k_gen2(Problem P, SearchArgs SF, Search
   else gen_body<false>(P, SB, gb, blockIdx.x - half, half);
 }
 
+// ---------------------------------------------------------------------------
+// level search
+// ---------------------------------------------------------------------------
+
+// LDS of a workgroup of the level search.
+struct LevelLds {
+  uint32_t ho[NT], hk[NT];     // a heavy list of at most NT keys
+  uint32_t pre[SUBQ + 1];      // prefix of the frontier's part counts
+  uint32_t off[NWAVES][WAVE];  // unit offsets of a wavefront's keys
+  PushBuf push[NWAVES];
+};
+
+// Claims a move's target and puts it aside for the next frontier if this
+// move is the first to reach it.  No record of the target is loaded (the
+// next generation does, with its units spread over the lanes).
+template <bool FWD>
+__device__ __forceinline__ void reach(const Problem &P, const NextGen &nx, const Target &t) {
+  const uint32_t sb = search_bit(P, t.key);
+  const uint32_t bit = 1u << (sb & 31u), w = sb >> 5;
+  const uint32_t *other = FWD ? P.coacc : P.vis;
+  uint32_t *mine = FWD ? P.vis : P.coacc;
+  const bool restricted = FWD ? P.restrict_fwd != 0 : P.restrict_bwd != 0;
+  bool fresh;
+  if (t.hot || restricted) {
+    const uint32_t wo = restricted ? other[w] : bit, wm = mine[w];  // one round trip
+    fresh = (wo & bit) && !(wm & bit) && (atomicOr(mine + w, bit) & bit) == 0;
+  } else {
+    fresh = (atomicOr(mine + w, bit) & bit) == 0;
+  }
+  buf_push(fresh, t.key, *nx.buf, nx.q);
+}
+
+// Generation g of a level search (one kernel).  Its items are the unit slots
+// of its heavy keys (one per thread) and its frontier keys, which a
+// wavefront takes in batches: the units of the batch's keys are numbered by
+// a scan and spread over the lanes (the key of a unit found by a binary
+// search in LDS, its records moved between lanes), so a wavefront's time
+// does not grow with its busiest key.  A batch is the frontier divided by the
+// wavefronts, at most 64 keys: a narrow frontier is spread over more
+// wavefronts, a wide one fills the lanes.  nb is a multiple of 8 (slots of
+// heavy keys are spread over the XCDs as in gen_body).
+template <bool FWD>
+__device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S, int g,
+                                           unsigned bid, unsigned nb, LevelLds &L) {
+  typedef typename Dir<FWD>::Info Info;
+  const unsigned lane = __lane_id(), wid = threadIdx.x / WAVE;
+  const uint32_t ovf = S.sc->overflow;  // loaded with the slot (one round trip)
+  const GenSlot cur = S.G[g % 3];
+  const uint32_t hcount = (uint32_t)(cur.hpack & 0xffffffffull);
+  const ull U = cur.hpack >> 32;
+  load_front(S.Q, g, L.pre);
+  if (lane == 0) L.push[wid].n = 0;
+  if (threadIdx.x < hcount) {
+    L.ho[threadIdx.x] = S.hoff[cur.hbase + threadIdx.x];
+    L.hk[threadIdx.x] = S.heavy[cur.hbase + threadIdx.x];
+  }
+  __syncthreads();
+  if (ovf) return;
+  const uint32_t nq = L.pre[SUBQ];
+  NextGen nx;
+  nx.slot = &S.G[(g + 1) % 3];
+  nx.hbase = cur.hbase + hcount;
+  nx.q = next_front(S.Q, g, bid * NWAVES + wid, S.sc);
+  nx.buf = &L.push[wid];
+  if (bid == 0) note_generation(S, g, nx.hbase, U + nq);
+  const unsigned xcd = bid & 7u, nl = (nb >> 3) * NWAVES;  // wavefronts per XCD
+  const unsigned lw = (bid >> 3) * NWAVES + wid;
+  // heavy slots xcd, xcd + 8, ...: batches of 64; then frontier batches
+  const ull hslots = U > xcd ? (U - xcd + 7) / 8 : 0;
+  const ull hb = (hslots + WAVE - 1) / WAVE;
+  uint32_t K = (nq + 8 * nl - 1) / (8 * nl);
+  if (K < 1) K = 1;
+  if (K > WAVE) K = WAVE;
+  for (ull j = lw;; j += nl) {
+    const bool hv = j < hb;
+    uint32_t key = 0, u0 = 0, units = 0, T = 1;
+    Rec A = {}, B = {};
+    bool have = false;
+    if (hv) {
+      const ull i = 8 * (j * WAVE + lane) + xcd;
+      if (i < U) {
+        const uint32_t *hk = hcount <= NT ? L.hk : S.heavy + cur.hbase;
+        const uint32_t *ho = hcount <= NT ? L.ho : S.hoff + cur.hbase;
+        uint32_t a = 0, b = hcount - 1;  // largest a with ho[a] <= i
+        while (a < b) {
+          const uint32_t mid = (a + b + 1) >> 1;
+          if (ho[mid] <= i) a = mid; else b = mid - 1;
+        }
+        key = hk[a];
+        u0 = (uint32_t)(i - ho[a]);
+        have = true;
+      }
+    } else {
+      const ull fb = (j - hb) * 8 + xcd;  // this batch of the frontier
+      if (fb * K >= nq) break;
+      const uint32_t i = (uint32_t)(fb * K) + lane;
+      have = lane < K && i < nq;
+      if (have) key = front_key(S.Q, g, L.pre, i);
+    }
+    if (have) {
+      A = load_rec(Dir<FWD>::viewA(P), key_qa(key, P.shiftB));
+      B = load_rec(Dir<FWD>::viewB(P), key_qb(key, P.shiftB));
+      units = Dir<FWD>::units(Dir<FWD>::make(key, P.shiftB, A, B));
+    }
+    if (!hv) {
+      // a key with many units waits one generation and is then spread over
+      // the whole grid
+      if (units > LEVEL_UNITS) {
+        list_heavy(S, nx, key, units);
+        units = 0;
+      }
+      const uint32_t incl = wave_incl_scan(units);
+      L.off[wid][lane] = incl - units;
+      T = __shfl(incl, WAVE - 1, WAVE);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    for (uint32_t r = 0; r < T; r += WAVE) {
+      bool go = have && u0 < units;  // a heavy slot past the key's units has none
+      uint32_t u = u0, k2 = key;
+      Rec A2 = A, B2 = B;
+      if (!hv) {
+        const uint32_t item = r + lane;
+        go = item < T;
+        uint32_t a = 0;  // the last lane whose units start at or before this one
+#pragma unroll
+        for (uint32_t h = WAVE / 2; h; h >>= 1)
+          if (L.off[wid][a + h] <= item) a += h;
+        a = go ? a : lane;
+        k2 = __shfl(key, a, WAVE);
+        A2 = shfl_rec(A, a);
+        B2 = shfl_rec(B, a);
+        u = item - L.off[wid][a];
+      }
+      if (go) {
+        const Info info = Dir<FWD>::make(k2, P.shiftB, A2, B2);
+        for_unit<FWD>(P, info, u,
+                      [&](const Target &t, const Rec &) { reach<FWD>(P, nx, t); });
+      }
+    }
+  }
+  push_flush(*nx.buf, nx.q);
+}
+
+template <bool FWD>
+__global__ __launch_bounds__(NT) void k_level(Problem P, SearchArgs S, int g) {
+  __shared__ LevelLds L;
+  level_body<FWD>(P, S, g, blockIdx.x, gridDim.x, L);
+}
+
+// Both searches side by side, half of the workgroups each.
+__global__ __launch_bounds__(NT) void k_level2(Problem P, SearchArgs SF, SearchArgs SB, int gf,
+                                               int gb) {
+  __shared__ LevelLds L;
+  const unsigned half = gridDim.x / 2;
+  if (blockIdx.x < half) level_body<true>(P, SF, gf, blockIdx.x, half, L);
+  else level_body<false>(P, SB, gb, blockIdx.x - half, half, L);
+}
+
 __global__ __launch_bounds__(NT) void k_collect(const uint8_t *__restrict__ flags, int V,
                                                 int32_t *__restrict__ list,
                                                 uint32_t *__restrict__ count) {
@@ -1208,7 +1490,12 @@ __global__ __launch_bounds__(NT) void k_seed_forward(Problem P, SearchArgs S,
                                                      const int32_t *__restrict__ lb,
                                                      const uint32_t *__restrict__ nb_p) {
   const ull na = *na_p, nb = *nb_p, n = na * nb;
-  const NextGen nx{&S.G[0], 0u, 0u};
+  __shared__ PushBuf s_push[NWAVES];
+  const uint32_t w = threadIdx.x / WAVE;
+  const NextGen nx{&S.G[0], 0u, next_front(S.Q, -1, blockIdx.x * NWAVES + w, S.sc),
+                   s_push + w};
+  if (__lane_id() == 0) s_push[w].n = 0;
+  __syncthreads();
   for (ull i0 = (ull)blockIdx.x * NT; i0 < n; i0 += (ull)gridDim.x * NT) {
     const ull i = i0 + threadIdx.x;
     uint32_t k = 0;
@@ -1220,22 +1507,28 @@ __global__ __launch_bounds__(NT) void k_seed_forward(Problem P, SearchArgs S,
       fresh = (!P.restrict_fwd || test_bit(P.coacc, sb)) && claim(P.vis, sb);
       ki = fwd_info(P, k);
     }
-    Next<true> nk;
-    nk.key = NO_KEY;
-    // depth = chain_max: every light start key joins the frontier
-    place<true>(P, S, nx, fresh, k, ki, nk, P.chain_max);
+    const uint32_t u = fresh ? Dir<true>::units(ki) : 0;
+    if (u > LIGHT_SEARCH) list_heavy(S, nx, k, u);
+    buf_push(u > 0 && u <= LIGHT_SEARCH, k, *nx.buf, nx.q);
   }
+  push_flush(*nx.buf, nx.q);
 }
 
 // Every accepting key (f = 0, and f = 1 where its A state has an epsilon
-// output) forms generation 0 of a backward search over all key pairs.
-__global__ __launch_bounds__(NT) void k_seed_backward_all(Problem P, SearchArgs S,
+// output) forms generation 0 of a backward search: over all key pairs, or
+// (restrict_bwd) of the accessible ones.
+__global__ __launch_bounds__(NT) void k_seed_backward(Problem P, SearchArgs S,
                                                           const int32_t *__restrict__ la,
                                                           const uint32_t *__restrict__ na_p,
                                                           const int32_t *__restrict__ lb,
                                                           const uint32_t *__restrict__ nb_p) {
   const ull na = *na_p, nb = *nb_p, n = 2 * na * nb;
-  const NextGen nx{&S.G[0], 0u, 0u};
+  __shared__ PushBuf s_push[NWAVES];
+  const uint32_t w = threadIdx.x / WAVE;
+  const NextGen nx{&S.G[0], 0u, next_front(S.Q, -1, blockIdx.x * NWAVES + w, S.sc),
+                   s_push + w};
+  if (__lane_id() == 0) s_push[w].n = 0;
+  __syncthreads();
   for (ull i0 = (ull)blockIdx.x * NT; i0 < n; i0 += (ull)gridDim.x * NT) {
     const ull i = i0 + threadIdx.x;
     uint32_t k = 0;
@@ -1246,34 +1539,17 @@ __global__ __launch_bounds__(NT) void k_seed_backward_all(Problem P, SearchArgs 
       const uint32_t qa = (uint32_t)la[pair / nb], f = (uint32_t)(i & 1);
       const bool eps = (P.aOut.srec[2 * (size_t)qa].w & (int32_t)FLAG_EPS_OUT) != 0;
       k = make_key(qa, (uint32_t)lb[pair % nb], f, P.shiftB);
-      // every pair is enumerated once, so it is placed once; a forward
-      // search running first may already have marked it co-accessible
-      fresh = f == 0 || eps;
-      if (fresh) set_bit(P.coacc, search_bit(P, k));
+      // every pair is enumerated once, so it is placed once
+      const uint32_t sb = search_bit(P, k);
+      fresh = (f == 0 || eps) && (!P.restrict_bwd || test_bit(P.vis, sb));
+      if (fresh) set_bit(P.coacc, sb);
       ki = bwd_info(P, k);
     }
-    Next<false> nk;
-    nk.key = NO_KEY;
-    place<false>(P, S, nx, fresh, k, ki, nk, P.chain_max);
+    const uint32_t u = fresh ? Dir<false>::units(ki) : 0;
+    if (u > LIGHT_SEARCH) list_heavy(S, nx, k, u);
+    buf_push(u > 0 && u <= LIGHT_SEARCH, k, *nx.buf, nx.q);
   }
-}
-
-// The accepting keys listed by the forward search (already co-accessible)
-// form generation 0 of the backward search.
-__global__ __launch_bounds__(NT) void k_seed_backward(Problem P, SearchArgs S,
-                                                      const uint32_t *__restrict__ list) {
-  const uint32_t n = S.sc->tail2;
-  const NextGen nx{&S.G[0], 0u, 0u};
-  for (ull i0 = (ull)blockIdx.x * NT; i0 < n; i0 += (ull)gridDim.x * NT) {
-    const ull i = i0 + threadIdx.x;
-    const bool valid = i < n;
-    const uint32_t k = valid ? list[i] : 0u;
-    Bwd ki;
-    if (valid) ki = bwd_info(P, k);
-    Next<false> nk;
-    nk.key = NO_KEY;
-    place<false>(P, S, nx, valid, k, ki, nk, P.chain_max);
-  }
+  push_flush(*nx.buf, nx.q);
 }
 
 // Number of moves the search examines (a statistic, on request): forward,
@@ -1996,10 +2272,10 @@ __global__ __launch_bounds__(NT) void k_item_ranges(Problem P, ull nkeys, int32_
 // launchers
 // ---------------------------------------------------------------------------
 hipError_t launch_validate(const DevGraph &g, int side, uint32_t *err, uint32_t *maxlab,
-                           hipStream_t s, uint32_t *nacc, bool check) {
+                           hipStream_t s, uint32_t *nacc, bool check, uint32_t *single) {
   size_t n = (size_t)(g.V + 1 > g.E ? g.V + 1 : g.E);
-  if (check) k_validate<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc);
-  else k_label_facts<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc);
+  if (check) k_validate<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc, single);
+  else k_label_facts<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc, single);
   return hipGetLastError();
 }
 
@@ -2085,35 +2361,35 @@ hipError_t launch_seed_forward(const Problem &P, const SearchArgs &S, int32_t *l
   return hipGetLastError();
 }
 
-hipError_t launch_seed_backward_all(const Problem &P, const SearchArgs &S, int32_t *la,
-                                    uint32_t *na, int32_t *lb, uint32_t *nb, hipStream_t s) {
+hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, int32_t *la,
+                                uint32_t *na, int32_t *lb, uint32_t *nb, hipStream_t s) {
   k_collect<<<grid_for((size_t)P.A.V, 1024), NT, 0, s>>>(P.A.accept, P.A.V, la, na);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_collect<<<grid_for((size_t)P.B.V, 1024), NT, 0, s>>>(P.B.accept, P.B.V, lb, nb);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_seed_backward_all<<<1024, NT, 0, s>>>(P, S, la, na, lb, nb);
-  return hipGetLastError();
-}
-
-hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, const uint32_t *acc_list,
-                                hipStream_t s) {
-  k_seed_backward<<<1024, NT, 0, s>>>(P, S, acc_list);
+  k_seed_backward<<<1024, NT, 0, s>>>(P, S, la, na, lb, nb);
   return hipGetLastError();
 }
 
 hipError_t launch_generation(const Problem &P, const SearchArgs &S, bool forward, int g,
                              hipStream_t s) {
   constexpr unsigned GRID = 1024;
-  if (forward) k_gen<true><<<GRID, NT, 0, s>>>(P, S, g);
-  else k_gen<false><<<GRID, NT, 0, s>>>(P, S, g);
+  if (!P.chains) {
+    if (forward) k_level<true><<<GRID, NT, 0, s>>>(P, S, g);
+    else k_level<false><<<GRID, NT, 0, s>>>(P, S, g);
+  } else {
+    if (forward) k_gen<true><<<GRID, NT, 0, s>>>(P, S, g);
+    else k_gen<false><<<GRID, NT, 0, s>>>(P, S, g);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_generation2(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
                               int gb, hipStream_t s) {
   constexpr unsigned GRID = 1024;
-  k_gen2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
+  if (!P.chains) k_level2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
+  else k_gen2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
   return hipGetLastError();
 }
 

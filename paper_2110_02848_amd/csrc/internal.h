@@ -15,6 +15,7 @@ constexpr int WAVE = 64;             // CDNA wavefront width
 constexpr int NWAVES = NT / WAVE;
 constexpr uint32_t LIGHT_UNITS = 32;   // compaction: per-state work above this goes to a workgroup
 constexpr uint32_t LIGHT_SEARCH = 64;  // search: a key with more units is split over threads
+constexpr uint32_t LEVEL_UNITS = 256;  // the same in a level search
 constexpr int CHAIN_MAX = 64;          // search: default depth-first budget per thread
 constexpr uint32_t NO_KEY = 0xFFFFFFFFu;
 
@@ -114,10 +115,9 @@ struct Problem {
   View bIn;    // B by (dst, ilabel)
   uint32_t shiftB;        // bits of the B state inside a key
   int chain_max;          // keys one search thread may follow depth-first
+  int chains;             // chain search (else level search)
   int restrict_fwd;       // forward search expands only keys already in coacc
   int restrict_bwd;       // backward search expands only keys already in vis
-  int mark_accept;        // forward search marks accepting keys co-accessible
-                          // and lists them as backward seeds
   // The two search bitmaps use the diagonal layout of search_bit(): a key
   // (qa, qb, f) sits at bit 2 (d rowA + qa) + f with d = (qb - qa) mod
   // 2^shiftB, so the keys of a chain that advances both states by one share
@@ -143,8 +143,27 @@ struct OutGraph {
   int32_t vbase, ebase, abase, aebase;
 };
 
+// A frontier list in SUBQ parts: in a level search their counters sit on
+// cache lines of their own (an atomic on a line holds it for 11.4 ns whichever
+// word it names, so one counter for all wavefronts was the serial part of a
+// wide generation); a chain search, which pushes little, keeps them side by
+// side in Scalars (stride 1), so that a generation reads them from two lines
+// and the host sees whether the next one has work.
+// Generation g's keys are keys[(g & 1) SUBQ rc + part rc + i],
+// i < min(cnt[g % 3][part], rc); a part that is full spills into the next, so
+// the list as a whole holds SUBQ rc keys.
+constexpr uint32_t SUBQ = 64, SUBQ_STRIDE = 32;  // parts; words between two counters
+constexpr size_t FRONT_WORDS = 3 * (size_t)SUBQ * SUBQ_STRIDE;  // counters of a list
+struct Frontier {
+  uint32_t *keys;
+  uint32_t rc;      // keys per part and generation
+  uint32_t stride;  // words between two counters: 1 or SUBQ_STRIDE
+  uint32_t *cnt;
+};
+
 // Work of one search generation, kept in one of three rotating slots
-// (generation g uses slot g % 3): frontier keys Q[qbase, qbase + qcount) and
+// (generation g uses slot g % 3): frontier keys Q[qbase, qbase + qcount)
+// (scores; a composition's are in its Frontier) and
 // heavy keys heavy[hbase, hbase + count) with their unit offsets, where
 // hpack = (total units << 32) | count.  Generation g fills the slot of g + 1
 // and clears the slot of g + 2.
@@ -153,12 +172,19 @@ struct GenSlot {
   unsigned long long hpack;
 };
 
+// What the last generation of a search that ran found: its work items, and
+// the levels that narrow generations went through beyond one each.
+struct SearchNote {
+  unsigned long long width;
+  uint32_t extra_levels, pad;
+};
+
 // Device scalars read back by the host (one pinned mirror).
 struct Scalars {
   uint32_t errA, errB;          // validation error bits
   uint32_t maxLabA, maxLabB;    // max matched label (A olabel, B ilabel)
   uint32_t nEpsStatesA;         // states of A with an epsilon-output arc
-  uint32_t tail2;               // accepting keys found by the forward search
+  uint32_t singleB;             // states of B with one out-arc
   uint32_t naccA, naccB;        // accepting states of A and B
   uint32_t pad0;
   uint32_t heavy;               // heavy states of C
@@ -172,18 +198,20 @@ struct Scalars {
   GenSlot G[3];                 // generation slots of a search
   GenSlot G2[3];                // of the backward search running beside it
   uint32_t gens2, pad1;         // its generations that had work
+  SearchNote note, note2;       // of the two searches
+  uint32_t front[2][3 * SUBQ];  // frontier counters of chain searches
 };
 
-// Arrays of one search (each holds up to `cap` keys).
+// Arrays of one search.
 struct SearchArgs {
-  uint32_t *Q;      // frontier keys, generation after generation
-  uint32_t *heavy;  // heavy keys, generation after generation
+  Frontier Q;       // frontier keys
+  uint32_t *heavy;  // heavy keys, generation after generation (up to cap)
   uint32_t *hoff;   // unit offset of each heavy key inside its generation
-  uint32_t *acc;    // forward search: accepting keys, the backward seeds
   uint32_t cap;
   Scalars *sc;
   GenSlot *G;       // this search's three generation slots
   uint32_t *gens;   // this search's count of generations that had work
+  SearchNote *note;
 };
 
 // ---------------------------------------------------------------------------
@@ -470,9 +498,11 @@ hipError_t radix_sort(unsigned long long *k0, int32_t *v0, unsigned long long *k
 // side 0 (A: matched label = olabel) or 1 (B: ilabel), its labels, the
 // largest matched label and whether the arcs are in label order; side 2
 // checks the structure only.  *nacc (if given) += number of accepting states.
+// *single (if given) += number of states with exactly one out-arc.
 // check = false skips the checks and only gathers the label facts and nacc.
 hipError_t launch_validate(const DevGraph &g, int side, uint32_t *err, uint32_t *maxlab,
-                           hipStream_t s, uint32_t *nacc = nullptr, bool check = true);
+                           hipStream_t s, uint32_t *nacc = nullptr, bool check = true,
+                           uint32_t *single = nullptr);
 // Views are built in two steps.  sort_view: sort the arcs of a view (side
 // 0: A by olabel, side 1: B by ilabel; by_dst selects in-views, for which
 // `off_tmp` (V+1 words) receives the group offsets; an out-view of an input
@@ -513,19 +543,14 @@ struct ViewJobs {
 hipError_t finish_views(ViewJobs J, hipStream_t s);
 // Collect the start states of A and B into la/lb (counts na/nb, zeroed by the
 // caller) and place every start key in generation 0 of the forward search.
-// Accepting keys reached by the forward search (start keys included) are
-// marked co-accessible and listed in S.acc (count in Scalars::tail2).
 hipError_t launch_seed_forward(const Problem &P, const SearchArgs &S, int32_t *la, uint32_t *na,
                                int32_t *lb, uint32_t *nb, hipStream_t s);
 // Collect the accepting states of A and B into la/lb (counts na/nb, zeroed
 // by the caller) and place every accepting key (f = 0, and f = 1 where
-// epsOutA) in generation 0 of a backward search over all key pairs.
-hipError_t launch_seed_backward_all(const Problem &P, const SearchArgs &S, int32_t *la,
-                                    uint32_t *na, int32_t *lb, uint32_t *nb, hipStream_t s);
-// Place the accepting keys listed by the forward search (acc_list) in
-// generation 0 of the backward search.
-hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, const uint32_t *acc_list,
-                                hipStream_t s);
+// epsOutA) in generation 0 of a backward search: over all key pairs, or
+// (restrict_bwd) those of the accessible ones.
+hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, int32_t *la,
+                                uint32_t *na, int32_t *lb, uint32_t *nb, hipStream_t s);
 // Generation g of the forward (or backward) search: one kernel.
 hipError_t launch_generation(const Problem &P, const SearchArgs &S, bool forward, int g,
                              hipStream_t s);
