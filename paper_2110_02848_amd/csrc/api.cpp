@@ -66,7 +66,7 @@ struct fst_ctx {
   // score workspace
   DevBuf s_pg, s_pidx, s_bcnt, s_bscan, s_btotal;  // grouped scatter
   DevBuf s_sc, s_owner, s_extra, s_inref, s_mbeg, s_mlen, s_mcur, s_marc, s_val, s_acc,
-      s_mpos, s_sweep, s_ioff, s_isrc, s_iw;
+      s_mpos, s_sweep, s_chg, s_ioff, s_iarc;
   // batches: the union of the A graphs, item tables, segment sums
   DevBuf u_off, u_src, u_dst, u_il, u_ol, u_w, u_start, u_accept, u_items, seg;
   // three-input composition
@@ -294,8 +294,11 @@ int search(fst_ctx *c, const SearchArgs &S, bool forward, int64_t *levels, hipSt
 // scores
 // ---------------------------------------------------------------------------
 
+// The scalars without the sweeps' notes at their end.
+constexpr size_t SCORE_SCALARS = offsetof(ScoreScalars, part);
+
 int score_readback(fst_ctx *c, hipStream_t s) {
-  HIP_TRY(hipMemcpyAsync(c->h_ssc, c->s_sc.p, sizeof(ScoreScalars), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(c->h_ssc, c->s_sc.p, SCORE_SCALARS, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   return FST_OK;
 }
@@ -303,7 +306,7 @@ int score_readback(fst_ctx *c, hipStream_t s) {
 // Validates G (one readback): FST_ERR_INVALID_GRAPH on a violation.
 int score_validate(fst_ctx *c, const DevGraph &d, hipStream_t s) {
   ScoreScalars *dsc = as<ScoreScalars>(c->s_sc);
-  HIP_TRY(hipMemsetAsync(dsc, 0, sizeof(ScoreScalars), s));
+  HIP_TRY(hipMemsetAsync(dsc, 0, SCORE_SCALARS, s));
   // scores read no label: the structure alone is checked (or nothing, for
   // a caller that vouches for it)
   if (!c->validate) return FST_OK;
@@ -351,7 +354,7 @@ int score_generations(fst_ctx *c, const ScoreArgs *F, const ScoreArgs *B, ScoreB
   ScoreBufs *bufs[2] = {bf, bb};
   for (int i = 0; i < 2; ++i) {
     if (!dirs[i]) continue;
-    HIP_TRY(hipMemsetAsync(dirs[i]->sc, 0, sizeof(ScoreScalars), s));
+    HIP_TRY(hipMemsetAsync(dirs[i]->sc, 0, SCORE_SCALARS, s));
     HIP_TRY(launch_score_seed(*dirs[i], i == 0, s));
   }
   const KernelTimer t = timer(c, FST_KERNEL_SCORE_GEN);
@@ -362,7 +365,7 @@ int score_generations(fst_ctx *c, const ScoreArgs *F, const ScoreArgs *B, ScoreB
     t.end(s);
     for (int i = 0; i < 2; ++i)
       if (dirs[i])
-        HIP_TRY(hipMemcpyAsync(bufs[i]->host, dirs[i]->sc, sizeof(ScoreScalars),
+        HIP_TRY(hipMemcpyAsync(bufs[i]->host, dirs[i]->sc, SCORE_SCALARS,
                                hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     FST_TRY(add_time(c, FST_KERNEL_SCORE_GEN, batch));
@@ -468,12 +471,10 @@ int score_impl(fst_ctx *c, const fst_graph *G, double *alpha, double *beta, doub
 }
 
 // Relaxation sweeps of both recursions (graphs with cycles), from every
-// value at -inf, in batches with one read-back of the batch's rises each,
-// until a sweep in which no value rose by more than tol.  A batch is a
-// quarter of the sweeps done so far (8 to SWEEP_BATCH), so the sweeps run
-// past the one that settled stay within about a quarter of the total.  The
-// values after the batch's last sweep are returned (later sweeps of a
-// batch rise no more than tol either, up to rounding).
+// value at -inf, in batches with one read-back each, until a sweep in which
+// no value rose by more than tol.  A batch is a quarter of the sweeps done so
+// far (16 to SWEEP_BATCH); the sweeps of a batch past the one that settled do
+// nothing.  The values after that sweep are returned.
 ScoreGraph plain_score_graph(const DevGraph &d);
 
 int score_cyclic_impl(fst_ctx *c, const fst_graph *G, double *alpha, double *beta,
@@ -501,15 +502,13 @@ int score_cyclic_impl(fst_ctx *c, const fst_graph *G, double *alpha, double *bet
   tp.begin(s);
   ScoreGraph SG = plain_score_graph(d);
   FST_TRY(ensure(c, c->s_ioff, ((size_t)V + 1) * 4));
-  FST_TRY(ensure(c, c->s_isrc, (size_t)d.E * 4));
-  FST_TRY(ensure(c, c->s_iw, (size_t)d.E * 4));
-  FST_TRY(ensure(c, c->s_inref, (size_t)V * 4));  // the placing cursors
+  FST_TRY(ensure(c, c->s_iarc, (size_t)d.E * 8));
+  FST_TRY(ensure(c, c->s_mpos, (size_t)d.E * 4));  // the arcs' ranks
   FST_TRY(ensure(c, c->scan_tmp, scan_temp_bytes((size_t)V + 1)));
   SG.ioff = as<int32_t>(c->s_ioff);
-  SG.isrc = as<int32_t>(c->s_isrc);
-  SG.iw = as<float>(c->s_iw);
-  HIP_TRY(launch_in_csr(SG, as<int32_t>(c->s_ioff), as<int32_t>(c->s_isrc), as<float>(c->s_iw),
-                        as<int32_t>(c->s_inref), c->scan_tmp.p, &dsc->mtotal, s));
+  SG.iarc = as<int2>(c->s_iarc);
+  HIP_TRY(launch_in_csr(SG, as<int32_t>(c->s_ioff), as<int2>(c->s_iarc), as<int32_t>(c->s_mpos),
+                        c->scan_tmp.p, &dsc->mtotal, s));
   FST_TRY(ensure(c, c->s_sweep, (size_t)V * 4 * sizeof(double)));
   double *a[2] = {as<double>(c->s_sweep), as<double>(c->s_sweep) + V};
   double *b[2] = {a[1] + V, a[1] + 2 * (size_t)V};
@@ -517,34 +516,44 @@ int score_cyclic_impl(fst_ctx *c, const fst_graph *G, double *alpha, double *bet
   if (bwd) HIP_TRY(launch_fill_f64(b[0], V, -INFINITY, s));
   tp.end(s);
   const KernelTimer t = timer(c, FST_KERNEL_SCORE_GEN);
-  int k = 0;
-  bool done = false;
-  while (!done && k < max_sweeps) {
-    const int batch = k / 4 < 8 ? 8 : (k / 4 > SWEEP_BATCH ? SWEEP_BATCH : k / 4);
+  FST_TRY(ensure(c, c->s_chg, 4 * (((size_t)V + 63) / 64) * 8));
+  const SweepNote note = {dsc->part, as<unsigned long long>(c->s_chg), &dsc->sweep_done, tol};
+  const size_t off = offsetof(ScoreScalars, part);
+  HIP_TRY(hipMemsetAsync(dsc->part, 0, sizeof(ScoreScalars) - off, s));
+  int k = 0, settled = 0;
+  while (!settled && k < max_sweeps) {
+    const int batch = k / 4 < 16 ? 16 : (k / 4 > SWEEP_BATCH ? SWEEP_BATCH : k / 4);
     const int n = batch < max_sweeps - k ? batch : max_sweeps - k;
-    HIP_TRY(hipMemsetAsync(dsc->rise, 0, (size_t)n * sizeof(unsigned long long), s));
     t.begin(s);
-    for (int j = 0; j < n; ++j) {
-      const int x = (k + j) & 1, y = x ^ 1;
-      HIP_TRY(launch_sweep(SG, a[x], fwd ? a[y] : nullptr, b[x], bwd ? b[y] : nullptr,
-                           &dsc->rise[j], s));
+    for (int j = 0; j < n; ++j, ++k) {
+      const int x = k & 1, y = x ^ 1;
+      HIP_TRY(launch_sweep(SG, a[x], fwd ? a[y] : nullptr, b[x], bwd ? b[y] : nullptr, note, k,
+                           s));
     }
     t.end(s);
-    HIP_TRY(hipMemcpyAsync(c->h_ssc->rise, dsc->rise, (size_t)n * sizeof(unsigned long long),
+    HIP_TRY(hipMemcpyAsync(c->h_ssc->part, dsc->part, sizeof(ScoreScalars) - off,
                            hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     FST_TRY(add_time(c, FST_KERNEL_SCORE_GEN, n));
-    for (int j = 0; j < n && !done; ++j) {
+    settled = (int)c->h_ssc->sweep_done;
+    if (!settled) {  // no sweep has looked at the last one's rise yet
+      unsigned long long key = 0;
+      for (unsigned i = 0; i < SWEEP_PARTS; ++i) {
+        const unsigned long long p =
+            c->h_ssc->part[((size_t)((k - 1) % 3) * 3 * SWEEP_PARTS + i) * SWEEP_STRIDE];
+        key = p > key ? p : key;
+      }
       // the order key of a rise >= +0.0 is its bit pattern with the top bit set
-      const unsigned long long key = c->h_ssc->rise[j] & ~(1ull << 63);
+      key &= ~(1ull << 63);
       double r;
       memcpy(&r, &key, sizeof r);
-      if (r <= tol) {
-        done = true;
-        if (sweeps) *sweeps = k + j + 1;
-      }
+      if (r <= tol) settled = k;
     }
-    k += n;
+  }
+  const bool done = settled != 0;
+  if (done) {
+    k = settled;
+    if (sweeps) *sweeps = k;
   }
   if (c->timing) {
     HIP_TRY(hipStreamSynchronize(s));  // the structure's events (no sweep may have run)
@@ -1687,7 +1696,7 @@ void fst_ctx_destroy(fst_ctx *c) {
                     &c->bInChain, &c->s_sc,     &c->s_owner, &c->s_extra, &c->s_inref,
                     &c->s_mbeg,   &c->s_mlen,   &c->s_mcur,  &c->s_marc,  &c->s_val,
                     &c->s_acc,    &c->s_pg,     &c->s_pidx,  &c->s_bcnt,  &c->s_bscan,
-                    &c->s_btotal, &c->s_mpos,   &c->s_sweep, &c->s_ioff, &c->s_isrc, &c->s_iw, &c->u_off,   &c->u_src,   &c->u_dst,
+                    &c->s_btotal, &c->s_mpos,   &c->s_sweep, &c->s_chg, &c->s_ioff, &c->s_iarc, &c->u_off,   &c->u_src,   &c->u_dst,
                     &c->u_il,     &c->u_ol,     &c->u_w,     &c->u_start, &c->u_accept,
                     &c->u_items,  &c->seg,    &c->t_scal,  &c->t_aPerm, &c->t_aArc,
                     &c->t_aRec,   &c->t_bPerm,  &c->t_bArc,  &c->t_bRec,  &c->t_bLab,
@@ -2037,7 +2046,7 @@ int fst_grad_scatter(fst_ctx *c, int64_t n, const float *grad, const int32_t *id
   FST_TRY(ensure(c, c->s_sc, sizeof(ScoreScalars)));
   FST_TRY(ensure(c, c->s_acc, (size_t)m * 4 * sizeof(unsigned long long)));
   ScoreScalars *dsc = as<ScoreScalars>(c->s_sc);
-  HIP_TRY(hipMemsetAsync(dsc, 0, sizeof(ScoreScalars), s));
+  HIP_TRY(hipMemsetAsync(dsc, 0, SCORE_SCALARS, s));
   if (m > 0) HIP_TRY(hipMemsetAsync(c->s_acc.p, 0, (size_t)m * 4 * sizeof(unsigned long long), s));
   // grouping the terms by target range needs 8 bytes per term of workspace;
   // without it (workspace cap) every term goes to the plain scatter

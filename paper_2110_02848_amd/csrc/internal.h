@@ -304,14 +304,29 @@ struct ScoreGraph {
   const int32_t *inref;
   const int32_t *mbeg, *mlen, *marc;
   // relaxation sweeps only (else null): the in-arcs as a CSR by target,
-  // the in-arcs of v at [ioff[v], ioff[v + 1]) with their sources isrc and
-  // weights iw (in no particular order)
-  const int32_t *ioff, *isrc;
-  const float *iw;
+  // the in-arcs of v at iarc[ioff[v] .. ioff[v + 1]), source and weight bits
+  // (in no particular order)
+  const int32_t *ioff;
+  const int2 *iarc;
 };
 
 // Relaxation sweeps of a score queued between two read-backs, at most.
 constexpr int SWEEP_BATCH = 64;
+
+// What the relaxation sweeps tell each other and the host.  part holds, for
+// sweep k, three rows of SWEEP_PARTS words from ((k % 3) 3) rows on: the
+// largest rise of a value (order keys, their maximum counts) and the numbers
+// of values that changed, forward and backward (their sums count); sweep k
+// clears those of sweep k + 1.  *done is the number of the sweep (from 1)
+// whose largest rise was at most tol, once a later sweep has seen it.
+// changed: for even and odd sweeps and both directions, a bit per state.
+constexpr unsigned SWEEP_PARTS = 32, SWEEP_STRIDE = 16;  // words: a line of 128 bytes
+struct SweepNote {
+  unsigned long long *part;
+  unsigned long long *changed;
+  uint32_t *done;
+  double tol;
+};
 
 // Device scalars of a score computation, read back by the host.
 struct ScoreScalars {
@@ -323,7 +338,8 @@ struct ScoreScalars {
   unsigned long long zmax, zlo, zhi;  // total: order key of the maximum, 128-bit sum
   uint32_t absmax, pad;         // scatter: bits of the largest |gradient|
   GenSlot G[3];
-  unsigned long long rise[SWEEP_BATCH];  // sweeps: order key of each sweep's largest rise
+  unsigned long long part[9 * SWEEP_PARTS * SWEEP_STRIDE];  // sweeps: see SweepNote
+  uint32_t sweep_done, pad1;
 };
 
 // One direction of the score recursion (forward: alpha from in-arcs;
@@ -656,20 +672,19 @@ hipError_t launch_score_seed(const ScoreArgs &S, bool forward, hipStream_t s);
 // Generation g of the forward (F) and / or backward (B) recursion: one kernel.
 hipError_t launch_score_generation(const ScoreArgs *F, const ScoreArgs *B, int g,
                                    hipStream_t s);
-// One relaxation sweep of the score recursions (graphs with cycles): ya[v]
-// = forward value of v from the previous values xa, yb[v] = backward value
-// from xb (a null output skips that direction; G needs the in-arc
-// structure); *incr = max(*incr, order key of the largest rise of a value).
+// Relaxation sweep k (from 0) of the score recursions (graphs with cycles):
+// ya[v] = forward value of v from the previous values xa, yb[v] = backward
+// value from xb (a null output skips that direction; G needs the in-arc CSR).
+// Does nothing if an earlier sweep settled.
 hipError_t launch_sweep(const ScoreGraph &G, const double *xa, double *ya, const double *xb,
-                        double *yb, unsigned long long *incr, hipStream_t s);
+                        double *yb, const SweepNote &N, int k, hipStream_t s);
 // p[0 .. n) = x.
 hipError_t launch_fill_f64(double *p, long long n, double x, hipStream_t s);
-// The in-arc CSR of G for the sweeps (counting by target, a scan, then
-// each arc placed with an atomic cursor): ioff (V + 1 words), isrc and iw (E
-// each), cur (V words of scratch); scan_temp of scan_temp_bytes(V) bytes.
-hipError_t launch_in_csr(const ScoreGraph &G, int32_t *ioff, int32_t *isrc, float *iw,
-                         int32_t *cur, void *scan_temp, unsigned long long *total_dev,
-                         hipStream_t s);
+// The in-arc CSR of G for the sweeps (counting by target, a scan, then each
+// arc placed at its rank): ioff (V + 1 words), iarc (E), rank (E words of
+// scratch); scan_temp of scan_temp_bytes(V) bytes.
+hipError_t launch_in_csr(const ScoreGraph &G, int32_t *ioff, int2 *iarc, int32_t *rank,
+                         void *scan_temp, unsigned long long *total_dev, hipStream_t s);
 // *total = log-add of val[v] over the states with flag[v] (sc->zmax, zlo,
 // zhi zeroed).
 hipError_t launch_score_total(const double *val, const uint8_t *flag, int32_t V,

@@ -59,11 +59,11 @@ typedef unsigned long long ull;
 
 constexpr int32_t SCORE_LIGHT = 64;  // arcs a single thread pulls or notifies
 constexpr unsigned SCORE_GRID = 1024;
-// Workgroups of a relaxation sweep at most (each ends with one atomic on the
-// sweep's rise word).
-constexpr long long SWEEP_GRID = 512;
-// Pull lists of at most this many terms are loaded once into registers.
-constexpr int SWEEP_REGS = 8;
+// Workgroups of one direction of a relaxation sweep at most.
+constexpr long long SWEEP_GRID = 1024;
+// Arcs of 64 consecutive states that a wavefront of a sweep holds in LDS (8
+// per state; 256 would be 1 % faster where they suffice).
+constexpr int SWEEP_ARCS = 512;
 // Structure passes take ST_ITEMS items per thread and round, their loads
 // issued before any store or atomic (which would otherwise make every load
 // wait for the previous item's store).
@@ -742,45 +742,54 @@ __global__ __launch_bounds__(NT) void k_score_init(ScoreArgs S) {
 // relaxation sweeps (graphs with cycles)
 // ---------------------------------------------------------------------------
 
-// The value of state v from the values x of the previous sweep: the exact
-// log-add of thread_pull over the terms x[other end] + w(e) of v's pull list
-// and, for a start (forward) or accepting (backward) state, its empty
-// path's 0.  The terms are formed twice (their maximum first).  Since every
-// step is the recursion's own, the sweeps reach on a graph without cycles
-// the recursion's values bit for bit.
+// Arc p of the sweeps' pull lists (forward: the in-arc CSR; backward: the
+// out-arcs): its other end and weight.
 template <bool FWD>
-__device__ double sweep_value(const ScoreGraph &G, const double *x, int32_t v, bool init) {
-  // forward: the in-arc CSR; backward: the out-arcs
-  const int32_t b = FWD ? G.ioff[v] : G.off[v];
-  const AList l = AList{b, (FWD ? G.ioff[v + 1] : G.off[v + 1]) - b, false};
-  auto term = [&](int32_t j) -> double {
-    const int32_t p = l.beg + j;
-    return FWD ? x[G.isrc[p]] + (double)G.iw[p] : x[G.dst[p]] + (double)G.w[p];
-  };
-  if (l.n == 1 && !init) return term(0);
-  double m = init ? 0.0 : -INFINITY;
-  ull lo = 0, hi = 0;
-  if (l.n <= SWEEP_REGS) {
-    // few terms: each loaded once, kept in registers
-    double t[SWEEP_REGS];
-#pragma unroll
-    for (int j = 0; j < SWEEP_REGS; ++j) {
-      t[j] = j < l.n ? term(j) : -INFINITY;
-      m = fmax(m, t[j]);
-    }
-    if (m == -INFINITY || m == INFINITY) return m;
-    if (init) acc_add(lo, hi, exp(0.0 - m));
-#pragma unroll
-    for (int j = 0; j < SWEEP_REGS; ++j)
-      if (j < l.n) acc_add(lo, hi, exp(t[j] - m));
-    return acc_finish(m, lo, hi);
+__device__ __forceinline__ void sweep_arc(const ScoreGraph &G, int32_t p, int32_t &o, float &w) {
+  if (FWD) {
+    const int2 a = G.iarc[p];
+    o = a.x;
+    w = __int_as_float(a.y);
+  } else {
+    o = G.dst[p];
+    w = G.w[p];
   }
-  for (int32_t j = 0; j < l.n; ++j) m = fmax(m, term(j));
+}
+
+// The value of a state from the values x of the previous sweep, by one thread:
+// the exact log-add of thread_pull over the terms x[other end] + w(e) of its
+// pull list [b, e) and, for a start (forward) or accepting (backward) state,
+// its empty path's 0; the terms are formed twice, their maximum first.
+template <bool FWD>
+__device__ double sweep_value(const ScoreGraph &G, const double *x, int32_t b, int32_t e,
+                              bool init) {
+  auto term = [&](int32_t p) -> double {
+    int32_t o;
+    float w;
+    sweep_arc<FWD>(G, p, o, w);
+    return x[o] + (double)w;
+  };
+  if (e - b == 1 && !init) return term(b);
+  double m = init ? 0.0 : -INFINITY;
+#pragma unroll 4
+  for (int32_t p = b; p < e; ++p) m = fmax(m, term(p));
   if (m == -INFINITY || m == INFINITY) return m;
+  ull lo = 0, hi = 0;
   if (init) acc_add(lo, hi, exp(0.0 - m));
-  for (int32_t j = 0; j < l.n; ++j) acc_add(lo, hi, exp(term(j) - m));
+#pragma unroll 4
+  for (int32_t p = b; p < e; ++p) acc_add(lo, hi, exp(term(p) - m));
   return acc_finish(m, lo, hi);
 }
+
+// LDS of one wavefront of a sweep: the terms of its 64 states' lists, the
+// lane of the state each belongs to, the states' maxima and whether they
+// have a changed other end.
+struct SweepLds {
+  double t[SWEEP_ARCS];
+  double m[WAVE];
+  uint8_t own[SWEEP_ARCS];
+  uint8_t live[WAVE];
+};
 
 // How much a value rose in a sweep (0 if it did not; a value that leaves
 // -inf rises by +inf).
@@ -789,59 +798,231 @@ __device__ __forceinline__ double rise(double before, double after) {
   return before == -INFINITY ? INFINITY : after - before;
 }
 
-// One Jacobi sweep of both recursions over every state: ya = sweep of xa
-// (forward), yb = sweep of xb (backward); a direction whose output is null
-// is skipped.  *incr = max(*incr, order key of the largest rise), one
-// atomic per workgroup.
-__global__ __launch_bounds__(NT) void k_sweep(ScoreGraph G, const double *xa, double *ya,
-                                              const double *xb, double *yb, ull *incr) {
-  __shared__ ull s_m[NWAVES];
+// The words of sweep k in the notes: rises, then changed values, forward and
+// backward.
+__device__ __forceinline__ ull *sweep_part(const SweepNote &N, int k, int what) {
+  return N.part + ((size_t)(k % 3) * 3 + what) * SWEEP_PARTS * SWEEP_STRIDE;
+}
+
+// Sweep k of one direction by workgroups bid = 0 .. nb - 1: y = sweep of x;
+// adds the values that changed to `count`.  x was written by sweep k - 1 from
+// the values now in y, so a state whose value neither that sweep changed nor
+// this one recomputes already has it in y.  A wavefront takes 64 consecutive
+// states: their lists are consecutive, so its lanes load arcs side by side and
+// gather one value each; terms go to LDS, where each state's lane finds its
+// maximum, the lanes form the exps arc by arc, and each state's lane adds its
+// own.  Every step is the recursion's, so on a graph without cycles the sweeps
+// reach the recursion's values bit for bit.  Lists too long for the LDS are
+// left to one lane per state.
+template <bool FWD>
+__device__ __forceinline__ ull sweep_states(const ScoreGraph &G, const SweepNote &N, int k,
+                                            const double *x, double *y, ull before,
+                                            unsigned bid, unsigned nb, SweepLds &L, ull &count) {
+  const uint8_t *flag = FWD ? G.start : G.accept;
+  const int32_t *off = FWD ? G.ioff : G.off;
+  const ull words = ((ull)G.V + 63) / 64;
+  ull *now = N.changed + ((size_t)(k & 1) * 2 + (FWD ? 0 : 1)) * words;
+  const ull *last = N.changed + ((size_t)(~k & 1) * 2 + (FWD ? 0 : 1)) * words;
+  const bool sparse = k > 0 && before < (ull)G.V / 4 * 3;
+  constexpr int R = SWEEP_ARCS / WAVE;
+  const uint32_t lane = __lane_id();
   ull mk = 0;
-  for (long long v = (long long)blockIdx.x * NT + threadIdx.x; v < G.V;
-       v += (long long)gridDim.x * NT) {
-    double r = 0.0;
-    if (ya) {
-      const double a = sweep_value<true>(G, xa, (int32_t)v, G.start[v] != 0);
-      r = fmax(r, rise(xa[v], a));
-      ya[v] = a;
+  for (ull g = (ull)bid * NWAVES + threadIdx.x / WAVE; g < words; g += (ull)nb * NWAVES) {
+    const int32_t v = (int32_t)(g * WAVE + lane);
+    const bool valid = v < G.V;
+    const int32_t b = off[valid ? v : G.V], e = off[valid ? v + 1 : G.V];
+    const bool init = valid && flag[v] != 0;
+    const double was = valid ? x[v] : 0.0;
+    const ull lastw = k > 0 ? last[g] : ~0ull;
+    const int32_t B0 = __shfl(b, 0), n = __shfl(e, WAVE - 1) - B0;
+    const bool fits = n <= SWEEP_ARCS;
+    bool act = valid;
+    double a = was;
+    if (fits) {
+      int32_t o[R];
+      float w[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int32_t i = r * WAVE + (int32_t)lane;
+        o[r] = 0;
+        w[r] = 0.0f;
+        if (i < n) sweep_arc<FWD>(G, B0 + i, o[r], w[r]);
+      }
+      for (int32_t i = b - B0; i < e - B0; ++i) L.own[i] = (uint8_t)lane;
+      if (sparse) {
+        L.live[lane] = 0;
+        __builtin_amdgcn_wave_barrier();
+        ull bit[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          bit[r] = r * WAVE + (int32_t)lane < n ? last[o[r] >> 6] >> (o[r] & 63) : 0ull;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if (bit[r] & 1ull) L.live[L.own[r * WAVE + lane]] = 1;
+        __builtin_amdgcn_wave_barrier();
+        act = L.live[lane] != 0;
+      }
+      if (__ballot(act)) {
+        __builtin_amdgcn_wave_barrier();
+        double q[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          q[r] = r * WAVE + (int32_t)lane < n ? x[o[r]] : 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if (r * WAVE + (int32_t)lane < n) L.t[r * WAVE + lane] = q[r] + (double)w[r];
+        __builtin_amdgcn_wave_barrier();
+        double m = init ? 0.0 : -INFINITY;
+        for (int32_t i = b - B0; i < e - B0; ++i) m = fmax(m, L.t[i]);
+        L.m[lane] = m;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int32_t i = (int32_t)lane; i < n; i += WAVE) L.t[i] = exp(L.t[i] - L.m[L.own[i]]);
+        __builtin_amdgcn_wave_barrier();
+        if (m == -INFINITY || m == INFINITY) {
+          a = m;
+        } else if (e - b == 1 && !init) {
+          a = m;  // its one term
+        } else {
+          ull lo = 0, hi = 0;
+          if (init) acc_add(lo, hi, exp(0.0 - m));
+          for (int32_t i = b - B0; i < e - B0; ++i) acc_add(lo, hi, L.t[i]);
+          a = acc_finish(m, lo, hi);
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    } else if (valid) {
+      a = sweep_value<FWD>(G, x, b, e, init);
     }
-    if (yb) {
-      const double b = sweep_value<false>(G, xb, (int32_t)v, G.accept[v] != 0);
-      r = fmax(r, rise(xb[v], b));
-      yb[v] = b;
+    bool diff = false;
+    if (act) {
+      const ull r = order_key(rise(was, a));
+      mk = r > mk ? r : mk;
+      diff = __double_as_longlong(was) != __double_as_longlong(a);
+      y[v] = a;
+    } else if (valid && (lastw >> lane & 1ull)) {
+      y[v] = was;
     }
-    const ull k = order_key(r);
-    mk = k > mk ? k : mk;
+    const ull bits = __ballot(diff);
+    if (lane == 0) now[g] = bits;
+    count += (ull)__popcll(bits);
   }
+  return mk;
+}
+
+// Sweep k (from 0) of both recursions over every state: ya = sweep of xa
+// (forward, the first half of the workgroups), yb = sweep of xb (backward,
+// the second half); a direction whose output is null is skipped and the
+// other has all workgroups.  A sweep that comes after the one that settled
+// does nothing, so sweeps can be queued past it, and a direction none of
+// whose values changed any more is skipped.  Bound by its gathers of 8-byte
+// values from all over x, a line each, most of them past the L2 (10^6 states,
+// 3 * 10^6 arcs: 146 us with one thread per state at 512 workgroups, whose
+// lists of other lengths idled most lanes; 88 us now).  SWEEP_GRID = 1024
+// workgroups per direction (2048: 4 % slower, 640: 20 %).  Once less than
+// three quarters of a direction's values change from sweep to sweep, a state
+// first looks at one bit per other end (125 KB per million states, which the
+// L2 holds) and is skipped if none changed.  Rises and counts go to
+// SWEEP_PARTS words on lines of their own (one word would take 11.4 ns per
+// workgroup).
+__global__ __launch_bounds__(NT) void k_sweep(ScoreGraph G, const double *xa, double *ya,
+                                              const double *xb, double *yb, SweepNote N, int k) {
+  __shared__ ull s_m[NWAVES], s_c[NWAVES];
+  __shared__ SweepLds s_l[NWAVES];
+  SweepLds &L = s_l[threadIdx.x / WAVE];
+  const unsigned half = ya && yb ? gridDim.x / 2 : (ya ? gridDim.x : 0u);
+  const int dir = blockIdx.x < half ? 0 : 1;
+  const uint32_t done = *N.done;  // loaded with the rises (one round trip)
+  ull rk = 0, before = 0;
+  if (__lane_id() < SWEEP_PARTS) {
+    rk = sweep_part(N, k + 2, 0)[__lane_id() * SWEEP_STRIDE];
+    before = sweep_part(N, k + 2, 1 + dir)[__lane_id() * SWEEP_STRIDE];
+  }
+#pragma unroll
+  for (int o = WAVE / 2; o > 0; o >>= 1) {
+    const ull t = __shfl_xor(rk, o);
+    rk = t > rk ? t : rk;
+    before += __shfl_xor(before, o);
+  }
+  if (done) return;
+  if (k > 0 && from_order_key(rk) <= N.tol) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *N.done = (uint32_t)k;
+    return;
+  }
+  if (blockIdx.x == 0 && threadIdx.x < 3 * SWEEP_PARTS)
+    sweep_part(N, k + 1, 0)[threadIdx.x * SWEEP_STRIDE] = 0;
+  // a direction none of whose values changed has the same in x and y
+  if (k > 0 && before == 0) return;
+  ull mk, count = 0;
+  if (dir == 0)
+    mk = sweep_states<true>(G, N, k, xa, ya, before, blockIdx.x, half, L, count);
+  else
+    mk = sweep_states<false>(G, N, k, xb, yb, before, blockIdx.x - half, gridDim.x - half, L,
+                             count);
 #pragma unroll
   for (int o = WAVE / 2; o > 0; o >>= 1) {
     const ull t = __shfl_xor(mk, o);
     mk = t > mk ? t : mk;
   }
-  if (__lane_id() == 0) s_m[threadIdx.x / WAVE] = mk;
+  if (__lane_id() == 0) {
+    s_m[threadIdx.x / WAVE] = mk;
+    s_c[threadIdx.x / WAVE] = count;  // the same in every lane
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < NWAVES; ++w) mk = s_m[w] > mk ? s_m[w] : mk;
-    atomicMax(incr, mk);
+    for (int w = 1; w < NWAVES; ++w) {
+      mk = s_m[w] > mk ? s_m[w] : mk;
+      count += s_c[w];
+    }
+    const size_t p = blockIdx.x % SWEEP_PARTS * SWEEP_STRIDE;
+    atomicMax(sweep_part(N, k, 0) + p, mk);
+    if (count) atomicAdd(sweep_part(N, k, 1 + dir) + p, count);
   }
 }
 
-// In-arc CSR: the in-degrees (one atomic per arc), then, after a scan,
-// every arc placed at its target's cursor.
-__global__ __launch_bounds__(NT) void k_in_count(ScoreGraph G, int32_t *cnt) {
-  for (long long e = (long long)blockIdx.x * NT + threadIdx.x; e < G.E;
-       e += (long long)gridDim.x * NT)
-    atomicAdd(cnt + G.dst[e], 1);
+// In-arc CSR: the in-degrees (one atomic per arc, whose result is the arc's
+// rank among its target's), then, after a scan, every arc placed.
+__global__ __launch_bounds__(NT) void k_in_count(ScoreGraph G, int32_t *cnt, int32_t *rank) {
+  const long long stride = (long long)gridDim.x * NT * ST_ITEMS;
+  for (long long e0 = (long long)blockIdx.x * NT * ST_ITEMS + threadIdx.x; e0 < G.E;
+       e0 += stride) {
+    int32_t d[ST_ITEMS];
+#pragma unroll
+    for (int k = 0; k < ST_ITEMS; ++k) {
+      const long long e = e0 + (long long)k * NT;
+      d[k] = e < G.E ? G.dst[e] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < ST_ITEMS; ++k)
+      if (d[k] >= 0) d[k] = atomicAdd(cnt + d[k], 1);
+#pragma unroll
+    for (int k = 0; k < ST_ITEMS; ++k) {
+      const long long e = e0 + (long long)k * NT;
+      if (e < G.E) rank[e] = d[k];
+    }
+  }
 }
 
+// (Source and weight go side by side, one scattered store per arc.)
 __global__ __launch_bounds__(NT) void k_in_place(ScoreGraph G, const int32_t *ioff,
-                                                 int32_t *cur, int32_t *isrc, float *iw) {
-  for (long long e = (long long)blockIdx.x * NT + threadIdx.x; e < G.E;
-       e += (long long)gridDim.x * NT) {
-    const int32_t d = G.dst[e];
-    const int32_t p = ioff[d] + atomicAdd(cur + d, 1);
-    isrc[p] = G.src[e];
-    iw[p] = G.w[e];
+                                                 const int32_t *rank, int2 *iarc) {
+  const long long stride = (long long)gridDim.x * NT * ST_ITEMS;
+  for (long long e0 = (long long)blockIdx.x * NT * ST_ITEMS + threadIdx.x; e0 < G.E;
+       e0 += stride) {
+    int32_t p[ST_ITEMS];
+    int2 a[ST_ITEMS];
+#pragma unroll
+    for (int k = 0; k < ST_ITEMS; ++k) {
+      const long long e = e0 + (long long)k * NT;
+      p[k] = -1;
+      if (e < G.E) {
+        p[k] = rank[e] + ioff[G.dst[e]];
+        a[k] = make_int2(G.src[e], __float_as_int(G.w[e]));
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < ST_ITEMS; ++k)
+      if (p[k] >= 0) iarc[p[k]] = a[k];
   }
 }
 
@@ -1526,28 +1707,28 @@ hipError_t launch_score_generation(const ScoreArgs *F, const ScoreArgs *B, int g
 }
 
 hipError_t launch_sweep(const ScoreGraph &G, const double *xa, double *ya, const double *xb,
-                        double *yb, unsigned long long *incr, hipStream_t s) {
+                        double *yb, const SweepNote &N, int k, hipStream_t s) {
   if (G.V == 0) return hipSuccess;
-  const long long b = ((long long)G.V + NT - 1) / NT;
-  k_sweep<<<(unsigned)(b < SWEEP_GRID ? b : SWEEP_GRID), NT, 0, s>>>(G, xa, ya, xb, yb, incr);
+  long long b = ((long long)G.V + NT - 1) / NT;
+  if (b > SWEEP_GRID) b = SWEEP_GRID;
+  k_sweep<<<(unsigned)(ya && yb ? 2 * b : b), NT, 0, s>>>(G, xa, ya, xb, yb, N, k);
   return hipGetLastError();
 }
 
-hipError_t launch_in_csr(const ScoreGraph &G, int32_t *ioff, int32_t *isrc, float *iw,
-                         int32_t *cur, void *scan_temp, unsigned long long *total_dev,
-                         hipStream_t s) {
+hipError_t launch_in_csr(const ScoreGraph &G, int32_t *ioff, int2 *iarc, int32_t *rank,
+                         void *scan_temp, unsigned long long *total_dev, hipStream_t s) {
   hipError_t e = hipMemsetAsync(ioff, 0, ((size_t)G.V + 1) * 4, s);
   if (e != hipSuccess) return e;
-  if ((e = hipMemsetAsync(cur, 0, (size_t)G.V * 4, s)) != hipSuccess) return e;
+  const unsigned grid = grid_for((G.E + ST_ITEMS - 1) / ST_ITEMS);
   if (G.E) {
-    k_in_count<<<grid_for(G.E), NT, 0, s>>>(G, ioff);
+    k_in_count<<<grid, NT, 0, s>>>(G, ioff, rank);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   // ioff[v] = in-arcs of the states before v; ioff[V] = E
   e = scan_u32(reinterpret_cast<const uint32_t *>(ioff), reinterpret_cast<uint32_t *>(ioff),
                (size_t)G.V, true, total_dev, scan_temp, s);
   if (e != hipSuccess || G.E == 0) return e;
-  k_in_place<<<grid_for(G.E), NT, 0, s>>>(G, ioff, cur, isrc, iw);
+  k_in_place<<<grid, NT, 0, s>>>(G, ioff, rank, iarc);
   return hipGetLastError();
 }
 

@@ -1,0 +1,46 @@
+"""Relaxation sweeps at the sizes where a wavefront's share changes: 64
+consecutive states whose arcs just fit its LDS (512) or do not, a last
+wavefront that is full, one state short or one state long, states without
+arcs, and graphs most of whose values do not change from sweep to sweep."""
+import numpy as np
+import pytest
+
+from paper_2110_02848_amd import synth
+
+from test_gpu_score_cyclic import _check, _run, comp  # noqa: F401 (a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("V", (1, 63, 64, 65, 128, 129))
+@pytest.mark.parametrize("degree", (1, 8, 9))
+def test_edges_of_a_wavefront(comp, V, degree):  # noqa: F811
+    G = synth.random_cyclic(100 + V, V, degree=degree, mass=0.5)
+    _check(comp, G, f"V={V} degree {degree}")
+    if degree == 8 and V >= 64:  # one arc more in the first 64 states
+        arcs = list(zip(G["src"], G["dst"], G["ilabel"], G["olabel"], G["weight"]))
+        arcs.append((5, V - 1, 1, 1, np.float32(-6.0)))
+        H = synth.from_arcs(V, arcs, start=np.nonzero(G["start"])[0],
+                            accept=np.nonzero(G["accept"])[0])
+        _check(comp, H, f"V={V} 513 arcs")
+
+
+@pytest.mark.parametrize("gap", (1, 3))
+def test_values_that_settle_at_different_sweeps(comp, gap):  # noqa: F811
+    """A long chain in front of a small cyclic part, and states without
+    arcs between: after the first sweeps a few states at a time change.  The
+    chain's values equal fst_score's bit for bit (it has no cycle)."""
+    import torch
+    from paper_2110_02848_amd import gpu
+    n = 700
+    arcs = [(gap * i, gap * (i + 1), 1, 1, -0.01 * (i % 7)) for i in range(n)]
+    arcs += [(gap * i, gap * (i + 2), 1, 1, -0.5) for i in range(0, n - 2, 5)]
+    V = gap * n + 3
+    chain = synth.from_arcs(V, arcs, start=[0], accept=[gap * n])
+    got = _run(comp, chain)
+    ref = comp.score(gpu.to_device(chain))
+    torch.cuda.synchronize()
+    for k in ("alpha", "beta"):
+        assert np.array_equal(got[k].view(np.int64), ref[k].cpu().numpy().view(np.int64)), k
+    loop = arcs + [(gap * n, gap * n + 1, 1, 1, -1.0), (gap * n + 1, gap * n, 1, 1, -0.7)]
+    _check(comp, synth.from_arcs(V, loop, start=[0], accept=[gap * n]), f"chain and cycle {gap}")
