@@ -344,28 +344,11 @@ __device__ __forceinline__ void settle(const ScoreArgs &S, const ScoreNext &nx, 
     // a forward merge's term goes to its in-list position (contiguous pull)
     if (slot < 0) slot = FWD ? S.G.E + S.mpos[e] : (long long)e;
     S.term[slot] = t;
-    // the lanes of the wavefront here that reach the same state count its
-    // pending counter down with one atomic (the lane that takes it to zero
-    // lists it) and raise its largest term with one atomic; one round per
-    // distinct state
-    const ull key = order_key(t);
-    ull rem = __ballot(true);
-    ready = false;
-    while (rem) {
-      const int leader = __ffsll((long long)rem) - 1;
-      const ull gm = __ballot(y == __shfl(y, leader));
-      ull kmax = 0;
-      for (ull b = gm; b; b &= b - 1) {
-        const ull o = __shfl(key, __ffsll((long long)b) - 1);
-        kmax = o > kmax ? o : kmax;
-      }
-      if ((int)__lane_id() == leader) {
-        atomicMax(S.mkey + y, kmax);
-        const int32_t k = (int32_t)__popcll(gm);
-        ready = atomicSub(S.pend + y, k) == k;
-      }
-      rem &= ~gm;
-    }
+    // every lane raises its state's largest term and counts its pending
+    // counter down by itself, all lanes at once (lanes that reach the same
+    // state are one request); the lane that takes it to zero lists it
+    atomicMax(S.mkey + y, order_key(t));
+    ready = atomicSub(S.pend + y, 1) == 1;
   }
   if (walk) {
     next = y;
