@@ -62,7 +62,7 @@ struct fst_ctx {
   DevBuf aOutPerm, aOutArc, aOutRec, aOutLut, bOutPerm, bOutArc, bOutRec, bOutLut;
   DevBuf aOutLab, aOutW, bOutLab, bOutW, bOutChain, bInChain;
   DevBuf aInOff, aInPerm, aInArc, aInRec, aInLut, bInOff, bInPerm, bInArc, bInRec, bInLut;
-  DevBuf vis, coacc, trim, wbase, fq, bq, fcnt, heavy, hoff, heavy2, hoff2, cnt, btot;
+  DevBuf vis, coacc, trim, wbase, fq, bq, fcnt, lin_f, lin_n, lin_m, heavy, hoff, heavy2, hoff2, cnt, btot;
   // score workspace
   DevBuf s_pg, s_pidx, s_bcnt, s_bscan, s_btotal;  // grouped scatter
   DevBuf s_sc, s_owner, s_extra, s_inref, s_mbeg, s_mlen, s_mcur, s_marc, s_val, s_acc,
@@ -634,6 +634,37 @@ int search_concurrent(fst_ctx *c, Problem P, const SearchArgs &SF, const SearchA
   return FST_OK;
 }
 
+// Both directions of a linear search, generation after generation in the same
+// kernels, until neither has work waiting.
+int search_linear(fst_ctx *c, const LinearArgs &F, const LinearArgs &B, hipStream_t s) {
+  const KernelTimer t = timer(c, FST_KERNEL_SEARCH_FORWARD);
+  // the first batch covers as many launches as the last search took
+  int g = 0, batch = c->gen_hint > 16 ? (c->gen_hint < 256 ? c->gen_hint : 256) : 16;
+  for (;;) {
+    t.begin(s);
+    for (int b = 0; b < batch; ++b, ++g) HIP_TRY(launch_linear(F, B, g, s));
+    t.end(s);
+    FST_TRY(readback(c, s));
+    FST_TRY(add_time(c, FST_KERNEL_SEARCH_FORWARD, batch));
+    const Scalars &h = *c->h_sc;
+    if (h.overflow) return FST_ERR_TOO_LARGE;
+    uint32_t any = 0;
+    for (int d = 0; d < 2; ++d) {
+      any |= (uint32_t)h.GL[d][g & 3].hpack;
+      for (uint32_t i = 0; i < SUBQ; ++i) any |= h.front[d][(g & 3) * SUBQ + i];
+    }
+    if (!any) break;
+    batch = 16;
+  }
+  c->stats.fwd_levels = c->h_sc->gens;
+  c->stats.bwd_levels = c->h_sc->gens2;
+  c->gen_hint = (int)(c->h_sc->gens > c->h_sc->gens2 ? c->h_sc->gens : c->h_sc->gens2);
+  return FST_OK;
+}
+
+// Masks of a linear search are kept when they take at most this much.
+constexpr size_t LINEAR_MASKS = (size_t)64 << 20;
+
 // Label buckets are kept when the table is at most this large, and at most
 // LUT_PER_ARC times the size of the graph's arc records (a graph with few
 // arcs per state finds a label in its short groups about as fast, and its
@@ -673,9 +704,9 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     HIP_TRY(launch_validate(dB, 1, &d_sc->errB, &d_sc->maxLabB, s, &d_sc->naccB, c->validate,
                             &d_sc->singleB));
   FST_TRY(readback(c, s));
-  const uint32_t info_bits = 1u << 16;  // validation's "not in label order" note
-  if ((c->h_sc->errA & ~info_bits) || (c->h_sc->errB & ~info_bits)) return FST_ERR_INVALID_GRAPH;
-  const bool presortedA = !(c->h_sc->errA & info_bits), presortedB = !(c->h_sc->errB & info_bits);
+  if ((c->h_sc->errA | c->h_sc->errB) & ~INFO_NOTES) return FST_ERR_INVALID_GRAPH;
+  const bool presortedA = !(c->h_sc->errA & INFO_UNSORTED);
+  const bool presortedB = !(c->h_sc->errB & INFO_UNSORTED);
   c->stats = fst_stats{};
   if (VA == 0 || VB == 0) return finish_empty(c, V_C, E_C);
 
@@ -781,31 +812,65 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   const unsigned long long capll = 2ull * (unsigned long long)VA * (unsigned long long)VB;
   const unsigned long long cap_full = capll < nkeys ? capll : nkeys;  // <= nkeys < 2^32
   unsigned long long cap_try = c->list_hint ? c->list_hint : c->list_start;
+  // Where the workspace has no room for a linear search the keys are followed
+  // one by one, then lists a quarter as long are tried.
+  bool try_linear = true, grew = false, linear = false;
   uint32_t *wbase = nullptr;
   for (;;) {
     const uint32_t cap = (uint32_t)(cap_try < cap_full ? cap_try : cap_full);
     auto searches = [&]() -> int {
-    FST_TRY(ensure(c, c->vis, snwords * 4));
-    FST_TRY(ensure(c, c->coacc, snwords * 4));
+    // Threads follow keys depth-first where most states of B have a single
+    // out-arc (a lexicon: a word's keys are one thread's walk and jumps);
+    // otherwise a level search spreads the units of every level over lanes.
+    const bool chains = c->chain_depth > 0 && 2ull * c->h_sc->singleB > (unsigned long long)VB;
+    // Where A is linear as well, the chains are followed 64 keys at a time:
+    // both directions need a row of bits per state of B and three such
+    // buffers for the bits that wait.
+    const uint32_t W = (uint32_t)(((size_t)VA + 63) / 64), nlab = maxA + 1;
+    const size_t rows = (size_t)VB * W, masks = ((size_t)nlab + 2) * (W + 2);
+    linear = try_linear && chains && c->order == FST_ORDER_CONCURRENT && EA > 0 &&
+             !(c->h_sc->errA & INFO_NOT_LINEAR) && rows < 0xffffffffull &&
+             masks * 8 <= LINEAR_MASKS;
+    if (linear) {
+      FST_TRY(ensure(c, c->lin_f, 2 * rows * 8));
+      FST_TRY(ensure(c, c->lin_n, 6 * rows * 8));
+      FST_TRY(ensure(c, c->lin_m, masks * 8));
+    }
+    if (!linear) {
+      FST_TRY(ensure(c, c->vis, snwords * 4));
+      FST_TRY(ensure(c, c->coacc, snwords * 4));
+    }
     FST_TRY(ensure(c, c->trim, nwords * 4));
     FST_TRY(ensure(c, c->wbase, nwords * 4));
     // two generations of a frontier of cap keys in SUBQ parts, per search
     const uint32_t rc = (cap + SUBQ - 1) / SUBQ;
-    const size_t fbytes = 2 * (size_t)SUBQ * rc * 4;
+    // (a linear search: four)
+    const size_t fbytes = (linear ? 4 : 2) * (size_t)SUBQ * rc * 4;
     FST_TRY(ensure(c, c->fq, fbytes));
     if (c->order == FST_ORDER_CONCURRENT) FST_TRY(ensure(c, c->bq, fbytes));
     FST_TRY(ensure(c, c->fcnt, 2 * FRONT_WORDS * 4));
-    FST_TRY(ensure(c, c->heavy, (size_t)cap * 4));
-    FST_TRY(ensure(c, c->hoff, (size_t)cap * 4));
-    if (c->order == FST_ORDER_CONCURRENT) {
-      FST_TRY(ensure(c, c->heavy2, (size_t)cap * 4));
-      FST_TRY(ensure(c, c->hoff2, (size_t)cap * 4));
+    if (linear) {
+      FST_TRY(ensure(c, c->heavy, (size_t)cap * sizeof(int4)));
+      FST_TRY(ensure(c, c->heavy2, (size_t)cap * sizeof(int4)));
+    } else {
+      FST_TRY(ensure(c, c->heavy, (size_t)cap * 4));
+      FST_TRY(ensure(c, c->hoff, (size_t)cap * 4));
+      if (c->order == FST_ORDER_CONCURRENT) {
+        FST_TRY(ensure(c, c->heavy2, (size_t)cap * 4));
+        FST_TRY(ensure(c, c->hoff2, (size_t)cap * 4));
+      }
     }
     FST_TRY(ensure(c, c->lists, ((size_t)VA + VB + 2) * 4));
     size_t scan_n = nwords > (size_t)cap + 1 ? nwords : (size_t)cap + 1;
     FST_TRY(ensure(c, c->scan_tmp, scan_temp_bytes(scan_n)));
-    HIP_TRY(hipMemsetAsync(c->vis.p, 0, snwords * 4, s));
-    HIP_TRY(hipMemsetAsync(c->coacc.p, 0, snwords * 4, s));
+    if (linear) {
+      HIP_TRY(hipMemsetAsync(c->lin_f.p, 0, 2 * rows * 8, s));
+      HIP_TRY(hipMemsetAsync(c->lin_n.p, 0, 6 * rows * 8, s));
+      HIP_TRY(hipMemsetAsync(c->lin_m.p, 0, masks * 8, s));
+    } else {
+      HIP_TRY(hipMemsetAsync(c->vis.p, 0, snwords * 4, s));
+      HIP_TRY(hipMemsetAsync(c->coacc.p, 0, snwords * 4, s));
+    }
 
     Problem &P = c->P;
     P = Problem{};
@@ -819,10 +884,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     P.maskB = (1u << shiftB) - 1u;
     P.rowA = (uint32_t)rowA;
     P.chain_max = c->chain_depth;
-    // Threads follow keys depth-first where most states of B have a single
-    // out-arc (a lexicon: a word's keys are one thread's walk and jumps);
-    // otherwise a level search spreads the units of every level over lanes.
-    P.chains = c->chain_depth > 0 && 2ull * c->h_sc->singleB > (unsigned long long)VB;
+    P.chains = chains;
     P.vis = as<uint32_t>(c->vis);
     P.coacc = as<uint32_t>(c->coacc);
     P.trim = as<uint32_t>(c->trim);
@@ -853,7 +915,44 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     };
     wbase = as<uint32_t>(c->wbase);
     phase_end(c, PH_PRE, s);
-    if (c->order == FST_ORDER_CONCURRENT) {
+    if (linear) {
+      LinearArgs F = {}, G = {};
+      F.v = views[1];
+      F.M = as<unsigned long long>(c->lin_m);
+      F.F = as<unsigned long long>(c->lin_f);
+      F.N = as<unsigned long long>(c->lin_n);
+      F.W = W;
+      F.VB = (uint32_t)VB;
+      F.nlab = nlab;
+      F.chain_max = c->chain_depth;
+      F.Q = Frontier{as<uint32_t>(c->fq), rc, 1, d_sc->front[0]};
+      F.heavy = as<int4>(c->heavy);
+      F.cap = cap;
+      F.sc = d_sc;
+      F.G = d_sc->GL[0];
+      F.gens = &d_sc->gens;
+      G = F;
+      G.v = views[3];
+      G.F += rows;
+      G.N += 3 * rows;
+      G.Q = Frontier{as<uint32_t>(c->bq), rc, 1, d_sc->front[1]};
+      G.heavy = as<int4>(c->heavy2);
+      G.G = d_sc->GL[1];
+      G.gens = &d_sc->gens2;
+      phase_begin(c, PH_FWD, s);
+      HIP_TRY(launch_linear_masks(dA, W, nlab, as<unsigned long long>(c->lin_m), s));
+      HIP_TRY(launch_linear_seed(F, G, dB, s));
+      FST_TRY(search_linear(c, F, G, s));
+      HIP_TRY(launch_linear_rows(F, G, dB, s));
+      P.linW = W;
+      P.vis = as<uint32_t>(c->lin_f);
+      HIP_TRY(launch_popcount(P.vis, 2 * rows, &d_sc->naccessible, s));
+      if (c->count_moves) HIP_TRY(launch_count_moves(P, 2 * rows, true, &d_sc->generated, s));
+      phase_end(c, PH_FWD, s);
+      phase_begin(c, PH_BWD, s);
+      HIP_TRY(launch_linear_trim(P, F.F, G.F, W, as<uint32_t>(c->trim), wbase, s));
+      phase_end(c, PH_BWD, s);
+    } else if (c->order == FST_ORDER_CONCURRENT) {
       // The forward search's first generations run alone (listing accepting
       // keys as in the forward-first order).  If it has ended by then, the
       // backward search follows as in that order; otherwise a backward search
@@ -896,7 +995,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
         phase_end(c, PH_BWD, s);
       } else {
         SearchArgs SB = S;
-        SB.Q = Frontier{as<uint32_t>(c->bq), rc, S.Q.stride, S.Q.cnt + 3 * SUBQ * S.Q.stride};
+        SB.Q = Frontier{as<uint32_t>(c->bq), rc, S.Q.stride, P.chains ? d_sc->front[1] : S.Q.cnt + FRONT_WORDS};
         SB.heavy = as<uint32_t>(c->heavy2);
         SB.hoff = as<uint32_t>(c->hoff2);
         SB.G = d_sc->G2;
@@ -964,9 +1063,21 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     const int rc = searches();
     if (rc == FST_ERR_TOO_LARGE && c->h_sc->overflow && (unsigned long long)cap < cap_full) {
       cap_try = 4ull * cap;
+      grew = true;
       // the search scalars start again from zero (validation's stay)
       HIP_TRY(hipMemsetAsync(&d_sc->heavy, 0,
                              sizeof(Scalars) - offsetof(Scalars, heavy), s));
+      continue;
+    }
+    if (rc == FST_ERR_NOMEM && (linear || (!grew && cap > 1024))) {
+      if (!linear) cap_try = cap / 4;
+      try_linear = false;
+      HIP_TRY(hipDeviceSynchronize());
+      for (DevBuf *b : {&c->lin_f, &c->lin_n, &c->lin_m, &c->fq, &c->bq, &c->heavy, &c->hoff,
+                        &c->heavy2, &c->hoff2}) {
+        c->ws_total -= b->cap;
+        release(*b);
+      }
       continue;
     }
     FST_TRY(rc);
@@ -1120,9 +1231,9 @@ int compose3_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, const fst_
   if (dB.V) HIP_TRY(launch_validate(dB, 1, &d3->errB, &d3->maxB, s, nullptr, c->validate));
   if (dD.V) HIP_TRY(launch_validate(dD, 1, &d3->errD, &d3->maxD, s, nullptr, c->validate));
   FST_TRY(readback3(c, s));
-  const uint32_t info = 1u << 16;  // validation's "not in label order" note
+  const uint32_t info = INFO_UNSORTED;
   const Scal3 v = *c->h_s3;
-  if ((v.errA & ~info) || (v.errB & ~info) || (v.errD & ~info)) return FST_ERR_INVALID_GRAPH;
+  if ((v.errA | v.errB | v.errD) & ~INFO_NOTES) return FST_ERR_INVALID_GRAPH;
   c->c3.stats = fst_stats{};
   if (dA.V == 0 || dB.V == 0 || dD.V == 0) {
     c->c3.n = c->c3.U = c->c3.narcs = 0;
@@ -1485,7 +1596,7 @@ int batch_impl(fst_ctx *c, const fst_graph *A, int32_t n, const fst_graph *B, hi
       HIP_TRY(launch_validate(dev_graph(&A[i]), 0, &d_sc->errA, &d_sc->maxLabA, s, nullptr,
                               c->validate));
   FST_TRY(readback(c, s));
-  if (c->h_sc->errA & ~(1u << 16)) return FST_ERR_INVALID_GRAPH;
+  if (c->h_sc->errA & ~INFO_NOTES) return FST_ERR_INVALID_GRAPH;
 
   // Parts: consecutive items whose union has a key space below 2^32 (with
   // its A states rounded up to 64 for the search layout, as the run checks)
@@ -1690,7 +1801,7 @@ void fst_ctx_destroy(fst_ctx *c) {
                     &c->bOutLut,  &c->aInOff,   &c->aInPerm, &c->aInArc,  &c->aInRec,
                     &c->aInLut,   &c->bInOff,   &c->bInPerm, &c->bInArc,  &c->bInRec,
                     &c->bInLut,   &c->vis,      &c->coacc,   &c->trim,    &c->wbase,   &c->heavy2,
-                    &c->hoff2,    &c->fq,       &c->fcnt,
+                    &c->hoff2,    &c->fq,       &c->fcnt,     &c->lin_f,   &c->lin_n,   &c->lin_m,
                     &c->bq,       &c->heavy,    &c->hoff,    &c->cnt,     &c->aOutLab,
                     &c->aOutW,    &c->bOutLab,  &c->bOutW,   &c->btot,    &c->bOutChain,
                     &c->bInChain, &c->s_sc,     &c->s_owner, &c->s_extra, &c->s_inref,

@@ -22,10 +22,6 @@ namespace {
 typedef unsigned long long ull;
 
 enum : uint32_t { ERR_OFFSETS = 1, ERR_SRC = 2, ERR_DST = 4, ERR_LABEL = 8, ERR_FLAG = 16 };
-// Validation also notes whether some state's arcs are not ordered by the
-// matched label (then the out-view is sorted; otherwise it is the input).
-constexpr uint32_t INFO_UNSORTED = 1u << 16;
-
 unsigned grid_for(size_t n, unsigned cap = 4096) {
   size_t g = (n + NT - 1) / NT;
   if (g < 1) g = 1;
@@ -136,6 +132,7 @@ __global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t 
             bits |= INFO_UNSORTED;  // not an error: the out-view needs a sort
           const int32_t lab = side == 0 ? ol : il;
           if (lab > 0 && (uint32_t)lab > mx) mx = (uint32_t)lab;
+          if (side == 0 && (lab == 0 || d != sv + 1)) bits |= INFO_NOT_LINEAR;
         }
       }
     }
@@ -184,6 +181,7 @@ __global__ __launch_bounds__(NT) void k_label_facts(DevGraph g, int side, uint32
     if (i < E && side != 2) {
       const int32_t lab = side == 0 ? g.ol[i] : g.il[i];
       if (lab > 0 && (uint32_t)lab > mx) mx = (uint32_t)lab;
+      if (side == 0 && (lab == 0 || g.dst[i] != g.src[i] + 1)) bits |= INFO_NOT_LINEAR;
       if (i > 0 && g.src[i - 1] == g.src[i] && (side == 0 ? g.ol[i - 1] : g.il[i - 1]) > lab)
         bits |= INFO_UNSORTED;
     }
@@ -432,7 +430,15 @@ __global__ __launch_bounds__(NT) void k_chains(ViewJobs J) {
         }
       }
     }
+    static_assert(4 * CHAIN_INT4 > 1 + 2 * CHAIN_STEPS, "a spare last word");
     w[0] = n;
+    if (n) {
+      const int4 r = b.srec[2 * (size_t)cur];
+      if (r.z - r.x == 1 && r.y == 1) {
+        w[0] |= CHAIN_EPS;
+        w[4 * CHAIN_INT4 - 1] = b.arec[r.x].y;
+      }
+    }
     int4 *c = b.chain + CHAIN_INT4 * v;
 #pragma unroll
     for (int q = 0; q < CHAIN_INT4; ++q)
@@ -1079,7 +1085,7 @@ __device__ __forceinline__ bool chain_jump(const Problem &P, const SearchArgs &S
     cw[4 * q + 2] = c.z;
     cw[4 * q + 3] = c.w;
   }
-  int n = cw[0];
+  int n = cw[0] & CHAIN_COUNT;
   if (n > P.chain_max - depth) n = P.chain_max - depth;
   // The A side of hop i is the bucket of label l_i at the A state hop i - 1
   // reached.  Hop 0 is looked up first; the buckets of the later hops are
@@ -1466,6 +1472,433 @@ __global__ __launch_bounds__(NT) void k_level2(Problem P, SearchArgs SF, SearchA
   else level_body<false>(P, SB, gb, blockIdx.x - half, half, L);
 }
 
+// ---------------------------------------------------------------------------
+// linear search
+// ---------------------------------------------------------------------------
+// Where every arc of A leads from a state to the next one and none has output
+// epsilon (the emissions of an utterance, or several utterances side by
+// side), the keys (t, b) of one state b of B are a row of bits over t, and a
+// move of B acts on 64 of them at once: an epsilon arc b -> b' gives b' the
+// bits of b, an arc of label l the bits d & M_l moved by one, M_l being the
+// states of A with an arc of label l.  Backward the same over the in-arcs,
+// moved back by one and masked there.  A thread holds its bits as a window
+// (t, d), bit i for A state t + i, so a move masks d and changes t.  The
+// search sets bits only in the rows of start states (backward: accepting
+// ones), of states that several arcs lead to and of states with several arcs;
+// the other states, each on one path out of one of those, get their rows
+// afterwards, whole words at a time (k_linear_rows: with an atomic per state
+// and thread in the search, those atomics were half of its time).
+
+__device__ __forceinline__ ull window(const ull *row, int32_t t) {
+  const uint32_t p = (uint32_t)(t + 64), s = p & 63u;  // a zero word comes first
+  const ull lo = row[p >> 6], hi = row[(p >> 6) + 1];
+  return s ? (lo >> s) | (hi << (64 - s)) : lo;
+}
+
+// The bits of window (t, d) that fall into word t >> 6 of a row, and into the
+// next one.
+__device__ __forceinline__ ull low_part(int32_t t, ull d) { return d << (t & 63); }
+__device__ __forceinline__ ull high_part(int32_t t, ull d) {
+  const int s = t & 63;
+  return s ? d >> (64 - s) : 0ull;
+}
+
+// Bits on their way to states where they will wait (those with several
+// arcs), gathered by a workgroup during a generation: a lexicon's root is
+// reached by ten thousand threads, whose own atomics on its few words would
+// follow each other.
+constexpr uint32_t GATHER = 128, GATHER_PROBES = 8;
+struct LinearLds {
+  uint32_t pre[SUBQ + 1], old[SUBQ + 1];  // prefix sums of part counts
+  int4 heavy[GATHER];                     // a heavy list of at most GATHER items
+  uint32_t item[GATHER];
+  ull bits[GATHER];
+};
+
+struct LinearNext {
+  GenSlot *slot;
+  uint32_t hbase;
+  NextFront q;
+  ull *N;
+  LinearLds *L;
+};
+
+// Adds bits x of word `item` to the workgroup's table; false if it has no
+// place left for it.
+__device__ __forceinline__ bool linear_gather(LinearLds &L, uint32_t item, ull x) {
+  uint32_t h = (item * 2654435761u) >> 25;
+  static_assert(GATHER == 128, "the hash yields 7 bits");
+  for (uint32_t p = 0; p < GATHER_PROBES; ++p) {
+    const uint32_t old = atomicCAS(&L.item[h], NO_KEY, item);
+    if (old == NO_KEY || old == item) {
+      atomicOr(&L.bits[h], x);
+      return true;
+    }
+    h = (h + 1) & (GATHER - 1);
+  }
+  return false;
+}
+
+// Bits wait at state b (arcs [s0, s0 + n)) for the next generation; the first
+// to wait in a word lists it.
+__device__ __forceinline__ void linear_wait(const LinearArgs &X, const LinearNext &nx, bool want,
+                                            uint32_t b, int32_t s0, uint32_t n, int32_t t,
+                                            ull d) {
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+    const ull x = part ? high_part(t, d) : low_part(t, d);
+    const uint32_t item = b * X.W + (uint32_t)((t >> 6) + part);
+    const bool list = want && x && atomicOr(nx.N + item, x) == 0;
+    if (list && n > LIGHT_SEARCH) {
+      const ull slots = ((ull)n + 7) & ~7ull;
+      const ull old = atomicAdd(&nx.slot->hpack, (slots << 32) | 1ull);
+      const ull pos = (ull)nx.hbase + (old & 0xffffffffull);
+      if (pos < X.cap && (old >> 32) + slots < (1ull << 32)) {
+        X.heavy[pos] = make_int4((int32_t)item, s0, (int32_t)n, (int32_t)(uint32_t)(old >> 32));
+      } else {
+        atomicOr(&X.sc->overflow, 2u);
+      }
+    }
+    front_push(list && n <= LIGHT_SEARCH, item, nx.q);
+  }
+}
+
+// Sets the bits of window (t, d) in the row of b (no return is waited for).
+__device__ __forceinline__ void linear_set(const LinearArgs &X, uint32_t b, int32_t t, ull d) {
+  const ull lo = low_part(t, d), hi = high_part(t, d);
+  ull *row = X.F + (size_t)b * X.W + (t >> 6);
+  if (lo) __hip_atomic_fetch_or(row, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (hi) __hip_atomic_fetch_or(row + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Follows the bits of window (t, d) at a state over arc a of its group, and on
+// along states with one arc.  A state that only one arc leads to (NBR_UNIQ)
+// gets bits that none before had, since each bit leaves a state once; at any
+// other state the atomics tell which bits are new.
+template <bool FWD>
+__device__ __forceinline__ void linear_follow(const LinearArgs &X, const LinearNext &nx, int2 a,
+                                              int32_t t, ull d) {
+  const uint32_t WM = X.W + 2;
+  bool go = true;
+  for (int depth = 0; go; ++depth) {
+    // over the arc
+    uint32_t b = nbr_of(a.y);
+    if (a.x != 0) {
+      if (!FWD) --t;
+      d = (uint32_t)a.x < X.nlab ? d & window(X.M + (size_t)a.x * WM, t) : 0ull;
+      if (FWD) ++t;
+    }
+    go = false;
+    if (d) {
+      // the records of b and, where only this arc leads to it (so that a chain
+      // is likely), its chain record, loaded together
+      const bool uniq = (a.y & NBR_UNIQ) != 0;
+      Rec r = load_rec(X.v, b);
+      int32_t cw[4 * CHAIN_INT4];
+      cw[0] = 0;
+      if (uniq && X.v.chain) {
+        const int4 *cr = X.v.chain + CHAIN_INT4 * (size_t)b;
+#pragma unroll
+        for (int q = 0; q < CHAIN_INT4; ++q) {
+          const int4 c = cr[q];
+          cw[4 * q] = c.x;
+          cw[4 * q + 1] = c.y;
+          cw[4 * q + 2] = c.z;
+          cw[4 * q + 3] = c.w;
+        }
+      }
+      if (!uniq) {
+        // bits already there are dropped by a plain load first
+        const ull lo = low_part(t, d), hi = high_part(t, d);
+        ull *row = X.F + (size_t)b * X.W + (t >> 6);
+        ull nlo = lo ? lo & ~row[0] : 0ull, nhi = hi ? hi & ~row[1] : 0ull;
+        if (r.r0.z - r.r0.x > 1) {  // they will wait: gathered first
+          const uint32_t item = b * X.W + (uint32_t)(t >> 6);
+          if (nlo && linear_gather(*nx.L, item, nlo)) nlo = 0;
+          if (nhi && linear_gather(*nx.L, item + 1, nhi)) nhi = 0;
+        }
+        if (nlo) nlo &= ~atomicOr(row, nlo);
+        if (nhi) nhi &= ~atomicOr(row + 1, nhi);
+        const int s = t & 63;
+        d = (nlo >> s) | (s ? nhi << (64 - s) : 0ull);
+      }
+      int32_t n = r.r0.z - r.r0.x;
+      bool eps = false;  // the state reached is known to have one arc, an epsilon arc
+      // along the chain of b, if it has one: labels and states in one record,
+      // the masks of all steps loaded together
+      const int m = cw[0] & CHAIN_COUNT;
+      if (d && m > 0 && depth < X.chain_max) {
+        ull win[CHAIN_STEPS];
+#pragma unroll
+        for (int i = 0; i < CHAIN_STEPS; ++i) {
+          const uint32_t l = (uint32_t)cw[1 + 2 * i];
+          const int32_t at = FWD ? t + i : t - 1 - i;
+          // a window that starts past A's last word, or ends before its first
+          // one, is empty
+          const bool in = i < m && l < X.nlab && at < (int32_t)(64 * X.W) && at >= -64;
+          win[i] = in ? window(X.M + (size_t)l * WM, at) : 0ull;
+        }
+#pragma unroll
+        for (int i = 0; i < CHAIN_STEPS; ++i)
+          if (i < m && d) {
+            d &= win[i];
+            t += FWD ? 1 : -1;
+            b = nbr_of(cw[2 + 2 * i]);
+            ++depth;
+          }
+        eps = (cw[0] & CHAIN_EPS) != 0;
+        n = 1;
+        if (d && (!eps || depth >= X.chain_max)) {
+          r = load_rec(X.v, b);
+          n = r.r0.z - r.r0.x;
+          eps = false;
+        }
+      }
+      // on over the one arc, or wait (a state with several arcs that only one
+      // leads to has its bits set here)
+      go = d && n == 1 && depth < X.chain_max;
+      if (d && n > 1 && uniq) linear_set(X, b, t, d);
+      if (eps) a = make_int2(0, cw[4 * CHAIN_INT4 - 1]);
+      else if (go) a = r.r0.y ? make_int2(0, r.r1.x) : make_int2(r.r1.y, r.r1.z);
+      linear_wait(X, nx, d && n > 0 && !go, b, r.r0.x, (uint32_t)n, t, d);
+    }
+  }
+}
+
+// Generation g of one direction: an arc of a heavy item per thread, then the
+// light items; the words of generation g - 1 are cleared.
+template <bool FWD>
+__device__ __forceinline__ void linear_body(const LinearArgs &X, int g, unsigned bid,
+                                            unsigned nb, LinearLds &L) {
+  uint32_t *const s_pre = L.pre, *const s_old = L.old;
+  const uint32_t ovf = X.sc->overflow;
+  const GenSlot cur = X.G[g & 3], old = X.G[(g + 3) & 3];
+  // prefix sums of the part counts of this and the last generation
+  if (threadIdx.x < 2 * WAVE) {
+    const bool last = threadIdx.x >= WAVE;
+    const uint32_t lane = threadIdx.x & (WAVE - 1);
+    uint32_t n = X.Q.cnt[((last ? g + 3 : g) & 3) * SUBQ + lane];
+    n = n < X.Q.rc ? n : X.Q.rc;
+    uint32_t *pre = last ? s_old : s_pre;
+    pre[lane + 1] = wave_incl_scan(n);
+    if (lane == 0) pre[0] = 0;
+  }
+  if (threadIdx.x < GATHER) {
+    L.item[threadIdx.x] = NO_KEY;
+    L.bits[threadIdx.x] = 0;
+  }
+  __syncthreads();
+  if (ovf) return;
+  const uint32_t hcount = (uint32_t)cur.hpack, ocount = (uint32_t)old.hpack;
+  const ull U = cur.hpack >> 32;
+  const uint32_t nq = s_pre[SUBQ];
+  const size_t nwords = (size_t)X.VB * X.W;
+  auto key_of = [&](int gen, const uint32_t *pre, uint32_t i) {
+    uint32_t a = 0;
+#pragma unroll
+    for (uint32_t h = SUBQ / 2; h; h >>= 1)
+      if (pre[a + h] <= i) a += h;
+    return X.Q.keys[((size_t)(gen & 3) * SUBQ + a) * X.Q.rc + (i - pre[a])];
+  };
+  LinearNext nx;
+  nx.slot = &X.G[(g + 1) & 3];
+  nx.hbase = cur.hbase + hcount;
+  nx.q.cnt = X.Q.cnt + ((g + 1) & 3) * SUBQ;
+  nx.q.keys = X.Q.keys + (size_t)((g + 1) & 3) * SUBQ * X.Q.rc;
+  nx.q.rc = X.Q.rc;
+  nx.q.stride = 1;
+  nx.q.part = (bid * NWAVES + threadIdx.x / WAVE) % SUBQ;
+  nx.q.sc = X.sc;
+  nx.N = X.N + (size_t)((g + 1) % 3) * nwords;
+  nx.L = &L;
+  if (bid == 0) {
+    if (threadIdx.x == 0) {
+      nx.slot->hbase = nx.hbase;  // read by generation g + 1 only
+      X.G[(g + 2) & 3].hpack = 0;
+      if (U + nq) *X.gens = (uint32_t)g + 1;
+    }
+    if (threadIdx.x < SUBQ) X.Q.cnt[((g + 2) & 3) * SUBQ + threadIdx.x] = 0;
+  }
+  // generation g - 1 read its words; generation g + 1 adds to them again
+  {
+    ull *N0 = X.N + (size_t)((g + 2) % 3) * nwords;
+    const uint32_t n = ocount + s_old[SUBQ];
+    for (uint32_t i = bid * NT + threadIdx.x; i < n; i += nb * NT)
+      N0[i < ocount ? (uint32_t)X.heavy[old.hbase + i].x : key_of(g + 3, s_old, i - ocount)] = 0;
+  }
+  const ull *N = X.N + (size_t)(g % 3) * nwords;
+  if (threadIdx.x < GATHER && threadIdx.x < hcount)
+    L.heavy[threadIdx.x] = X.heavy[cur.hbase + threadIdx.x];
+  if (hcount) __syncthreads();
+  const int4 *hv = hcount <= GATHER ? L.heavy : X.heavy + cur.hbase;
+  const ull n = U + nq;
+  const unsigned xcd = bid & 7u, nl = nb >> 3;
+  for (ull j = (ull)(bid >> 3) * NT + threadIdx.x; (bid >> 3) < nl; j += (ull)nl * NT) {
+    const ull i = 8 * j + xcd;
+    if (i >= n) break;
+    uint32_t item;
+    int32_t p0, p1;  // arcs to follow
+    if (i < U) {
+      uint32_t a = 0, b = hcount - 1;  // largest a whose offset is <= i
+      while (a < b) {
+        const uint32_t mid = (a + b + 1) >> 1;
+        if ((uint32_t)hv[mid].w <= i) a = mid; else b = mid - 1;
+      }
+      const int4 h = hv[a];
+      const int32_t u = (int32_t)(i - (uint32_t)h.w);
+      item = (uint32_t)h.x;
+      p0 = h.y + u;
+      p1 = u < h.z ? p0 + 1 : p0;  // a slot past the item's arcs has none
+    } else {
+      item = key_of(g, s_pre, (uint32_t)(i - U));
+      const int4 r = X.v.srec[2 * (size_t)(item / X.W)];
+      p0 = r.x;
+      p1 = r.z;
+    }
+    const int32_t t = (int32_t)(item % X.W) * 64;
+    const ull d = N[item];
+    for (int32_t p = p0; p < p1; ++p) linear_follow<FWD>(X, nx, X.v.arec[p], t, d);
+  }
+  // the gathered bits
+  __syncthreads();
+  if (threadIdx.x < GATHER) {
+    const uint32_t item = L.item[threadIdx.x];
+    ull x = L.bits[threadIdx.x];
+    uint32_t b = 0;
+    int4 r = make_int4(0, 0, 0, 0);
+    if (item != NO_KEY) {
+      b = item / X.W;
+      r = X.v.srec[2 * (size_t)b];
+      x &= ~atomicOr(X.F + item, x);
+    }
+    linear_wait(X, nx, item != NO_KEY && x, b, r.x, (uint32_t)(r.z - r.x),
+                (int32_t)((item - b * X.W) * 64), x);
+  }
+}
+
+__global__ __launch_bounds__(NT, 4) void k_linear(LinearArgs F, LinearArgs B, int g) {
+  __shared__ LinearLds L;
+  const unsigned half = gridDim.x / 2;
+  if (blockIdx.x < half) linear_body<true>(F, g, blockIdx.x, half, L);
+  else linear_body<false>(B, g, blockIdx.x - half, half, L);
+}
+
+// The rows that the search left out (see above): a wavefront takes the words
+// of some arcs (or 63 words of one) out of states whose rows the search has
+// set, and follows them while one arc leads on; lane l's window starts at its
+// word (one lane more than words: it writes the last word of a row moved
+// back), so after some moves word t >> 6 of a row is the low part of lane l's
+// bits and the high part of lane l - 1's.
+template <bool FWD>
+__device__ __forceinline__ void linear_rows(const LinearArgs &X, const DevGraph &B,
+                                            unsigned bid, unsigned nb) {
+  const uint32_t W = X.W, lane = __lane_id(), WL = W + 1;
+  const bool wide = WL > WAVE;
+  const uint32_t per = wide ? 1u : WAVE / WL;  // arcs per wavefront and round
+  const uint32_t sweeps = wide ? (WL + WAVE - 2) / (WAVE - 1) : 1u;
+  const ull n = (((ull)B.E + per - 1) / per) * sweeps;
+  for (ull j = (ull)bid * NWAVES + threadIdx.x / WAVE; j < n; j += (ull)nb * NWAVES) {
+    const ull p = (j / sweeps) * per + (wide ? 0u : lane / WL);
+    // wide: lane 0 holds the word before the 63 that this round writes
+    const int32_t w = wide ? (int32_t)((j % sweeps) * (WAVE - 1) + lane) - 1
+                           : (int32_t)(lane % WL);
+    bool on = p < (ull)B.E && (wide || lane < per * WL) && w <= (int32_t)W;
+    const bool feed = wide && lane == 0;
+    int2 a = make_int2(0, 0);
+    ull d = 0;
+    if (on) {
+      const int32_t e = X.v.perm[p];
+      const uint32_t o = (uint32_t)(FWD ? B.src[e] : B.dst[e]);
+      const int4 r = X.v.srec[2 * (size_t)o];
+      a = X.v.arec[p];
+      // from a state whose row is set, to one whose row is not
+      on = (a.y & NBR_UNIQ) && !((r.w & (int32_t)FLAG_UNIQ) && r.z - r.x == 1);
+      if (on && w >= 0 && w < (int32_t)W) d = X.F[(size_t)o * W + (uint32_t)w];
+    }
+    int32_t t = 64 * w;
+    while (__ballot(on && d)) {
+      uint32_t b = 0;
+      Rec r = {};
+      if (on) {
+        b = nbr_of(a.y);
+        r = load_rec(X.v, b);
+        if (a.x != 0) {
+          if (!FWD) --t;
+          const bool in = d && (uint32_t)a.x < X.nlab;
+          d = in ? d & window(X.M + (size_t)a.x * (W + 2), t) : 0ull;
+          if (FWD) ++t;
+        }
+      }
+      const ull hi = high_part(t, d);
+      ull from = __shfl_up(hi, 1);
+      if (lane == 0 || (!wide && w == 0)) from = 0;
+      const int32_t arcs = r.r0.z - r.r0.x;
+      on = on && arcs <= 1;
+      const int32_t at = t >> 6;
+      if (on && !feed && at >= 0 && at < (int32_t)W)
+        X.F[(size_t)b * W + (uint32_t)at] = low_part(t, d) | from;
+      on = on && arcs == 1;
+      a = r.r0.y ? make_int2(0, r.r1.x) : make_int2(r.r1.y, r.r1.z);
+      on = on && (a.y & NBR_UNIQ);
+    }
+  }
+}
+
+__global__ __launch_bounds__(NT) void k_linear_rows(LinearArgs F, LinearArgs G, DevGraph B) {
+  const unsigned half = gridDim.x / 2;
+  if (blockIdx.x < half) linear_rows<true>(F, B, blockIdx.x, half);
+  else linear_rows<false>(G, B, blockIdx.x - half, half);
+}
+
+__global__ __launch_bounds__(NT) void k_linear_masks(DevGraph A, uint32_t W, uint32_t nlab,
+                                                     ull *__restrict__ M) {
+  const long long n = A.E > A.V ? A.E : A.V;
+  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < n;
+       i += (long long)gridDim.x * NT) {
+    if (i < A.E) {
+      const uint32_t t = (uint32_t)A.src[i];
+      atomicOr(M + (size_t)A.ol[i] * (W + 2) + 1 + (t >> 6), 1ull << (t & 63u));
+    }
+    if (i < A.V) {
+      const size_t w = 1 + (size_t)(i >> 6);
+      if (A.start[i]) atomicOr(M + (size_t)nlab * (W + 2) + w, 1ull << (i & 63));
+      if (A.accept[i]) atomicOr(M + (size_t)(nlab + 1) * (W + 2) + w, 1ull << (i & 63));
+    }
+  }
+}
+
+// Start (accepting) states of B take the bits of A's and wait in generation 0.
+__global__ __launch_bounds__(NT) void k_linear_seed(LinearArgs F, LinearArgs B,
+                                                    const uint8_t *__restrict__ start,
+                                                    const uint8_t *__restrict__ accept) {
+  const bool fwd = blockIdx.y == 0;
+  const LinearArgs &X = fwd ? F : B;
+  const ull *row = X.M + (size_t)(X.nlab + (fwd ? 0 : 1)) * (X.W + 2) + 1;
+  LinearNext nx;
+  nx.slot = &X.G[0];
+  nx.hbase = 0;
+  nx.q.cnt = X.Q.cnt;
+  nx.q.keys = X.Q.keys;
+  nx.q.rc = X.Q.rc;
+  nx.q.stride = 1;
+  nx.q.part = (blockIdx.x * NWAVES + threadIdx.x / WAVE) % SUBQ;
+  nx.q.sc = X.sc;
+  nx.N = X.N;
+  for (ull b0 = (ull)blockIdx.x * NT; b0 < X.VB; b0 += (ull)gridDim.x * NT) {
+    const uint32_t b = (uint32_t)b0 + threadIdx.x;
+    const bool on = b < X.VB && (fwd ? start[b] : accept[b]) != 0;
+    if (__ballot(on) == 0) continue;
+    int4 r = make_int4(0, 0, 0, 0);
+    if (on) r = X.v.srec[2 * (size_t)b];
+    const uint32_t n = (uint32_t)(r.z - r.x);
+    for (uint32_t w = 0; w < X.W; ++w) {
+      const ull d = row[w];
+      if (on && d) X.F[(size_t)b * X.W + w] = d;
+      linear_wait(X, nx, on && d && n > 0, b, r.x, n, (int32_t)(64 * w), d);
+    }
+  }
+}
+
 __global__ __launch_bounds__(NT) void k_collect(const uint8_t *__restrict__ flags, int V,
                                                 int32_t *__restrict__ list,
                                                 uint32_t *__restrict__ count) {
@@ -1565,7 +1998,10 @@ __global__ __launch_bounds__(NT) void k_count_moves(Problem P, ull nwords,
   for (ull k = (ull)blockIdx.x * NT + threadIdx.x; k < nbits; k += (ull)gridDim.x * NT) {
     if (!test_bit(bm, (uint32_t)k)) continue;
     uint32_t key = (uint32_t)k;
-    if (FWD) {
+    if (FWD && P.linW) {
+      const uint32_t b = (uint32_t)(k / (64 * P.linW));
+      key = make_key((uint32_t)(k - (ull)b * 64 * P.linW), b, 0u, P.shiftB);
+    } else if (FWD) {
       const uint32_t x = (uint32_t)(k >> 1), d = x / P.rowA, qa = x - d * P.rowA;
       key = make_key(qa, (d + qa) & P.maskB, (uint32_t)(k & 1u), P.shiftB);
     }
@@ -1662,6 +2098,46 @@ __global__ __launch_bounds__(NT) void k_trim(Problem P, uint32_t VA, uint32_t nt
             cnt[o + jj] = (uint32_t)__popc(out[jj]);
           }
       }
+    }
+  }
+}
+
+// The same from the rows of a linear search (F AND G; f = 0 only): a tile is
+// the 64 A states of one word x 256 B states.
+__global__ __launch_bounds__(NT) void k_linear_trim(Problem P, const ull *__restrict__ F,
+                                                    const ull *__restrict__ G, uint32_t W,
+                                                    ull ntiles, uint32_t *__restrict__ trim,
+                                                    uint32_t *__restrict__ cnt) {
+  static_assert(NT == 256, "one B state per thread and tile");
+  __shared__ ull L[NT];
+  const uint32_t WR = (P.maskB >> 4) + 1, VA = (uint32_t)P.A.V, VB = (uint32_t)P.B.V;
+  const uint32_t r = threadIdx.x >> 2, q = threadIdx.x & 3u;
+  for (ull t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    // consecutive tiles share rows' lines: the words of the same B states
+    const uint32_t w = (uint32_t)(t % W), b0 = (uint32_t)(t / W) * NT;
+    const uint32_t b = b0 + threadIdx.x;
+    __syncthreads();  // the previous tile's LDS readers are done
+    L[threadIdx.x] = b < VB ? F[(size_t)b * W + w] & G[(size_t)b * W + w] : 0ull;
+    __syncthreads();
+    uint32_t out[4];
+#pragma unroll
+    for (uint32_t jj = 0; jj < 4; ++jj) {
+      const uint32_t j = 4 * q + jj;
+      uint32_t wv = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < 16; ++u)
+        wv |= (uint32_t)(L[16 * j + u] >> r & 1ull) << (2 * u);
+      out[jj] = wv;
+    }
+    const uint32_t qa = w * 64 + r;
+    if (qa < VA) {
+      const size_t o = (size_t)qa * WR + (b0 >> 4) + 4 * q;
+#pragma unroll
+      for (uint32_t jj = 0; jj < 4; ++jj)
+        if ((b0 >> 4) + 4 * q + jj < WR) {
+          trim[o + jj] = out[jj];
+          cnt[o + jj] = (uint32_t)__popc(out[jj]);
+        }
     }
   }
 }
@@ -2390,6 +2866,40 @@ hipError_t launch_generation2(const Problem &P, const SearchArgs &SF, const Sear
   constexpr unsigned GRID = 1024;
   if (!P.chains) k_level2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
   else k_gen2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
+  return hipGetLastError();
+}
+
+hipError_t launch_linear_masks(const DevGraph &A, uint32_t W, uint32_t nlab,
+                               unsigned long long *M, hipStream_t s) {
+  const size_t n = (size_t)(A.E > A.V ? A.E : A.V);
+  k_linear_masks<<<grid_for(n), NT, 0, s>>>(A, W, nlab, M);
+  return hipGetLastError();
+}
+
+hipError_t launch_linear_seed(const LinearArgs &F, const LinearArgs &B, const DevGraph &gB,
+                              hipStream_t s) {
+  k_linear_seed<<<dim3(grid_for((size_t)gB.V, 1024), 2), NT, 0, s>>>(F, B, gB.start, gB.accept);
+  return hipGetLastError();
+}
+
+hipError_t launch_linear(const LinearArgs &F, const LinearArgs &B, int g, hipStream_t s) {
+  constexpr unsigned GRID = 128;
+  k_linear<<<2 * GRID, NT, 0, s>>>(F, B, g);
+  return hipGetLastError();
+}
+
+hipError_t launch_linear_rows(const LinearArgs &F, const LinearArgs &G, const DevGraph &gB,
+                              hipStream_t s) {
+  if (gB.E == 0) return hipSuccess;
+  k_linear_rows<<<4096, NT, 0, s>>>(F, G, gB);
+  return hipGetLastError();
+}
+
+hipError_t launch_linear_trim(const Problem &P, const unsigned long long *F,
+                              const unsigned long long *G, uint32_t W, uint32_t *trim,
+                              uint32_t *cnt, hipStream_t s) {
+  const ull nb = ((ull)P.maskB + 1 + NT - 1) / NT, n = nb * W;
+  k_linear_trim<<<(unsigned)(n < 16384 ? n : 16384), NT, 0, s>>>(P, F, G, W, n, trim, cnt);
   return hipGetLastError();
 }
 

@@ -18,6 +18,12 @@ constexpr uint32_t LIGHT_SEARCH = 64;  // search: a key with more units is split
 constexpr uint32_t LEVEL_UNITS = 256;  // the same in a level search
 constexpr int CHAIN_MAX = 64;          // search: default depth-first budget per thread
 constexpr uint32_t NO_KEY = 0xFFFFFFFFu;
+// Validation's notes, above its error bits: some state's arcs are not ordered
+// by the matched label (then the out-view is sorted; otherwise it is the
+// input); and, for A, some arc is not from a state to the next one with an
+// output other than epsilon (A is not linear).
+constexpr uint32_t INFO_UNSORTED = 1u << 16, INFO_NOT_LINEAR = 1u << 17;
+constexpr uint32_t INFO_NOTES = INFO_UNSORTED | INFO_NOT_LINEAR;
 
 // The output passes give every wavefront one chunk of OUT_WORDS consecutive
 // trim words (its states are consecutive ids), so the arcs a wavefront
@@ -98,6 +104,10 @@ struct View {
 
 constexpr int CHAIN_STEPS = 11;
 constexpr int CHAIN_INT4 = (1 + 2 * CHAIN_STEPS + 3) / 4;  // int4 per chain record
+// A two-input chain record's first word: its steps, and CHAIN_EPS when the
+// state they lead to has one arc, an epsilon arc, whose other end is the
+// record's last word.
+constexpr int32_t CHAIN_COUNT = 0xff, CHAIN_EPS = 0x100;
 
 constexpr uint32_t FLAG_ACCEPT = 1u, FLAG_EPS_OUT = 2u, FLAG_START = 4u, FLAG_UNIQ = 8u,
                    FLAG_DISTINCT = 16u;
@@ -116,6 +126,7 @@ struct Problem {
   uint32_t shiftB;        // bits of the B state inside a key
   int chain_max;          // keys one search thread may follow depth-first
   int chains;             // chain search (else level search)
+  uint32_t linW;          // linear search: words per row of its bits (else 0)
   int restrict_fwd;       // forward search expands only keys already in coacc
   int restrict_bwd;       // backward search expands only keys already in vis
   // The two search bitmaps use the diagonal layout of search_bit(): a key
@@ -199,7 +210,29 @@ struct Scalars {
   GenSlot G2[3];                // of the backward search running beside it
   uint32_t gens2, pad1;         // its generations that had work
   SearchNote note, note2;       // of the two searches
-  uint32_t front[2][3 * SUBQ];  // frontier counters of chain searches
+  uint32_t front[2][4 * SUBQ];  // frontier counters of chain and linear searches
+  GenSlot GL[2][4];             // generation slots of a linear search
+};
+
+// One direction of a linear search (see k_linear): the view of B it follows;
+// F the reached bits, bit t of row b (W words per state of B) for key (t, b);
+// N three buffers like F, the bits that wait for generation g in buffer g %
+// 3; M the A states with an arc of each label, rows of W + 2 words (a zero
+// word before and after), then one row of the start and one of the accepting
+// states (labels nlab and nlab + 1); items (b W + word) wait in Q (four
+// buffers of SUBQ rc keys) and, where b has many arcs, in heavy.
+struct LinearArgs {
+  View v;
+  const unsigned long long *M;
+  unsigned long long *F, *N;
+  uint32_t W, VB, nlab;
+  int chain_max;
+  Frontier Q;
+  int4 *heavy;  // up to cap: item, its group's first arc and arcs, unit offset
+  uint32_t cap;
+  Scalars *sc;
+  GenSlot *G;  // four slots
+  uint32_t *gens;
 };
 
 // Arrays of one search.
@@ -512,7 +545,8 @@ hipError_t radix_sort(unsigned long long *k0, int32_t *v0, unsigned long long *k
 // ---------------------------------------------------------------------------
 // Validation of g's structure (offsets, sources, targets, flags) and, for
 // side 0 (A: matched label = olabel) or 1 (B: ilabel), its labels, the
-// largest matched label and whether the arcs are in label order; side 2
+// largest matched label, whether the arcs are in label order and (side 0)
+// whether every arc leads from a state to the next without epsilon; side 2
 // checks the structure only.  *nacc (if given) += number of accepting states.
 // *single (if given) += number of states with exactly one out-arc.
 // check = false skips the checks and only gathers the label facts and nacc.
@@ -575,6 +609,19 @@ hipError_t launch_generation(const Problem &P, const SearchArgs &S, bool forward
 // each).
 hipError_t launch_generation2(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
                               int gb, hipStream_t s);
+// Linear search: M (cleared by the caller) from A's arcs, start and accepting
+// states; the seeds of both directions; generation g of both; the rows that
+// the search leaves out; and, like launch_trim, the trim bitmap from the rows.
+hipError_t launch_linear_masks(const DevGraph &A, uint32_t W, uint32_t nlab,
+                               unsigned long long *M, hipStream_t s);
+hipError_t launch_linear_seed(const LinearArgs &F, const LinearArgs &B, const DevGraph &gB,
+                              hipStream_t s);
+hipError_t launch_linear(const LinearArgs &F, const LinearArgs &B, int g, hipStream_t s);
+hipError_t launch_linear_rows(const LinearArgs &F, const LinearArgs &G, const DevGraph &gB,
+                              hipStream_t s);
+hipError_t launch_linear_trim(const Problem &P, const unsigned long long *F,
+                              const unsigned long long *G, uint32_t W, uint32_t *trim,
+                              uint32_t *cnt, hipStream_t s);
 // *out += number of moves the forward search examines out of the keys set in
 // P.vis (search layout, nwords words), or (backward) the backward search
 // examines into the keys set in P.trim (key order, nwords words): a

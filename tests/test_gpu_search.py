@@ -70,3 +70,100 @@ def test_single_arc_states_of_b(order, more):
     c = _composer(order)
     check_pair(c, A, B, f"single arcs {more} {order}", ref=oracle.compose(A, B, oracle.ORDER_FORWARD))
     c.close()
+
+
+# ---- linear search: A's arcs lead from a state to the next, B mostly chains ----
+
+def _frames(rng, T, C, p_gap=0.3, cuts=()):
+    """Linear A of T frames: a random subset of the labels in each frame (some
+    twice), no arc over the frames in cuts (utterances side by side)."""
+    arcs = []
+    for t in range(T):
+        if t in cuts:
+            continue
+        for c in range(1, C + 1):
+            for _ in range(1 if rng.random() < 0.9 else 2):
+                if rng.random() >= p_gap:
+                    arcs.append((t, t + 1, 1 + c % 3, c, float(rng.standard_normal())))
+    start = [0] + [c + 1 for c in cuts] + ([T // 2] if T > 3 else [])
+    return synth.from_arcs(T + 1, arcs, start=start, accept=[T, T // 3] + list(cuts))
+
+
+def _words(rng, lens, C):
+    """Words out of a root and back, as in a lexicon, some with epsilon inside."""
+    arcs, s = [], 1
+    for L in lens:
+        arcs.append((0, s, 0, 1 + L % 5, 0.0))
+        for _ in range(int(L)):
+            arcs.append((s, s + 1, 0 if rng.random() < 0.1 else int(rng.integers(1, C + 1)), 0,
+                         float(rng.standard_normal())))
+            s += 1
+        arcs.append((s, 0, 0, 0, -0.1))
+        s += 1
+    return synth.from_arcs(s, arcs, start=[0], accept=[0])
+
+
+def _branches(rng, V, C):
+    """Chains that split (a state that one arc leads to, with several) and
+    meet again, dead ends, several start and accepting states."""
+    arcs = []
+    for s in range(V):
+        x = rng.random()
+        n = 1 if x < 0.7 else (0 if x < 0.75 else int(rng.integers(2, 5)))
+        for i in range(n):
+            d = s + 1 + i if rng.random() < 0.8 and s + 1 + i < V else int(rng.integers(0, V))
+            arcs.append((s, d, 0 if rng.random() < 0.15 else int(rng.integers(1, C + 2)),
+                         int(rng.integers(0, 4)), float(rng.standard_normal())))
+    return synth.from_arcs(V, arcs, start=[0, V // 2], accept=[V - 1, V // 3, 0])
+
+
+LINEAR = [("words", T) for T in (1, 2, 62, 63, 64, 65, 127, 128, 191, 4031, 4032, 4095)]
+LINEAR += [("branches", T) for T in (1, 63, 64, 130, 4040)] + [("long words", 300)]
+
+
+@pytest.mark.parametrize("kind,T", LINEAR)
+def test_linear_search(kind, T):
+    """Rows of one word to more than a wavefront's lanes, words (of the
+    lexicon) shorter and longer than a chain record and than a thread's walk,
+    frames that lack labels, utterances side by side: against the oracle, and
+    with the walk cut short."""
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(T)
+    C = 5
+    A = _frames(rng, T, C, p_gap=0.1 if T > 1000 else 0.3, cuts=(T // 2, T - 9) if T > 60 else ())
+    if kind == "words":
+        B = _words(rng, rng.integers(1, 7, size=12 if T > 1000 else 150), C)
+    elif kind == "long words":
+        B = _words(rng, [1, 2, 10, 11, 12, 13, 22, 23, 63, 64, 65, 66, 130, 200], 1)
+        A = _frames(rng, T, 1, p_gap=0.0, cuts=(T - 9,))
+    else:
+        B = _branches(rng, 25 if T > 1000 else 90, C)
+    ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
+    c = _composer("CONCURRENT")
+    for depth in (64, 3, 1):
+        c.set_option(gpu.FST_OPT_CHAIN_DEPTH, depth)
+        check_pair(c, A, B, f"linear {kind} T={T} depth {depth}", ref=ref)
+    c.set_option(gpu.FST_OPT_LIST_CAPACITY, 1)
+    check_pair(c, A, B, f"linear {kind} T={T} lists from one entry", ref=ref)
+    c.close()
+
+
+def test_linear_search_without_room():
+    """Workspace caps that leave no room for the rows, then none for lists of
+    the first size: the keys are followed one by one, with shorter lists."""
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(3)
+    A, B = _frames(rng, 700, 4), _words(rng, rng.integers(1, 9, size=300), 4)
+    ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
+    fits = []
+    for cap in [1 << k for k in range(18, 28)]:
+        c = _composer("CONCURRENT")
+        c.set_option(gpu.FST_OPT_MAX_WORKSPACE, cap)
+        try:
+            check_pair(c, A, B, f"cap {cap}", ref=ref)
+            fits.append(cap)
+        except gpu.FstError as e:
+            assert e.code == gpu.FST_ERR_NOMEM and not fits  # a larger cap never fails
+        c.close()
+    # the bitmaps (4 MB each), the views and short lists fit 32 MB
+    assert fits and fits[0] <= 1 << 25
