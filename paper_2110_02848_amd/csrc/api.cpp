@@ -57,12 +57,12 @@ struct fst_ctx {
   bool have_times = false;
   bool timed_run = false;
 
-  DevBuf scal, lists;
+  DevBuf scal, lists, eps;
   DevBuf k0, k1, v0, v1, sort_tmp, scan_tmp;
   DevBuf aOutPerm, aOutArc, aOutRec, aOutLut, bOutPerm, bOutArc, bOutRec, bOutLut;
   DevBuf aOutLab, aOutW, bOutLab, bOutW, bOutChain, bInChain;
   DevBuf aInOff, aInPerm, aInArc, aInRec, aInLut, bInOff, bInPerm, bInArc, bInRec, bInLut;
-  DevBuf vis, coacc, trim, wbase, fq, bq, fcnt, lin_f, lin_n, lin_m, heavy, hoff, heavy2, hoff2, cnt, btot;
+  DevBuf vis, coacc, trim, wbase, fq, bq, fcnt, lin, heavy, hoff, heavy2, hoff2, cnt, btot;
   // score workspace
   DevBuf s_pg, s_pidx, s_bcnt, s_bscan, s_btotal;  // grouped scatter
   DevBuf s_sc, s_owner, s_extra, s_inref, s_mbeg, s_mlen, s_mcur, s_marc, s_val, s_acc,
@@ -683,6 +683,39 @@ bool want_lut(const fst_ctx *c, int32_t V, int32_t E, uint32_t lab_max) {
   return c->buckets && b <= LUT_BUDGET && b <= LUT_PER_ARC * (size_t)E * sizeof(int2);
 }
 
+// build_views with the sort's storage: all views in one sort where they have
+// at most 2^20 arcs (their launches are what takes time; a large view sorts
+// fewer bits alone) and there is room, else one after the other.
+int sorted_views(fst_ctx *c, const ViewBuild &B, hipStream_t s) {
+  auto build = [&](const ViewBuild &V) -> int {
+    const size_t n = views_sort_entries(V);
+    FST_TRY(ensure(c, c->k0, n * 8));
+    FST_TRY(ensure(c, c->k1, n * 8));
+    FST_TRY(ensure(c, c->v0, n * 4));
+    FST_TRY(ensure(c, c->v1, n * 4));
+    FST_TRY(ensure(c, c->sort_tmp, sort_temp_bytes(n)));
+    HIP_TRY(build_views(V, as<unsigned long long>(c->k0), as<int32_t>(c->v0),
+                        as<unsigned long long>(c->k1), as<int32_t>(c->v1), c->sort_tmp.p, s));
+    return FST_OK;
+  };
+  if (views_sort_entries(B) <= (size_t)1 << 20) {
+    const int rc = build(B);
+    if (rc != FST_ERR_NOMEM) return rc;
+    HIP_TRY(hipDeviceSynchronize());
+    for (DevBuf *b : {&c->k0, &c->k1, &c->v0, &c->v1, &c->sort_tmp}) {
+      c->ws_total -= b->cap;
+      release(*b);
+    }
+  }
+  for (int i = 0; i < 4; ++i) {
+    ViewBuild V = {};
+    V.v[0] = B.v[i];
+    V.eps = B.v[i].side == 0 ? B.eps : nullptr;  // (A's epsilon outputs)
+    FST_TRY(build(V));
+  }
+  return FST_OK;
+}
+
 int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, int64_t *V_C,
              int64_t *E_C) {
   FST_TRY(check_graph_args(A));
@@ -725,12 +758,6 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   const int labA = bitlen(c->h_sc->maxLabA), labB = bitlen(c->h_sc->maxLabB);
 
   // ---- label-sorted views ----
-  const size_t Emax = (size_t)(EA > EB ? EA : EB);
-  FST_TRY(ensure(c, c->k0, Emax * 8));
-  FST_TRY(ensure(c, c->k1, Emax * 8));
-  FST_TRY(ensure(c, c->v0, Emax * 4));
-  FST_TRY(ensure(c, c->v1, Emax * 4));
-  FST_TRY(ensure(c, c->sort_tmp, sort_temp_bytes(Emax)));
   const uint32_t maxA = c->h_sc->maxLabA, maxB = c->h_sc->maxLabB;
   const bool lutA = want_lut(c, (int32_t)VA, (int32_t)EA, maxA);
   const bool lutB = want_lut(c, (int32_t)VB, (int32_t)EB, maxB);
@@ -743,8 +770,6 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       {&c->bOutPerm, &c->bOutArc, &c->bOutRec, &c->bOutLut, nullptr, &c->bOutLab, &c->bOutW},
       {&c->aInPerm, &c->aInArc, &c->aInRec, &c->aInLut, &c->aInOff, nullptr, nullptr},
       {&c->bInPerm, &c->bInArc, &c->bInRec, &c->bInLut, &c->bInOff, nullptr, nullptr}};
-  unsigned long long *k0 = as<unsigned long long>(c->k0), *k1 = as<unsigned long long>(c->k1);
-  int32_t *v0 = as<int32_t>(c->v0), *v1 = as<int32_t>(c->v1);
   int4 *rec[4], *lutp[4];
   int2 *arc[4];
   int32_t *perm[4], *olab[4];
@@ -771,13 +796,18 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     perm[i] = as<int32_t>(*vb[i].perm);
     lutp[i] = lut ? as<int4>(*vb[i].lut) : nullptr;
   }
+  ViewBuild VB4 = {};
+  FST_TRY(ensure(c, c->eps, (size_t)VA));
+  HIP_TRY(hipMemsetAsync(c->eps.p, 0, (size_t)VA, s));
+  VB4.eps = as<uint8_t>(c->eps);
   for (int i = 0; i < 4; ++i) {
     const bool isA = (i % 2) == 0, in = i >= 2;
-    HIP_TRY(sort_view(isA ? dA : dB, isA ? 0 : 1, in, isA ? presortedA : presortedB,
-                      isA ? labA : labB, rec[i], arc[i], perm[i], olab[i], wv[i],
-                      in ? as<int32_t>(*vb[i].off) : nullptr, i == 2 ? rec[0] : nullptr, k0, v0,
-                      k1, v1, c->sort_tmp.p, nullptr, s));
+    VB4.v[i] = ViewIn{isA ? dA : dB, isA ? 0 : 1, in ? 1 : 0,
+                      in || !(isA ? presortedA : presortedB) ? 1 : 0, isA ? labA : labB,
+                      rec[i], arc[i], perm[i], olab[i],
+                      in ? as<int32_t>(*vb[i].off) : nullptr, wv[i], 0, 0};
   }
+  FST_TRY(sorted_views(c, VB4, s));
   // a view's FLAG_UNIQ comes from the opposite view (i ^ 2) of the same graph
   ViewJobs J = {};
   View views[4];
@@ -832,9 +862,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
              !(c->h_sc->errA & INFO_NOT_LINEAR) && rows < 0xffffffffull &&
              masks * 8 <= LINEAR_MASKS;
     if (linear) {
-      FST_TRY(ensure(c, c->lin_f, 2 * rows * 8));
-      FST_TRY(ensure(c, c->lin_n, 6 * rows * 8));
-      FST_TRY(ensure(c, c->lin_m, masks * 8));
+      FST_TRY(ensure(c, c->lin, (8 * rows + masks) * 8));
     }
     if (!linear) {
       FST_TRY(ensure(c, c->vis, snwords * 4));
@@ -860,13 +888,11 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
         FST_TRY(ensure(c, c->hoff2, (size_t)cap * 4));
       }
     }
-    FST_TRY(ensure(c, c->lists, ((size_t)VA + VB + 2) * 4));
+    FST_TRY(ensure(c, c->lists, ((size_t)VA + VB) * 4));
     size_t scan_n = nwords > (size_t)cap + 1 ? nwords : (size_t)cap + 1;
     FST_TRY(ensure(c, c->scan_tmp, scan_temp_bytes(scan_n)));
     if (linear) {
-      HIP_TRY(hipMemsetAsync(c->lin_f.p, 0, 2 * rows * 8, s));
-      HIP_TRY(hipMemsetAsync(c->lin_n.p, 0, 6 * rows * 8, s));
-      HIP_TRY(hipMemsetAsync(c->lin_m.p, 0, masks * 8, s));
+      HIP_TRY(hipMemsetAsync(c->lin.p, 0, (8 * rows + masks) * 8, s));
     } else {
       HIP_TRY(hipMemsetAsync(c->vis.p, 0, snwords * 4, s));
       HIP_TRY(hipMemsetAsync(c->coacc.p, 0, snwords * 4, s));
@@ -892,7 +918,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
 
     // ---- the two searches ----
     int32_t *la = as<int32_t>(c->lists), *lb = la + VA;
-    uint32_t *cnts = reinterpret_cast<uint32_t *>(lb + VB);
+    uint32_t *ns = d_sc->lists, *na = ns + 2;  // start, accepting states listed
     SearchArgs S;
     S.Q = P.chains ? Frontier{as<uint32_t>(c->fq), rc, 1, d_sc->front[0]}
                    : Frontier{as<uint32_t>(c->fq), rc, SUBQ_STRIDE, as<uint32_t>(c->fcnt)};
@@ -918,9 +944,11 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     if (linear) {
       LinearArgs F = {}, G = {};
       F.v = views[1];
-      F.M = as<unsigned long long>(c->lin_m);
-      F.F = as<unsigned long long>(c->lin_f);
-      F.N = as<unsigned long long>(c->lin_n);
+      // the rows reached, both directions, three buffers of waiting bits
+      // each, the masks
+      F.F = as<unsigned long long>(c->lin);
+      F.N = F.F + 2 * rows;
+      F.M = F.F + 8 * rows;
       F.W = W;
       F.VB = (uint32_t)VB;
       F.nlab = nlab;
@@ -940,12 +968,12 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       G.G = d_sc->GL[1];
       G.gens = &d_sc->gens2;
       phase_begin(c, PH_FWD, s);
-      HIP_TRY(launch_linear_masks(dA, W, nlab, as<unsigned long long>(c->lin_m), s));
+      HIP_TRY(launch_linear_masks(dA, W, nlab, F.F + 8 * rows, s));
       HIP_TRY(launch_linear_seed(F, G, dB, s));
       FST_TRY(search_linear(c, F, G, s));
       HIP_TRY(launch_linear_rows(F, G, dB, s));
       P.linW = W;
-      P.vis = as<uint32_t>(c->lin_f);
+      P.vis = as<uint32_t>(c->lin);
       HIP_TRY(launch_popcount(P.vis, 2 * rows, &d_sc->naccessible, s));
       if (c->count_moves) HIP_TRY(launch_count_moves(P, 2 * rows, true, &d_sc->generated, s));
       phase_end(c, PH_FWD, s);
@@ -964,9 +992,8 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       P.restrict_fwd = 0;
       P.restrict_bwd = 0;
       phase_begin(c, PH_FWD, s);
-      // the generation slots are still zero from the run's first memset
-      HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
-      HIP_TRY(launch_seed_forward(P, S, la, cnts, lb, cnts + 1, s));
+      // the generation slots and counts are still zero from the first memset
+      HIP_TRY(launch_seed_forward(P, S, la, ns, lb, ns + 1, s));
       const KernelTimer tf = timer(c, FST_KERNEL_SEARCH_FORWARD);
       tf.begin(s);
       for (int g = 0; g < FIRST; ++g) HIP_TRY(launch_generation(P, S, true, g, s));
@@ -988,8 +1015,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
         phase_begin(c, PH_BWD, s);
         P.restrict_bwd = 1;
         FST_TRY(second_search());
-        HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
-        HIP_TRY(launch_seed_backward(P, S, la, cnts, lb, cnts + 1, s));
+        HIP_TRY(launch_seed_backward(P, S, la, na, lb, na + 1, s));
         FST_TRY(search(c, S, false, &c->stats.bwd_levels, s));
         HIP_TRY(launch_trim(P, (uint32_t)VA, as<uint32_t>(c->trim), wbase, s));
         phase_end(c, PH_BWD, s);
@@ -1001,8 +1027,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
         SB.G = d_sc->G2;
         SB.gens = &d_sc->gens2;
         SB.note = &d_sc->note2;
-        HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
-        HIP_TRY(launch_seed_backward(P, SB, la, cnts, lb, cnts + 1, s));
+        HIP_TRY(launch_seed_backward(P, SB, la, na, lb, na + 1, s));
         FST_TRY(search_concurrent(c, P, S, SB, FIRST, s));
         HIP_TRY(launch_popcount(P.vis, snwords, &d_sc->naccessible, s));
         if (c->count_moves) HIP_TRY(launch_count_moves(P, snwords, true, &d_sc->generated, s));
@@ -1018,15 +1043,13 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       P.restrict_fwd = 1;
       P.restrict_bwd = 0;
       phase_begin(c, PH_BWD, s);
-      HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
       HIP_TRY(hipMemsetAsync(d_sc->G, 0, sizeof(d_sc->G), s));
-      HIP_TRY(launch_seed_backward(P, S, la, cnts, lb, cnts + 1, s));
+      HIP_TRY(launch_seed_backward(P, S, la, na, lb, na + 1, s));
       FST_TRY(search(c, S, false, &c->stats.bwd_levels, s));
       phase_end(c, PH_BWD, s);
       phase_begin(c, PH_FWD, s);
-      HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
       FST_TRY(second_search());
-      HIP_TRY(launch_seed_forward(P, S, la, cnts, lb, cnts + 1, s));
+      HIP_TRY(launch_seed_forward(P, S, la, ns, lb, ns + 1, s));
       FST_TRY(search(c, S, true, &c->stats.fwd_levels, s));
       HIP_TRY(launch_popcount(P.vis, snwords, &d_sc->naccessible, s));
       if (c->count_moves) HIP_TRY(launch_count_moves(P, snwords, true, &d_sc->generated, s));
@@ -1036,9 +1059,8 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       P.restrict_fwd = 0;
       P.restrict_bwd = 1;
       phase_begin(c, PH_FWD, s);
-      HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
       HIP_TRY(hipMemsetAsync(d_sc->G, 0, sizeof(d_sc->G), s));
-      HIP_TRY(launch_seed_forward(P, S, la, cnts, lb, cnts + 1, s));
+      HIP_TRY(launch_seed_forward(P, S, la, ns, lb, ns + 1, s));
       FST_TRY(search(c, S, true, &c->stats.fwd_levels, s));
       HIP_TRY(launch_popcount(P.vis, snwords, &d_sc->naccessible, s));
       if (c->count_moves) HIP_TRY(launch_count_moves(P, snwords, true, &d_sc->generated, s));
@@ -1047,8 +1069,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       // backward search, seeded by the accepting keys among them
       phase_begin(c, PH_BWD, s);
       FST_TRY(second_search());
-      HIP_TRY(hipMemsetAsync(cnts, 0, 8, s));
-      HIP_TRY(launch_seed_backward(P, S, la, cnts, lb, cnts + 1, s));
+      HIP_TRY(launch_seed_backward(P, S, la, na, lb, na + 1, s));
       FST_TRY(search(c, S, false, &c->stats.bwd_levels, s));
       // the backward search may set co-accessible bits of keys it never
       // expands (not accessible); the trim set is what remains after masking
@@ -1073,7 +1094,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       if (!linear) cap_try = cap / 4;
       try_linear = false;
       HIP_TRY(hipDeviceSynchronize());
-      for (DevBuf *b : {&c->lin_f, &c->lin_n, &c->lin_m, &c->fq, &c->bq, &c->heavy, &c->hoff,
+      for (DevBuf *b : {&c->lin, &c->fq, &c->bq, &c->heavy, &c->hoff,
                         &c->heavy2, &c->hoff2}) {
         c->ws_total -= b->cap;
         release(*b);
@@ -1088,41 +1109,55 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
 
   // ---- numbering and arc counts ----
   phase_begin(c, PH_COUNT, s);
-  HIP_TRY(scan_u32(wbase, wbase, nwords, false, &d_sc->total, c->scan_tmp.p, s));
-  FST_TRY(readback(c, s));
-  const unsigned long long nst = c->h_sc->total;
-  if (nst > (unsigned long long)INT32_MAX) return FST_ERR_TOO_LARGE;
-  const uint32_t nstates = (uint32_t)nst;
-  // the search lists are free now: the forward queue takes the counts of
-  // 255 arcs or more, the backward queue the heavy states (id, key)
-  FST_TRY(ensure(c, c->fq, ((size_t)nstates + 1) * 4));
-  FST_TRY(ensure(c, c->bq, ((size_t)nstates + 1) * 8));
-  uint32_t *cnt32 = as<uint32_t>(c->fq);
-  uint2 *heavy = as<uint2>(c->bq);
+  HIP_TRY(scan_u32(wbase, wbase, nwords, false, &d_sc->nstates, c->scan_tmp.p, s));
   const Problem &P = c->P;
   const size_t nchunks = out_chunks(nwords);
-  FST_TRY(ensure(c, c->cnt, (size_t)nstates + 1));
   FST_TRY(ensure(c, c->btot, (nchunks + 1) * 4));
   FST_TRY(ensure(c, c->scan_tmp, scan_temp_bytes(nchunks + 1)));
-  uint8_t *cnt8 = as<uint8_t>(c->cnt);
   uint32_t *btot = as<uint32_t>(c->btot);
-  HIP_TRY(hipMemsetAsync(&d_sc->heavy, 0, sizeof(uint32_t), s));
-  HIP_TRY(hipMemsetAsync(&d_sc->total, 0, sizeof(unsigned long long), s));
+  // the search lists are free now: the forward queue takes the counts of
+  // 255 arcs or more, the backward queue the heavy states (id, key).  The
+  // count is queued for as many states as the buffers hold, as after a call of
+  // about this size, without waiting for their number; where they turn out to
+  // be too small, or the queues were never made, it is queued (again) after
+  // the read-back.
   const KernelTimer tc = timer(c, FST_KERNEL_COUNT);
-  tc.begin(s);
-  if (nstates) {
-    HIP_TRY(launch_count(P, nwords, cnt8, cnt32, btot, heavy, d_sc, s));
+  auto room = [&]() -> unsigned long long {
+    size_t n = c->cnt.cap;
+    n = n < c->fq.cap / 4 ? n : c->fq.cap / 4;
+    n = n < c->bq.cap / 8 ? n : c->bq.cap / 8;
+    return n < (size_t)INT32_MAX ? n : (size_t)INT32_MAX;
+  };
+  auto count = [&](uint32_t cap) -> int {
+    uint8_t *cnt8 = as<uint8_t>(c->cnt);
+    uint32_t *cnt32 = as<uint32_t>(c->fq);
+    uint2 *heavy = as<uint2>(c->bq);
+    tc.begin(s);
+    HIP_TRY(launch_count(P, nwords, cnt8, cnt32, btot, heavy, cap, d_sc, s));
     HIP_TRY(launch_count_heavy(P, heavy, &d_sc->heavy, cnt8, cnt32, btot, s));
-  }
-  tc.end(s);
-  // exclusive arc offset of every chunk; the total is E_C
-  if (nstates)
+    tc.end(s);
+    // exclusive arc offset of every chunk; the total is E_C
     HIP_TRY(scan_u32(btot, btot, nchunks, false, &d_sc->total, c->scan_tmp.p, s));
-  phase_end(c, PH_COUNT, s);
+    phase_end(c, PH_COUNT, s);
+    return FST_OK;
+  };
+  const unsigned long long cap0 = room();
+  if (cap0) FST_TRY(count((uint32_t)cap0));
   FST_TRY(readback(c, s));
+  const unsigned long long nst = c->h_sc->nstates;
+  if (nst > (unsigned long long)INT32_MAX) return FST_ERR_TOO_LARGE;
+  const uint32_t nstates = (uint32_t)nst;
+  if (!cap0 || nst > cap0) {
+    FST_TRY(ensure(c, c->fq, ((size_t)nstates + 1) * 4));
+    FST_TRY(ensure(c, c->bq, ((size_t)nstates + 1) * 8));
+    FST_TRY(ensure(c, c->cnt, (size_t)nstates + 1));
+    HIP_TRY(hipMemsetAsync(&d_sc->heavy, 0, sizeof(uint32_t), s));
+    FST_TRY(count(nstates));
+    FST_TRY(readback(c, s));
+  }
   const unsigned long long narcs = c->h_sc->total;
   if (narcs > (unsigned long long)INT32_MAX) return FST_ERR_TOO_LARGE;
-  FST_TRY(add_time(c, FST_KERNEL_COUNT, nstates ? 2 : 1));
+  FST_TRY(add_time(c, FST_KERNEL_COUNT, 2));
 
   c->nstates = nstates;
   c->out_words = nwords;
@@ -1156,7 +1191,7 @@ int readback3(fst_ctx *c, hipStream_t s) {
 // given buffers; lab/w (the other side's label and the weight in sorted
 // order) only when lab is given.
 int view3(fst_ctx *c, const DevGraph &g, int side, bool presorted, uint32_t maxlab, DevBuf &perm,
-          DevBuf &arc, DevBuf &rec, DevBuf *lab, DevBuf *w, DevBuf &lut, View &v, hipStream_t s) {
+          DevBuf &arc, DevBuf &rec, DevBuf *lab, DevBuf *w, DevBuf &lut, View &v, ViewIn &in) {
   FST_TRY(ensure(c, perm, (size_t)g.E * 4));
   FST_TRY(ensure(c, arc, (size_t)g.E * 8));
   FST_TRY(ensure(c, rec, (size_t)g.V * 2 * sizeof(int4)));
@@ -1168,17 +1203,14 @@ int view3(fst_ctx *c, const DevGraph &g, int side, bool presorted, uint32_t maxl
     olab = as<int32_t>(*lab);
     wv = as<float>(*w);
   }
-  HIP_TRY(sort_view(g, side, false, presorted, bitlen(maxlab), as<int4>(rec), as<int2>(arc),
-                    as<int32_t>(perm), olab, wv, nullptr, nullptr, as<unsigned long long>(c->k0),
-                    as<int32_t>(c->v0), as<unsigned long long>(c->k1), as<int32_t>(c->v1),
-                    c->sort_tmp.p, nullptr, s));
+  in = ViewIn{g, side, 0, presorted ? 0 : 1, bitlen(maxlab), as<int4>(rec), as<int2>(arc),
+              as<int32_t>(perm), olab, nullptr, wv, 0, 0};
   v = View{as<int4>(rec), as<int2>(arc), as<int32_t>(perm), nullptr, 0, olab, wv, nullptr};
   // bucket table under the same budget as the two-input views
   if (want_lut(c, g.V, g.E, maxlab)) {
     FST_TRY(ensure(c, lut, lut_bytes(g.V, maxlab)));
     v.lut = as<int4>(lut);
     v.lstride = (int32_t)maxlab + 1;
-    HIP_TRY(launch3_lut(v, g.V, s));
   }
   return FST_OK;
 }
@@ -1249,23 +1281,21 @@ int compose3_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, const fst_
   c->c3.stats.key_space = (int64_t)1 << kbits;
 
   // label-sorted views
-  int32_t EA = dA.E, EB = dB.E, ED = dD.E;
-  const size_t Emax = (size_t)(EA > EB ? (EA > ED ? EA : ED) : (EB > ED ? EB : ED));
-  FST_TRY(ensure(c, c->k0, Emax * 8));
-  FST_TRY(ensure(c, c->k1, Emax * 8));
-  FST_TRY(ensure(c, c->v0, Emax * 4));
-  FST_TRY(ensure(c, c->v1, Emax * 4));
-  FST_TRY(ensure(c, c->sort_tmp, sort_temp_bytes(Emax)));
   Problem3 P = {};
   P.A = dA;
   P.B = dB;
   P.D = dD;
+  ViewBuild VB3 = {};
   FST_TRY(view3(c, dA, 0, !(v.errA & info), v.maxA, c->t_aPerm, c->t_aArc, c->t_aRec,
-                &c->t_aLab, &c->t_aW, c->t_aLut, P.aOut, s));
+                &c->t_aLab, &c->t_aW, c->t_aLut, P.aOut, VB3.v[0]));
   FST_TRY(view3(c, dB, 1, !(v.errB & info), v.maxB, c->t_bPerm, c->t_bArc, c->t_bRec,
-                &c->t_bLab, &c->t_bW, c->t_bLut, P.bOut, s));
+                &c->t_bLab, &c->t_bW, c->t_bLut, P.bOut, VB3.v[1]));
   FST_TRY(view3(c, dD, 1, !(v.errD & info), v.maxD, c->t_dPerm, c->t_dArc, c->t_dRec,
-                &c->t_dLab, &c->t_dW, c->t_dLut, P.dOut, s));
+                &c->t_dLab, &c->t_dW, c->t_dLut, P.dOut, VB3.v[2]));
+  FST_TRY(sorted_views(c, VB3, s));
+  if (P.aOut.lut) HIP_TRY(launch3_lut(P.aOut, dA.V, s));
+  if (P.bOut.lut) HIP_TRY(launch3_lut(P.bOut, dB.V, s));
+  if (P.dOut.lut) HIP_TRY(launch3_lut(P.dOut, dD.V, s));
   // chain records of B for the search's chain jumps (which look up A's
   // buckets: only with A's bucket table)
   if (P.aOut.lut) {
@@ -1795,13 +1825,13 @@ void fst_ctx_destroy(fst_ctx *c) {
   if (!c) return;
   DeviceGuard g(c->device);
   (void)hipDeviceSynchronize();
-  DevBuf *bufs[] = {&c->scal,     &c->lists,    &c->k0,      &c->k1,      &c->v0,
+  DevBuf *bufs[] = {&c->scal,     &c->eps,      &c->lists,    &c->k0,      &c->k1,      &c->v0,
                     &c->v1,       &c->sort_tmp, &c->scan_tmp, &c->aOutPerm, &c->aOutArc,
                     &c->aOutRec,  &c->aOutLut,  &c->bOutPerm, &c->bOutArc, &c->bOutRec,
                     &c->bOutLut,  &c->aInOff,   &c->aInPerm, &c->aInArc,  &c->aInRec,
                     &c->aInLut,   &c->bInOff,   &c->bInPerm, &c->bInArc,  &c->bInRec,
                     &c->bInLut,   &c->vis,      &c->coacc,   &c->trim,    &c->wbase,   &c->heavy2,
-                    &c->hoff2,    &c->fq,       &c->fcnt,     &c->lin_f,   &c->lin_n,   &c->lin_m,
+                    &c->hoff2,    &c->fq,       &c->fcnt,     &c->lin,
                     &c->bq,       &c->heavy,    &c->hoff,    &c->cnt,     &c->aOutLab,
                     &c->aOutW,    &c->bOutLab,  &c->bOutW,   &c->btot,    &c->bOutChain,
                     &c->bInChain, &c->s_sc,     &c->s_owner, &c->s_extra, &c->s_inref,

@@ -215,110 +215,10 @@ __global__ __launch_bounds__(NT) void k_label_facts(DevGraph g, int side, uint32
 // ---------------------------------------------------------------------------
 // label-sorted views
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(NT) void k_make_keys(DevGraph g, int side, int by_dst, int lab_bits,
-                                                  ull *__restrict__ k, int32_t *__restrict__ v) {
-  for (long long e = (long long)blockIdx.x * NT + threadIdx.x; e < g.E;
-       e += (long long)gridDim.x * NT) {
-    ull grp = (ull)(uint32_t)(by_dst ? g.dst[e] : g.src[e]);
-    ull lab = (ull)(uint32_t)(side == 0 ? g.ol[e] : g.il[e]);
-    k[e] = (grp << lab_bits) | lab;
-    v[e] = (int32_t)e;
-  }
-}
-
-// Sorted (key, arc) pairs -> arc records {label, other end} and arc ids.
-__global__ __launch_bounds__(NT) void k_split(DevGraph g, int by_dst, const ull *__restrict__ k,
-                                              const int32_t *__restrict__ v, long long n,
-                                              int lab_bits, const int4 *__restrict__ eps_rec,
-                                              int side, int32_t *__restrict__ perm,
-                                              int32_t *__restrict__ olab, float *__restrict__ wv,
-                                              int2 *__restrict__ arec) {
-  const ull mask = (lab_bits >= 64) ? ~0ull : ((1ull << lab_bits) - 1ull);
-  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < n;
-       i += (long long)gridDim.x * NT) {
-    // without sorted pairs (k null) the arcs are already in view order
-    const int32_t e = k ? v[i] : (int32_t)i;
-    perm[i] = e;
-    if (olab) {
-      olab[i] = side == 0 ? g.il[e] : g.ol[e];
-      wv[i] = g.w[e];
-    }
-    int32_t nb = by_dst ? g.src[e] : g.dst[e];
-    if (eps_rec && eps_rec[2 * (size_t)nb].y > 0) nb |= NBR_EPS;
-    arec[i] = make_int2(k ? (int32_t)(k[i] & mask) : (side == 0 ? g.ol[e] : g.il[e]), nb);
-  }
-}
-
-// off[v] = first sorted position whose group is >= v (v = 0..V).
-// off[v] = first position whose key's group is >= v, for v <= V: by binary
-// search (one thread per group; for graphs with few arcs per state) ...
-__global__ __launch_bounds__(NT) void k_group_offsets(const ull *__restrict__ k, long long n,
-                                                      int V, int lab_bits,
-                                                      int32_t *__restrict__ off) {
-  for (long long v = (long long)blockIdx.x * NT + threadIdx.x; v <= V;
-       v += (long long)gridDim.x * NT) {
-    ull x = (ull)v << lab_bits;
-    long long lo = 0, hi = n;
-    while (lo < hi) {
-      long long mid = lo + ((hi - lo) >> 1);
-      if (k[mid] < x) lo = mid + 1; else hi = mid;
-    }
-    off[v] = (int32_t)lo;
-  }
-}
-
-// ... or from adjacent keys (one thread per position; runs of empty groups
-// are short when there are at least a few arcs per four states)
-__global__ __launch_bounds__(NT) void k_group_bounds(const ull *__restrict__ k, long long n,
-                                                     int V, int lab_bits,
-                                                     int32_t *__restrict__ off) {
-  // position i (0 <= i <= n) starts the groups after the group of key i - 1
-  // up to the group of key i (groups past the last key start at n)
-  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i <= n;
-       i += (long long)gridDim.x * NT) {
-    const long long g0 = i > 0 ? (long long)(k[i - 1] >> lab_bits) + 1 : 0;
-    const long long g1 = i < n ? (long long)(k[i] >> lab_bits) : (long long)V;
-    for (long long v = g0; v <= g1; ++v) off[v] = (int32_t)i;
-  }
-}
-
-// State records.  eps_mode: 0 = no epsOutA flag (views of B), 1 = A's
-// out-view (flag from its own epsilon count), 2 = A's in-view (flag from
-// A's out-view records in eps_rec).
-__global__ __launch_bounds__(NT) void k_state_rec(const int32_t *__restrict__ off,
-                                                  const int2 *__restrict__ arec, int V,
-                                                  const uint8_t *__restrict__ accept,
-                                                  const uint8_t *__restrict__ start,
-                                                  int eps_mode, const int4 *__restrict__ eps_rec,
-                                                  int4 *__restrict__ srec,
-                                                  uint32_t *eps_states) {
-  __shared__ uint32_t s_w[NWAVES];
-  uint32_t neps_states = 0;
-  for (long long v = (long long)blockIdx.x * NT + threadIdx.x; v < V;
-       v += (long long)gridDim.x * NT) {
-    const int32_t s0 = off[v], s1 = off[v + 1];
-    const int32_t n = lb_label(arec, s0, s1, 1) - s0;
-    int32_t flags = accept[v] ? (int32_t)FLAG_ACCEPT : 0;
-    if ((eps_mode == 1 && n > 0) || (eps_mode == 2 && eps_rec[2 * v].y > 0))
-      flags |= (int32_t)FLAG_EPS_OUT;
-    if (start && start[v]) flags |= (int32_t)FLAG_START;
-    srec[2 * v] = make_int4(s0, n, s1, flags);
-    neps_states += n > 0 ? 1u : 0u;
-  }
-  if (eps_states) {
-    const uint32_t tot = block_sum(neps_states, s_w);
-    if (threadIdx.x == 0 && tot) atomicAdd(eps_states, tot);
-  }
-}
-
-// Groups longer than this are never marked FLAG_UNIQ in A (their labels are
-// not checked one by one).
-constexpr int32_t UNIQ_SCAN_MAX = 256;
-
-// The four views are finished together: each kernel runs over the
-// concatenated states (or arcs, or bucket entries) of all views; a thread
-// finds its view with a few comparisons against the prefix sums.
-__device__ __forceinline__ int job_of(const ViewJobs &J, const long long *begin, long long i) {
+// The views of a call are built together: each kernel runs over the
+// concatenated arcs (or states) of all of them.  At most operands' sizes the
+// build is bound by its launches (about 4.5 us each): 13 instead of 38.
+__device__ __forceinline__ int view_of(const long long *begin, long long i) {
   int j = 0;
 #pragma unroll
   for (int t = 1; t < 4; ++t)
@@ -326,11 +226,99 @@ __device__ __forceinline__ int job_of(const ViewJobs &J, const long long *begin,
   return j;
 }
 
+// Sort keys (view, group, label) of the arcs of the views to be sorted, and
+// A's states with an epsilon output (eps, cleared by the caller).
+__global__ __launch_bounds__(NT) void k_view_keys(ViewBuild B, ull *__restrict__ k,
+                                                  int32_t *__restrict__ v, long long eps_arcs) {
+  const long long n = B.sbegin[4] > eps_arcs ? B.sbegin[4] : eps_arcs;
+  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < n;
+       i += (long long)gridDim.x * NT) {
+    if (i < B.sbegin[4]) {
+      const int j = view_of(B.sbegin, i);
+      const ViewIn &w = B.v[j];
+      const long long e = i - B.sbegin[j];
+      const ull grp = (ull)(uint32_t)(w.by_dst ? w.g.dst[e] : w.g.src[e]);
+      const ull lab = (ull)(uint32_t)(w.side == 0 ? w.g.ol[e] : w.g.il[e]);
+      k[i] = ((((ull)(uint32_t)w.rank << B.grp_bits) | grp) << B.lab_bits) | lab;
+      v[i] = (int32_t)e;
+    }
+    if (i < eps_arcs && B.v[0].g.ol[i] == 0) B.eps[B.v[0].g.src[i]] = 1;
+  }
+}
+
+// Arc records {label, other end}, arc ids, and (out-views) output-side labels
+// and weights of every view in its order; and the group offsets of in-views
+// from adjacent arcs (runs of empty groups are short when there are at least
+// a few arcs per four states; else k_view_offsets).
+__global__ __launch_bounds__(NT) void k_view_arcs(ViewBuild B, const int32_t *__restrict__ v) {
+  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < B.ebegin[4];
+       i += (long long)gridDim.x * NT) {
+    const int j = view_of(B.ebegin, i);
+    const ViewIn &w = B.v[j];
+    const long long p = i - B.ebegin[j];
+    const int32_t *order = w.sorted ? v + B.sbegin[j] : nullptr;
+    const int32_t e = order ? order[p] : (int32_t)p;
+    w.perm[p] = e;
+    const int32_t il = w.g.il[e], ol = w.g.ol[e];
+    if (w.olab) {
+      w.olab[p] = w.side == 0 ? il : ol;
+      w.wv[p] = w.g.w[e];
+    }
+    int32_t nb = w.by_dst ? w.g.src[e] : w.g.dst[e];
+    if (w.off && w.scan_off) {  // in-view
+      const int32_t g1 = w.g.dst[e], g0 = p > 0 ? w.g.dst[order[p - 1]] + 1 : 0;
+      for (int32_t q = g0; q <= g1; ++q) w.off[q] = (int32_t)p;
+      if (p + 1 == w.g.E)
+        for (int32_t q = g1 + 1; q <= w.g.V; ++q) w.off[q] = w.g.E;
+    }
+    if (w.by_dst && w.side == 0 && B.eps[nb]) nb |= NBR_EPS;
+    w.arec[p] = make_int2(w.side == 0 ? ol : il, nb);
+  }
+}
+
+// Group offsets of an in-view with few arcs per state: off[q] = first position
+// whose group is >= q, by binary search over the sorted keys.
+__global__ __launch_bounds__(NT) void k_view_offsets(ViewBuild B, int j,
+                                                     const ull *__restrict__ k) {
+  const ViewIn &w = B.v[j];
+  for (long long q = (long long)blockIdx.x * NT + threadIdx.x; q <= w.g.V;
+       q += (long long)gridDim.x * NT) {
+    const ull x = (((ull)(uint32_t)w.rank << B.grp_bits) + (ull)q) << B.lab_bits;
+    long long lo = 0, hi = w.g.E;
+    while (lo < hi) {
+      const long long mid = lo + ((hi - lo) >> 1);
+      if (k[B.sbegin[j] + mid] < x) lo = mid + 1; else hi = mid;
+    }
+    w.off[q] = (int32_t)lo;
+  }
+}
+
+// First record of every state.
+__global__ __launch_bounds__(NT) void k_view_states(ViewBuild B) {
+  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < B.vbegin[4];
+       i += (long long)gridDim.x * NT) {
+    const int j = view_of(B.vbegin, i);
+    const ViewIn &w = B.v[j];
+    const long long q = i - B.vbegin[j];
+    const int32_t *off = w.by_dst ? w.off : w.g.off;
+    const int32_t s0 = off[q], s1 = off[q + 1];
+    const int32_t n = lb_label(w.arec, s0, s1, 1) - s0;
+    int32_t flags = w.g.accept[q] ? (int32_t)FLAG_ACCEPT : 0;
+    if (w.side == 0 && (w.by_dst ? B.eps[q] != 0 : n > 0)) flags |= (int32_t)FLAG_EPS_OUT;
+    if (!w.by_dst && w.g.start[q]) flags |= (int32_t)FLAG_START;
+    w.srec[2 * q] = make_int4(s0, n, s1, flags);
+  }
+}
+
+// Groups longer than this are never marked FLAG_UNIQ in A (their labels are
+// not checked one by one).
+constexpr int32_t UNIQ_SCAN_MAX = 256;
+
 // FLAG_UNIQ of a view's records, from the opposite view's groups.
 __global__ __launch_bounds__(NT) void k_mark_unique(ViewJobs J) {
   for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < J.vbegin[4];
        i += (long long)gridDim.x * NT) {
-    const int j = job_of(J, J.vbegin, i);
+    const int j = view_of(J.vbegin, i);
     const ViewJob &b = J.j[j];
     const long long v = i - J.vbegin[j];
     const int4 o = b.other[2 * v];
@@ -363,102 +351,105 @@ __global__ __launch_bounds__(NT) void k_mark_unique(ViewJobs J) {
   }
 }
 
-// Mark every arc whose other end has FLAG_UNIQ in its view.
-__global__ __launch_bounds__(NT) void k_mark_arcs(ViewJobs J) {
-  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < J.ebegin[4];
-       i += (long long)gridDim.x * NT) {
-    const int j = job_of(J, J.ebegin, i);
-    const ViewJob &b = J.j[j];
-    const long long e = i - J.ebegin[j];
-    const int2 a = b.arec[e];
-    if (b.srec[2 * (size_t)(a.y & NBR_MASK)].w & (int32_t)FLAG_UNIQ)
-      b.arec[e] = make_int2(a.x, a.y | NBR_UNIQ);
-  }
+// What follows from FLAG_UNIQ, in one kernel whose parts do not wait for each
+// other: every arc whose other end has the flag is marked; the second record
+// of every state, and FLAG_DISTINCT; chain records; label buckets.  A part
+// that needs an arc's mark forms it from the other end's record, since the
+// arc may be marked or not yet (neither changes what the parts read).
+__device__ __forceinline__ int32_t marked(const ViewJob &b, int32_t y) {
+  return (y & ~NBR_UNIQ) |
+         (b.srec[2 * (size_t)(y & NBR_MASK)].w & (int32_t)FLAG_UNIQ ? NBR_UNIQ : 0);
 }
 
 // Second state record: the first epsilon and first non-epsilon arcs; and
 // FLAG_DISTINCT in the first.
-__global__ __launch_bounds__(NT) void k_state_inline(ViewJobs J) {
-  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < J.vbegin[4];
-       i += (long long)gridDim.x * NT) {
-    const int j = job_of(J, J.vbegin, i);
-    const ViewJob &b = J.j[j];
-    const long long v = i - J.vbegin[j];
-    const int4 r = b.srec[2 * v];
-    const int2 first_ne = r.x + r.y < r.z ? b.arec[r.x + r.y] : make_int2(0, 0);
-    b.srec[2 * v + 1] = make_int4(r.y > 0 ? b.arec[r.x].y : 0, first_ne.x, first_ne.y, 0);
-    // labels are sorted inside the group: distinct unless two neighbours are
-    // equal (eight arcs per round, loaded together)
-    bool d = r.z - r.x - r.y <= DISTINCT_SCAN_MAX;
-    int32_t last = -1;  // label before the round (none: -1, labels are >= 0)
-    for (int32_t k0 = r.x + r.y; d && k0 < r.z; k0 += 8) {
-      int32_t l[8];
+__device__ __forceinline__ void finish_state(const ViewJob &b, long long v) {
+  const int4 r = b.srec[2 * v];
+  const int2 first_ne = r.x + r.y < r.z ? b.arec[r.x + r.y] : make_int2(0, 0);
+  const int32_t first_eps = r.y > 0 ? b.arec[r.x].y : 0;
+  b.srec[2 * v + 1] = make_int4(r.y > 0 ? marked(b, first_eps) : 0, first_ne.x,
+                                r.x + r.y < r.z ? marked(b, first_ne.y) : 0, 0);
+  // labels are sorted inside the group: distinct unless two neighbours are
+  // equal (eight arcs per round, loaded together)
+  bool d = r.z - r.x - r.y <= DISTINCT_SCAN_MAX;
+  int32_t last = -1;  // label before the round (none: -1, labels are >= 0)
+  for (int32_t k0 = r.x + r.y; d && k0 < r.z; k0 += 8) {
+    int32_t l[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) l[q] = k0 + q < r.z ? b.arec[k0 + q].x : -1 - q;
+    for (int q = 0; q < 8; ++q) l[q] = k0 + q < r.z ? b.arec[k0 + q].x : -1 - q;
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if ((q ? l[q - 1] : last) == l[q]) d = false;
-      last = l[7];
-    }
-    if (d) b.srec[2 * v] = make_int4(r.x, r.y, r.z, r.w | (int32_t)FLAG_DISTINCT);
+    for (int q = 0; q < 8; ++q)
+      if ((q ? l[q - 1] : last) == l[q]) d = false;
+    last = l[7];
   }
+  if (d) b.srec[2 * v] = make_int4(r.x, r.y, r.z, r.w | (int32_t)FLAG_DISTINCT);
 }
 
-// Chain records of the views that have them (see View).
-__global__ __launch_bounds__(NT) void k_chains(ViewJobs J) {
-  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < J.vbegin[4];
-       i += (long long)gridDim.x * NT) {
-    const int j = job_of(J, J.vbegin, i);
-    const ViewJob &b = J.j[j];
-    if (!b.chain) continue;
-    const long long v = i - J.vbegin[j];
-    int32_t w[4 * CHAIN_INT4] = {};
-    int n = 0;
-    uint32_t cur = (uint32_t)v;
+// Chain record (see View).
+__device__ __forceinline__ void finish_chain(const ViewJob &b, long long v) {
+  int32_t w[4 * CHAIN_INT4] = {};
+  int n = 0;
+  uint32_t cur = (uint32_t)v;
+  int4 r = b.srec[2 * (size_t)cur];
 #pragma unroll
-    for (int k = 0; k < CHAIN_STEPS; ++k) {
-      if (n == k) {
-        const int4 r = b.srec[2 * (size_t)cur];
-        const int2 a = r.z - r.x == 1 ? b.arec[r.x] : make_int2(0, 0);
-        const bool step = r.z - r.x == 1 && a.x != 0 && (a.y & NBR_UNIQ) &&
-                          !(b.out_view && (r.w & (int32_t)FLAG_ACCEPT));
-        if (step) {
+  for (int k = 0; k < CHAIN_STEPS; ++k) {
+    if (n == k) {
+      const int2 a = r.z - r.x == 1 ? b.arec[r.x] : make_int2(0, 0);
+      if (r.z - r.x == 1 && a.x != 0 && !(b.out_view && (r.w & (int32_t)FLAG_ACCEPT))) {
+        const uint32_t to = (uint32_t)(a.y & NBR_MASK);
+        const int4 rt = b.srec[2 * (size_t)to];
+        if (rt.w & (int32_t)FLAG_UNIQ) {
           w[1 + 2 * k] = a.x;
-          w[2 + 2 * k] = a.y;
-          cur = (uint32_t)(a.y & NBR_MASK);
+          w[2 + 2 * k] = a.y | NBR_UNIQ;
+          cur = to;
+          r = rt;
           n = k + 1;
         }
       }
     }
-    static_assert(4 * CHAIN_INT4 > 1 + 2 * CHAIN_STEPS, "a spare last word");
-    w[0] = n;
-    if (n) {
-      const int4 r = b.srec[2 * (size_t)cur];
-      if (r.z - r.x == 1 && r.y == 1) {
-        w[0] |= CHAIN_EPS;
-        w[4 * CHAIN_INT4 - 1] = b.arec[r.x].y;
-      }
-    }
-    int4 *c = b.chain + CHAIN_INT4 * v;
-#pragma unroll
-    for (int q = 0; q < CHAIN_INT4; ++q)
-      c[q] = make_int4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
   }
+  static_assert(4 * CHAIN_INT4 > 1 + 2 * CHAIN_STEPS, "a spare last word");
+  w[0] = n;
+  if (n && r.z - r.x == 1 && r.y == 1) {
+    w[0] |= CHAIN_EPS;
+    w[4 * CHAIN_INT4 - 1] = marked(b, b.arec[r.x].y);
+  }
+  int4 *c = b.chain + CHAIN_INT4 * v;
+#pragma unroll
+  for (int q = 0; q < CHAIN_INT4; ++q)
+    c[q] = make_int4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
 }
 
-// Label buckets: lut[v * S + l] = {first position of label l, first > l,
-// neighbour of the first arc (or -1), 0}, for the views that have them.
-__global__ __launch_bounds__(NT) void k_build_lut(ViewJobs J) {
-  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < J.lbegin[4];
+__global__ __launch_bounds__(NT) void k_view_finish(ViewJobs J) {
+  // states, their chains, arcs, buckets: the longest parts first
+  const long long nv = J.vbegin[4], ne = J.ebegin[4], nl = J.lbegin[4];
+  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < 2 * nv + ne + nl;
        i += (long long)gridDim.x * NT) {
-    const int j = job_of(J, J.lbegin, i);
-    const ViewJob &b = J.j[j];
-    const long long x = i - J.lbegin[j];
-    const int32_t v = (int32_t)(x / b.lstride), l = (int32_t)(x % b.lstride);
-    const int4 r = b.srec[2 * (size_t)v];
-    const int32_t lo = lb_label(b.arec, r.x, r.z, l);
-    const int32_t hi = lb_label(b.arec, lo, r.z, l + 1);
-    b.lut[x] = make_int4(lo, hi, lo < hi ? b.arec[lo].y : -1, 0);
+    if (i < 2 * nv) {
+      const long long s = i < nv ? i : i - nv;
+      const int j = view_of(J.vbegin, s);
+      const ViewJob &b = J.j[j];
+      if (i < nv) finish_state(b, s - J.vbegin[j]);
+      else if (b.chain) finish_chain(b, s - J.vbegin[j]);
+    } else if (i < 2 * nv + ne) {
+      const long long a = i - 2 * nv;
+      const int j = view_of(J.ebegin, a);
+      const ViewJob &b = J.j[j];
+      int32_t *y = &b.arec[a - J.ebegin[j]].y;
+      *y = marked(b, *y);
+    } else {
+      // lut[v * S + l] = {first position of label l, first > l, neighbour of
+      // the first arc (or -1), 0}
+      const long long x0 = i - 2 * nv - ne;
+      const int j = view_of(J.lbegin, x0);
+      const ViewJob &b = J.j[j];
+      const long long x = x0 - J.lbegin[j];
+      const int32_t v = (int32_t)(x / b.lstride), l = (int32_t)(x % b.lstride);
+      const int4 r = b.srec[2 * (size_t)v];
+      const int32_t lo = lb_label(b.arec, r.x, r.z, l);
+      const int32_t hi = lb_label(b.arec, lo, r.z, l + 1);
+      b.lut[x] = make_int4(lo, hi, lo < hi ? marked(b, b.arec[lo].y) : -1, 0);
+    }
   }
 }
 
@@ -1899,9 +1890,17 @@ __global__ __launch_bounds__(NT) void k_linear_seed(LinearArgs F, LinearArgs B,
   }
 }
 
-__global__ __launch_bounds__(NT) void k_collect(const uint8_t *__restrict__ flags, int V,
-                                                int32_t *__restrict__ list,
-                                                uint32_t *__restrict__ count) {
+// The flagged states of A (first row of workgroups) and of B.
+__global__ __launch_bounds__(NT) void k_collect(const uint8_t *__restrict__ fa, int VA,
+                                                int32_t *__restrict__ la,
+                                                uint32_t *__restrict__ na,
+                                                const uint8_t *__restrict__ fb, int VB,
+                                                int32_t *__restrict__ lb,
+                                                uint32_t *__restrict__ nb) {
+  const uint8_t *flags = blockIdx.y ? fb : fa;
+  const int V = blockIdx.y ? VB : VA;
+  int32_t *list = blockIdx.y ? lb : la;
+  uint32_t *count = blockIdx.y ? nb : na;
   for (long long v = (long long)blockIdx.x * NT + threadIdx.x; v < V;
        v += (long long)gridDim.x * NT) {
     bool want = flags[v] != 0;
@@ -2535,13 +2534,15 @@ __global__ __launch_bounds__(NT) void k_count(Problem P, ull nwords, ull nchunks
                                               uint8_t *__restrict__ cnt8,
                                               uint32_t *__restrict__ cnt32,
                                               uint32_t *__restrict__ btot,
-                                              uint2 *__restrict__ heavy, Scalars *sc) {
+                                              uint2 *__restrict__ heavy, uint32_t cap,
+                                              Scalars *sc) {
   const ull chunk = (ull)blockIdx.x * NWAVES + threadIdx.x / WAVE;
   if (chunk >= nchunks) return;  // the whole wavefront
   __shared__ uint16_t s_keys[NWAVES][OUT_WORDS * 32];
   uint16_t *list = s_keys[threadIdx.x / WAVE];
   const TrimChunk t = trim_chunk(P, chunk, nwords);
   const uint32_t first = t.count ? P.wbase[t.w0] : 0u;
+  if ((ull)first + t.count > cap) return;  // no room: the host counts again
   trim_expand(t, list);
   uint32_t sum = 0;
   // each round reads the next round's keys before its own loads
@@ -2755,47 +2756,53 @@ hipError_t launch_validate(const DevGraph &g, int side, uint32_t *err, uint32_t 
   return hipGetLastError();
 }
 
-hipError_t sort_view(const DevGraph &g, int side, bool by_dst, bool presorted, int lab_bits,
-                     int4 *srec, int2 *arec, int32_t *perm, int32_t *olab, float *w,
-                     int32_t *off_tmp, const int4 *eps_rec, unsigned long long *k0, int32_t *v0,
-                     unsigned long long *k1, int32_t *v1, void *sort_temp, uint32_t *eps_states,
-                     hipStream_t s) {
-  const size_t E = (size_t)g.E;
+size_t views_sort_entries(const ViewBuild &B) {
+  size_t n = 0;
+  for (int j = 0; j < 4; ++j)
+    if (B.v[j].sorted) n += (size_t)B.v[j].g.E;
+  return n;
+}
+
+hipError_t build_views(ViewBuild B, unsigned long long *k0, int32_t *v0, unsigned long long *k1,
+                       int32_t *v1, void *sort_temp, hipStream_t s) {
   hipError_t e;
-  if (E) {
-    const bool sort = by_dst || !presorted;
-    bool second = false;
-    if (sort) {
-      k_make_keys<<<grid_for(E), NT, 0, s>>>(g, side, by_dst ? 1 : 0, lab_bits, k0, v0);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      int bits = bitlen((unsigned long long)(g.V > 0 ? g.V - 1 : 0)) + lab_bits;
-      if ((e = radix_sort(k0, v0, k1, v1, E, bits, sort_temp, s, &second)) != hipSuccess)
-        return e;
-    }
-    const ull *ks = sort ? (second ? k1 : k0) : nullptr;
-    const int32_t *vs = sort ? (second ? v1 : v0) : nullptr;
-    k_split<<<grid_for(E), NT, 0, s>>>(g, by_dst ? 1 : 0, ks, vs, (long long)E, lab_bits, eps_rec,
-                                       side, perm, olab, w, arec);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (by_dst) {
-      if (4 * E >= (size_t)g.V)
-        k_group_bounds<<<grid_for(E + 1, 2048), NT, 0, s>>>(ks, (long long)E, g.V, lab_bits,
-                                                           off_tmp);
-      else
-        k_group_offsets<<<grid_for((size_t)g.V + 1), NT, 0, s>>>(ks, (long long)E, g.V,
-                                                                lab_bits, off_tmp);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-  } else if (by_dst) {
-    k_group_offsets<<<grid_for((size_t)g.V + 1), NT, 0, s>>>(nullptr, 0, g.V, lab_bits, off_tmp);
+  int ranks = 0;
+  B.lab_bits = B.grp_bits = 0;
+  for (int j = 0; j < 4; ++j) {
+    ViewIn &w = B.v[j];
+    B.ebegin[j + 1] = B.ebegin[j] + w.g.E;
+    B.vbegin[j + 1] = B.vbegin[j] + w.g.V;
+    B.sbegin[j + 1] = B.sbegin[j] + (w.sorted ? w.g.E : 0);
+    w.scan_off = 4 * (long long)w.g.E >= w.g.V && w.g.E > 0;
+    if (!w.sorted) continue;
+    w.rank = ranks++;
+    const int gb = bitlen((unsigned long long)(w.g.V > 0 ? w.g.V - 1 : 0));
+    if (gb > B.grp_bits) B.grp_bits = gb;
+    if (w.lab_bits > B.lab_bits) B.lab_bits = w.lab_bits;
+  }
+  const long long n = B.sbegin[4], eps_arcs = B.eps ? B.v[0].g.E : 0;
+  bool second = false;
+  if (n || eps_arcs) {
+    k_view_keys<<<grid_for((size_t)(n > eps_arcs ? n : eps_arcs)), NT, 0, s>>>(B, k0, v0,
+                                                                              eps_arcs);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const int32_t *off = by_dst ? off_tmp : g.off;
-  if (g.V) {
-    const int eps_mode = side == 1 ? 0 : (by_dst ? 2 : 1);
-    k_state_rec<<<grid_for((size_t)g.V, 256), NT, 0, s>>>(off, arec, g.V, g.accept,
-                                                          by_dst ? nullptr : g.start, eps_mode,
-                                                          eps_rec, srec, eps_states);
+  if (n) {
+    const int bits = B.lab_bits + B.grp_bits + bitlen((unsigned long long)(ranks - 1));
+    if ((e = radix_sort(k0, v0, k1, v1, (size_t)n, bits, sort_temp, s, &second)) != hipSuccess)
+      return e;
+  }
+  if (B.ebegin[4]) {
+    k_view_arcs<<<grid_for((size_t)B.ebegin[4]), NT, 0, s>>>(B, second ? v1 : v0);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  for (int j = 0; j < 4; ++j)
+    if (B.v[j].by_dst && !B.v[j].scan_off) {
+      k_view_offsets<<<grid_for((size_t)B.v[j].g.V + 1), NT, 0, s>>>(B, j, second ? k1 : k0);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+  if (B.vbegin[4]) {
+    k_view_states<<<grid_for((size_t)B.vbegin[4]), NT, 0, s>>>(B);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
@@ -2807,20 +2814,9 @@ hipError_t finish_views(ViewJobs J, hipStream_t s) {
     k_mark_unique<<<grid_for((size_t)J.vbegin[4]), NT, 0, s>>>(J);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (J.ebegin[4]) {
-    k_mark_arcs<<<grid_for((size_t)J.ebegin[4]), NT, 0, s>>>(J);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (J.vbegin[4]) {
-    k_state_inline<<<grid_for((size_t)J.vbegin[4]), NT, 0, s>>>(J);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (J.j[0].chain || J.j[1].chain || J.j[2].chain || J.j[3].chain) {
-      k_chains<<<grid_for((size_t)J.vbegin[4]), NT, 0, s>>>(J);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-  }
-  if (J.lbegin[4]) {
-    k_build_lut<<<grid_for((size_t)J.lbegin[4], 8192), NT, 0, s>>>(J);
+  const size_t n = (size_t)(2 * J.vbegin[4] + J.ebegin[4] + J.lbegin[4]);
+  if (n) {
+    k_view_finish<<<grid_for(n, 8192), NT, 0, s>>>(J);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
@@ -2828,22 +2824,22 @@ hipError_t finish_views(ViewJobs J, hipStream_t s) {
 
 hipError_t launch_seed_forward(const Problem &P, const SearchArgs &S, int32_t *la, uint32_t *na,
                                int32_t *lb, uint32_t *nb, hipStream_t s) {
-  k_collect<<<grid_for((size_t)P.A.V, 1024), NT, 0, s>>>(P.A.start, P.A.V, la, na);
-  hipError_t e = hipGetLastError();
+  const size_t V = (size_t)(P.A.V > P.B.V ? P.A.V : P.B.V);
+  k_collect<<<dim3(grid_for(V, 1024), 2), NT, 0, s>>>(P.A.start, P.A.V, la, na, P.B.start, P.B.V, lb,
+                                                      nb);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_collect<<<grid_for((size_t)P.B.V, 1024), NT, 0, s>>>(P.B.start, P.B.V, lb, nb);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   k_seed_forward<<<64, NT, 0, s>>>(P, S, la, na, lb, nb);
   return hipGetLastError();
 }
 
 hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, int32_t *la,
                                 uint32_t *na, int32_t *lb, uint32_t *nb, hipStream_t s) {
-  k_collect<<<grid_for((size_t)P.A.V, 1024), NT, 0, s>>>(P.A.accept, P.A.V, la, na);
-  hipError_t e = hipGetLastError();
+  const size_t V = (size_t)(P.A.V > P.B.V ? P.A.V : P.B.V);
+  k_collect<<<dim3(grid_for(V, 1024), 2), NT, 0, s>>>(P.A.accept, P.A.V, la, na, P.B.accept, P.B.V, lb,
+                                                      nb);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_collect<<<grid_for((size_t)P.B.V, 1024), NT, 0, s>>>(P.B.accept, P.B.V, lb, nb);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   k_seed_backward<<<1024, NT, 0, s>>>(P, S, la, na, lb, nb);
   return hipGetLastError();
 }
@@ -2934,11 +2930,13 @@ hipError_t launch_trim(const Problem &P, uint32_t VA, uint32_t *trim, uint32_t *
 }
 
 hipError_t launch_count(const Problem &P, size_t nwords, uint8_t *cnt8, uint32_t *cnt32,
-                        uint32_t *btot, uint2 *heavy, Scalars *sc, hipStream_t s) {
+                        uint32_t *btot, uint2 *heavy, uint32_t cap, Scalars *sc,
+                        hipStream_t s) {
   const size_t nchunks = out_chunks(nwords);
   if (!nchunks) return hipSuccess;
   if (!P.trim || !P.wbase) return hipErrorInvalidValue;  // no trim bitmap to expand
-  k_count<<<out_grid(nchunks), NT, 0, s>>>(P, nwords, nchunks, cnt8, cnt32, btot, heavy, sc);
+  k_count<<<out_grid(nchunks), NT, 0, s>>>(P, nwords, nchunks, cnt8, cnt32, btot, heavy, cap,
+                                             sc);
   return hipGetLastError();
 }
 

@@ -205,7 +205,9 @@ struct Scalars {
   unsigned long long generated; // moves out of accessible keys (on request)
   unsigned long long generated_bwd; // predecessor moves of co-accessible keys (on request)
   unsigned long long naccessible; // keys reached by the forward search
-  unsigned long long total;     // scan totals
+  unsigned long long total;     // arcs of C
+  unsigned long long nstates;   // states of C
+  uint32_t lists[4];            // start states of A and B listed, then accepting ones
   GenSlot G[3];                 // generation slots of a search
   GenSlot G2[3];                // of the backward search running beside it
   uint32_t gens2, pad1;         // its generations that had work
@@ -553,22 +555,34 @@ hipError_t radix_sort(unsigned long long *k0, int32_t *v0, unsigned long long *k
 hipError_t launch_validate(const DevGraph &g, int side, uint32_t *err, uint32_t *maxlab,
                            hipStream_t s, uint32_t *nacc = nullptr, bool check = true,
                            uint32_t *single = nullptr);
-// Views are built in two steps.  sort_view: sort the arcs of a view (side
-// 0: A by olabel, side 1: B by ilabel; by_dst selects in-views, for which
-// `off_tmp` (V+1 words) receives the group offsets; an out-view of an input
-// whose groups are already in label order (presorted) is not sorted) into
-// arec / perm, gather olab / w for out-views, and write the first record of
-// every state.  k0/v0/k1/v1 are E-sized sort buffers.  eps_rec is A's
-// out-view records when building A's in-view (to carry epsOutA), else null.
-// If eps_states is set, it counts the states with an epsilon arc in the
-// view.  Then finish_views (once all four views are sorted) sets FLAG_UNIQ
-// (from the opposite view of the same graph), marks the arcs, writes the
-// second record of every state and the label buckets.
-hipError_t sort_view(const DevGraph &g, int side, bool by_dst, bool presorted, int lab_bits,
-                     int4 *srec, int2 *arec, int32_t *perm, int32_t *olab, float *w,
-                     int32_t *off_tmp, const int4 *eps_rec, unsigned long long *k0, int32_t *v0,
-                     unsigned long long *k1, int32_t *v1, void *sort_temp, uint32_t *eps_states,
-                     hipStream_t s);
+// Views are built in two steps.  build_views: the arcs of up to four views
+// (side 0: A by olabel, side 1: B by ilabel; by_dst: in-views) in the order of
+// their group and label (an out-view whose groups are already in label order
+// is not sorted), into arec / perm, for out-views also olab / wv, for
+// in-views the group offsets off (V + 1 words), and the first record of every
+// state.  eps (a byte per state of A, cleared; view 0 is then A's out-view)
+// receives epsOutA, which A's in-view carries.  k0/v0/k1/v1 hold
+// views_sort_entries() sort entries.  Then finish_views sets FLAG_UNIQ (from
+// the opposite view of the same graph), marks the arcs, writes the second
+// record of every state, the chain records and the label buckets.
+struct ViewIn {
+  DevGraph g;
+  int32_t side, by_dst, sorted, lab_bits;
+  int4 *srec;
+  int2 *arec;
+  int32_t *perm, *olab, *off;
+  float *wv;
+  int32_t rank, scan_off;  // set by build_views
+};
+struct ViewBuild {
+  ViewIn v[4];
+  uint8_t *eps;
+  long long ebegin[5], vbegin[5], sbegin[5];  // set by build_views, as are
+  int32_t lab_bits, grp_bits;                 // these
+};
+size_t views_sort_entries(const ViewBuild &B);
+hipError_t build_views(ViewBuild B, unsigned long long *k0, int32_t *v0, unsigned long long *k1,
+                       int32_t *v1, void *sort_temp, hipStream_t s);
 
 // One view for finish_views: its records and arcs, the opposite view's
 // (`other`), the states excluded from FLAG_UNIQ (start states for out-views,
@@ -641,8 +655,10 @@ hipError_t launch_trim(const Problem &P, uint32_t VA, uint32_t *trim, uint32_t *
 // wavefront: cnt8[id] (255: the count is in cnt32[id]) for light states,
 // heavy states listed in `heavy` as (id, key) (their number in
 // Scalars::heavy), btot[chunk] = the chunk's light total.
+// Nothing is written for chunks with states from cap on (the arrays' size).
 hipError_t launch_count(const Problem &P, size_t nwords, uint8_t *cnt8, uint32_t *cnt32,
-                        uint32_t *btot, uint2 *heavy, Scalars *sc, hipStream_t s);
+                        uint32_t *btot, uint2 *heavy, uint32_t cap, Scalars *sc,
+                        hipStream_t s);
 // Counts of the heavy states (cnt8 / cnt32, added to their chunk's btot).
 hipError_t launch_count_heavy(const Problem &P, const uint2 *heavy, const uint32_t *nheavy_dev,
                               uint8_t *cnt8, uint32_t *cnt32, uint32_t *btot, hipStream_t s);

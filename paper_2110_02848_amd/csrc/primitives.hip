@@ -9,6 +9,9 @@ namespace {
 
 constexpr int SCAN_ITEMS = 8;
 constexpr size_t SCAN_TILE = (size_t)NT * SCAN_ITEMS;
+// Tiles up to which each workgroup of a scan adds up the tiles before its own
+// (8 loads per thread at most; above, the sums are scanned by a launch more).
+constexpr size_t SCAN_LOCAL = 2048;
 // Elements per thread of a sort tile: small inputs (the views of most
 // operands) take short tiles for more workgroups, large ones long tiles for a
 // smaller digit histogram.
@@ -43,10 +46,19 @@ __global__ __launch_bounds__(NT) void k_scan_reduce(const TI *__restrict__ in, s
 template <typename TI, typename TO>
 __global__ __launch_bounds__(NT) void k_scan_final(const TI *in, TO *out, size_t n,
                                                    const ull *__restrict__ part_scanned,
-                                                   ull *__restrict__ total, int out_last) {
+                                                   ull *__restrict__ total, int out_last,
+                                                   int local) {
   __shared__ ull s_w[NWAVES];
   const size_t base = (size_t)blockIdx.x * SCAN_TILE;
-  ull carry = part_scanned ? part_scanned[blockIdx.x] : 0ull;
+  ull carry = 0;
+  if (local) {  // the tiles' sums as they are: added up here
+    for (unsigned t = threadIdx.x; t < blockIdx.x; t += NT) carry += part_scanned[t];
+    ull all;
+    (void)block_excl_scan<ull>(carry, s_w, all);
+    carry = all;
+  } else if (part_scanned) {
+    carry = part_scanned[blockIdx.x];
+  }
   for (int r = 0; r < SCAN_ITEMS; ++r) {
     size_t i = base + (size_t)r * NT + threadIdx.x;
     ull x = (i < n) ? (ull)in[i] : 0ull;
@@ -73,7 +85,7 @@ hipError_t scan_rec(const TI *in, TO *out, size_t n, bool out_last, ull *total, 
                     hipStream_t s) {
   size_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
   if (nb <= 1) {
-    k_scan_final<TI, TO><<<1, NT, 0, s>>>(in, out, n, nullptr, total, out_last ? 1 : 0);
+    k_scan_final<TI, TO><<<1, NT, 0, s>>>(in, out, n, nullptr, total, out_last ? 1 : 0, 0);
     return hipGetLastError();
   }
   ull *part = reinterpret_cast<ull *>(temp);
@@ -81,11 +93,16 @@ hipError_t scan_rec(const TI *in, TO *out, size_t n, bool out_last, ull *total, 
   k_scan_reduce<TI><<<(unsigned)nb, NT, 0, s>>>(in, n, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (nb <= SCAN_LOCAL) {
+    k_scan_final<TI, TO><<<(unsigned)nb, NT, 0, s>>>(in, out, n, part, total, out_last ? 1 : 0,
+                                                     1);
+    return hipGetLastError();
+  }
   // Scan the block sums in place.  Their grand total is written to *total,
   // which the final pass below overwrites (stream order) with the real one.
   e = scan_rec<ull, ull>(part, part, nb, false, total, rest, s);
   if (e != hipSuccess) return e;
-  k_scan_final<TI, TO><<<(unsigned)nb, NT, 0, s>>>(in, out, n, part, total, out_last ? 1 : 0);
+  k_scan_final<TI, TO><<<(unsigned)nb, NT, 0, s>>>(in, out, n, part, total, out_last ? 1 : 0, 0);
   return hipGetLastError();
 }
 
