@@ -57,7 +57,7 @@ struct fst_ctx {
   bool have_times = false;
   bool timed_run = false;
 
-  DevBuf scal, lists, eps;
+  DevBuf scal, lists, eps, keys;
   DevBuf k0, k1, v0, v1, sort_tmp, scan_tmp;
   DevBuf aOutPerm, aOutArc, aOutRec, aOutLut, bOutPerm, bOutArc, bOutRec, bOutLut;
   DevBuf aOutLab, aOutW, bOutLab, bOutW, bOutChain, bInChain;
@@ -79,6 +79,7 @@ struct fst_ctx {
   int lv3_hint[2] = {0, 0};  // levels the last three-input searches took (bwd, fwd)
   unsigned long long list_hint = 0;  // search list capacity the last run needed
   int gen_hint = 0;  // launches the last concurrent search took
+  unsigned long long state_hint = 0;  // states of the last C
   unsigned long long list_start = 1ull << 22;  // FST_OPT_LIST_CAPACITY
   struct {
     bool ready = false;
@@ -1110,30 +1111,43 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   // ---- numbering and arc counts ----
   phase_begin(c, PH_COUNT, s);
   HIP_TRY(scan_u32(wbase, wbase, nwords, false, &d_sc->nstates, c->scan_tmp.p, s));
-  const Problem &P = c->P;
-  const size_t nchunks = out_chunks(nwords);
-  FST_TRY(ensure(c, c->btot, (nchunks + 1) * 4));
-  FST_TRY(ensure(c, c->scan_tmp, scan_temp_bytes(nchunks + 1)));
-  uint32_t *btot = as<uint32_t>(c->btot);
+  // Compaction by state (its list of keys takes 4 bytes a state), or by chunks
+  // of trim words where the workspace has no room for the list.
+  Problem &P = c->P;
+  bool by_state = true;
   // the search lists are free now: the forward queue takes the counts of
   // 255 arcs or more, the backward queue the heavy states (id, key).  The
   // count is queued for as many states as the buffers hold, as after a call of
   // about this size, without waiting for their number; where they turn out to
-  // be too small, or the queues were never made, it is queued (again) after
-  // the read-back.
+  // be too small, or were never made, it is queued (again) after the
+  // read-back.
   const KernelTimer tc = timer(c, FST_KERNEL_COUNT);
   auto room = [&]() -> unsigned long long {
-    size_t n = c->cnt.cap;
+    unsigned long long n = c->cnt.cap;
     n = n < c->fq.cap / 4 ? n : c->fq.cap / 4;
     n = n < c->bq.cap / 8 ? n : c->bq.cap / 8;
-    return n < (size_t)INT32_MAX ? n : (size_t)INT32_MAX;
+    if (by_state) {  // its grid covers the room: no more than the last call suggests
+      const unsigned long long last = c->state_hint + c->state_hint / 4 + 4096;
+      n = n < c->keys.cap / 4 ? n : c->keys.cap / 4;
+      n = n < last ? n : last;
+    }
+    return n < (unsigned long long)INT32_MAX ? n : (unsigned long long)INT32_MAX;
   };
   auto count = [&](uint32_t cap) -> int {
+    // 64 states, in whole workgroups, or OUT_WORDS trim words a chunk
+    const size_t nchunks = by_state ? ((size_t)cap + NT - 1) / NT * NWAVES : out_chunks(nwords);
+    FST_TRY(ensure(c, c->btot, (nchunks + 1) * 4));
+    FST_TRY(ensure(c, c->scan_tmp, scan_temp_bytes(nchunks + 1)));
     uint8_t *cnt8 = as<uint8_t>(c->cnt);
-    uint32_t *cnt32 = as<uint32_t>(c->fq);
+    uint32_t *cnt32 = as<uint32_t>(c->fq), *btot = as<uint32_t>(c->btot);
     uint2 *heavy = as<uint2>(c->bq);
+    P.keys = by_state ? as<uint32_t>(c->keys) : nullptr;
     tc.begin(s);
-    HIP_TRY(launch_count(P, nwords, cnt8, cnt32, btot, heavy, cap, d_sc, s));
+    if (by_state)
+      HIP_TRY(launch_count_states(P, nwords, &d_sc->nstates, as<uint32_t>(c->keys), cnt8, cnt32,
+                                  btot, heavy, cap, d_sc, s));
+    else
+      HIP_TRY(launch_count(P, nwords, cnt8, cnt32, btot, heavy, cap, d_sc, s));
     HIP_TRY(launch_count_heavy(P, heavy, &d_sc->heavy, cnt8, cnt32, btot, s));
     tc.end(s);
     // exclusive arc offset of every chunk; the total is E_C
@@ -1147,17 +1161,22 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   const unsigned long long nst = c->h_sc->nstates;
   if (nst > (unsigned long long)INT32_MAX) return FST_ERR_TOO_LARGE;
   const uint32_t nstates = (uint32_t)nst;
+  c->state_hint = nstates;
   if (!cap0 || nst > cap0) {
     FST_TRY(ensure(c, c->fq, ((size_t)nstates + 1) * 4));
     FST_TRY(ensure(c, c->bq, ((size_t)nstates + 1) * 8));
     FST_TRY(ensure(c, c->cnt, (size_t)nstates + 1));
+    const int rc = ensure(c, c->keys, ((size_t)nstates + 1) * 4);
+    if (rc != FST_OK && rc != FST_ERR_NOMEM) return rc;
+    by_state = rc == FST_OK;
     HIP_TRY(hipMemsetAsync(&d_sc->heavy, 0, sizeof(uint32_t), s));
+    HIP_TRY(hipMemsetAsync(&d_sc->total, 0, sizeof(unsigned long long), s));
     FST_TRY(count(nstates));
     FST_TRY(readback(c, s));
   }
   const unsigned long long narcs = c->h_sc->total;
   if (narcs > (unsigned long long)INT32_MAX) return FST_ERR_TOO_LARGE;
-  FST_TRY(add_time(c, FST_KERNEL_COUNT, 2));
+  FST_TRY(add_time(c, FST_KERNEL_COUNT, by_state ? 3 : 2));
 
   c->nstates = nstates;
   c->out_words = nwords;
@@ -1825,7 +1844,7 @@ void fst_ctx_destroy(fst_ctx *c) {
   if (!c) return;
   DeviceGuard g(c->device);
   (void)hipDeviceSynchronize();
-  DevBuf *bufs[] = {&c->scal,     &c->eps,      &c->lists,    &c->k0,      &c->k1,      &c->v0,
+  DevBuf *bufs[] = {&c->scal,     &c->eps,      &c->keys,     &c->lists,    &c->k0,      &c->k1,      &c->v0,
                     &c->v1,       &c->sort_tmp, &c->scan_tmp, &c->aOutPerm, &c->aOutArc,
                     &c->aOutRec,  &c->aOutLut,  &c->bOutPerm, &c->bOutArc, &c->bOutRec,
                     &c->bOutLut,  &c->aInOff,   &c->aInPerm, &c->aInArc,  &c->aInRec,

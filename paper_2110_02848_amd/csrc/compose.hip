@@ -2198,6 +2198,15 @@ __device__ __forceinline__ void put_count(uint8_t *__restrict__ cnt8, uint32_t *
   if (c >= 255u) cnt32[id] = c;
 }
 
+// The output chunk of state id (with key `key`), and a chunk's first state:
+// 64 states where the keys are listed, else the states of OUT_WORDS trim words.
+__device__ __forceinline__ ull chunk_of(const Problem &P, uint32_t id, uint32_t key) {
+  return P.keys ? id / WAVE : (key >> 5) / OUT_WORDS;
+}
+__device__ __forceinline__ ull chunk_first(const Problem &P, ull chunk) {
+  return P.keys ? chunk * WAVE : P.wbase[chunk * OUT_WORDS];
+}
+
 // Arcs of the states of chunk c before state `id` (a state of that chunk,
 // or the first state after it): summed by the whole workgroup, valid in
 // thread 0.
@@ -2205,7 +2214,7 @@ __device__ __forceinline__ uint32_t chunk_arcs_before(const Problem &P, ull chun
                                                       const uint8_t *__restrict__ cnt8,
                                                       const uint32_t *__restrict__ cnt32,
                                                       uint32_t *s_w) {
-  const ull first = P.wbase[chunk * OUT_WORDS];
+  const ull first = chunk_first(P, chunk);
   uint32_t part = 0;
   for (ull j = first + threadIdx.x; j < id; j += NT) part += count_of(cnt8, cnt32, j);
   return block_sum(part, s_w);
@@ -2594,7 +2603,7 @@ __global__ __launch_bounds__(NT) void k_count_heavy(Problem P, const uint2 *__re
     const uint32_t c = heavy_count(P, hk.y, s_w);
     if (threadIdx.x == 0) {
       put_count(cnt8, cnt32, hk.x, c);
-      atomicAdd(btot + (hk.y >> 5) / OUT_WORDS, c);
+      atomicAdd(btot + chunk_of(P, hk.x, hk.y), c);
     }
     __syncthreads();  // s_w is read by thread 0 before the next state's sum
   }
@@ -2662,11 +2671,240 @@ __device__ __forceinline__ void fill_light(const Problem &P, ull nwords, ull nch
   }
 }
 
+// ---------------------------------------------------------------------------
+// compaction by state
+// ---------------------------------------------------------------------------
+// A chunk of trim words leaves lanes idle where the trim keys are far apart,
+// a thread's moves one after the other are a chain of dependent loads, and a
+// store between two moves holds up the loads of the next (a wait for a load
+// also waits for every earlier store).  So the keys are listed first (4 bytes
+// a state), a wavefront takes 64 states, a thread looks up four units of its
+// state at a time, and the fill puts the kept moves into LDS before the
+// wavefront writes them side by side.  Fill by chunks and by state: 850,000
+// states of 2.5 arcs 378 -> 66 us, 3.2 million of 1.3 arcs 659 -> 150 us, 15.5
+// million of a lexicon with provenance 341 -> 219 us, 36.7 million without 521
+// -> 474 us (its count 156 -> 186 us with the list).  By chunks is left for a
+// workspace without room for the list.
+
+// The keys of the states of C in order.
+__global__ __launch_bounds__(NT) void k_state_keys(Problem P, ull nwords, ull nchunks,
+                                                   uint32_t *__restrict__ keys, uint32_t cap) {
+  const ull chunk = (ull)blockIdx.x * NWAVES + threadIdx.x / WAVE;
+  if (chunk >= nchunks) return;  // the whole wavefront
+  __shared__ uint16_t s_keys[NWAVES][OUT_WORDS * 32];
+  uint16_t *list = s_keys[threadIdx.x / WAVE];
+  const TrimChunk t = trim_chunk(P, chunk, nwords);
+  if (!t.count) return;
+  const uint32_t first = P.wbase[t.w0];
+  if ((ull)first + t.count > cap) return;  // no room: the host counts again
+  trim_expand(t, list);
+  for (uint32_t i = __lane_id(); i < t.count; i += WAVE)
+    keys[first + i] = trim_key_at(t, list, i);
+}
+
+// Matching units walk B's arcs only where B has fewer and their labels are
+// distinct (the canonical order is by label, then A's arc), else A's.
+__device__ __forceinline__ bool walks_b(const Fwd &s) {
+  return s.nB < s.nA && (s.flB & (int32_t)FLAG_DISTINCT) != 0;
+}
+__device__ __forceinline__ uint32_t walk_units(const Fwd &s) {
+  const uint32_t m = s.mU ? (walks_b(s) ? s.nB : s.nA) : 0u;
+  return s.eA + (uint32_t)s.be + m;
+}
+
+// Calls f(kept, target key, pa, pb) for every move of a state in canonical
+// order (positions in the out-views, -1: none), four units at a time: their
+// arcs, then their label ranges, then their first targets' trim words are
+// loaded together.
+template <class F>
+__device__ __forceinline__ void enum_moves(const Problem &P, const Fwd &s, F &&f) {
+  constexpr int K = 4;
+  const uint32_t sh = P.shiftB, n = walk_units(s);
+  const bool wb = walks_b(s);
+  for (uint32_t u0 = 0; u0 < n; u0 += K) {
+    int2 ar[K];
+    int32_t p[K], lo[K], hi[K], nb[K];
+    uint32_t d[K], tw[K];
+    bool match[K], onB[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t u = u0 + (uint32_t)k;
+      const bool ea = u < s.eA, eb = !ea && u < s.eA + (uint32_t)s.be;
+      const int32_t j = (int32_t)(u - s.eA - (uint32_t)s.be);
+      match[k] = !ea && !eb;
+      onB[k] = eb || (match[k] && wb);
+      p[k] = ea ? s.aS + (int32_t)u
+                : (eb ? s.bS + (int32_t)(u - s.eA)
+                      : (wb ? s.bS + s.be + j : s.aS + s.ae + j));
+      ar[k] = make_int2(0, 0);
+      if (u < n) ar[k] = (onB[k] ? P.bOut.arec : P.aOut.arec)[p[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      lo[k] = hi[k] = 0;
+      nb[k] = 0;
+      if (u0 + (uint32_t)k < n) {
+        hi[k] = 1;
+        if (match[k]) {
+          if (wb) label_range(P.aOut, s.qa, s.aS + s.ae, s.aE, ar[k].x, lo[k], hi[k], nb[k]);
+          else label_range(P.bOut, s.qb, s.bS + s.be, s.bE, ar[k].x, lo[k], hi[k], nb[k]);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t mine = nbr_of(ar[k].y);
+      const uint32_t oth = match[k] ? nbr_of(nb[k]) : (onB[k] ? s.qa : s.qb);
+      d[k] = onB[k] ? make_key(oth, mine, match[k] ? 0u : s.epsA, sh)
+                    : make_key(mine, oth, 0u, sh);
+      tw[k] = lo[k] < hi[k] ? P.trim[d[k] >> 5] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (lo[k] >= hi[k]) continue;
+      const int32_t q0 = match[k] ? lo[k] : -1;
+      f(((tw[k] >> (d[k] & 31u)) & 1u) != 0, d[k], onB[k] ? q0 : p[k], onB[k] ? p[k] : q0);
+      for (int32_t q = lo[k] + 1; q < hi[k]; ++q) {  // more arcs of the label
+        const uint32_t mine = nbr_of(ar[k].y);
+        const uint32_t oth = nbr_of((wb ? P.aOut.arec : P.bOut.arec)[q].y);
+        const uint32_t dq = wb ? make_key(oth, mine, 0u, sh) : make_key(mine, oth, 0u, sh);
+        f(test_bit(P.trim, dq), dq, wb ? q : p[k], wb ? p[k] : q);
+      }
+    }
+  }
+}
+
+// Kept-arc counts, 64 states per wavefront (btot[w] = their light total);
+// grid: at most cap states.
+__global__ __launch_bounds__(NT) void k_count_states(Problem P, const ull *__restrict__ nstates,
+                                                     uint8_t *__restrict__ cnt8,
+                                                     uint32_t *__restrict__ cnt32,
+                                                     uint32_t *__restrict__ btot,
+                                                     uint2 *__restrict__ heavy, uint32_t cap,
+                                                     Scalars *sc) {
+  const uint32_t id = blockIdx.x * NT + threadIdx.x;
+  const ull n = *nstates;
+  if (n > cap) return;  // no room: the host counts again
+  uint32_t c = 0, key = 0;
+  bool hv = false;
+  if (id < n) {
+    key = P.keys[id];
+    const Fwd s = fwd_info<false>(P, key);
+    if (walk_units(s) > LIGHT_UNITS) {
+      hv = true;
+    } else if (lone_move(s)) {
+      c = 1;
+    } else {
+      enum_moves(P, s, [&](bool kept, uint32_t, int32_t, int32_t) { c += kept ? 1u : 0u; });
+    }
+    put_count(cnt8, cnt32, id, c);
+  }
+  const unsigned long long m = __ballot(hv);
+  if (m) {
+    const int leader = __ffsll(m) - 1;
+    uint32_t hb = 0;
+    if ((int)__lane_id() == leader) hb = atomicAdd(&sc->heavy, (uint32_t)__popcll(m));
+    hb = __shfl(hb, leader, WAVE);
+    if (hv) heavy[hb + __popcll(m & __lanemask_lt())] = make_uint2(id, key);
+  }
+  const uint32_t sum = wave_sum(c);
+  if (__lane_id() == 0) btot[id / WAVE] = sum;
+}
+
+// Kept moves of a wavefront's states on their way out.
+constexpr uint32_t FILL_MOVES = 384;
+struct FillLds {
+  uint32_t d[FILL_MOVES];
+  int32_t pa[FILL_MOVES], pb[FILL_MOVES];
+  uint8_t own[FILL_MOVES];
+  uint32_t pos[WAVE];  // a state's first arc position, less its first entry
+};
+
+__device__ __forceinline__ void fill_states(const Problem &P, uint32_t nstates,
+                                            const uint8_t *__restrict__ cnt8,
+                                            const uint32_t *__restrict__ cnt32,
+                                            const uint32_t *__restrict__ btot, const OutGraph &O,
+                                            unsigned block) {
+  __shared__ FillLds s_l[NWAVES];
+  FillLds &L = s_l[threadIdx.x / WAVE];
+  const uint32_t id = block * NT + threadIdx.x, lane = __lane_id();
+  const bool valid = id < nstates;
+  const uint32_t c = valid ? count_of(cnt8, cnt32, id) : 0u;
+  const uint32_t base = (id - lane) < nstates ? btot[id / WAVE] : 0u;
+  const uint32_t key = valid ? P.keys[id] : 0u;
+  Fwd s = {};
+  bool light = false;
+  if (valid) {
+    s = fwd_info(P, key);
+    light = walk_units(s) <= LIGHT_UNITS;
+  }
+  uint32_t pos = base + wave_incl_scan(c) - c;
+  const uint32_t lc = light ? c : 0u, lincl = wave_incl_scan(lc);
+  const uint32_t total = __shfl(lincl, WAVE - 1, WAVE);
+  const bool fits = total <= FILL_MOVES;
+  if (light && fits && c) {
+    uint32_t e = lincl - lc;
+    L.pos[lane] = pos - e;
+    // one move that is kept (see lone_move): from the records, no trim word
+    Move m;
+    m.fast = false;
+    if (lone_move(s)) m = single_move(P, s);
+    if (m.fast) {
+      L.d[e] = m.d;
+      L.pa[e] = m.pa;
+      L.pb[e] = m.pb;
+      L.own[e] = (uint8_t)lane;
+    } else {
+      enum_moves(P, s, [&](bool kept, uint32_t d, int32_t pa, int32_t pb) {
+        if (kept) {
+          L.d[e] = d;
+          L.pa[e] = pa;
+          L.pb[e] = pb;
+          L.own[e] = (uint8_t)lane;
+          ++e;
+        }
+      });
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (fits) {
+    for (uint32_t e = lane; e < total; e += WAVE) {
+      Move m;
+      m.d = L.d[e];
+      m.pa = L.pa[e];
+      m.pb = L.pb[e];
+      const uint32_t own = L.own[e];
+      put_move(O, P, L.pos[own] + e, id - lane + own, m);
+    }
+  } else if (light && c) {  // too many: every thread writes its own
+    uint32_t at = pos;
+    enum_moves(P, s, [&](bool kept, uint32_t d, int32_t pa, int32_t pb) {
+      if (kept) {
+        Move m;
+        m.d = d;
+        m.pa = pa;
+        m.pb = pb;
+        put_move(O, P, at++, id, m);
+      }
+    });
+  }
+  if (valid) {
+    out_store(O.arc_offset + id, (int32_t)pos + O.ebase);
+    out_store(O.accept + id, (uint8_t)(s.accept ? 1 : 0));
+    out_store(O.start + id, (uint8_t)(s.start ? 1 : 0));
+    if (O.key_a) out_store(O.key_a + id, (int32_t)s.qa + O.abase);
+    if (O.key_b) out_store(O.key_b + id, (int32_t)s.qb);
+    if (O.key_f) out_store(O.key_f + id, (uint8_t)s.f);
+  }
+}
+
 // The fill in one launch: workgroups [0, hb) write the heavy states (one
 // workgroup per state, the heavy list strided over them), the others the
 // light chunks, so the heavy states' workgroup loops run under the light
 // work.  A heavy state's first arc position is its chunk's offset plus the
 // counts of the chunk's earlier states, summed by its workgroup.
+template <bool STATES>
 __global__ __launch_bounds__(NT) void k_fill(Problem P, ull nwords, ull nchunks,
                                              const uint8_t *__restrict__ cnt8,
                                              const uint32_t *__restrict__ cnt32,
@@ -2678,7 +2916,7 @@ __global__ __launch_bounds__(NT) void k_fill(Problem P, ull nwords, ull nchunks,
     __shared__ uint32_t s_pos;
     for (uint32_t h = blockIdx.x; h < nheavy; h += hb) {
       const uint2 hk = heavy[h];
-      const ull chunk = (hk.y >> 5) / OUT_WORDS;
+      const ull chunk = chunk_of(P, hk.x, hk.y);
       const uint32_t before = chunk_arcs_before(P, chunk, hk.x, cnt8, cnt32, s_w);
       if (threadIdx.x == 0) s_pos = btot[chunk] + before;
       __syncthreads();
@@ -2688,7 +2926,8 @@ __global__ __launch_bounds__(NT) void k_fill(Problem P, ull nwords, ull nchunks,
     return;
   }
   const unsigned block = blockIdx.x - hb;
-  fill_light(P, nwords, nchunks, cnt8, cnt32, btot, O, block);
+  if (STATES) fill_states(P, nstates, cnt8, cnt32, btot, O, block);
+  else fill_light(P, nwords, nchunks, cnt8, cnt32, btot, O, block);
   if (block == gridDim.x - hb - 1 && threadIdx.x == 0)
     O.arc_offset[nstates] = (int32_t)narcs + O.ebase;
 }
@@ -2732,7 +2971,7 @@ __global__ __launch_bounds__(NT) void k_item_ranges(Problem P, ull nkeys, int32_
     const uint32_t st = K >= nkeys ? nstates : new_id(P, (uint32_t)K);
     // the item's first state is the first trim key >= K: a state of K's
     // chunk, or the first state after it
-    const ull chunk = (K >> 5) / OUT_WORDS;
+    const ull chunk = chunk_of(P, st, (uint32_t)K);
     uint32_t before = 0;
     if (st < nstates) before = chunk_arcs_before(P, chunk, st, cnt8, cnt32, s_w);
     if (threadIdx.x == 0) {
@@ -2940,6 +3179,20 @@ hipError_t launch_count(const Problem &P, size_t nwords, uint8_t *cnt8, uint32_t
   return hipGetLastError();
 }
 
+hipError_t launch_count_states(const Problem &P, size_t nwords, const unsigned long long *nstates,
+                               uint32_t *keys, uint8_t *cnt8, uint32_t *cnt32, uint32_t *btot,
+                               uint2 *heavy, uint32_t cap, Scalars *sc, hipStream_t s) {
+  const size_t nchunks = out_chunks(nwords);
+  if (!nchunks) return hipSuccess;
+  if (!P.trim || !P.wbase || !P.keys) return hipErrorInvalidValue;
+  k_state_keys<<<out_grid(nchunks), NT, 0, s>>>(P, nwords, nchunks, keys, cap);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || cap == 0) return e;
+  k_count_states<<<(cap + NT - 1) / NT, NT, 0, s>>>(P, nstates, cnt8, cnt32, btot, heavy, cap,
+                                                    sc);
+  return hipGetLastError();
+}
+
 hipError_t launch_count_heavy(const Problem &P, const uint2 *heavy, const uint32_t *nheavy_dev,
                               uint8_t *cnt8, uint32_t *cnt32, uint32_t *btot, hipStream_t s) {
   k_count_heavy<<<1024, NT, 0, s>>>(P, heavy, nheavy_dev, cnt8, cnt32, btot);
@@ -2953,8 +3206,12 @@ hipError_t launch_fill(const Problem &P, size_t nwords, const uint8_t *cnt8,
   const size_t nchunks = out_chunks(nwords);
   if (nchunks && (!P.trim || !P.wbase)) return hipErrorInvalidValue;  // no trim bitmap
   const unsigned hb = nheavy < 4096 ? nheavy : 4096;
-  k_fill<<<hb + out_grid(nchunks), NT, 0, s>>>(P, nwords, nchunks, cnt8, cnt32, btot, nstates,
-                                               narcs, heavy, nheavy, hb, O);
+  if (P.keys)
+    k_fill<true><<<hb + (nstates + NT - 1) / NT + 1, NT, 0, s>>>(
+        P, nwords, nchunks, cnt8, cnt32, btot, nstates, narcs, heavy, nheavy, hb, O);
+  else
+    k_fill<false><<<hb + out_grid(nchunks), NT, 0, s>>>(P, nwords, nchunks, cnt8, cnt32, btot,
+                                                        nstates, narcs, heavy, nheavy, hb, O);
   return hipGetLastError();
 }
 

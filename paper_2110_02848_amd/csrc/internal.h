@@ -139,6 +139,7 @@ struct Problem {
   uint32_t *coacc;        // co-accessible keys (search layout)
   const uint32_t *trim;   // accessible and co-accessible keys (key order)
   const uint32_t *wbase;  // exclusive popcount prefix of trim words
+  const uint32_t *keys;   // the keys of C's states (compaction by state), or null
 };
 
 // Output arrays of C.  The arrays may start inside a larger C (one part of
@@ -659,6 +660,12 @@ hipError_t launch_trim(const Problem &P, uint32_t VA, uint32_t *trim, uint32_t *
 hipError_t launch_count(const Problem &P, size_t nwords, uint8_t *cnt8, uint32_t *cnt32,
                         uint32_t *btot, uint2 *heavy, uint32_t cap, Scalars *sc,
                         hipStream_t s);
+// The same by state (P.keys = keys): the keys are listed, and btot[w] is the
+// light total of states [64 w, 64 w + 64), for the first cap states rounded
+// up to NT; *nstates (device) is the number of states.
+hipError_t launch_count_states(const Problem &P, size_t nwords, const unsigned long long *nstates,
+                               uint32_t *keys, uint8_t *cnt8, uint32_t *cnt32, uint32_t *btot,
+                               uint2 *heavy, uint32_t cap, Scalars *sc, hipStream_t s);
 // Counts of the heavy states (cnt8 / cnt32, added to their chunk's btot).
 hipError_t launch_count_heavy(const Problem &P, const uint2 *heavy, const uint32_t *nheavy_dev,
                               uint8_t *cnt8, uint32_t *cnt32, uint32_t *btot, hipStream_t s);

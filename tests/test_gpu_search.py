@@ -167,3 +167,68 @@ def test_linear_search_without_room():
         c.close()
     # the bitmaps (4 MB each), the views and short lists fit 32 MB
     assert fits and fits[0] <= 1 << 25
+
+
+# ---- compaction by state ----
+
+def _fans(rng, degrees, n_sym):
+    """A graph whose state i has degrees[i] arcs (a few epsilon, labels with
+    repeats), all to states drawn at random, every state accepting."""
+    V = len(degrees)
+    arcs = [(s, int(rng.integers(0, V)), int(rng.integers(0, n_sym + 1)) if rng.random() < 0.9
+             else 0, int(rng.integers(1, n_sym + 1)) if rng.random() < 0.9 else 0,
+             float(rng.standard_normal())) for s in range(V) for _ in range(int(degrees[s]))]
+    return synth.from_arcs(V, arcs, start=range(V), accept=range(V))
+
+
+@pytest.mark.parametrize("degrees", [(1,) * 64, (2,) * 65, (3,) * 63 + (40,), (33,) * 9,
+                                     (31, 32, 33, 3, 4, 5, 7, 8, 9, 0, 1, 200), (6,) * 130])
+@pytest.mark.parametrize("n_sym", (1, 3, 12))
+def test_compaction_by_state(degrees, n_sym):
+    """States with as many moves as a thread takes at a time (4), as make a
+    state heavy (32) and as a wavefront's LDS holds (384), repeated labels on
+    either side, the second call counting without waiting for the number of
+    states, and a call without room for the list of keys."""
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(len(degrees) + n_sym)
+    A = _fans(rng, degrees, n_sym)
+    B = _fans(rng, rng.integers(1, 5, size=6), n_sym)
+    c = _composer("CONCURRENT")
+    for X, Y in ((A, B), (B, A)):
+        ref = oracle.compose(X, Y, oracle.ORDER_FORWARD)
+        for k in range(2):
+            check_pair(c, X, Y, f"by state {len(degrees)} {n_sym} call {k}", ref=ref)
+    c.close()
+
+
+def test_compaction_without_room():
+    """The least workspace cap that a call fits (to 64 KB): compaction by
+    chunks; somewhat larger caps reach the list of keys."""
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(9)
+    A, B = (synth.random_fst(rng, 300, 4, 5, 0.1, 0.3, start=range(9)) for _ in range(2))
+    ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
+
+    def fits(cap):
+        c = _composer("CONCURRENT")
+        c.set_option(gpu.FST_OPT_MAX_WORKSPACE, cap)
+        try:
+            for k in range(2):
+                check_pair(c, A, B, f"cap {cap} call {k}", ref=ref)
+            return True
+        except gpu.FstError as e:
+            assert e.code == gpu.FST_ERR_NOMEM
+            return False
+        finally:
+            c.close()
+
+    lo, hi = 1 << 16, 1 << 26
+    assert fits(hi)
+    while hi - lo > 1 << 16:
+        mid = (lo + hi) // 2
+        if fits(mid):
+            hi = mid
+        else:
+            lo = mid
+    for more in range(0, 12):
+        assert fits(hi + more * (1 << 16)), more
