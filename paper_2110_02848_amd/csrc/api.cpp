@@ -80,6 +80,7 @@ struct fst_ctx {
   unsigned long long list_hint = 0;  // search list capacity the last run needed
   int gen_hint = 0;  // launches the last concurrent search took
   unsigned long long state_hint = 0;  // states of the last C
+  int score_hint = 0;  // generations the last score took
   unsigned long long list_start = 1ull << 22;  // FST_OPT_LIST_CAPACITY
   struct {
     bool ready = false;
@@ -359,7 +360,8 @@ int score_generations(fst_ctx *c, const ScoreArgs *F, const ScoreArgs *B, ScoreB
     HIP_TRY(launch_score_seed(*dirs[i], i == 0, s));
   }
   const KernelTimer t = timer(c, FST_KERNEL_SCORE_GEN);
-  int g = 0, batch = 4;
+  // the first batch is as many generations as the last score took
+  int g = 0, batch = c->score_hint > 4 ? (c->score_hint < 256 ? c->score_hint : 256) : 4;
   for (;;) {
     t.begin(s);
     for (int b = 0; b < batch; ++b, ++g) HIP_TRY(launch_score_generation(F, B, g, s));
@@ -379,11 +381,18 @@ int score_generations(fst_ctx *c, const ScoreArgs *F, const ScoreArgs *B, ScoreB
       more = more || nx.qcount != 0 || (uint32_t)nx.hpack != 0;
     }
     if (!more) break;
-    batch = batch == 4 ? 16 : (batch < 64 ? 2 * batch : 64);
+    batch = batch < 16 ? 16 : (batch < 64 ? 2 * batch : 64);
   }
+  c->score_hint = 0;
   for (int i = 0; i < 2; ++i)
-    if (dirs[i] && bufs[i]->host->finished != (unsigned long long)dirs[i]->G.V)
-      return FST_ERR_CYCLIC;
+    if (dirs[i] && (int)bufs[i]->host->gens > c->score_hint)
+      c->score_hint = (int)bufs[i]->host->gens;
+  for (int i = 0; i < 2; ++i) {
+    if (!dirs[i]) continue;
+    unsigned long long fin = 0;
+    for (unsigned p = 0; p < FIN_PARTS; ++p) fin += bufs[i]->host->finished[p * FIN_STRIDE];
+    if (fin != (unsigned long long)dirs[i]->G.V) return FST_ERR_CYCLIC;
+  }
   return FST_OK;
 }
 

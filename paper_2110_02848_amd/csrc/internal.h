@@ -364,12 +364,15 @@ struct SweepNote {
   double tol;
 };
 
+constexpr unsigned FIN_PARTS = 32, FIN_STRIDE = 16;
 // Device scalars of a score computation, read back by the host.
 struct ScoreScalars {
   uint32_t err, maxlab;      // validation
   uint32_t overflow, gens;   // a list overflowed; generations that had work
   uint32_t nmerge, bad;      // merges; a provenance index out of range
-  unsigned long long finished;  // states given a value
+  // states given a value, in FIN_PARTS words on lines of their own (an atomic
+  // per wavefront on one word was 18 us of a generation of 10^5 threads)
+  unsigned long long finished[FIN_PARTS * FIN_STRIDE];
   unsigned long long mtotal;    // in-arcs of all merges
   unsigned long long zmax, zlo, zhi;  // total: order key of the maximum, 128-bit sum
   uint32_t absmax, pad;         // scatter: bits of the largest |gradient|

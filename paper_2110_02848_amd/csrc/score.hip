@@ -367,6 +367,66 @@ __device__ __forceinline__ void notified(const ScoreGraph &G, const int4 &rv, in
   w = G.w[e];
 }
 
+// settle for every arc a state notifies, NOTIFY at a time: their arc ids,
+// other ends, records, and then their atomics, are in flight together.
+constexpr int NOTIFY = 4;
+template <bool FWD>
+__device__ __forceinline__ void notify_all(const ScoreArgs &S, const ScoreNext &nx, const int4 &rv,
+                                           int32_t nd, double x, int depth, int32_t &next,
+                                           double &next_val, int4 &next_rec) {
+  for (int32_t j0 = 0; j0 < nd; j0 += NOTIFY) {
+    int32_t e[NOTIFY], y[NOTIFY], mp[NOTIFY], left[NOTIFY];
+    float w[NOTIFY];
+    int4 ry[NOTIFY];
+#pragma unroll
+    for (int k = 0; k < NOTIFY; ++k) {
+      e[k] = -1;
+      if (j0 + k < nd) e[k] = (rec_flags(rv) & REC_IND) ? S.G.marc[rv.x + j0 + k] : rv.x + j0 + k;
+    }
+#pragma unroll
+    for (int k = 0; k < NOTIFY; ++k) {
+      y[k] = -1;
+      mp[k] = 0;
+      w[k] = 0.0f;
+      if (e[k] >= 0) {
+        y[k] = FWD ? S.G.dst[e[k]] : S.G.src[e[k]];
+        w[k] = S.G.w[e[k]];
+        if (FWD) mp[k] = S.mpos[e[k]];  // read below for merges only
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < NOTIFY; ++k) {
+      ry[k] = make_int4(0, 0, 0, 0);
+      if (y[k] >= 0) ry[k] = S.rec[y[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < NOTIFY; ++k) {
+      left[k] = 0;
+      if (y[k] < 0) continue;
+      const double t = x + (double)w[k];
+      const uint32_t fy = rec_flags(ry[k]);
+      if (fy & REC_SINGLE) {
+        left[k] = 1;
+        if (next < 0 && depth + 1 < S.chain && !(fy & REC_HEAVY)) {
+          next = y[k];
+          next_val = one_term(t, (fy & REC_INIT) != 0);
+          next_rec = ry[k];
+          left[k] = 0;
+        } else {
+          S.term[e[k]] = t;
+        }
+      } else {
+        S.term[FWD ? S.G.E + mp[k] : (long long)e[k]] = t;
+        atomicMax(S.mkey + y[k], order_key(t));
+        left[k] = atomicSub(S.pend + y[k], 1);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < NOTIFY; ++k)
+      list_ready<FWD>(S, nx, left[k] == 1, y[k], ry[k]);
+  }
+}
+
 // A settle left for later: state y (record ry) gets the term x + w over arc
 // e (slot as in settle).  y < 0: none.
 struct Pending {
@@ -423,12 +483,7 @@ __device__ __forceinline__ void walk_from(const ScoreArgs &S, const ScoreNext &n
     int32_t next = -1;
     double next_val = 0.0;
     int4 next_rec = rv;
-    for (int32_t j = 0; j < nd; ++j) {
-      int32_t e, y;
-      float w;
-      notified<FWD>(S.G, rv, j, e, y, w);
-      settle<FWD>(S, nx, y, S.rec[y], w, e, -1, x, depth, next, next_val, next_rec);
-    }
+    notify_all<FWD>(S, nx, rv, nd, x, depth, next, next_val, next_rec);
     if (next < 0) break;
     v = next;
     x = next_val;
@@ -612,7 +667,9 @@ __device__ void gen_body(const ScoreArgs &S, int g, unsigned bid, unsigned nb) {
   // one atomic per wavefront
 #pragma unroll
   for (int o = WAVE / 2; o > 0; o >>= 1) fin += __shfl_xor(fin, o);
-  if (__lane_id() == 0 && fin) atomicAdd(&sc->finished, (ull)fin);
+  if (__lane_id() == 0 && fin)
+    atomicAdd(sc->finished + (bid * NWAVES + threadIdx.x / WAVE) % FIN_PARTS * FIN_STRIDE,
+              (ull)fin);
 }
 
 template <bool FWD>
