@@ -611,8 +611,8 @@ int search_concurrent(fst_ctx *c, Problem P, const SearchArgs &SF, const SearchA
     // the first batch covers as many launches as the last search took
     int batch = fdone || bdone ? 8 : 16;
     // (a level search: and one that finds nothing)
-    const int hint = c->gen_hint + (P.chains ? 0 : 1);
-    if (first && hint > batch) batch = hint < 256 ? hint : 256;
+    const int hint = c->gen_hint + 1;
+    if (first && c->gen_hint) batch = hint < 256 ? hint : 256;
     first = false;
     t.begin(s);
     for (int b = 0; b < batch; ++b) {
@@ -649,7 +649,7 @@ int search_concurrent(fst_ctx *c, Problem P, const SearchArgs &SF, const SearchA
 int search_linear(fst_ctx *c, const LinearArgs &F, const LinearArgs &B, hipStream_t s) {
   const KernelTimer t = timer(c, FST_KERNEL_SEARCH_FORWARD);
   // the first batch covers as many launches as the last search took
-  int g = 0, batch = c->gen_hint > 16 ? (c->gen_hint < 256 ? c->gen_hint : 256) : 16;
+  int g = 0, batch = c->gen_hint ? (c->gen_hint < 256 ? c->gen_hint : 256) : 16;
   for (;;) {
     t.begin(s);
     for (int b = 0; b < batch; ++b, ++g) HIP_TRY(launch_linear(F, B, g, s));
@@ -1258,7 +1258,7 @@ int levels3(fst_ctx *c, const Problem3 &P, const Search3 &S, bool forward, uint3
     for (int b = 0; b < batch; ++b, ++g) HIP_TRY(launch3_level(P, S, forward, g, s));
     t.end(s);
     FST_TRY(readback3(c, s));
-    FST_TRY(add_time(c, FST_KERNEL_SEARCH3, 2 * batch));
+    FST_TRY(add_time(c, FST_KERNEL_SEARCH3, batch));
     const Lvl3 &nx = c->h_s3->ring[g % 3];
     // keys in the set: those of the frontiers and those walks went on to
     if (c->h_s3->overflow ||

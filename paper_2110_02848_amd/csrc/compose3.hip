@@ -779,30 +779,6 @@ __device__ __forceinline__ uint32_t walk_fwd(const Problem3 &P, const Search3 &S
   return went;
 }
 
-// Level l of the forward search: frontier entries [fbase, fbase + fcount)
-// of ring[l % 3], each the start of a depth-first walk; heavy keys met go to
-// this level's chunks (k3_fwd_chunks, next).  Block 0 publishes the next
-// level's frontier base and clears the ring slot of level l + 2.
-__global__ __launch_bounds__(NT) void k3_fwd(Problem3 P, Search3 S, int l) {
-  const Lvl3 cur = S.ring[l % 3];
-  Lvl3 *nx = &S.ring[(l + 1) % 3];
-  const uint32_t nbase = cur.fbase + cur.fcount;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    nx->fbase = nbase;
-    Lvl3 *done = &S.ring[(l + 2) % 3];
-    done->fcount = 0;
-    done->ccount = 0;
-    if (cur.fcount || cur.ccount) S.sc->levels = (uint32_t)l + 1;
-  }
-  uint32_t went = 0;
-  if (!S.sc->overflow)
-    for (ull i = (ull)blockIdx.x * NT + threadIdx.x; i < cur.fcount; i += (ull)gridDim.x * NT) {
-      const uint32_t slot = S.F[cur.fbase + i];
-      went += walk_fwd(P, S, slot, P.tab[slot], nx, nbase, &S.ring[l % 3], l);
-    }
-  wave_add(went, &S.sc->ncont);
-}
-
 // Units [u0, u1) of the key in `slot` when they are all arcs of its B
 // state with input epsilon (a lexicon root's word entries), each with at
 // most one D arc for its output (or none needed): their arc records, D
@@ -909,26 +885,51 @@ __device__ __forceinline__ bool expand_beps(const Problem3 &P, const Search3 &S,
   return true;
 }
 
-// The chunks of level l: CHUNK3 units each, then a depth-first walk from
-// the first new key; heavy keys met on the walk go to the next level's
-// chunks.
-__global__ __launch_bounds__(NT) void k3_fwd_chunks(Problem3 P, Search3 S, int l) {
+// By one thread of level l: the next level's frontier base, and the ring slot
+// of level l + 2.
+__device__ __forceinline__ void note_level(const Search3 &S, int l, const Lvl3 &cur) {
+  S.ring[(l + 1) % 3].fbase = cur.fbase + cur.fcount;
+  Lvl3 *done = &S.ring[(l + 2) % 3];
+  done->fcount = 0;
+  done->ccount = 0;
+  if (cur.fcount || cur.ccount) S.sc->levels = (uint32_t)l + 1;
+}
+
+// Level l of the forward search.  The first half of the workgroups takes the
+// frontier entries [fbase, fbase + fcount) of ring[l % 3], each the start of a
+// depth-first walk; the second half takes the level's chunks, CHUNK3 units
+// each, then a walk from the first new key.  Heavy keys met on a walk go to
+// the next level's chunks, so that the two halves run side by side (both are
+// bound by the latency of their walks, 42 and 61 us a level one after the
+// other).
+__global__ __launch_bounds__(NT) void k3_fwd(Problem3 P, Search3 S, int l) {
   const Lvl3 cur = S.ring[l % 3];
   Lvl3 *nx = &S.ring[(l + 1) % 3];
   const uint32_t nbase = cur.fbase + cur.fcount;
-  const uint32_t nch = S.sc->overflow ? 0 : (cur.ccount < S.ccap ? cur.ccount : S.ccap);
-  const uint2 *list = chunks_of(S, l);
+  const bool ovf = S.sc->overflow != 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) note_level(S, l, cur);
+  const unsigned half = gridDim.x / 2;
   uint32_t went = 0;
-  for (ull i = (ull)blockIdx.x * NT + threadIdx.x; i < nch; i += (ull)gridDim.x * NT) {
-    const uint2 c = list[i];
-    const Units3 u = units_of(P, P.tab[c.x]);
-    const uint32_t n = nunits(u);
-    const uint32_t u1 = c.y + CHUNK3 < n ? c.y + CHUNK3 : n;
-    uint32_t cont = NO_SLOT;
-    ull cont_key = 0;
-    if (!expand_beps(P, S, c.x, u, c.y, u1, nx, nbase, &cont, &cont_key))
-      expand_units(P, S, c.x, u, c.y, u1, nx, nbase, &cont, &cont_key);
-    if (cont != NO_SLOT) went += 1 + walk_fwd(P, S, cont, cont_key, nx, nbase, nx, l + 1);
+  if (blockIdx.x < half) {
+    const uint32_t n = ovf ? 0 : cur.fcount;
+    for (ull i = (ull)blockIdx.x * NT + threadIdx.x; i < n; i += (ull)half * NT) {
+      const uint32_t slot = S.F[cur.fbase + i];
+      went += walk_fwd(P, S, slot, P.tab[slot], nx, nbase, nx, l + 1);
+    }
+  } else {
+    const uint32_t nch = ovf ? 0 : (cur.ccount < S.ccap ? cur.ccount : S.ccap);
+    const uint2 *list = chunks_of(S, l);
+    for (ull i = (ull)(blockIdx.x - half) * NT + threadIdx.x; i < nch; i += (ull)half * NT) {
+      const uint2 c = list[i];
+      const Units3 u = units_of(P, P.tab[c.x]);
+      const uint32_t n = nunits(u);
+      const uint32_t u1 = c.y + CHUNK3 < n ? c.y + CHUNK3 : n;
+      uint32_t cont = NO_SLOT;
+      ull cont_key = 0;
+      if (!expand_beps(P, S, c.x, u, c.y, u1, nx, nbase, &cont, &cont_key))
+        expand_units(P, S, c.x, u, c.y, u1, nx, nbase, &cont, &cont_key);
+      if (cont != NO_SLOT) went += 1 + walk_fwd(P, S, cont, cont_key, nx, nbase, nx, l + 1);
+    }
   }
   wave_add(went, &S.sc->ncont);
 }
@@ -1073,38 +1074,31 @@ __device__ __forceinline__ uint32_t walk_bwd(const Problem3 &P, const Search3 &S
   return went;
 }
 
+// Level l of the backward search: frontier and chunks side by side (see
+// k3_fwd).
 __global__ __launch_bounds__(NT) void k3_bwd(Problem3 P, Search3 S, int l) {
   const Lvl3 cur = S.ring[l % 3];
   Lvl3 *nx = &S.ring[(l + 1) % 3];
   const uint32_t nbase = cur.fbase + cur.fcount;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    nx->fbase = nbase;
-    Lvl3 *done = &S.ring[(l + 2) % 3];
-    done->fcount = 0;
-    done->ccount = 0;
-    if (cur.fcount || cur.ccount) S.sc->levels = (uint32_t)l + 1;
-  }
+  const bool ovf = S.sc->overflow != 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) note_level(S, l, cur);
+  const unsigned half = gridDim.x / 2;
   uint32_t went = 0;
-  if (!S.sc->overflow)
-    for (ull i = (ull)blockIdx.x * NT + threadIdx.x; i < cur.fcount; i += (ull)gridDim.x * NT)
-      went += walk_bwd(P, S, S.F[cur.fbase + i], nx, nbase, &S.ring[l % 3], l);
-  wave_add(went, &S.sc->ncont);
-}
-
-__global__ __launch_bounds__(NT) void k3_bwd_chunks(Problem3 P, Search3 S, int l) {
-  const Lvl3 cur = S.ring[l % 3];
-  Lvl3 *nx = &S.ring[(l + 1) % 3];
-  const uint32_t nbase = cur.fbase + cur.fcount;
-  const uint32_t nch = S.sc->overflow ? 0 : (cur.ccount < S.ccap ? cur.ccount : S.ccap);
-  const uint2 *list = chunks_of(S, l);
-  uint32_t went = 0;
-  for (ull i = (ull)blockIdx.x * NT + threadIdx.x; i < nch; i += (ull)gridDim.x * NT) {
-    const uint2 c = list[i];
-    const uint32_t p0 = P.in_off[c.x] + c.y, pe = P.in_off[c.x + 1];
-    const uint32_t p1 = p0 + CHUNK3 < pe ? p0 + CHUNK3 : pe;
-    uint32_t cont = NO_SLOT;
-    bwd_range(P, S, p0, p1, nx, nbase, &cont);
-    if (cont != NO_SLOT) went += 1 + walk_bwd(P, S, cont, nx, nbase, nx, l + 1);
+  if (blockIdx.x < half) {
+    const uint32_t n = ovf ? 0 : cur.fcount;
+    for (ull i = (ull)blockIdx.x * NT + threadIdx.x; i < n; i += (ull)half * NT)
+      went += walk_bwd(P, S, S.F[cur.fbase + i], nx, nbase, nx, l + 1);
+  } else {
+    const uint32_t nch = ovf ? 0 : (cur.ccount < S.ccap ? cur.ccount : S.ccap);
+    const uint2 *list = chunks_of(S, l);
+    for (ull i = (ull)(blockIdx.x - half) * NT + threadIdx.x; i < nch; i += (ull)half * NT) {
+      const uint2 c = list[i];
+      const uint32_t p0 = P.in_off[c.x] + c.y, pe = P.in_off[c.x + 1];
+      const uint32_t p1 = p0 + CHUNK3 < pe ? p0 + CHUNK3 : pe;
+      uint32_t cont = NO_SLOT;
+      bwd_range(P, S, p0, p1, nx, nbase, &cont);
+      if (cont != NO_SLOT) went += 1 + walk_bwd(P, S, cont, nx, nbase, nx, l + 1);
+    }
   }
   wave_add(went, &S.sc->ncont);
 }
@@ -1293,13 +1287,8 @@ hipError_t launch3_seed(const Problem3 &P, const Search3 &S, const int32_t *list
 hipError_t launch3_level(const Problem3 &P, const Search3 &S, bool forward, int l,
                          hipStream_t s) {
   constexpr unsigned GRID = 1024;
-  if (forward) {
-    k3_fwd<<<GRID, NT, 0, s>>>(P, S, l);
-    k3_fwd_chunks<<<GRID, NT, 0, s>>>(P, S, l);
-  } else {
-    k3_bwd<<<GRID, NT, 0, s>>>(P, S, l);
-    k3_bwd_chunks<<<GRID, NT, 0, s>>>(P, S, l);
-  }
+  if (forward) k3_fwd<<<2 * GRID, NT, 0, s>>>(P, S, l);
+  else k3_bwd<<<2 * GRID, NT, 0, s>>>(P, S, l);
   return hipGetLastError();
 }
 

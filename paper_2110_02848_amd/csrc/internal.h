@@ -703,7 +703,7 @@ hipError_t launch3_starts(const DevGraph &A, const DevGraph &B, const DevGraph &
                           int32_t *lists, uint32_t *counts, hipStream_t s);
 hipError_t launch3_seed(const Problem3 &P, const Search3 &S, const int32_t *lists,
                         const uint32_t *counts, hipStream_t s);
-// Level l of the forward (or backward) search: two kernels.
+// Level l of the forward (or backward) search: one kernel.
 hipError_t launch3_level(const Problem3 &P, const Search3 &S, bool forward, int l,
                          hipStream_t s);
 // The generated arcs as (target, source) pairs for a sort by target; then,
