@@ -57,7 +57,7 @@ struct fst_ctx {
   bool have_times = false;
   bool timed_run = false;
 
-  DevBuf scal, lists, eps, keys;
+  DevBuf scal, lists, keys;
   DevBuf k0, k1, v0, v1, sort_tmp, scan_tmp;
   DevBuf aOutPerm, aOutArc, aOutRec, aOutLut, bOutPerm, bOutArc, bOutRec, bOutLut;
   DevBuf aOutLab, aOutW, bOutLab, bOutW, bOutChain, bInChain;
@@ -733,19 +733,18 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   const DevGraph dA = dev_graph(A), dB = dev_graph(B);
   const int32_t VA = dA.V, VB = dB.V, EA = dA.E, EB = dB.E;
 
-  FST_TRY(ensure(c, c->scal, sizeof(Scalars)));
+  // the scalars, and a byte per state of A (its epsilon outputs) after them,
+  // are cleared together
+  const size_t scal_bytes = sizeof(Scalars) + (size_t)VA;
+  FST_TRY(ensure(c, c->scal, scal_bytes));
   Scalars *d_sc = as<Scalars>(c->scal);
   for (int k = 0; k < NKERNELS; ++k) {
     c->kms[k] = 0.f;
     c->klaunches[k] = 0;
   }
   phase_begin(c, PH_PRE, s);
-  HIP_TRY(hipMemsetAsync(d_sc, 0, sizeof(Scalars), s));
-  if (VA)
-    HIP_TRY(launch_validate(dA, 0, &d_sc->errA, &d_sc->maxLabA, s, &d_sc->naccA, c->validate));
-  if (VB)
-    HIP_TRY(launch_validate(dB, 1, &d_sc->errB, &d_sc->maxLabB, s, &d_sc->naccB, c->validate,
-                            &d_sc->singleB));
+  HIP_TRY(hipMemsetAsync(d_sc, 0, scal_bytes, s));
+  HIP_TRY(launch_validate2(dA, dB, d_sc, c->validate, s));
   FST_TRY(readback(c, s));
   if ((c->h_sc->errA | c->h_sc->errB) & ~INFO_NOTES) return FST_ERR_INVALID_GRAPH;
   const bool presortedA = !(c->h_sc->errA & INFO_UNSORTED);
@@ -807,9 +806,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     lutp[i] = lut ? as<int4>(*vb[i].lut) : nullptr;
   }
   ViewBuild VB4 = {};
-  FST_TRY(ensure(c, c->eps, (size_t)VA));
-  HIP_TRY(hipMemsetAsync(c->eps.p, 0, (size_t)VA, s));
-  VB4.eps = as<uint8_t>(c->eps);
+  VB4.eps = reinterpret_cast<uint8_t *>(d_sc + 1);
   for (int i = 0; i < 4; ++i) {
     const bool isA = (i % 2) == 0, in = i >= 2;
     VB4.v[i] = ViewIn{isA ? dA : dB, isA ? 0 : 1, in ? 1 : 0,
@@ -1853,7 +1850,7 @@ void fst_ctx_destroy(fst_ctx *c) {
   if (!c) return;
   DeviceGuard g(c->device);
   (void)hipDeviceSynchronize();
-  DevBuf *bufs[] = {&c->scal,     &c->eps,      &c->keys,     &c->lists,    &c->k0,      &c->k1,      &c->v0,
+  DevBuf *bufs[] = {&c->scal,     &c->keys,     &c->lists,    &c->k0,      &c->k1,      &c->v0,
                     &c->v1,       &c->sort_tmp, &c->scan_tmp, &c->aOutPerm, &c->aOutArc,
                     &c->aOutRec,  &c->aOutLut,  &c->bOutPerm, &c->bOutArc, &c->bOutRec,
                     &c->bOutLut,  &c->aInOff,   &c->aInPerm, &c->aInArc,  &c->aInRec,

@@ -64,9 +64,8 @@ __device__ __forceinline__ int32_t lb_label(const int2 *a, int32_t lo, int32_t h
 // before any check (the source check's offsets depend on the source).
 constexpr int VAL_ITEMS = 8;
 
-__global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t *err,
-                                                 uint32_t *maxlab, uint32_t *nacc,
-                                                 uint32_t *single) {
+__device__ __forceinline__ void validate(const DevGraph &g, int side, uint32_t *err,
+                                         uint32_t *maxlab, uint32_t *nacc, uint32_t *single) {
   uint32_t bits = 0, mx = 0, na = 0, n1 = 0;
   const long long V = g.V, E = g.E;
   const long long n = (V + 1 > E) ? V + 1 : E;
@@ -162,6 +161,19 @@ __global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t 
     if (na && nacc) atomicAdd(nacc, na);
     if (n1 && single) atomicAdd(single, n1);
   }
+}
+
+__global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t *err,
+                                                 uint32_t *maxlab, uint32_t *nacc,
+                                                 uint32_t *single) {
+  validate(g, side, err, maxlab, nacc, single);
+}
+
+// A (first row of workgroups) and B of a composition.
+__global__ __launch_bounds__(NT) void k_validate2(DevGraph A, DevGraph B, Scalars *sc) {
+  const bool a = blockIdx.y == 0;
+  validate(a ? A : B, a ? 0 : 1, a ? &sc->errA : &sc->errB, a ? &sc->maxLabA : &sc->maxLabB,
+           a ? &sc->naccA : &sc->naccB, a ? nullptr : &sc->singleB);
 }
 
 // What the composition needs from a graph whose structure the caller
@@ -2992,6 +3004,29 @@ hipError_t launch_validate(const DevGraph &g, int side, uint32_t *err, uint32_t 
   size_t n = (size_t)(g.V + 1 > g.E ? g.V + 1 : g.E);
   if (check) k_validate<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc, single);
   else k_label_facts<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc, single);
+  return hipGetLastError();
+}
+
+hipError_t launch_validate2(const DevGraph &A, const DevGraph &B, Scalars *sc, bool check,
+                            hipStream_t s) {
+  if (!check) {
+    hipError_t e = hipSuccess;
+    if (A.V) e = launch_validate(A, 0, &sc->errA, &sc->maxLabA, s, &sc->naccA, false);
+    if (e == hipSuccess && B.V)
+      e = launch_validate(B, 1, &sc->errB, &sc->maxLabB, s, &sc->naccB, false, &sc->singleB);
+    return e;
+  }
+  // (a graph without states has no offsets to check)
+  if (!A.V || !B.V) {
+    if (A.V) return launch_validate(A, 0, &sc->errA, &sc->maxLabA, s, &sc->naccA);
+    if (B.V)
+      return launch_validate(B, 1, &sc->errB, &sc->maxLabB, s, &sc->naccB, true, &sc->singleB);
+    return hipSuccess;
+  }
+  const size_t na = (size_t)(A.V + 1 > A.E ? A.V + 1 : A.E);
+  const size_t nb = (size_t)(B.V + 1 > B.E ? B.V + 1 : B.E);
+  const size_t n = ((na > nb ? na : nb) + VAL_ITEMS - 1) / VAL_ITEMS;
+  k_validate2<<<dim3(grid_for(n, 2048), 2), NT, 0, s>>>(A, B, sc);
   return hipGetLastError();
 }
 

@@ -559,6 +559,10 @@ hipError_t radix_sort(unsigned long long *k0, int32_t *v0, unsigned long long *k
 hipError_t launch_validate(const DevGraph &g, int side, uint32_t *err, uint32_t *maxlab,
                            hipStream_t s, uint32_t *nacc = nullptr, bool check = true,
                            uint32_t *single = nullptr);
+// The same for A and B of a composition, into its scalars (one launch).
+hipError_t launch_validate2(const DevGraph &A, const DevGraph &B, Scalars *sc, bool check,
+                            hipStream_t s);
+
 // Views are built in two steps.  build_views: the arcs of up to four views
 // (side 0: A by olabel, side 1: B by ilabel; by_dst: in-views) in the order of
 // their group and label (an out-view whose groups are already in label order
