@@ -81,6 +81,7 @@ struct fst_ctx {
   int gen_hint = 0;  // launches the last concurrent search took
   unsigned long long state_hint = 0;  // states of the last C
   int score_hint = 0;  // generations the last score took
+  bool small = true;   // small searches may be used (off while one is run again)
   unsigned long long list_start = 1ull << 22;  // FST_OPT_LIST_CAPACITY
   struct {
     bool ready = false;
@@ -852,6 +853,13 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   // Where the workspace has no room for a linear search the keys are followed
   // one by one, then lists a quarter as long are tried.
   bool try_linear = true, grew = false, linear = false;
+  // A small search's words are all written by it, and the host need not wait
+  // for it to queue what follows.
+  const bool small = c->small && c->order == FST_ORDER_CONCURRENT &&
+                     (unsigned long long)VA * (unsigned long long)VB <= SMALL_PAIRS &&
+                     nsbits <= SMALL_SEARCH_BITS &&
+                     !(c->chain_depth > 0 &&
+                       2ull * c->h_sc->singleB > (unsigned long long)VB);
   uint32_t *wbase = nullptr;
   for (;;) {
     const uint32_t cap = (uint32_t)(cap_try < cap_full ? cap_try : cap_full);
@@ -900,7 +908,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     FST_TRY(ensure(c, c->scan_tmp, scan_temp_bytes(scan_n)));
     if (linear) {
       HIP_TRY(hipMemsetAsync(c->lin.p, 0, (8 * rows + masks) * 8, s));
-    } else {
+    } else if (!small) {
       HIP_TRY(hipMemsetAsync(c->vis.p, 0, snwords * 4, s));
       HIP_TRY(hipMemsetAsync(c->coacc.p, 0, snwords * 4, s));
     }
@@ -937,7 +945,8 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     S.gens = &d_sc->gens;
     S.note = &d_sc->note;
     // (a chain search's counters were cleared with the scalars)
-    if (!P.chains) HIP_TRY(hipMemsetAsync(c->fcnt.p, 0, 2 * FRONT_WORDS * 4, s));
+    if (!P.chains && !small)
+      HIP_TRY(hipMemsetAsync(c->fcnt.p, 0, 2 * FRONT_WORDS * 4, s));
     // a second search on the same lists (they hold no keys once the first
     // has ended, but counters)
     auto second_search = [&]() -> int {
@@ -986,6 +995,17 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       phase_end(c, PH_FWD, s);
       phase_begin(c, PH_BWD, s);
       HIP_TRY(launch_linear_trim(P, F.F, G.F, W, as<uint32_t>(c->trim), wbase, s));
+      phase_end(c, PH_BWD, s);
+    } else if (small) {
+      phase_begin(c, PH_FWD, s);
+      const KernelTimer tf = timer(c, FST_KERNEL_SEARCH_FORWARD);
+      tf.begin(s);
+      HIP_TRY(launch_small(P, d_sc, s));
+      tf.end(s);
+      if (c->count_moves) HIP_TRY(launch_count_moves(P, snwords, true, &d_sc->generated, s));
+      phase_end(c, PH_FWD, s);
+      phase_begin(c, PH_BWD, s);
+      HIP_TRY(launch_trim(P, (uint32_t)VA, as<uint32_t>(c->trim), wbase, s));
       phase_end(c, PH_BWD, s);
     } else if (c->order == FST_ORDER_CONCURRENT) {
       // The forward search's first generations run alone (listing accepting
@@ -1164,6 +1184,17 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   const unsigned long long cap0 = room();
   if (cap0) FST_TRY(count((uint32_t)cap0));
   FST_TRY(readback(c, s));
+  if (small) {
+    if (c->h_sc->overflow) {  // a level had too many keys: level search
+      c->small = false;
+      const int rc = run_impl(c, A, B, s, V_C, E_C);
+      c->small = true;
+      return rc;
+    }
+    FST_TRY(add_time(c, FST_KERNEL_SEARCH_FORWARD, 1));
+    c->stats.fwd_levels = c->h_sc->gens;
+    c->stats.bwd_levels = c->h_sc->gens2;
+  }
   const unsigned long long nst = c->h_sc->nstates;
   if (nst > (unsigned long long)INT32_MAX) return FST_ERR_TOO_LARGE;
   const uint32_t nstates = (uint32_t)nst;

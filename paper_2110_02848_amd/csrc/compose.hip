@@ -1476,6 +1476,139 @@ __global__ __launch_bounds__(NT) void k_level2(Problem P, SearchArgs SF, SearchA
 }
 
 // ---------------------------------------------------------------------------
+// small search
+// ---------------------------------------------------------------------------
+// Up to SMALL_PAIRS state pairs both searches run in one launch, a workgroup of
+// SMALL_NT threads each: bitmap and frontiers in LDS, a level per barrier
+// instead of per launch.  A level then takes its three dependent loads
+// (records, arc, bucket; about 2 us) where a launch of the level search takes
+// 8 us; with more pairs one workgroup would have more units than that saves.
+constexpr int SMALL_NT = 1024, SMALL_WAVES = SMALL_NT / WAVE;
+constexpr uint32_t SMALL_LIST = 6144;  // keys of a level
+struct SmallLds {
+  uint32_t bits[SMALL_SEARCH_BITS / 32];
+  uint32_t list[2][SMALL_LIST];
+  uint32_t off[SMALL_WAVES][WAVE];
+  uint32_t n[2];
+  uint32_t sum;
+};
+
+// The lanes with `fresh` append their keys (one LDS atomic per wavefront).
+__device__ __forceinline__ void small_push(SmallLds &L, int to, bool fresh, uint32_t key) {
+  const unsigned long long m = __ballot(fresh);
+  if (m == 0) return;
+  const int leader = __ffsll(m) - 1;
+  uint32_t base = 0;
+  if ((int)__lane_id() == leader) base = atomicAdd(&L.n[to], (uint32_t)__popcll(m));
+  base = __shfl(base, leader, WAVE);
+  const uint32_t pos = base + (uint32_t)__popcll(m & __lanemask_lt());
+  if (fresh && pos < SMALL_LIST) L.list[to][pos] = key;
+}
+
+__device__ __forceinline__ bool small_claim(const Problem &P, SmallLds &L, uint32_t key) {
+  const uint32_t sb = search_bit(P, key), bit = 1u << (sb & 31u);
+  return (atomicOr(&L.bits[sb >> 5], bit) & bit) == 0;
+}
+
+template <bool FWD>
+__device__ __forceinline__ void small_body(const Problem &P, Scalars *sc, SmallLds &L) {
+  typedef typename Dir<FWD>::Info Info;
+  const uint32_t tid = threadIdx.x, lane = __lane_id(), wid = tid / WAVE;
+  const uint32_t VA = (uint32_t)P.A.V, VB = (uint32_t)P.B.V;
+  const uint32_t words = (P.rowA << (31 - __clz((int)(P.maskB + 1)) + 1)) / 32;
+  for (uint32_t w = tid; w < words; w += SMALL_NT) L.bits[w] = 0;
+  if (tid < 2) L.n[tid] = 0;
+  if (tid == 0) L.sum = 0;
+  __syncthreads();
+  // level 0: every pair of start (accepting) states; backward f = 1 as well
+  // where the A state has an epsilon output
+  for (uint32_t i0 = 0; i0 < VA * VB; i0 += SMALL_NT) {
+    const uint32_t i = i0 + tid, qa = i / VB, qb = i - qa * VB;
+    bool on = false, dual = false;
+    if (i < VA * VB) {
+      on = FWD ? P.A.start[qa] && P.B.start[qb] : P.A.accept[qa] && P.B.accept[qb];
+      if (!FWD && on) dual = (P.aOut.srec[2 * (size_t)qa].w & (int32_t)FLAG_EPS_OUT) != 0;
+    }
+#pragma unroll
+    for (uint32_t f = 0; f < (FWD ? 1u : 2u); ++f) {
+      const bool put = f ? dual : on;
+      const uint32_t key = make_key(qa, qb, f, P.shiftB);
+      if (put) (void)small_claim(P, L, key);
+      small_push(L, 0, put, key);
+    }
+  }
+  __syncthreads();
+  uint32_t levels = 0;
+  for (int cur = 0;; cur ^= 1) {
+    const uint32_t n = L.n[cur];  // the same for all threads (a barrier before)
+    if (n == 0 || n > SMALL_LIST) break;
+    ++levels;
+    uint32_t K = (n + SMALL_WAVES - 1) / SMALL_WAVES;
+    if (K > WAVE) K = WAVE;
+    for (uint32_t k0 = wid * K; k0 < n; k0 += SMALL_WAVES * K) {
+      const bool have = lane < K && k0 + lane < n;
+      uint32_t key = 0, units = 0;
+      Rec A = {}, B = {};
+      if (have) {
+        key = L.list[cur][k0 + lane];
+        A = load_rec(Dir<FWD>::viewA(P), key_qa(key, P.shiftB));
+        B = load_rec(Dir<FWD>::viewB(P), key_qb(key, P.shiftB));
+        units = Dir<FWD>::units(Dir<FWD>::make(key, P.shiftB, A, B));
+      }
+      const uint32_t incl = wave_incl_scan(units);
+      L.off[wid][lane] = incl - units;
+      const uint32_t T = __shfl(incl, WAVE - 1, WAVE);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (uint32_t r = 0; r < T; r += WAVE) {
+        const uint32_t item = r + lane;
+        const bool go = item < T;
+        uint32_t a = 0;  // the last lane whose units start at or before this one
+#pragma unroll
+        for (uint32_t h = WAVE / 2; h; h >>= 1)
+          if (L.off[wid][a + h] <= item) a += h;
+        a = go ? a : lane;
+        const uint32_t k2 = __shfl(key, a, WAVE);
+        const Rec A2 = shfl_rec(A, a), B2 = shfl_rec(B, a);
+        const uint32_t u = item - L.off[wid][a];
+        if (go) {
+          const Info info = Dir<FWD>::make(k2, P.shiftB, A2, B2);
+          for_unit<FWD>(P, info, u, [&](const Target &t, const Rec &) {
+            small_push(L, cur ^ 1, small_claim(P, L, t.key), t.key);
+          });
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();  // the next level is listed
+    if (tid == 0) L.n[cur] = 0;
+    __syncthreads();
+  }
+  if (tid == 0) {
+    *(FWD ? &sc->gens : &sc->gens2) = levels;
+    // a level too long for its list: the host searches again otherwise
+    if (L.n[0] > SMALL_LIST || L.n[1] > SMALL_LIST) atomicOr(&sc->overflow, 4u);
+  }
+  uint32_t *out = FWD ? P.vis : P.coacc, c = 0;
+  for (uint32_t w = tid; w < words; w += SMALL_NT) {
+    out[w] = L.bits[w];
+    c += (uint32_t)__popc(L.bits[w]);
+  }
+  if (FWD) {
+    c = wave_sum(c);
+    if (lane == 0) atomicAdd(&L.sum, c);
+    __syncthreads();
+    if (tid == 0) sc->naccessible = L.sum;
+  }
+}
+
+__global__ __launch_bounds__(SMALL_NT) void k_small(Problem P, Scalars *sc) {
+  __shared__ SmallLds L;
+  if (blockIdx.x == 0) small_body<true>(P, sc, L);
+  else small_body<false>(P, sc, L);
+}
+
+// ---------------------------------------------------------------------------
 // linear search
 // ---------------------------------------------------------------------------
 // Where every arc of A leads from a state to the next one and none has output
@@ -3136,6 +3269,11 @@ hipError_t launch_generation2(const Problem &P, const SearchArgs &SF, const Sear
   constexpr unsigned GRID = 1024;
   if (!P.chains) k_level2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
   else k_gen2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
+  return hipGetLastError();
+}
+
+hipError_t launch_small(const Problem &P, Scalars *sc, hipStream_t s) {
+  k_small<<<2, SMALL_NT, 0, s>>>(P, sc);
   return hipGetLastError();
 }
 

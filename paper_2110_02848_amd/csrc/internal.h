@@ -631,6 +631,11 @@ hipError_t launch_generation(const Problem &P, const SearchArgs &S, bool forward
 // each).
 hipError_t launch_generation2(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
                               int gb, hipStream_t s);
+// Small search: both directions in one launch, for at most SMALL_PAIRS pairs of
+// states whose search bitmaps have at most SMALL_SEARCH_BITS bits; writes the
+// whole bitmaps, gens, gens2 and naccessible, and overflow if it gave up.
+constexpr unsigned long long SMALL_PAIRS = 8192, SMALL_SEARCH_BITS = 1ull << 16;
+hipError_t launch_small(const Problem &P, Scalars *sc, hipStream_t s);
 // Linear search: M (cleared by the caller) from A's arcs, start and accepting
 // states; the seeds of both directions; generation g of both; the rows that
 // the search leaves out; and, like launch_trim, the trim bitmap from the rows.

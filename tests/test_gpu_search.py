@@ -232,3 +232,24 @@ def test_compaction_without_room():
             lo = mid
     for more in range(0, 12):
         assert fits(hi + more * (1 << 16)), more
+
+
+# ---- small search ----
+
+@pytest.mark.parametrize("VA,VB,starts", [(1, 1, 1), (64, 128, 3), (128, 64, 3), (8192, 1, 5),
+                                          (1, 8192, 5), (91, 90, 4), (90, 91, 91), (3, 2730, 2),
+                                          (90, 91, 60), (63, 65, 63)])
+def test_small_search(VA, VB, starts):
+    """State pairs up to the limit of a small search (8192) and past it, levels
+    of more keys than its lists hold (6144: every pair starts and accepts),
+    narrow and wide operands."""
+    rng = np.random.default_rng(VA + VB)
+    A = synth.random_fst(rng, VA, 3, 4, 0.2, 0.2 if starts < 60 else 1.0,
+                         start=range(min(VA, starts)))
+    B = synth.random_fst(rng, VB, 3, 4, 0.2, 0.2 if starts < 60 else 1.0,
+                         start=range(min(VB, starts)))
+    ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
+    c = _composer("CONCURRENT")
+    for k in range(2):
+        check_pair(c, A, B, f"small {VA} {VB} {starts} call {k}", ref=ref)
+    c.close()
