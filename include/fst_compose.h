@@ -138,8 +138,9 @@ FST_API void fst_ctx_destroy(fst_ctx *ctx);
  * bucket tables for a graph whose table fits in 256 MiB and in 64 times its
  * arc records (8 bytes per arc); 0 = binary search only) and
  * FST_OPT_CHAIN_DEPTH (default 64: how many newly found keys one search
- * thread may expand depth-first before handing keys to the next frontier;
- * 0 = plain frontier-by-frontier search).  FST_OPT_COUNT_MOVES = 1 makes
+ * thread may expand depth-first before handing keys to the next frontier,
+ * where B is mostly chains; 0 = plain frontier-by-frontier search, as
+ * elsewhere).  FST_OPT_COUNT_MOVES = 1 makes
  * each run also count the moves out of all accessible keys and the
  * predecessor moves of all co-accessible keys (extra passes, reported in
  * fst_stats.generated and fst_stats.generated_backward).
@@ -156,14 +157,18 @@ FST_API void fst_ctx_destroy(fst_ctx *ctx);
  * the forward search has ended and held back while its frontier is far
  * wider than the forward one (kernel FST_KERNEL_SEARCH_FORWARD then times
  * the launches that advance either search, and FST_KERNEL_SEARCH_BACKWARD
- * has none).  FST_OPT_VALIDATE (default 1) checks every input graph's
+ * has none).  The concurrent order searches up to 8,192 state pairs in one
+ * launch (unless B is mostly chains: most of its states have one out-arc), and
+ * where B is and every arc of A leads from a state to the next one with an
+ * output other than epsilon, it follows 64 keys of a state of B at a time
+ * (generations then advance both directions).  FST_OPT_VALIDATE (default 1) checks every input graph's
  * structure as described at fst_graph; 0 is for callers that vouch for
  * their graphs: the checks are skipped (the composition still reads the
  * largest label, the label order and the accepting states; a score reads
  * nothing before it starts), and a graph that breaks the rules then gives
  * unspecified results, which may include reads outside its arrays.
  * FST_OPT_LIST_CAPACITY (entries, 0 = default 2^22) is the first size of
- * the search's work lists (frontier, heavy and accepting keys); a search
+ * the search's work lists (frontier and heavy keys); a search
  * that overflows them runs again with four times the size (never more than
  * 2 V_A V_B), and the context keeps the size that sufficed for later calls;
  * the result is the same. */

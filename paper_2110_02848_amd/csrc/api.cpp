@@ -361,8 +361,10 @@ int score_generations(fst_ctx *c, const ScoreArgs *F, const ScoreArgs *B, ScoreB
     HIP_TRY(launch_score_seed(*dirs[i], i == 0, s));
   }
   const KernelTimer t = timer(c, FST_KERNEL_SCORE_GEN);
-  // the first batch is as many generations as the last score took
-  int g = 0, batch = c->score_hint > 4 ? (c->score_hint < 256 ? c->score_hint : 256) : 4;
+  // batches up to as many generations as the last score took: the first of 32
+  // at most (this graph may be much smaller), then 64
+  const int hint = c->score_hint;
+  int g = 0, batch = hint > 4 ? (hint < 32 ? hint : 32) : 4;
   for (;;) {
     t.begin(s);
     for (int b = 0; b < batch; ++b, ++g) HIP_TRY(launch_score_generation(F, B, g, s));
@@ -383,6 +385,7 @@ int score_generations(fst_ctx *c, const ScoreArgs *F, const ScoreArgs *B, ScoreB
     }
     if (!more) break;
     batch = batch < 16 ? 16 : (batch < 64 ? 2 * batch : 64);
+    if (hint > g && hint - g < 64) batch = hint - g;
   }
   c->score_hint = 0;
   for (int i = 0; i < 2; ++i)

@@ -5,11 +5,14 @@
 //    per-state label buckets, so that joining A's output labels with B's
 //    input labels costs one bucket lookup per arc instead of a scan of the
 //    arc-pair cross product;
-//  * the search over composite keys in generations: a light key is expanded
-//    by one thread, which then follows the light keys it reaches first
-//    depth-first; heavy keys (many epsilon arcs, large label joins) are cut
-//    into work units spread over the whole grid; new keys are claimed in a
-//    bitmap and appended with one atomic per wavefront (ballot + popcount);
+//  * the search over composite keys in generations, in one of four forms:
+//    small (one launch, bitmap and frontiers in LDS), level (the units of a
+//    frontier spread over lanes), chain (B mostly chains: a thread follows the
+//    light keys it reaches first depth-first) and linear (A's arcs lead from
+//    state to state as well: 64 keys of a state of B at a time); heavy keys
+//    (many epsilon arcs, large label joins) are cut into work units spread
+//    over the whole grid; new keys are claimed in a bitmap and appended with
+//    one atomic per wavefront (ballot + popcount);
 //  * the same search run backwards over in-arcs for co-accessibility;
 //  * compaction: a popcount prefix over the trim bitmap numbers the states in
 //    key order; arcs are counted, scanned and written in canonical order.

@@ -358,15 +358,6 @@ __device__ __forceinline__ void settle(const ScoreArgs &S, const ScoreNext &nx, 
   list_ready<FWD>(S, nx, ready && !walk, y, ry);
 }
 
-// Notified arc j of a state's notify list: arc id, other end, weight.
-template <bool FWD>
-__device__ __forceinline__ void notified(const ScoreGraph &G, const int4 &rv, int32_t j,
-                                         int32_t &e, int32_t &y, float &w) {
-  e = (rec_flags(rv) & REC_IND) ? G.marc[rv.x + j] : rv.x + j;
-  y = FWD ? G.dst[e] : G.src[e];
-  w = G.w[e];
-}
-
 // settle for every arc a state notifies, NOTIFY at a time: their arc ids,
 // other ends, records, and then their atomics, are in flight together.
 constexpr int NOTIFY = 4;

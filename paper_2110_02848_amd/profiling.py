@@ -43,12 +43,13 @@ from collections import defaultdict
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 
-# Kernel groups.  The search groups every launch of a search generation:
-# both searches side by side (k_gen2) and either search alone.
+# Kernel groups.  The search groups every launch of a search generation, in
+# whichever of its forms.
 FAMILIES = {
-    "search": ("k_gen<true>", "k_gen<false>", "k_gen2("),
-    "count": ("k_count(", "k_count_heavy("),
-    "fill": ("k_fill(", "k_fill_light(", "k_fill_heavy("),
+    "search": ("k_gen<true>", "k_gen<false>", "k_gen2(", "k_level<true>", "k_level<false>",
+               "k_level2(", "k_linear(", "k_small("),
+    "count": ("k_count(", "k_count_heavy(", "k_count_states(", "k_state_keys("),
+    "fill": ("k_fill<true>", "k_fill<false>"),
     # scores of the composed graph (bench.py --task score)
     "score_gen": ("k_score_gen<true>", "k_score_gen<false>", "k_score_gen2("),
     "score_structure": ("k_owner(", "k_extra(", "k_merge_index(", "k_merge_place(",
@@ -57,7 +58,7 @@ FAMILIES = {
     "scatter": ("k_absmax(", "k_bucket_count(", "k_bucket_place(", "k_scatter(",
                 "k_scatter_final("),
     # three inputs at once (bench.py --task compose3)
-    "search3": ("k3_fwd(", "k3_fwd_chunks(", "k3_bwd(", "k3_bwd_chunks("),
+    "search3": ("k3_fwd(", "k3_bwd("),
     "compact3": ("k3_arc_keys(", "k3_run_starts(", "k3_run_ends(", "k3_seed_bwd(", "k3_collect(", "k3_ids(",
                  "k3_out_light<", "k3_out_heavy<", "k3_fill_states("),
 }
