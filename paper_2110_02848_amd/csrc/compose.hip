@@ -510,12 +510,6 @@ __device__ __forceinline__ int32_t opaque(int32_t x) {
   return x;
 }
 
-// Claim a key that few threads are expected to reach at once.
-__device__ __forceinline__ bool claim_cold(uint32_t *bm, uint32_t k) {
-  const uint32_t bit = 1u << (k & 31u);
-  return (atomicOr(bm + (k >> 5), bit) & bit) == 0;
-}
-
 // Claim key k in bitmap bm; true for exactly one caller per key.  The plain
 // load first matters: keys such as a lexicon root are reached by thousands
 // of threads at once, and only the first few should reach the atomic.
