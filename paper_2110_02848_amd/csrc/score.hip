@@ -857,7 +857,9 @@ __device__ __forceinline__ ull sweep_states(const ScoreGraph &G, const SweepNote
   const bool sparse = k > 0 && before < (ull)G.V / 4 * 3;
   constexpr int R = SWEEP_ARCS / WAVE;
   const uint32_t lane = __lane_id();
-  ull mk = 0;
+  // a direction that runs has risen by 0 at least, also where it skips every
+  // state (0 itself is the key of a NaN, which would not settle)
+  ull mk = order_key(0.0);
   for (ull g = (ull)bid * NWAVES + threadIdx.x / WAVE; g < words; g += (ull)nb * NWAVES) {
     const int32_t v = (int32_t)(g * WAVE + lane);
     const bool valid = v < G.V;

@@ -7,7 +7,7 @@ import pytest
 
 from paper_2110_02848_amd import synth
 
-from test_gpu_score_cyclic import _check, _run, comp  # noqa: F401 (a fixture)
+from test_gpu_score_cyclic import _check, _run, comp, settled_sweep  # noqa: F401 (a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -42,5 +42,27 @@ def test_values_that_settle_at_different_sweeps(comp, gap):  # noqa: F811
     torch.cuda.synchronize()
     for k in ("alpha", "beta"):
         assert np.array_equal(got[k].view(np.int64), ref[k].cpu().numpy().view(np.int64)), k
+    # (the paths with the most arcs add less than a unit in the last place)
+    assert got["sweeps"] == settled_sweep(chain) < n + 2
     loop = arcs + [(gap * n, gap * n + 1, 1, 1, -1.0), (gap * n + 1, gap * n, 1, 1, -0.7)]
     _check(comp, synth.from_arcs(V, loop, start=[0], accept=[gap * n]), f"chain and cycle {gap}")
+
+
+@pytest.mark.parametrize("V", (1, 2, 8, 20, 64, 65, 100, 700))
+@pytest.mark.parametrize("dirs", ((True, True), (True, False), (False, True)))
+def test_the_sweep_that_settled(comp, V, dirs):  # noqa: F811
+    """A path of V states ends in a state that nobody pulls from (the start
+    state, backward): sweep V gives it its value, sweep V + 1 raises none and
+    is the one that settled, wherever a batch of sweeps ends."""
+    G = synth.from_arcs(V, [(i, i + 1, 1, 1, -0.01 * (i % 7)) for i in range(V - 1)], start=[0],
+                        accept=[V - 1])
+    assert settled_sweep(G) == V + 1
+    for tol in (0.0, 0.5):
+        got = _run(comp, G, alpha=dirs[0], beta=dirs[1], tol=tol)
+        assert got["sweeps"] == V + 1, (got["sweeps"], V, tol)
+    # no sweep more is needed, and one less is not enough
+    assert _run(comp, G, alpha=dirs[0], beta=dirs[1], max_sweeps=V + 1)["sweeps"] == V + 1
+    from paper_2110_02848_amd import gpu
+    with pytest.raises(gpu.FstError) as e:
+        _run(comp, G, alpha=dirs[0], beta=dirs[1], max_sweeps=V)
+    assert e.value.code == gpu.FST_ERR_NOT_CONVERGED
