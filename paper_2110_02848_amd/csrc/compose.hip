@@ -1234,7 +1234,8 @@ __device__ __forceinline__ void gen_body(const Problem &P, const SearchArgs &S, 
   __shared__ uint32_t s_ho[NT], s_hk[NT];
   __shared__ uint32_t s_pre[SUBQ + 1];
   load_front(S.Q, g, s_pre);
-  if (threadIdx.x < hcount) {
+  // (before the return below: a list that overflowed asks for more than it holds)
+  if (threadIdx.x < list_entries(cur.hbase, hcount, S.cap)) {
     s_ho[threadIdx.x] = S.hoff[cur.hbase + threadIdx.x];
     s_hk[threadIdx.x] = S.heavy[cur.hbase + threadIdx.x];
   }
@@ -1365,7 +1366,8 @@ __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S
   const ull U = cur.hpack >> 32;
   load_front(S.Q, g, L.pre);
   if (lane == 0) L.push[wid].n = 0;
-  if (threadIdx.x < hcount) {
+  // (before the return below: a list that overflowed asks for more than it holds)
+  if (threadIdx.x < list_entries(cur.hbase, hcount, S.cap)) {
     L.ho[threadIdx.x] = S.hoff[cur.hbase + threadIdx.x];
     L.hk[threadIdx.x] = S.heavy[cur.hbase + threadIdx.x];
   }

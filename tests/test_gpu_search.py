@@ -55,6 +55,26 @@ def test_keys_with_many_moves(order, fans):
 
 
 @pytest.mark.parametrize("order", ORDERS)
+@pytest.mark.parametrize("chains", (0, 1))
+def test_heavy_list_overflows(order, chains):
+    """More heavy keys in a generation than the list's first size holds: the
+    generations queued behind it must not read past the list."""
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(17 + chains)
+    A = synth.random_fst(rng, 170, 600, 9, 0.5, 0.1, start=range(30))
+    arcs = [(s, (s + 1) % 50, 1 + s % 9, 1, 0.5) for s in range(50)]
+    if not chains:
+        arcs += [(s, (s + 7) % 50, 1 + s % 5, 2, 0.25) for s in range(50)]
+    B = synth.from_arcs(50, arcs, start=range(50), accept=[9])
+    ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
+    c = _composer(order)
+    for cap in (1024, 256, 100, 1):  # whole pages of entries, and fewer
+        c.set_option(gpu.FST_OPT_LIST_CAPACITY, cap)
+        check_pair(c, A, B, f"heavy lists from {cap} {order} chains {chains}", ref=ref)
+    c.close()
+
+
+@pytest.mark.parametrize("order", ORDERS)
 @pytest.mark.parametrize("more", (0, 1))
 def test_single_arc_states_of_b(order, more):
     """n states of B with one arc among 2 n (level search) or 2 n - 1."""
