@@ -1648,6 +1648,7 @@ struct LinearLds {
   int4 heavy[GATHER];                     // a heavy list of at most GATHER items
   uint32_t item[GATHER];
   ull bits[GATHER];
+  uint32_t ovf;
 };
 
 struct LinearNext {
@@ -1822,10 +1823,15 @@ __device__ __forceinline__ void linear_body(const LinearArgs &X, int g, unsigned
     L.item[threadIdx.x] = NO_KEY;
     L.bits[threadIdx.x] = 0;
   }
-  __syncthreads();
-  if (ovf) return;
+  // a generation's lists may overflow while this workgroup starts: the flag
+  // one wavefront saw holds for all of them (they share the LDS from here on)
+  if (threadIdx.x == 0) L.ovf = ovf;
   const uint32_t hcount = (uint32_t)cur.hpack, ocount = (uint32_t)old.hpack;
   const ull U = cur.hpack >> 32;
+  if (threadIdx.x < GATHER && threadIdx.x < list_entries(cur.hbase, hcount, X.cap))
+    L.heavy[threadIdx.x] = X.heavy[cur.hbase + threadIdx.x];
+  __syncthreads();
+  if (L.ovf) return;
   const uint32_t nq = s_pre[SUBQ];
   const size_t nwords = (size_t)X.VB * X.W;
   auto key_of = [&](int gen, const uint32_t *pre, uint32_t i) {
@@ -1862,9 +1868,6 @@ __device__ __forceinline__ void linear_body(const LinearArgs &X, int g, unsigned
       N0[i < ocount ? (uint32_t)X.heavy[old.hbase + i].x : key_of(g + 3, s_old, i - ocount)] = 0;
   }
   const ull *N = X.N + (size_t)(g % 3) * nwords;
-  if (threadIdx.x < GATHER && threadIdx.x < hcount)
-    L.heavy[threadIdx.x] = X.heavy[cur.hbase + threadIdx.x];
-  if (hcount) __syncthreads();
   const int4 *hv = hcount <= GATHER ? L.heavy : X.heavy + cur.hbase;
   const ull n = U + nq;
   const unsigned xcd = bid & 7u, nl = nb >> 3;
