@@ -19,4 +19,10 @@ FSTC_BOTH constexpr uint32_t list_entries(uint32_t base, uint32_t count, uint32_
   return base >= cap ? 0u : (count < cap - base ? count : cap - base);
 }
 
+// State `lane` of the g-th 64 of V states, V where there is none.  (The lanes
+// past the last state of V > 2^31 - 64 do not fit 32 bits.)
+FSTC_BOTH constexpr int32_t lane_state(uint64_t g, uint32_t lane, int32_t V) {
+  return g * 64 + lane < (uint64_t)V ? (int32_t)(g * 64 + lane) : V;
+}
+
 }  // namespace fstc

@@ -861,9 +861,10 @@ __device__ __forceinline__ ull sweep_states(const ScoreGraph &G, const SweepNote
   // state (0 itself is the key of a NaN, which would not settle)
   ull mk = order_key(0.0);
   for (ull g = (ull)bid * NWAVES + threadIdx.x / WAVE; g < words; g += (ull)nb * NWAVES) {
-    const int32_t v = (int32_t)(g * WAVE + lane);
+    static_assert(WAVE == 64, "a state per lane");
+    const int32_t v = lane_state(g, lane, G.V);
     const bool valid = v < G.V;
-    const int32_t b = off[valid ? v : G.V], e = off[valid ? v + 1 : G.V];
+    const int32_t b = off[v], e = off[valid ? v + 1 : v];
     const bool init = valid && flag[v] != 0;
     const double was = valid ? x[v] : 0.0;
     const ull lastw = k > 0 ? last[g] : ~0ull;

@@ -19,6 +19,17 @@ CASES = {
         static_assert(list_entries(1, 0xffffffffu, 4096) == 4095);
         static_assert(list_entries(0xfffffff0u, 256, 0xffffffffu) == 15);
     """,
+    # 64 states at a time up to the largest graph
+    "lane_state": """
+        static_assert(lane_state(0, 0, 0) == 0);
+        static_assert(lane_state(0, 5, 5) == 5);
+        static_assert(lane_state(0, 4, 5) == 4);
+        static_assert(lane_state(1, 0, 64) == 64);
+        static_assert(lane_state(0x1ffffff, 62, 0x7fffffff) == 0x7ffffffe);
+        static_assert(lane_state(0x1ffffff, 63, 0x7fffffff) == 0x7fffffff);
+        static_assert(lane_state(0x1ffffff, 63, 0x7fffffc1) == 0x7fffffc1);
+        static_assert(lane_state(0x2000000, 0, 0x7fffffff) == 0x7fffffff);
+    """,
 }
 
 
