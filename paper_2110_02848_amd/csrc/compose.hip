@@ -2849,25 +2849,21 @@ __global__ __launch_bounds__(NT) void k_state_keys(Problem P, ull nwords, ull nc
     keys[first + i] = trim_key_at(t, list, i);
 }
 
-// Matching units walk B's arcs only where B has fewer and their labels are
-// distinct (the canonical order is by label, then A's arc), else A's.
-__device__ __forceinline__ bool walks_b(const Fwd &s) {
-  return s.nB < s.nA && (s.flB & (int32_t)FLAG_DISTINCT) != 0;
-}
-__device__ __forceinline__ uint32_t walk_units(const Fwd &s) {
-  const uint32_t m = s.mU ? (walks_b(s) ? s.nB : s.nA) : 0u;
-  return s.eA + (uint32_t)s.be + m;
-}
+// Matching units walk the arcs of the side with fewer, as fwd_units counts them.
+__device__ __forceinline__ bool walks_b(const Fwd &s) { return s.nB < s.nA; }
 
 // Calls f(kept, target key, pa, pb) for every move of a state in canonical
 // order (positions in the out-views, -1: none), four units at a time: their
 // arcs, then their label ranges, then their first targets' trim words are
-// loaded together.
+// loaded together.  Where B's arcs are walked and several have a label (a
+// state with a loop and an arc onward on one token), the first of them emits
+// the label's moves, by A's arc and then by B's.
 template <class F>
 __device__ __forceinline__ void enum_moves(const Problem &P, const Fwd &s, F &&f) {
   constexpr int K = 4;
-  const uint32_t sh = P.shiftB, n = walk_units(s);
-  const bool wb = walks_b(s);
+  const uint32_t sh = P.shiftB, n = out_units(s);
+  const bool wb = walks_b(s), several = wb && !(s.flB & (int32_t)FLAG_DISTINCT);
+  int32_t last = -1;  // label of the arc of B before the round
   for (uint32_t u0 = 0; u0 < n; u0 += K) {
     int2 ar[K];
     int32_t p[K], lo[K], hi[K], nb[K];
@@ -2890,7 +2886,8 @@ __device__ __forceinline__ void enum_moves(const Problem &P, const Fwd &s, F &&f
     for (int k = 0; k < K; ++k) {
       lo[k] = hi[k] = 0;
       nb[k] = 0;
-      if (u0 + (uint32_t)k < n) {
+      const bool again = several && match[k] && ar[k].x == (k ? ar[k - 1].x : last);
+      if (u0 + (uint32_t)k < n && !again) {
         hi[k] = 1;
         if (match[k]) {
           if (wb) label_range(P.aOut, s.qa, s.aS + s.ae, s.aE, ar[k].x, lo[k], hi[k], nb[k]);
@@ -2898,6 +2895,7 @@ __device__ __forceinline__ void enum_moves(const Problem &P, const Fwd &s, F &&f
         }
       }
     }
+    last = ar[K - 1].x;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const uint32_t mine = nbr_of(ar[k].y);
@@ -2911,6 +2909,18 @@ __device__ __forceinline__ void enum_moves(const Problem &P, const Fwd &s, F &&f
       if (lo[k] >= hi[k]) continue;
       const int32_t q0 = match[k] ? lo[k] : -1;
       f(((tw[k] >> (d[k] & 31u)) & 1u) != 0, d[k], onB[k] ? q0 : p[k], onB[k] ? p[k] : q0);
+      if (several && match[k]) {
+        for (int32_t q = lo[k]; q < hi[k]; ++q) {
+          const uint32_t da = nbr_of(q == lo[k] ? nb[k] : P.aOut.arec[q].y);
+          for (int32_t pb = q == lo[k] ? p[k] + 1 : p[k]; pb < s.bE; ++pb) {
+            const int2 b = P.bOut.arec[pb];
+            if (b.x != ar[k].x) break;
+            const uint32_t dq = make_key(da, nbr_of(b.y), 0u, sh);
+            f(test_bit(P.trim, dq), dq, q, pb);
+          }
+        }
+        continue;
+      }
       for (int32_t q = lo[k] + 1; q < hi[k]; ++q) {  // more arcs of the label
         const uint32_t mine = nbr_of(ar[k].y);
         const uint32_t oth = nbr_of((wb ? P.aOut.arec : P.bOut.arec)[q].y);
@@ -2937,7 +2947,7 @@ __global__ __launch_bounds__(NT) void k_count_states(Problem P, const ull *__res
   if (id < n) {
     key = P.keys[id];
     const Fwd s = fwd_info<false>(P, key);
-    if (walk_units(s) > LIGHT_UNITS) {
+    if (out_units(s) > LIGHT_UNITS) {
       hv = true;
     } else if (lone_move(s)) {
       c = 1;
@@ -2983,7 +2993,7 @@ __device__ __forceinline__ void fill_states(const Problem &P, uint32_t nstates,
   bool light = false;
   if (valid) {
     s = fwd_info(P, key);
-    light = walk_units(s) <= LIGHT_UNITS;
+    light = out_units(s) <= LIGHT_UNITS;
   }
   uint32_t pos = base + wave_incl_scan(c) - c;
   const uint32_t lc = light ? c : 0u, lincl = wave_incl_scan(lc);

@@ -221,6 +221,45 @@ def test_compaction_by_state(degrees, n_sym):
     c.close()
 
 
+def _out_units(A, B, C):
+    """Work units of C's states: epsilon arcs, and the arcs of the side with
+    fewer others."""
+    def counts(g, lab):
+        V = int(g["num_states"])
+        eps = np.bincount(g["src"][g[lab] == 0], minlength=V)
+        return eps, np.bincount(g["src"], minlength=V) - eps
+    (ea, na), (eb, nb) = counts(A, "olabel"), counts(B, "ilabel")
+    a, b = C["key_a"], C["key_b"]
+    return np.where(C["key_f"] == 0, ea[a], 0) + eb[b] + np.minimum(na[a], nb[b])
+
+
+@pytest.mark.parametrize("repeats_in_a", (0, 1))
+@pytest.mark.parametrize("degree", (1, 2, 3, 4, 5, 8, 9, 31, 33))
+def test_compaction_walks_the_side_with_fewer_arcs(repeats_in_a, degree):
+    """States of B with a loop and arcs onward on the same label, against A's
+    with many more arcs, their labels all different or not: the moves of a
+    label in order, and no state with few units handed to a workgroup."""
+    rng = np.random.default_rng(degree)
+    V, n_sym = 120, 40 if not repeats_in_a else 17
+    arcs = [(s, int(rng.integers(0, V)), 1 + i % 3, 1 + i % n_sym, float(rng.standard_normal()))
+            for s in range(V) for i in range(40)]
+    A = synth.from_arcs(V, arcs, start=range(V), accept=range(V))
+    W, barcs = 90, []
+    for s in range(W):
+        labs = rng.integers(1, n_sym + 1, size=3)
+        for i in range(degree):  # the first one a loop
+            barcs.append((s, s if i == 0 else int(rng.integers(0, W)), int(labs[min(i // 2, 2)]),
+                          int(rng.integers(0, 4)), float(rng.standard_normal())))
+    B = synth.from_arcs(W, barcs, start=range(W), accept=range(W))
+    c = _composer("CONCURRENT")
+    for X, Y in ((A, B), (B, A)):
+        ref = oracle.compose(X, Y, oracle.ORDER_FORWARD)
+        for k in range(2):
+            got, _ = check_pair(c, X, Y, f"loops {repeats_in_a} {degree} call {k}", ref=ref)
+        assert c.stats()["heavy_states"] == int(np.sum(_out_units(X, Y, got) > 32))
+    c.close()
+
+
 def test_compaction_without_room():
     """The least workspace cap that a call fits (to 64 KB): compaction by
     chunks; somewhat larger caps reach the list of keys."""
