@@ -1318,11 +1318,16 @@ __global__ __launch_bounds__(NT, 4) void k_gen2(Problem P, SearchArgs SF, Search
 // level search
 // ---------------------------------------------------------------------------
 
+// Targets of a unit that one lane takes after each other (about 0.7 us each);
+// targets of a unit that are spread over the lanes at a time.
+constexpr int32_t LEVEL_SERIAL = 8, LEVEL_TAKE = 1 << 20;
+
 // LDS of a workgroup of the level search.
 struct LevelLds {
   uint32_t ho[NT], hk[NT];     // a heavy list of at most NT keys
   uint32_t pre[SUBQ + 1];      // prefix of the frontier's part counts
   uint32_t off[NWAVES][WAVE];  // unit offsets of a wavefront's keys
+  uint32_t toff[NWAVES][WAVE]; // target offsets of its lanes' units
   PushBuf push[NWAVES];
 };
 
@@ -1358,7 +1363,6 @@ __device__ __forceinline__ void reach(const Problem &P, const NextGen &nx, const
 template <bool FWD>
 __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S, int g,
                                            unsigned bid, unsigned nb, LevelLds &L) {
-  typedef typename Dir<FWD>::Info Info;
   const unsigned lane = __lane_id(), wid = threadIdx.x / WAVE;
   const uint32_t ovf = S.sc->overflow;  // loaded with the slot (one round trip)
   const GenSlot cur = S.G[g % 3];
@@ -1449,10 +1453,48 @@ __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S
         B2 = shfl_rec(B, a);
         u = item - L.off[wid][a];
       }
-      if (go) {
-        const Info info = Dir<FWD>::make(k2, P.shiftB, A2, B2);
-        for_unit<FWD>(P, info, u,
-                      [&](const Target &t, const Rec &) { reach<FWD>(P, nx, t); });
+      UnitRange range;
+      range.lo = range.hi = range.nb0 = 0;
+      range.fixed = range.flags = 0;
+      if (go) range = Dir<FWD>::range(P, Dir<FWD>::make(k2, P.shiftB, A2, B2), u);
+      auto take = [&](const UnitRange &x) {
+        for_range<FWD>(P, x, [&](const Target &t, const Rec &) { reach<FWD>(P, nx, t); });
+      };
+      if (__ballot(range.hi - range.lo > LEVEL_SERIAL) == 0) {
+        take(range);
+        continue;
+      }
+      // some unit has many targets (an arc of A, and a label that many of B's
+      // arcs here have): the targets are numbered and spread over the lanes,
+      // as the units are
+      while (__ballot(range.lo < range.hi)) {
+        const int32_t rest = range.hi - range.lo;
+        const uint32_t n = rest < LEVEL_TAKE ? (uint32_t)rest : (uint32_t)LEVEL_TAKE;
+        const uint32_t incl = wave_incl_scan(n), all = __shfl(incl, WAVE - 1, WAVE);
+        uint32_t *off = L.toff[wid];
+        off[lane] = incl - n;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (uint32_t i0 = 0; i0 < all; i0 += WAVE) {
+          const uint32_t i = i0 + lane;
+          uint32_t a = 0;  // the last lane whose targets start at or before this one
+#pragma unroll
+          for (uint32_t h = WAVE / 2; h; h >>= 1)
+            if (off[a + h] <= i) a += h;
+          UnitRange one = range;
+          one.lo = __shfl(range.lo, (int)a) + (int32_t)(i - off[a]);
+          one.hi = one.lo + 1;
+          one.fixed = __shfl(range.fixed, (int)a);
+          one.flags = __shfl(range.flags, (int)a);
+          if (i < all) {
+            const int2 *arcs = FWD ? ((one.flags & VARY_A) ? P.aOut.arec : P.bOut.arec)
+                                   : ((one.flags & VARY_A) ? P.aIn.arec : P.bIn.arec);
+            one.nb0 = arcs[one.lo].y;
+            take(one);
+          }
+        }
+        __builtin_amdgcn_wave_barrier();
+        range.lo += (int32_t)n;
       }
     }
   }

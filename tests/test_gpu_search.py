@@ -55,6 +55,28 @@ def test_keys_with_many_moves(order, fans):
 
 
 @pytest.mark.parametrize("order", ORDERS)
+@pytest.mark.parametrize("n", (7, 8, 9, 63, 64, 65, 130, 700))
+def test_units_with_many_targets(order, n):
+    """One arc of A against n arcs of B with its label, out of a state and
+    back into it: targets taken by one lane (8 at most) or spread over all."""
+    rng = np.random.default_rng(n)
+    arcs = [(0, 1 + i, 1 + (i % 50 == 7), 1 + i % 3, float(rng.standard_normal()))
+            for i in range(n)]
+    arcs += [(1 + i, 0, 1 + (i % 40 == 3), 0, -0.5) for i in range(n)]
+    arcs += [(1 + i, 1 + i, 1, 2, -1.5) for i in range(n)]  # two arcs a state: level search
+    arcs += [(0, 1 + i, 0, 4, -1.0) for i in range(3)]
+    B = synth.from_arcs(n + 1, arcs, start=[0], accept=[0, n])
+    VA = 8200 // (n + 1) + 5  # more state pairs than a small search takes
+    aarcs = [(t, (t + 1) % VA, 1, 1 + t % 2, 0.1 * (t % 3)) for t in range(VA)]
+    aarcs += [(t, (t + 2) % VA, 2, 0 if t % 5 == 0 else 1, -0.2) for t in range(VA)]
+    A = synth.from_arcs(VA, aarcs, start=[0, VA // 2], accept=[1, VA - 1])
+    c = _composer(order)
+    for X, Y in ((A, B), (B, A)):
+        check_pair(c, X, Y, f"{n} targets {order}", ref=oracle.compose(X, Y, oracle.ORDER_FORWARD))
+    c.close()
+
+
+@pytest.mark.parametrize("order", ORDERS)
 @pytest.mark.parametrize("chains", (0, 1))
 def test_heavy_list_overflows(order, chains):
     """More heavy keys in a generation than the list's first size holds: the
