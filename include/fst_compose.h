@@ -157,9 +157,12 @@ FST_API void fst_ctx_destroy(fst_ctx *ctx);
  * the forward search has ended and held back while its frontier is far
  * wider than the forward one (kernel FST_KERNEL_SEARCH_FORWARD then times
  * the launches that advance either search, and FST_KERNEL_SEARCH_BACKWARD
- * has none).  The concurrent order searches up to 8,192 state pairs in one
- * launch (unless B is mostly chains: most of its states have one out-arc), and
- * where B is and every arc of A leads from a state to the next one with an
+ * has none).  The concurrent order searches small operands in one launch:
+ * up to 8,192 state pairs, 65,536 bits of V_A rounded up to 64 times V_B
+ * rounded up to a power of two (16 at least) times 2, and 81,920 work units
+ * over all pairs (epsilon arcs, and the other arcs of the side with fewer; 24
+ * a pair and 4,096), unless B is mostly chains (most of its states have one
+ * out-arc).  Where B is and every arc of A leads from a state to the next one with an
  * output other than epsilon, it follows 64 keys of a state of B at a time
  * (generations then advance both directions).  FST_OPT_VALIDATE (default 1) checks every input graph's
  * structure as described at fst_graph; 0 is for callers that vouch for

@@ -730,6 +730,32 @@ int sorted_views(fst_ctx *c, const ViewBuild &B, hipStream_t s) {
   return FST_OK;
 }
 
+// Whether A and B (facts of validation read back; search bitmaps of nsbits
+// bits) take a small search: in the concurrent order, at most SMALL_PAIRS state
+// pairs and bitmaps of at most SMALL_SEARCH_BITS bits, B not mostly chains,
+// and at most SMALL_UNITS work units over all pairs and SMALL_UNITS_PAIR per
+// pair.  Units bound it because one workgroup takes them all (ms a call, by
+// small and by level search): 64 o 64 states of 16 arcs (72,000 units) 0.39 and
+// 0.42, of 24 (108,000) 0.50 and 0.46, of 256 (1.8 million) 6.8 and 0.75; 20 o 20
+// states of 30 arcs (33 units a pair) 0.31 and 0.36, of 100 arcs (110) 0.45 and
+// 0.31, since a wavefront takes a key's units alone.
+constexpr unsigned long long SMALL_UNITS = 81920, SMALL_UNITS_PAIR = 24, SMALL_UNITS_MIN = 4096;
+
+bool small_search(const fst_ctx *c, const DevGraph &A, const DevGraph &B,
+                  unsigned long long nsbits) {
+  const Scalars &h = *c->h_sc;
+  const unsigned long long VA = (unsigned long long)A.V, VB = (unsigned long long)B.V;
+  if (!c->small || c->order != FST_ORDER_CONCURRENT || VA * VB > SMALL_PAIRS ||
+      nsbits > SMALL_SEARCH_BITS || (c->chain_depth > 0 && 2ull * h.singleB > VB))
+    return false;
+  // epsilon moves (B's from both filter states), and the arcs of the smaller side
+  const unsigned long long mA = ((unsigned long long)A.E - h.nepsA) * VB;
+  const unsigned long long mB = ((unsigned long long)B.E - h.nepsB) * VA;
+  const unsigned long long units =
+      h.nepsA * VB + (h.nepsA ? 2 : 1) * (h.nepsB * VA) + (mA < mB ? mA : mB);
+  return units <= SMALL_UNITS && units <= SMALL_UNITS_PAIR * VA * VB + SMALL_UNITS_MIN;
+}
+
 int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, int64_t *V_C,
              int64_t *E_C) {
   FST_TRY(check_graph_args(A));
@@ -858,11 +884,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   bool try_linear = true, grew = false, linear = false;
   // A small search's words are all written by it, and the host need not wait
   // for it to queue what follows.
-  const bool small = c->small && c->order == FST_ORDER_CONCURRENT &&
-                     (unsigned long long)VA * (unsigned long long)VB <= SMALL_PAIRS &&
-                     nsbits <= SMALL_SEARCH_BITS &&
-                     !(c->chain_depth > 0 &&
-                       2ull * c->h_sc->singleB > (unsigned long long)VB);
+  const bool small = small_search(c, dA, dB, nsbits);
   uint32_t *wbase = nullptr;
   for (;;) {
     const uint32_t cap = (uint32_t)(cap_try < cap_full ? cap_try : cap_full);

@@ -68,8 +68,9 @@ __device__ __forceinline__ int32_t lb_label(const int2 *a, int32_t lo, int32_t h
 constexpr int VAL_ITEMS = 8;
 
 __device__ __forceinline__ void validate(const DevGraph &g, int side, uint32_t *err,
-                                         uint32_t *maxlab, uint32_t *nacc, uint32_t *single) {
-  uint32_t bits = 0, mx = 0, na = 0, n1 = 0;
+                                         uint32_t *maxlab, uint32_t *nacc, uint32_t *single,
+                                         uint32_t *neps) {
+  uint32_t bits = 0, mx = 0, na = 0, n1 = 0, ne = 0;
   const long long V = g.V, E = g.E;
   const long long n = (V + 1 > E) ? V + 1 : E;
   const long long tile = (long long)NT * VAL_ITEMS;
@@ -135,21 +136,24 @@ __device__ __forceinline__ void validate(const DevGraph &g, int side, uint32_t *
           const int32_t lab = side == 0 ? ol : il;
           if (lab > 0 && (uint32_t)lab > mx) mx = (uint32_t)lab;
           if (side == 0 && (lab == 0 || d != sv + 1)) bits |= INFO_NOT_LINEAR;
+          ne += lab == 0 ? 1u : 0u;
         }
       }
     }
   }
   // one atomic per workgroup: same-address atomics serialize
-  __shared__ uint32_t s_bits[NWAVES], s_mx[NWAVES], s_na[NWAVES], s_n1[NWAVES];
+  __shared__ uint32_t s_bits[NWAVES], s_mx[NWAVES], s_na[NWAVES], s_n1[NWAVES], s_ne[NWAVES];
   bits = wave_or(bits);
   mx = wave_max(mx);
   na = wave_sum(na);
   n1 = wave_sum(n1);
+  ne = wave_sum(ne);
   if (__lane_id() == 0) {
     s_bits[threadIdx.x / WAVE] = bits;
     s_mx[threadIdx.x / WAVE] = mx;
     s_na[threadIdx.x / WAVE] = na;
     s_n1[threadIdx.x / WAVE] = n1;
+    s_ne[threadIdx.x / WAVE] = ne;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -158,25 +162,27 @@ __device__ __forceinline__ void validate(const DevGraph &g, int side, uint32_t *
       mx = s_mx[w] > mx ? s_mx[w] : mx;
       na += s_na[w];
       n1 += s_n1[w];
+      ne += s_ne[w];
     }
     if (bits) atomicOr(err, bits);
     if (mx) atomicMax(maxlab, mx);
     if (na && nacc) atomicAdd(nacc, na);
     if (n1 && single) atomicAdd(single, n1);
+    if (ne && neps) atomicAdd(neps, ne);
   }
 }
 
 __global__ __launch_bounds__(NT) void k_validate(DevGraph g, int side, uint32_t *err,
                                                  uint32_t *maxlab, uint32_t *nacc,
-                                                 uint32_t *single) {
-  validate(g, side, err, maxlab, nacc, single);
+                                                 uint32_t *single, uint32_t *neps) {
+  validate(g, side, err, maxlab, nacc, single, neps);
 }
 
 // A (first row of workgroups) and B of a composition.
 __global__ __launch_bounds__(NT) void k_validate2(DevGraph A, DevGraph B, Scalars *sc) {
   const bool a = blockIdx.y == 0;
   validate(a ? A : B, a ? 0 : 1, a ? &sc->errA : &sc->errB, a ? &sc->maxLabA : &sc->maxLabB,
-           a ? &sc->naccA : &sc->naccB, a ? nullptr : &sc->singleB);
+           a ? &sc->naccA : &sc->naccB, a ? nullptr : &sc->singleB, a ? &sc->nepsA : &sc->nepsB);
 }
 
 // What the composition needs from a graph whose structure the caller
@@ -185,8 +191,8 @@ __global__ __launch_bounds__(NT) void k_validate2(DevGraph A, DevGraph B, Scalar
 // with the same source), and the number of accepting states; no checks.
 __global__ __launch_bounds__(NT) void k_label_facts(DevGraph g, int side, uint32_t *err,
                                                     uint32_t *maxlab, uint32_t *nacc,
-                                                    uint32_t *single) {
-  uint32_t bits = 0, mx = 0, na = 0, n1 = 0;
+                                                    uint32_t *single, uint32_t *neps) {
+  uint32_t bits = 0, mx = 0, na = 0, n1 = 0, ne = 0;
   const long long V = g.V, E = g.E;
   const long long n = V > E ? V : E;
   for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < n;
@@ -196,21 +202,24 @@ __global__ __launch_bounds__(NT) void k_label_facts(DevGraph g, int side, uint32
     if (i < E && side != 2) {
       const int32_t lab = side == 0 ? g.ol[i] : g.il[i];
       if (lab > 0 && (uint32_t)lab > mx) mx = (uint32_t)lab;
+      ne += lab == 0 ? 1u : 0u;
       if (side == 0 && (lab == 0 || g.dst[i] != g.src[i] + 1)) bits |= INFO_NOT_LINEAR;
       if (i > 0 && g.src[i - 1] == g.src[i] && (side == 0 ? g.ol[i - 1] : g.il[i - 1]) > lab)
         bits |= INFO_UNSORTED;
     }
   }
-  __shared__ uint32_t s_bits[NWAVES], s_mx[NWAVES], s_na[NWAVES], s_n1[NWAVES];
+  __shared__ uint32_t s_bits[NWAVES], s_mx[NWAVES], s_na[NWAVES], s_n1[NWAVES], s_ne[NWAVES];
   bits = wave_or(bits);
   mx = wave_max(mx);
   na = wave_sum(na);
   n1 = wave_sum(n1);
+  ne = wave_sum(ne);
   if (__lane_id() == 0) {
     s_bits[threadIdx.x / WAVE] = bits;
     s_mx[threadIdx.x / WAVE] = mx;
     s_na[threadIdx.x / WAVE] = na;
     s_n1[threadIdx.x / WAVE] = n1;
+    s_ne[threadIdx.x / WAVE] = ne;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -219,11 +228,13 @@ __global__ __launch_bounds__(NT) void k_label_facts(DevGraph g, int side, uint32
       mx = s_mx[w] > mx ? s_mx[w] : mx;
       na += s_na[w];
       n1 += s_n1[w];
+      ne += s_ne[w];
     }
     if (bits) atomicOr(err, bits);
     if (mx) atomicMax(maxlab, mx);
     if (na && nacc) atomicAdd(nacc, na);
     if (n1 && single) atomicAdd(single, n1);
+    if (ne && neps) atomicAdd(neps, ne);
   }
 }
 
@@ -1322,12 +1333,91 @@ __global__ __launch_bounds__(NT, 4) void k_gen2(Problem P, SearchArgs SF, Search
 // targets of a unit that are spread over the lanes at a time.
 constexpr int32_t LEVEL_SERIAL = 8, LEVEL_TAKE = 1 << 20;
 
+// What a wavefront numbers: its keys' units and its units' targets.
+struct SpreadLds {
+  uint32_t unit[WAVE], target[WAVE];
+};
+
+// The last lane whose items start at or before item i.
+__device__ __forceinline__ uint32_t spread_lane(const uint32_t *off, uint32_t i) {
+  uint32_t a = 0;
+#pragma unroll
+  for (uint32_t h = WAVE / 2; h; h >>= 1)
+    if (off[a + h] <= i) a += h;
+  return a;
+}
+
+// Calls f(target) for every target of the lanes' units (the whole wavefront).
+// Where some unit has many (an arc of A, and a label that many of B's arcs here
+// have), the targets are numbered and spread over the lanes.
+template <bool FWD, class F>
+__device__ __forceinline__ void spread_targets(const Problem &P, SpreadLds &L, UnitRange x, F &&f) {
+  auto take = [&](const UnitRange &r) {
+    for_range<FWD>(P, r, [&](const Target &t, const Rec &) { f(t); });
+  };
+  if (__ballot(x.hi - x.lo > LEVEL_SERIAL) == 0) {
+    take(x);
+    return;
+  }
+  const uint32_t lane = __lane_id();
+  while (__ballot(x.lo < x.hi)) {
+    const int32_t rest = x.hi - x.lo;
+    const uint32_t n = rest < LEVEL_TAKE ? (uint32_t)rest : (uint32_t)LEVEL_TAKE;
+    const uint32_t incl = wave_incl_scan(n), all = __shfl(incl, WAVE - 1, WAVE);
+    L.target[lane] = incl - n;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t i0 = 0; i0 < all; i0 += WAVE) {
+      const uint32_t i = i0 + lane, a = spread_lane(L.target, i);
+      UnitRange one = x;
+      one.lo = __shfl(x.lo, (int)a) + (int32_t)(i - L.target[a]);
+      one.hi = one.lo + 1;
+      one.fixed = __shfl(x.fixed, (int)a);
+      one.flags = __shfl(x.flags, (int)a);
+      if (i < all) {
+        const int2 *arcs = FWD ? ((one.flags & VARY_A) ? P.aOut.arec : P.bOut.arec)
+                               : ((one.flags & VARY_A) ? P.aIn.arec : P.bIn.arec);
+        one.nb0 = arcs[one.lo].y;
+        take(one);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    x.lo += (int32_t)n;
+  }
+}
+
+// Calls f(target) for every target of the lanes' keys (with records A and B,
+// `units` units; few enough that a wavefront's fit 32 bits): the units are
+// numbered by a scan and spread over the lanes (the key of a unit found by a
+// binary search in LDS, its records moved between lanes), so a wavefront's
+// time does not grow with its busiest key.
+template <bool FWD, class F>
+__device__ __forceinline__ void spread_units(const Problem &P, SpreadLds &L, uint32_t key,
+                                             const Rec &A, const Rec &B, uint32_t units, F &&f) {
+  const uint32_t lane = __lane_id();
+  const uint32_t incl = wave_incl_scan(units), all = __shfl(incl, WAVE - 1, WAVE);
+  L.unit[lane] = incl - units;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (uint32_t r = 0; r < all; r += WAVE) {
+    const uint32_t item = r + lane;
+    const bool go = item < all;
+    const uint32_t a = go ? spread_lane(L.unit, item) : lane;
+    const uint32_t k2 = __shfl(key, a, WAVE);
+    const Rec A2 = shfl_rec(A, a), B2 = shfl_rec(B, a);
+    const uint32_t u = item - L.unit[a];
+    UnitRange x = {};
+    if (go) x = Dir<FWD>::range(P, Dir<FWD>::make(k2, P.shiftB, A2, B2), u);
+    spread_targets<FWD>(P, L, x, f);
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
 // LDS of a workgroup of the level search.
 struct LevelLds {
   uint32_t ho[NT], hk[NT];     // a heavy list of at most NT keys
   uint32_t pre[SUBQ + 1];      // prefix of the frontier's part counts
-  uint32_t off[NWAVES][WAVE];  // unit offsets of a wavefront's keys
-  uint32_t toff[NWAVES][WAVE]; // target offsets of its lanes' units
+  SpreadLds spread[NWAVES];
   PushBuf push[NWAVES];
 };
 
@@ -1353,10 +1443,7 @@ __device__ __forceinline__ void reach(const Problem &P, const NextGen &nx, const
 
 // Generation g of a level search (one kernel).  Its items are the unit slots
 // of its heavy keys (one per thread) and its frontier keys, which a
-// wavefront takes in batches: the units of the batch's keys are numbered by
-// a scan and spread over the lanes (the key of a unit found by a binary
-// search in LDS, its records moved between lanes), so a wavefront's time
-// does not grow with its busiest key.  A batch is the frontier divided by the
+// wavefront takes in batches (see spread_units).  A batch is the frontier divided by the
 // wavefronts, at most 64 keys: a narrow frontier is spread over more
 // wavefronts, a wide one fills the lanes.  nb is a multiple of 8 (slots of
 // heavy keys are spread over the XCDs as in gen_body).
@@ -1394,7 +1481,7 @@ __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S
   if (K > WAVE) K = WAVE;
   for (ull j = lw;; j += nl) {
     const bool hv = j < hb;
-    uint32_t key = 0, u0 = 0, units = 0, T = 1;
+    uint32_t key = 0, u0 = 0, units = 0;
     Rec A = {}, B = {};
     bool have = false;
     if (hv) {
@@ -1423,80 +1510,20 @@ __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S
       B = load_rec(Dir<FWD>::viewB(P), key_qb(key, P.shiftB));
       units = Dir<FWD>::units(Dir<FWD>::make(key, P.shiftB, A, B));
     }
-    if (!hv) {
-      // a key with many units waits one generation and is then spread over
-      // the whole grid
-      if (units > LEVEL_UNITS) {
-        list_heavy(S, nx, key, units);
-        units = 0;
-      }
-      const uint32_t incl = wave_incl_scan(units);
-      L.off[wid][lane] = incl - units;
-      T = __shfl(incl, WAVE - 1, WAVE);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+    auto take = [&](const Target &t) { reach<FWD>(P, nx, t); };
+    if (hv) {  // a unit per lane (a slot past the key's units has none)
+      UnitRange x = {};
+      if (u0 < units) x = Dir<FWD>::range(P, Dir<FWD>::make(key, P.shiftB, A, B), u0);
+      spread_targets<FWD>(P, L.spread[wid], x, take);
+      continue;
     }
-    for (uint32_t r = 0; r < T; r += WAVE) {
-      bool go = have && u0 < units;  // a heavy slot past the key's units has none
-      uint32_t u = u0, k2 = key;
-      Rec A2 = A, B2 = B;
-      if (!hv) {
-        const uint32_t item = r + lane;
-        go = item < T;
-        uint32_t a = 0;  // the last lane whose units start at or before this one
-#pragma unroll
-        for (uint32_t h = WAVE / 2; h; h >>= 1)
-          if (L.off[wid][a + h] <= item) a += h;
-        a = go ? a : lane;
-        k2 = __shfl(key, a, WAVE);
-        A2 = shfl_rec(A, a);
-        B2 = shfl_rec(B, a);
-        u = item - L.off[wid][a];
-      }
-      UnitRange range;
-      range.lo = range.hi = range.nb0 = 0;
-      range.fixed = range.flags = 0;
-      if (go) range = Dir<FWD>::range(P, Dir<FWD>::make(k2, P.shiftB, A2, B2), u);
-      auto take = [&](const UnitRange &x) {
-        for_range<FWD>(P, x, [&](const Target &t, const Rec &) { reach<FWD>(P, nx, t); });
-      };
-      if (__ballot(range.hi - range.lo > LEVEL_SERIAL) == 0) {
-        take(range);
-        continue;
-      }
-      // some unit has many targets (an arc of A, and a label that many of B's
-      // arcs here have): the targets are numbered and spread over the lanes,
-      // as the units are
-      while (__ballot(range.lo < range.hi)) {
-        const int32_t rest = range.hi - range.lo;
-        const uint32_t n = rest < LEVEL_TAKE ? (uint32_t)rest : (uint32_t)LEVEL_TAKE;
-        const uint32_t incl = wave_incl_scan(n), all = __shfl(incl, WAVE - 1, WAVE);
-        uint32_t *off = L.toff[wid];
-        off[lane] = incl - n;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (uint32_t i0 = 0; i0 < all; i0 += WAVE) {
-          const uint32_t i = i0 + lane;
-          uint32_t a = 0;  // the last lane whose targets start at or before this one
-#pragma unroll
-          for (uint32_t h = WAVE / 2; h; h >>= 1)
-            if (off[a + h] <= i) a += h;
-          UnitRange one = range;
-          one.lo = __shfl(range.lo, (int)a) + (int32_t)(i - off[a]);
-          one.hi = one.lo + 1;
-          one.fixed = __shfl(range.fixed, (int)a);
-          one.flags = __shfl(range.flags, (int)a);
-          if (i < all) {
-            const int2 *arcs = FWD ? ((one.flags & VARY_A) ? P.aOut.arec : P.bOut.arec)
-                                   : ((one.flags & VARY_A) ? P.aIn.arec : P.bIn.arec);
-            one.nb0 = arcs[one.lo].y;
-            take(one);
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
-        range.lo += (int32_t)n;
-      }
+    // a key with many units waits one generation and is then spread over the
+    // whole grid
+    if (units > LEVEL_UNITS) {
+      list_heavy(S, nx, key, units);
+      units = 0;
     }
+    spread_units<FWD>(P, L.spread[wid], key, A, B, units, take);
   }
   push_flush(*nx.buf, nx.q);
 }
@@ -1519,17 +1546,18 @@ __global__ __launch_bounds__(NT) void k_level2(Problem P, SearchArgs SF, SearchA
 // ---------------------------------------------------------------------------
 // small search
 // ---------------------------------------------------------------------------
-// Up to SMALL_PAIRS state pairs both searches run in one launch, a workgroup of
-// SMALL_NT threads each: bitmap and frontiers in LDS, a level per barrier
-// instead of per launch.  A level then takes its three dependent loads
-// (records, arc, bucket; about 2 us) where a launch of the level search takes
-// 8 us; with more pairs one workgroup would have more units than that saves.
+// Up to SMALL_PAIRS state pairs with few units (see small_search) both searches
+// run in one launch, a workgroup of SMALL_NT threads each: bitmap and frontiers
+// in LDS, a level per barrier instead of per launch.  A level then takes its
+// three dependent loads (records, arc, bucket; about 2 us) where a launch of the
+// level search takes 8 us; with more units, or many at a few keys, one workgroup
+// is the longer way.
 constexpr int SMALL_NT = 1024, SMALL_WAVES = SMALL_NT / WAVE;
 constexpr uint32_t SMALL_LIST = 6144;  // keys of a level
 struct SmallLds {
   uint32_t bits[SMALL_SEARCH_BITS / 32];
   uint32_t list[2][SMALL_LIST];
-  uint32_t off[SMALL_WAVES][WAVE];
+  SpreadLds spread[SMALL_WAVES];
   uint32_t n[2];
   uint32_t sum;
 };
@@ -1553,7 +1581,6 @@ __device__ __forceinline__ bool small_claim(const Problem &P, SmallLds &L, uint3
 
 template <bool FWD>
 __device__ __forceinline__ void small_body(const Problem &P, Scalars *sc, SmallLds &L) {
-  typedef typename Dir<FWD>::Info Info;
   const uint32_t tid = threadIdx.x, lane = __lane_id(), wid = tid / WAVE;
   const uint32_t VA = (uint32_t)P.A.V, VB = (uint32_t)P.B.V;
   const uint32_t words = (P.rowA << (31 - __clz((int)(P.maskB + 1)) + 1)) / 32;
@@ -1596,30 +1623,9 @@ __device__ __forceinline__ void small_body(const Problem &P, Scalars *sc, SmallL
         B = load_rec(Dir<FWD>::viewB(P), key_qb(key, P.shiftB));
         units = Dir<FWD>::units(Dir<FWD>::make(key, P.shiftB, A, B));
       }
-      const uint32_t incl = wave_incl_scan(units);
-      L.off[wid][lane] = incl - units;
-      const uint32_t T = __shfl(incl, WAVE - 1, WAVE);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      for (uint32_t r = 0; r < T; r += WAVE) {
-        const uint32_t item = r + lane;
-        const bool go = item < T;
-        uint32_t a = 0;  // the last lane whose units start at or before this one
-#pragma unroll
-        for (uint32_t h = WAVE / 2; h; h >>= 1)
-          if (L.off[wid][a + h] <= item) a += h;
-        a = go ? a : lane;
-        const uint32_t k2 = __shfl(key, a, WAVE);
-        const Rec A2 = shfl_rec(A, a), B2 = shfl_rec(B, a);
-        const uint32_t u = item - L.off[wid][a];
-        if (go) {
-          const Info info = Dir<FWD>::make(k2, P.shiftB, A2, B2);
-          for_unit<FWD>(P, info, u, [&](const Target &t, const Rec &) {
-            small_push(L, cur ^ 1, small_claim(P, L, t.key), t.key);
-          });
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
+      spread_units<FWD>(P, L.spread[wid], key, A, B, units, [&](const Target &t) {
+        small_push(L, cur ^ 1, small_claim(P, L, t.key), t.key);
+      });
     }
     __syncthreads();  // the next level is listed
     if (tid == 0) L.n[cur] = 0;
@@ -3197,28 +3203,25 @@ __global__ __launch_bounds__(NT) void k_item_ranges(Problem P, ull nkeys, int32_
 // launchers
 // ---------------------------------------------------------------------------
 hipError_t launch_validate(const DevGraph &g, int side, uint32_t *err, uint32_t *maxlab,
-                           hipStream_t s, uint32_t *nacc, bool check, uint32_t *single) {
+                           hipStream_t s, uint32_t *nacc, bool check, uint32_t *single,
+                           uint32_t *neps) {
   size_t n = (size_t)(g.V + 1 > g.E ? g.V + 1 : g.E);
-  if (check) k_validate<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc, single);
-  else k_label_facts<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc, single);
+  if (check) k_validate<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc, single, neps);
+  else k_label_facts<<<grid_for(n, 2048), NT, 0, s>>>(g, side, err, maxlab, nacc, single, neps);
   return hipGetLastError();
 }
 
 hipError_t launch_validate2(const DevGraph &A, const DevGraph &B, Scalars *sc, bool check,
                             hipStream_t s) {
-  if (!check) {
-    hipError_t e = hipSuccess;
-    if (A.V) e = launch_validate(A, 0, &sc->errA, &sc->maxLabA, s, &sc->naccA, false);
-    if (e == hipSuccess && B.V)
-      e = launch_validate(B, 1, &sc->errB, &sc->maxLabB, s, &sc->naccB, false, &sc->singleB);
-    return e;
-  }
   // (a graph without states has no offsets to check)
-  if (!A.V || !B.V) {
-    if (A.V) return launch_validate(A, 0, &sc->errA, &sc->maxLabA, s, &sc->naccA);
-    if (B.V)
-      return launch_validate(B, 1, &sc->errB, &sc->maxLabB, s, &sc->naccB, true, &sc->singleB);
-    return hipSuccess;
+  if (!check || !A.V || !B.V) {
+    hipError_t e = hipSuccess;
+    if (A.V)
+      e = launch_validate(A, 0, &sc->errA, &sc->maxLabA, s, &sc->naccA, check, nullptr, &sc->nepsA);
+    if (e == hipSuccess && B.V)
+      e = launch_validate(B, 1, &sc->errB, &sc->maxLabB, s, &sc->naccB, check, &sc->singleB,
+                          &sc->nepsB);
+    return e;
   }
   const size_t na = (size_t)(A.V + 1 > A.E ? A.V + 1 : A.E);
   const size_t nb = (size_t)(B.V + 1 > B.E ? B.V + 1 : B.E);

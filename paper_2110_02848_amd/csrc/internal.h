@@ -199,6 +199,7 @@ struct Scalars {
   uint32_t nEpsStatesA;         // states of A with an epsilon-output arc
   uint32_t singleB;             // states of B with one out-arc
   uint32_t naccA, naccB;        // accepting states of A and B
+  uint32_t nepsA, nepsB;        // their epsilon arcs (by the matched label)
   uint32_t pad0;
   uint32_t heavy;               // heavy states of C
   uint32_t overflow;            // a capacity was exceeded
@@ -555,11 +556,12 @@ hipError_t radix_sort(unsigned long long *k0, int32_t *v0, unsigned long long *k
 // largest matched label, whether the arcs are in label order and (side 0)
 // whether every arc leads from a state to the next without epsilon; side 2
 // checks the structure only.  *nacc (if given) += number of accepting states.
-// *single (if given) += number of states with exactly one out-arc.
+// *single (if given) += number of states with exactly one out-arc, *neps that
+// of arcs whose matched label is epsilon.
 // check = false skips the checks and only gathers the label facts and nacc.
 hipError_t launch_validate(const DevGraph &g, int side, uint32_t *err, uint32_t *maxlab,
                            hipStream_t s, uint32_t *nacc = nullptr, bool check = true,
-                           uint32_t *single = nullptr);
+                           uint32_t *single = nullptr, uint32_t *neps = nullptr);
 // The same for A and B of a composition, into its scalars (one launch).
 hipError_t launch_validate2(const DevGraph &A, const DevGraph &B, Scalars *sc, bool check,
                             hipStream_t s);

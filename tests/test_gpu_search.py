@@ -323,13 +323,26 @@ def test_compaction_without_room():
 
 # ---- small search ----
 
-@pytest.mark.parametrize("VA,VB,starts", [(1, 1, 1), (64, 128, 3), (128, 64, 3), (8192, 1, 5),
-                                          (1, 8192, 5), (91, 90, 4), (90, 91, 91), (3, 2730, 2),
-                                          (90, 91, 60), (63, 65, 63)])
-def test_small_search(VA, VB, starts):
+def _search_launches(c):
+    import torch
+    torch.cuda.synchronize()
+    return c.kernel_times()["search_forward"][1]
+
+
+@pytest.mark.parametrize("VA,VB,starts,small", [
+    (1, 1, 1, 1), (64, 128, 3, 1), (128, 64, 3, 1), (91, 90, 4, 1), (90, 91, 91, 0),
+    (90, 91, 60, 0), (63, 65, 63, 1),
+    # narrow operands whose search bitmaps (rows of 64 A states, columns of a
+    # power of two of B states, 16 at least) still have at most 65,536 bits ...
+    (2048, 1, 5, 1), (1, 512, 5, 1), (2000, 4, 3, 1), (33, 256, 4, 0),
+    # ... and whose do not: another search
+    (2049, 1, 5, 0), (8192, 1, 5, 0), (1, 513, 5, 0), (1, 8192, 5, 0), (3, 2730, 2, 0)])
+def test_small_search(VA, VB, starts, small):
     """State pairs up to the limit of a small search (8192) and past it, levels
-    of more keys than its lists hold (6144: every pair starts and accepts),
-    narrow and wide operands."""
+    of more keys than its lists hold (6144: every pair starts and accepts; then
+    it is run again as a level search), narrow and wide operands, and which
+    search it was (a small one is one launch)."""
+    from paper_2110_02848_amd import gpu
     rng = np.random.default_rng(VA + VB)
     A = synth.random_fst(rng, VA, 3, 4, 0.2, 0.2 if starts < 60 else 1.0,
                          start=range(min(VA, starts)))
@@ -337,6 +350,44 @@ def test_small_search(VA, VB, starts):
                          start=range(min(VB, starts)))
     ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
     c = _composer("CONCURRENT")
+    c.set_option(gpu.FST_OPT_TIMING, 1)
     for k in range(2):
         check_pair(c, A, B, f"small {VA} {VB} {starts} call {k}", ref=ref)
+        assert (_search_launches(c) == 1) == bool(small)
     c.close()
+
+
+def _arcs_of(rng, V, arcs_a_state, n_sym, n_eps):
+    """V states of that many arcs, n_eps of all with epsilon on both sides."""
+    n = V * arcs_a_state
+    il = rng.integers(1, n_sym + 1, size=n)
+    il[rng.permutation(n)[:n_eps]] = 0
+    arcs = [(i // arcs_a_state, int(rng.integers(0, V)), int(il[i]), int(il[i]),
+             float(rng.standard_normal())) for i in range(n)]
+    return synth.from_arcs(V, arcs, start=[0], accept=range(0, V, 3))
+
+
+@pytest.mark.parametrize("VA,dA,eA,VB,dB,eB,small", [
+    # units: epsilon arcs of A x VB, of B x VA (twice where A has some), and
+    # the smaller of the other arcs x the other's states
+    (64, 20, 0, 64, 20, 0, 1), (64, 20, 0, 64, 30, 0, 1),  # 81,920
+    (64, 21, 0, 64, 21, 0, 0),                             # 86,016
+    (64, 20, 1, 64, 20, 0, 1), (64, 20, 1, 64, 20, 1, 0),  # 81,920 and 81,984
+    (20, 34, 0, 20, 34, 0, 1), (20, 35, 0, 20, 35, 0, 0),  # 13,600 and 14,000 of 13,696
+    (1, 4120, 0, 1, 5000, 0, 1), (1, 4121, 0, 1, 4121, 0, 0), (1, 30000, 0, 1, 30000, 0, 0),
+    (500, 4, 0, 1, 9000, 0, 1), (500, 4, 0, 1, 9000, 40, 0)])  # 2,000 and 20,000 more
+def test_small_search_units(VA, dA, eA, VB, dB, eB, small):
+    """Small searches end at a number of work units, over all pairs and per
+    pair, whichever side they come from."""
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(VA * dA + dB)
+    n_sym = max(4, dA * dB // 4)
+    A, B = _arcs_of(rng, VA, dA, n_sym, eA), _arcs_of(rng, VB, dB, n_sym, eB)
+    ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
+    for validate in (1, 0):
+        c = _composer("CONCURRENT")
+        c.set_option(gpu.FST_OPT_TIMING, 1)
+        c.set_option(gpu.FST_OPT_VALIDATE, validate)
+        check_pair(c, A, B, f"units {VA} {dA} {eA} {VB} {dB} {eB}", ref=ref)
+        assert (_search_launches(c) == 1) == bool(small)
+        c.close()
