@@ -958,6 +958,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
 
     // ---- the two searches ----
     int32_t *la = as<int32_t>(c->lists), *lb = la + VA;
+    const unsigned long long pairs = (unsigned long long)c->h_sc->naccA * c->h_sc->naccB;
     uint32_t *ns = d_sc->lists, *na = ns + 2;  // start, accepting states listed
     SearchArgs S;
     S.Q = P.chains ? Frontier{as<uint32_t>(c->fq), rc, 1, d_sc->front[0]}
@@ -1040,7 +1041,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       // With few accepting pairs the backward search starts at once (its
       // seeds cannot outnumber much of the forward work).
       const int FIRST =
-          (unsigned long long)c->h_sc->naccA * c->h_sc->naccB <= FEW_ACCEPTING_PAIRS ? 0 : 4;
+          pairs <= FEW_ACCEPTING_PAIRS ? 0 : 4;
       P.restrict_fwd = 0;
       P.restrict_bwd = 0;
       phase_begin(c, PH_FWD, s);
@@ -1067,7 +1068,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
         phase_begin(c, PH_BWD, s);
         P.restrict_bwd = 1;
         FST_TRY(second_search());
-        HIP_TRY(launch_seed_backward(P, S, la, na, lb, na + 1, s));
+        HIP_TRY(launch_seed_backward(P, S, la, na, lb, na + 1, pairs, snwords, s));
         FST_TRY(search(c, S, false, &c->stats.bwd_levels, s));
         HIP_TRY(launch_trim(P, (uint32_t)VA, as<uint32_t>(c->trim), wbase, s));
         phase_end(c, PH_BWD, s);
@@ -1079,7 +1080,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
         SB.G = d_sc->G2;
         SB.gens = &d_sc->gens2;
         SB.note = &d_sc->note2;
-        HIP_TRY(launch_seed_backward(P, SB, la, na, lb, na + 1, s));
+        HIP_TRY(launch_seed_backward(P, SB, la, na, lb, na + 1, pairs, snwords, s));
         FST_TRY(search_concurrent(c, P, S, SB, FIRST, s));
         HIP_TRY(launch_popcount(P.vis, snwords, &d_sc->naccessible, s));
         if (c->count_moves) HIP_TRY(launch_count_moves(P, snwords, true, &d_sc->generated, s));
@@ -1096,7 +1097,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       P.restrict_bwd = 0;
       phase_begin(c, PH_BWD, s);
       HIP_TRY(hipMemsetAsync(d_sc->G, 0, sizeof(d_sc->G), s));
-      HIP_TRY(launch_seed_backward(P, S, la, na, lb, na + 1, s));
+      HIP_TRY(launch_seed_backward(P, S, la, na, lb, na + 1, pairs, snwords, s));
       FST_TRY(search(c, S, false, &c->stats.bwd_levels, s));
       phase_end(c, PH_BWD, s);
       phase_begin(c, PH_FWD, s);
@@ -1121,7 +1122,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       // backward search, seeded by the accepting keys among them
       phase_begin(c, PH_BWD, s);
       FST_TRY(second_search());
-      HIP_TRY(launch_seed_backward(P, S, la, na, lb, na + 1, s));
+      HIP_TRY(launch_seed_backward(P, S, la, na, lb, na + 1, pairs, snwords, s));
       FST_TRY(search(c, S, false, &c->stats.bwd_levels, s));
       // the backward search may set co-accessible bits of keys it never
       // expands (not accessible); the trim set is what remains after masking

@@ -521,6 +521,12 @@ __device__ __forceinline__ int32_t opaque(int32_t x) {
   return x;
 }
 
+// The key at bit sb of the search layout.
+__device__ __forceinline__ uint32_t search_key(const Problem &P, uint32_t sb) {
+  const uint32_t x = sb >> 1, d = x / P.rowA, qa = x - d * P.rowA;
+  return make_key(qa, (d + qa) & P.maskB, sb & 1u, P.shiftB);
+}
+
 // Claim key k in bitmap bm; true for exactly one caller per key.  The plain
 // load first matters: keys such as a lexicon root are reached by thousands
 // of threads at once, and only the first few should reach the atomic.
@@ -2109,6 +2115,15 @@ __global__ __launch_bounds__(NT) void k_collect(const uint8_t *__restrict__ fa, 
   }
 }
 
+// A seed (where `fresh`) with moves waits for generation 0.
+template <bool FWD>
+__device__ __forceinline__ void seed(const SearchArgs &S, const NextGen &nx, bool fresh,
+                                     uint32_t k, const typename Dir<FWD>::Info &ki) {
+  const uint32_t u = fresh ? Dir<FWD>::units(ki) : 0;
+  if (u > LIGHT_SEARCH) list_heavy(S, nx, k, u);
+  buf_push(u > 0 && u <= LIGHT_SEARCH, k, *nx.buf, nx.q);
+}
+
 // Start keys (sa, sb, 0) for every pair of start states (Algorithm 1) form
 // generation 0 of the forward search.
 __global__ __launch_bounds__(NT) void k_seed_forward(Problem P, SearchArgs S,
@@ -2134,9 +2149,7 @@ __global__ __launch_bounds__(NT) void k_seed_forward(Problem P, SearchArgs S,
       fresh = (!P.restrict_fwd || test_bit(P.coacc, sb)) && claim(P.vis, sb);
       ki = fwd_info(P, k);
     }
-    const uint32_t u = fresh ? Dir<true>::units(ki) : 0;
-    if (u > LIGHT_SEARCH) list_heavy(S, nx, k, u);
-    buf_push(u > 0 && u <= LIGHT_SEARCH, k, *nx.buf, nx.q);
+    seed<true>(S, nx, fresh, k, ki);
   }
   push_flush(*nx.buf, nx.q);
 }
@@ -2169,12 +2182,37 @@ __global__ __launch_bounds__(NT) void k_seed_backward(Problem P, SearchArgs S,
       // every pair is enumerated once, so it is placed once
       const uint32_t sb = search_bit(P, k);
       fresh = (f == 0 || eps) && (!P.restrict_bwd || test_bit(P.vis, sb));
-      if (fresh) set_bit(P.coacc, sb);
-      ki = bwd_info(P, k);
+      if (fresh) {
+        set_bit(P.coacc, sb);
+        ki = bwd_info(P, k);
+      }
     }
-    const uint32_t u = fresh ? Dir<false>::units(ki) : 0;
-    if (u > LIGHT_SEARCH) list_heavy(S, nx, k, u);
-    buf_push(u > 0 && u <= LIGHT_SEARCH, k, *nx.buf, nx.q);
+    seed<false>(S, nx, fresh, k, ki);
+  }
+  push_flush(*nx.buf, nx.q);
+}
+
+// The same of the accessible keys (restrict_bwd), a word of their bitmap at a
+// time: for graphs with more accepting pairs than the bitmap has words.
+__global__ __launch_bounds__(NT) void k_seed_backward_keys(Problem P, SearchArgs S, ull nwords) {
+  __shared__ PushBuf s_push[NWAVES];
+  const uint32_t wid = threadIdx.x / WAVE;
+  const NextGen nx{&S.G[0], 0u, next_front(S.Q, -1, blockIdx.x * NWAVES + wid, S.sc),
+                   s_push + wid};
+  if (__lane_id() == 0) s_push[wid].n = 0;
+  __syncthreads();
+  for (ull w = (ull)blockIdx.x * NT + threadIdx.x; w < nwords; w += (ull)gridDim.x * NT) {
+    for (uint32_t bits = P.vis[w]; bits; bits &= bits - 1) {
+      const uint32_t sb = (uint32_t)(32 * w) + (uint32_t)__ffs((int)bits) - 1;
+      const uint32_t k = search_key(P, sb);
+      const bool fresh = P.A.accept[key_qa(k, P.shiftB)] && P.B.accept[key_qb(k, P.shiftB)];
+      Bwd ki;
+      if (fresh) {
+        set_bit(P.coacc, sb);
+        ki = bwd_info(P, k);
+      }
+      seed<false>(S, nx, fresh, k, ki);
+    }
   }
   push_flush(*nx.buf, nx.q);
 }
@@ -2196,8 +2234,7 @@ __global__ __launch_bounds__(NT) void k_count_moves(Problem P, ull nwords,
       const uint32_t b = (uint32_t)(k / (64 * P.linW));
       key = make_key((uint32_t)(k - (ull)b * 64 * P.linW), b, 0u, P.shiftB);
     } else if (FWD) {
-      const uint32_t x = (uint32_t)(k >> 1), d = x / P.rowA, qa = x - d * P.rowA;
-      key = make_key(qa, (d + qa) & P.maskB, (uint32_t)(k & 1u), P.shiftB);
+      key = search_key(P, key);
     }
     const typename Dir<FWD>::Info s = Dir<FWD>::info(P, key);
     const uint32_t nu = Dir<FWD>::units(s);
@@ -3308,7 +3345,12 @@ hipError_t launch_seed_forward(const Problem &P, const SearchArgs &S, int32_t *l
 }
 
 hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, int32_t *la,
-                                uint32_t *na, int32_t *lb, uint32_t *nb, hipStream_t s) {
+                                uint32_t *na, int32_t *lb, uint32_t *nb,
+                                unsigned long long pairs, size_t nwords, hipStream_t s) {
+  if (P.restrict_bwd && 2 * pairs > nwords) {
+    k_seed_backward_keys<<<grid_for(nwords, 4096), NT, 0, s>>>(P, S, nwords);
+    return hipGetLastError();
+  }
   const size_t V = (size_t)(P.A.V > P.B.V ? P.A.V : P.B.V);
   k_collect<<<dim3(grid_for(V, 1024), 2), NT, 0, s>>>(P.A.accept, P.A.V, la, na, P.B.accept, P.B.V, lb,
                                                       nb);

@@ -620,12 +620,17 @@ hipError_t finish_views(ViewJobs J, hipStream_t s);
 // caller) and place every start key in generation 0 of the forward search.
 hipError_t launch_seed_forward(const Problem &P, const SearchArgs &S, int32_t *la, uint32_t *na,
                                int32_t *lb, uint32_t *nb, hipStream_t s);
-// Collect the accepting states of A and B into la/lb (counts na/nb, zeroed
-// by the caller) and place every accepting key (f = 0, and f = 1 where
-// epsOutA) in generation 0 of a backward search: over all key pairs, or
-// (restrict_bwd) those of the accessible ones.
+// Place every accepting key (f = 0, and f = 1 where epsOutA) in generation 0 of
+// a backward search: over all key pairs, or (restrict_bwd) those of the
+// accessible ones.  The accepting states of A and B are collected into la/lb
+// (counts na/nb, zeroed by the caller) and their pairs enumerated; of the
+// accessible keys, where there are more pairs than half the words of the search
+// bitmap (nwords), that is read instead (it was cleared for the search, so a
+// pass over it is never the larger part: 20,000 o 20,000 states that all accept
+// and hardly match, 6.5 ms by pairs).
 hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, int32_t *la,
-                                uint32_t *na, int32_t *lb, uint32_t *nb, hipStream_t s);
+                                uint32_t *na, int32_t *lb, uint32_t *nb,
+                                unsigned long long pairs, size_t nwords, hipStream_t s);
 // Generation g of the forward (or backward) search: one kernel.
 hipError_t launch_generation(const Problem &P, const SearchArgs &S, bool forward, int g,
                              hipStream_t s);

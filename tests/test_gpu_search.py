@@ -114,6 +114,27 @@ def test_single_arc_states_of_b(order, more):
     c.close()
 
 
+@pytest.mark.parametrize("order", ORDERS)
+@pytest.mark.parametrize("p_accept", (0.02, 0.2, 0.25, 1.0))
+@pytest.mark.parametrize("deep", (0, 1))
+def test_backward_seeds(order, p_accept, deep):
+    """Few accepting pairs to many (with more than half the words of the search
+    bitmap, 5,120, the accessible keys are read instead: 300 states of which a
+    quarter accept have 5,625), with f = 1 among them, forward searches of one
+    generation and of many, B with several arcs a state and with one."""
+    rng = np.random.default_rng(int(100 * p_accept) + deep)
+    V, n_sym = 300, 3 if deep else 40
+    A = synth.random_fst(rng, V, 4, n_sym, 0.1, 0.0, start=range(4))
+    A["accept"][rng.permutation(V)[:int(p_accept * V)]] = 1
+    for degree in (3, 1):
+        B = synth.random_fst(rng, V, degree, n_sym, 0.1, 0.0, start=range(5))
+        B["accept"][rng.permutation(V)[:int(p_accept * V)]] = 1
+        c = _composer(order)
+        check_pair(c, A, B, f"seeds {order} {p_accept} {deep} degree {degree}",
+                   ref=oracle.compose(A, B, oracle.ORDER_FORWARD))
+        c.close()
+
+
 # ---- linear search: A's arcs lead from a state to the next, B mostly chains ----
 
 def _frames(rng, T, C, p_gap=0.3, cuts=()):
