@@ -1427,24 +1427,21 @@ struct LevelLds {
   PushBuf push[NWAVES];
 };
 
-// Claims a move's target and puts it aside for the next frontier if this
-// move is the first to reach it.  No record of the target is loaded (the
-// next generation does, with its units spread over the lanes).
+// Claims a move's target: true if this move is the first to reach it.  No record
+// of the target is loaded (the next generation does, with its units spread
+// over the lanes).
 template <bool FWD>
-__device__ __forceinline__ void reach(const Problem &P, const NextGen &nx, const Target &t) {
+__device__ __forceinline__ bool reach(const Problem &P, const Target &t) {
   const uint32_t sb = search_bit(P, t.key);
   const uint32_t bit = 1u << (sb & 31u), w = sb >> 5;
   const uint32_t *other = FWD ? P.coacc : P.vis;
   uint32_t *mine = FWD ? P.vis : P.coacc;
   const bool restricted = FWD ? P.restrict_fwd != 0 : P.restrict_bwd != 0;
-  bool fresh;
   if (t.hot || restricted) {
     const uint32_t wo = restricted ? other[w] : bit, wm = mine[w];  // one round trip
-    fresh = (wo & bit) && !(wm & bit) && (atomicOr(mine + w, bit) & bit) == 0;
-  } else {
-    fresh = (atomicOr(mine + w, bit) & bit) == 0;
+    return (wo & bit) && !(wm & bit) && (atomicOr(mine + w, bit) & bit) == 0;
   }
-  buf_push(fresh, t.key, *nx.buf, nx.q);
+  return (atomicOr(mine + w, bit) & bit) == 0;
 }
 
 // Generation g of a level search (one kernel).  Its items are the unit slots
@@ -1516,7 +1513,7 @@ __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S
       B = load_rec(Dir<FWD>::viewB(P), key_qb(key, P.shiftB));
       units = Dir<FWD>::units(Dir<FWD>::make(key, P.shiftB, A, B));
     }
-    auto take = [&](const Target &t) { reach<FWD>(P, nx, t); };
+    auto take = [&](const Target &t) { buf_push(reach<FWD>(P, t), t.key, *nx.buf, nx.q); };
     if (hv) {  // a unit per lane (a slot past the key's units has none)
       UnitRange x = {};
       if (u0 < units) x = Dir<FWD>::range(P, Dir<FWD>::make(key, P.shiftB, A, B), u0);
@@ -1547,6 +1544,128 @@ __global__ __launch_bounds__(NT) void k_level2(Problem P, SearchArgs SF, SearchA
   const unsigned half = gridDim.x / 2;
   if (blockIdx.x < half) level_body<true>(P, SF, gf, blockIdx.x, half, L);
   else level_body<false>(P, SB, gb, blockIdx.x - half, half, L);
+}
+
+// Narrow levels: while a frontier has few keys, one workgroup per direction runs
+// level after level, the frontier in LDS and a barrier between levels (about 2
+// to 3 us; a launch of k_level2 takes 7).  It stops before generation note->gen:
+// after NARROW_LEVELS levels, or with a heavy key listed, more than
+// NARROW_UNITS units in a level or more keys than the list holds; what waits
+// (note->width) is then in that generation's frontier, as if each level had
+// been a launch.
+constexpr uint32_t NARROW_UNITS = 16384;
+constexpr int NARROW_LEVELS = 128, NARROW_NT = 1024, NARROW_WAVES = NARROW_NT / WAVE;
+struct NarrowLds {
+  uint32_t list[2][NARROW_KEYS];
+  SpreadLds spread[NARROW_WAVES];
+  uint32_t pre[SUBQ + 1];
+  uint32_t n[2];
+  uint32_t units, heavy, ovf;
+};
+
+template <bool FWD>
+__device__ __forceinline__ void narrow_body(const Problem &P, const SearchArgs &S, int g0,
+                                            NarrowLds &L) {
+  const uint32_t tid = threadIdx.x, lane = __lane_id(), wid = tid / WAVE;
+  const GenSlot first = S.G[g0 % 3];
+  load_front(S.Q, g0, L.pre);
+  if (tid == 0) {
+    L.ovf = S.sc->overflow;
+    L.units = L.heavy = L.n[1] = 0;
+  }
+  __syncthreads();
+  const uint32_t nq = L.pre[SUBQ];
+  const ull U = first.hpack >> 32;
+  if (L.ovf || U || nq == 0 || nq > NARROW_KEYS) {  // nothing for it here
+    if (tid == 0) {
+      S.note->gen = (uint32_t)g0;
+      S.note->width = U ? NARROW_KEYS + 1 : nq;
+    }
+    return;
+  }
+  for (uint32_t i = tid; i < nq; i += NARROW_NT) L.list[0][i] = front_key(S.Q, g0, L.pre, i);
+  if (tid == 0) L.n[0] = nq;
+  // no launch has anything left in the lists: all three generations' counters
+  // and slots start again
+  __syncthreads();
+  for (uint32_t i = tid; i < 3 * SUBQ; i += NARROW_NT) S.Q.cnt[(size_t)i * S.Q.stride] = 0;
+  if (tid < 3) {
+    S.G[tid].hpack = 0;
+    S.G[tid].hbase = first.hbase;
+  }
+  __threadfence();
+  __syncthreads();
+  int g = g0;
+  for (int cur = 0;; cur ^= 1, ++g) {
+    const uint32_t n = L.n[cur];  // the same for all threads (a barrier before)
+    const bool wide = n > NARROW_KEYS || L.heavy || (n && L.units > NARROW_UNITS);
+    const bool stop = n == 0 || wide || g - g0 == NARROW_LEVELS;
+    __syncthreads();
+    if (stop) {
+      // what waits goes to generation g's frontier (keys past the list's end
+      // are there already)
+      const NextFront q = next_front(S.Q, g - 1, wid, S.sc);
+      const uint32_t m = n < NARROW_KEYS ? n : NARROW_KEYS;
+      for (uint32_t i = wid * WAVE; i < m; i += NARROW_NT)
+        front_push(i + lane < m, i + lane < m ? L.list[cur][i + lane] : 0u, q);
+      if (tid == 0) {
+        S.note->gen = (uint32_t)g;
+        S.note->width = wide ? NARROW_KEYS + 1 : n;
+        *S.gens = (uint32_t)g;
+      }
+      return;
+    }
+    if (tid == 0) L.units = 0;
+    __syncthreads();
+    NextGen nx;
+    nx.slot = &S.G[(g + 1) % 3];
+    nx.hbase = first.hbase;
+    nx.q = next_front(S.Q, g, wid, S.sc);
+    nx.buf = nullptr;
+    uint32_t K = (n + NARROW_WAVES - 1) / NARROW_WAVES;
+    if (K > WAVE) K = WAVE;
+    for (uint32_t k0 = wid * K; k0 < n; k0 += NARROW_WAVES * K) {
+      const bool have = lane < K && k0 + lane < n;
+      uint32_t key = 0, units = 0;
+      Rec A = {}, B = {};
+      if (have) {
+        key = L.list[cur][k0 + lane];
+        A = load_rec(Dir<FWD>::viewA(P), key_qa(key, P.shiftB));
+        B = load_rec(Dir<FWD>::viewB(P), key_qb(key, P.shiftB));
+        units = Dir<FWD>::units(Dir<FWD>::make(key, P.shiftB, A, B));
+      }
+      if (units > LEVEL_UNITS) {
+        list_heavy(S, nx, key, units);
+        L.heavy = 1;
+        units = 0;
+      }
+      spread_units<FWD>(P, L.spread[wid], key, A, B, units, [&](const Target &t) {
+        const bool fresh = reach<FWD>(P, t);
+        const ull m = __ballot(fresh);
+        if (m == 0) return;
+        const int leader = __ffsll(m) - 1;
+        uint32_t base = 0;
+        if ((int)lane == leader) base = atomicAdd(&L.n[cur ^ 1], (uint32_t)__popcll(m));
+        base = __shfl(base, leader, WAVE);
+        const uint32_t pos = base + (uint32_t)__popcll(m & __lanemask_lt());
+        if (fresh && pos < NARROW_KEYS) L.list[cur ^ 1][pos] = t.key;
+        front_push(fresh && pos >= NARROW_KEYS, t.key, nx.q);
+      });
+      const uint32_t all = wave_sum(units);
+      if (lane == 0) atomicAdd(&L.units, all);
+    }
+    __syncthreads();  // the next level is listed
+    if (tid == 0) L.n[cur] = 0;
+    __syncthreads();
+  }
+}
+
+// Both directions, or (dirs: 1 forward, 2 backward) one.
+__global__ __launch_bounds__(NARROW_NT) void k_narrow(Problem P, SearchArgs SF, SearchArgs SB,
+                                                      int gf, int gb, int dirs) {
+  __shared__ NarrowLds L;
+  if ((dirs & 1) && blockIdx.x == 0) narrow_body<true>(P, SF, gf, L);
+  else narrow_body<false>(P, SB, gb, L);
 }
 
 // ---------------------------------------------------------------------------
@@ -3361,23 +3480,27 @@ hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, int32_t *
 }
 
 hipError_t launch_generation(const Problem &P, const SearchArgs &S, bool forward, int g,
-                             hipStream_t s) {
-  constexpr unsigned GRID = 1024;
+                             unsigned grid, hipStream_t s) {
   if (!P.chains) {
-    if (forward) k_level<true><<<GRID, NT, 0, s>>>(P, S, g);
-    else k_level<false><<<GRID, NT, 0, s>>>(P, S, g);
+    if (forward) k_level<true><<<grid, NT, 0, s>>>(P, S, g);
+    else k_level<false><<<grid, NT, 0, s>>>(P, S, g);
   } else {
-    if (forward) k_gen<true><<<GRID, NT, 0, s>>>(P, S, g);
-    else k_gen<false><<<GRID, NT, 0, s>>>(P, S, g);
+    if (forward) k_gen<true><<<grid, NT, 0, s>>>(P, S, g);
+    else k_gen<false><<<grid, NT, 0, s>>>(P, S, g);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_generation2(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
-                              int gb, hipStream_t s) {
-  constexpr unsigned GRID = 1024;
-  if (!P.chains) k_level2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
-  else k_gen2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
+                              int gb, unsigned grid, hipStream_t s) {
+  if (!P.chains) k_level2<<<2 * grid, NT, 0, s>>>(P, SF, SB, gf, gb);
+  else k_gen2<<<2 * grid, NT, 0, s>>>(P, SF, SB, gf, gb);
+  return hipGetLastError();
+}
+
+hipError_t launch_narrow(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
+                         int gb, int dirs, hipStream_t s) {
+  k_narrow<<<dirs == 3 ? 2 : 1, NARROW_NT, 0, s>>>(P, SF, SB, gf, gb, dirs);
   return hipGetLastError();
 }
 

@@ -185,11 +185,11 @@ struct GenSlot {
   unsigned long long hpack;
 };
 
-// What the last generation of a search that ran found: its work items, and
-// the levels that narrow generations went through beyond one each.
+// What the last generation of a search that ran found: its work items; after
+// narrow levels the items that wait, and the generation they wait for.
 struct SearchNote {
   unsigned long long width;
-  uint32_t extra_levels, pad;
+  uint32_t gen, pad;
 };
 
 // Device scalars read back by the host (one pinned mirror).
@@ -631,14 +631,20 @@ hipError_t launch_seed_forward(const Problem &P, const SearchArgs &S, int32_t *l
 hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, int32_t *la,
                                 uint32_t *na, int32_t *lb, uint32_t *nb,
                                 unsigned long long pairs, size_t nwords, hipStream_t s);
-// Generation g of the forward (or backward) search: one kernel.
+// Generation g of the forward (or backward) search: one kernel of `grid`
+// workgroups per direction (a multiple of 8).
 hipError_t launch_generation(const Problem &P, const SearchArgs &S, bool forward, int g,
-                             hipStream_t s);
+                             unsigned grid, hipStream_t s);
 // Generation gf of a forward search (SF) and generation gb of a backward
 // search (SB) running side by side in one kernel (half of the workgroups
 // each).
 hipError_t launch_generation2(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
-                              int gb, hipStream_t s);
+                              int gb, unsigned grid, hipStream_t s);
+// Narrow levels of a level search, many in one launch (dirs: 1 forward from
+// generation gf, 2 backward from gb, 3 both); see SearchNote.
+constexpr uint32_t NARROW_KEYS = 2048;
+hipError_t launch_narrow(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
+                         int gb, int dirs, hipStream_t s);
 // Small search: both directions in one launch, for at most SMALL_PAIRS pairs of
 // states whose search bitmaps have at most SMALL_SEARCH_BITS bits; writes the
 // whole bitmaps, gens, gens2 and naccessible, and overflow if it gave up.

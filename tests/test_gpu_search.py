@@ -135,6 +135,68 @@ def test_backward_seeds(order, p_accept, deep):
         c.close()
 
 
+def _deep(rng, parts, VA):
+    """A path of two-arc states through B with fans on the way: a part n > 0 is
+    n such states, -n a state with n arcs (on several labels) to n states that
+    meet again.  A: a few states that all have arcs of every label."""
+    n_sym, arcs, s = 4, [], 0
+    for n in parts:
+        if isinstance(n, tuple):
+            m, n = n
+            for i in range(m):
+                arcs.append((s, s + 1 + i, 1 + i % n_sym, 3, 0.1))
+                for j in range(n):
+                    t = s + 1 + m + i * n + j
+                    arcs += [(s + 1 + i, t, 1 + j % n_sym, 1, 0.1), (t, s + 1 + m * (n + 1), 1, 2, 0.1),
+                             (t, s + 1 + m * (n + 1), 2 + j % 3, 2, 0.3)]
+            s += 1 + m * (n + 1)
+        elif n > 0:
+            for _ in range(n):
+                arcs.append((s, s + 1, int(rng.integers(1, n_sym + 1)), 1, -0.1))
+                arcs.append((s, s + 2, int(rng.integers(1, n_sym + 1)), 2, -0.2))
+                s += 1
+        else:
+            n = -n
+            for i in range(n):
+                arcs.append((s, s + 3 + i, 1 + i % n_sym, 3, 0.1))
+                arcs.append((s + 3 + i, s + 3 + n, 1 + i % 3, 0, -0.3))
+                arcs.append((s + 3 + i, s + 3 + n, 0, 4, 0.2))
+            arcs += [(s + 1, s + 3, 1, 1, 0.0), (s + 1, s + 4, 2, 1, 0.0),
+                     (s + 2, s + 3, 3, 1, 0.0), (s + 2, s + 4, 2, 1, 0.0)]
+            s += 3 + n
+    B = synth.from_arcs(s + 3, arcs, start=[0], accept=[s, s + 1, s // 2])
+    aarcs = [(a, (a + c) % VA, c, c, 0.1 * c) for a in range(VA) for c in range(1, n_sym + 1)]
+    A = synth.from_arcs(VA, aarcs, start=[0], accept=range(VA))
+    return A, B
+
+
+@pytest.mark.parametrize("order", ORDERS)
+@pytest.mark.parametrize("VA,parts", [
+    (9, [1000]),                        # narrow all the way: more than 128 levels a launch
+    (16, [300, -200, 300]),             # a key of 200 units
+    (3, [300, (20, 150), 400, (4, 200), 300]),  # levels past a narrow list's end (2,048)
+    (3, [1500, -254, 700, -255, 700, -256, 40, -257, 300, -600, 300]),  # heavy keys or just not
+    (16, [300, -30, 20, -120, 60, -119, 100, -25, 25])])
+def test_narrow_levels(order, VA, parts):
+    """Deep products with few keys a level: many levels in one launch, handed
+    back to the grid where a level has many keys, many units or a heavy key;
+    and with work lists that overflow."""
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(len(parts) + VA)
+    A, B = _deep(rng, parts, VA)
+    assert VA * B["num_states"] > 8192  # no small search
+    ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
+    assert ref["num_states"] > 2000
+    c = _composer(order)
+    for k in range(2):
+        check_pair(c, A, B, f"narrow {VA} {parts} {order} call {k}", ref=ref)
+    assert c.stats()["fwd_levels"] > 64
+    for cap in (64, 1):
+        c.set_option(gpu.FST_OPT_LIST_CAPACITY, cap)
+        check_pair(c, A, B, f"narrow {VA} {parts} {order} lists from {cap}", ref=ref)
+    c.close()
+
+
 # ---- linear search: A's arcs lead from a state to the next, B mostly chains ----
 
 def _frames(rng, T, C, p_gap=0.3, cuts=()):
