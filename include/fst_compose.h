@@ -217,9 +217,12 @@ FST_API int fst_compose_phase_times(const fst_ctx *ctx, float *ms, int n);
 
 /* Kernels timed with FST_OPT_TIMING on: every launch of the forward search
  * kernel; every launch of the backward search kernel; the arc-count kernels
- * (states with few moves, then states with many: 2 launches, also if C is
- * empty); the fill kernels (every state's offset and flags with the arcs of
- * light states, then heavy states' arcs if any). */
+ * (C's keys listed, states with few moves, states with many: 3 launches, 2
+ * where the workspace has no room for the keys, the more where the call
+ * queued a count for too few states and counted again, none for an empty C
+ * whose number of states was waited for); the fill kernels (every state's
+ * offset and flags with the arcs of light states, then heavy states' arcs if
+ * any). */
 enum fst_kernel {
   FST_KERNEL_SEARCH_FORWARD = 0,
   FST_KERNEL_SEARCH_BACKWARD = 1,

@@ -371,6 +371,29 @@ def test_compaction_walks_the_side_with_fewer_arcs(repeats_in_a, degree):
     c.close()
 
 
+def test_count_launches():
+    """What FST_OPT_TIMING reports of the count: a call that waits for the
+    number of states, one that does not, one that has to count again, and
+    empty results after each other."""
+    import torch
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(11)
+    small = [synth.random_fst(rng, 150, 4, 5, 0.1, 0.3, start=range(9)) for _ in range(2)]
+    large = [synth.random_fst(rng, 700, 5, 6, 0.1, 0.3, start=range(9)) for _ in range(2)]
+    none = [synth.random_fst(rng, 200, 4, 5, 0.0, 0.0, start=range(9)) for _ in range(2)]
+    none[0]["accept"][:] = none[1]["accept"][:] = 0
+    c = _composer("CONCURRENT")
+    c.set_option(gpu.FST_OPT_TIMING, 1)
+    for pair, launches in ((small, 3), (small, 3), (large, 6), (large, 3), (none, 3), (none, 0),
+                           (none, 0), (small, 3), (small, 3)):
+        got, ref = check_pair(c, *pair, f"count of {pair[0]['num_states']}")
+        torch.cuda.synchronize()
+        ms, n = c.kernel_times()["count"]
+        assert n == launches and (ms > 0) == (n > 0), (n, launches, ms)
+    assert ref["num_states"] > 0
+    c.close()
+
+
 def test_compaction_without_room():
     """The least workspace cap that a call fits (to 64 KB): compaction by
     chunks; somewhat larger caps reach the list of keys."""
