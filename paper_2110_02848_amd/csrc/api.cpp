@@ -182,6 +182,40 @@ void release(DevBuf &b) {
   b.cap = 0;
 }
 
+// Frees buffers (after the work that uses them); whether any was held.
+int release_all(fst_ctx *c, std::initializer_list<DevBuf *> bufs, bool *held) {
+  *held = false;
+  for (DevBuf *b : bufs) *held = *held || b->p;
+  if (!*held) return FST_OK;
+  if (hipDeviceSynchronize() != hipSuccess) return FST_ERR_HIP;
+  for (DevBuf *b : bufs) {
+    c->ws_total -= b->cap;
+    release(*b);
+  }
+  return FST_OK;
+}
+
+// What only a two-input search needs: no fill reads it.
+int release_search(fst_ctx *c, bool *held) {
+  return release_all(
+      c, {&c->k0, &c->k1, &c->v0, &c->v1, &c->sort_tmp, &c->lists, &c->vis, &c->coacc,
+          &c->fcnt, &c->lin, &c->heavy, &c->hoff, &c->heavy2, &c->hoff2, &c->aInOff,
+          &c->aInPerm, &c->aInArc, &c->aInRec, &c->aInLut, &c->bInOff, &c->bInPerm, &c->bInArc,
+          &c->bInRec, &c->bInLut, &c->bOutChain, &c->bInChain}, held);
+}
+
+// A call that finds no room (f() returns FST_ERR_NOMEM) runs once more without
+// what earlier calls have left in the workspace, so that their sizes do not
+// decide whether it fits.
+template <class F>
+int with_room(fst_ctx *c, F &&f) {
+  const int rc = f();
+  if (rc != FST_ERR_NOMEM) return rc;
+  bool held = false;
+  FST_TRY(release_search(c, &held));
+  return held ? f() : rc;
+}
+
 template <typename T>
 T *as(DevBuf &b) {
   return reinterpret_cast<T *>(b.p);
@@ -939,8 +973,10 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   const unsigned long long cap_full = capll < nkeys ? capll : nkeys;  // <= nkeys < 2^32
   unsigned long long cap_try = c->list_hint ? c->list_hint : c->list_start;
   // Where the workspace has no room for a linear search the keys are followed
-  // one by one, then lists a quarter as long are tried.
-  bool try_linear = true, grew = false, linear = false;
+  // one by one, then lists a quarter as long are tried; where those overflow,
+  // sizes between the two.
+  unsigned long long too_small = 0, too_large = 0;
+  bool try_linear = true, linear = false;
   // A small search's words are all written by it, and the host need not wait
   // for it to queue what follows.
   const bool small = small_search(c, dA, dB, nsbits);
@@ -1195,22 +1231,25 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     };
     const int rc = searches();
     if (rc == FST_ERR_TOO_LARGE && c->h_sc->overflow && (unsigned long long)cap < cap_full) {
+      too_small = cap;
       cap_try = 4ull * cap;
-      grew = true;
+      if (too_large && cap_try >= too_large) cap_try = (cap + too_large) / 2;
+      if (too_large && too_large - cap <= cap / 4) return FST_ERR_NOMEM;
       // the search scalars start again from zero (validation's stay)
       HIP_TRY(hipMemsetAsync(&d_sc->heavy, 0,
                              sizeof(Scalars) - offsetof(Scalars, heavy), s));
       continue;
     }
-    if (rc == FST_ERR_NOMEM && (linear || (!grew && cap > 1024))) {
-      if (!linear) cap_try = cap / 4;
-      try_linear = false;
-      HIP_TRY(hipDeviceSynchronize());
-      for (DevBuf *b : {&c->lin, &c->fq, &c->bq, &c->heavy, &c->hoff,
-                        &c->heavy2, &c->hoff2}) {
-        c->ws_total -= b->cap;
-        release(*b);
+    if (rc == FST_ERR_NOMEM) {
+      if (!linear) {
+        too_large = cap;
+        if (too_small ? cap - too_small <= too_small / 4 : cap <= 1024) return rc;
+        cap_try = too_small ? (too_small + cap) / 2 : cap / 4;
       }
+      try_linear = false;
+      bool held;
+      FST_TRY(release_all(c, {&c->lin, &c->fq, &c->bq, &c->heavy, &c->hoff, &c->heavy2, &c->hoff2},
+                          &held));
       continue;
     }
     FST_TRY(rc);
@@ -1267,8 +1306,12 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     phase_end(c, PH_COUNT, s);
     return FST_OK;
   };
-  const unsigned long long cap0 = c->state_hint ? room() : 0;
-  if (cap0) FST_TRY(count((uint32_t)cap0));
+  unsigned long long cap0 = c->state_hint ? room() : 0;
+  if (cap0) {
+    const int rc = count((uint32_t)cap0);
+    if (rc == FST_ERR_NOMEM) cap0 = 0;  // the number may be smaller than the room
+    else FST_TRY(rc);
+  }
   FST_TRY(readback(c, s));
   if (cap0) FST_TRY(add_time(c, FST_KERNEL_COUNT, 3));
   if (small) {
@@ -1291,15 +1334,25 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     P.keys = by_state ? as<uint32_t>(c->keys) : nullptr;
     phase_end(c, PH_COUNT, s);
   } else if (!cap0 || nst > cap0) {
-    FST_TRY(ensure(c, c->fq, ((size_t)nstates + 1) * 4));
-    FST_TRY(ensure(c, c->bq, ((size_t)nstates + 1) * 8));
-    FST_TRY(ensure(c, c->cnt, (size_t)nstates + 1));
-    const int rc = ensure(c, c->keys, ((size_t)nstates + 1) * 4);
+    // (the searches are over: their room is free as well)
+    FST_TRY(with_room(c, [&]() -> int {
+      FST_TRY(ensure(c, c->fq, ((size_t)nstates + 1) * 4));
+      FST_TRY(ensure(c, c->bq, ((size_t)nstates + 1) * 8));
+      return ensure(c, c->cnt, (size_t)nstates + 1);
+    }));
+    int rc = with_room(c, [&]() { return ensure(c, c->keys, ((size_t)nstates + 1) * 4); });
     if (rc != FST_OK && rc != FST_ERR_NOMEM) return rc;
     by_state = rc == FST_OK;
     HIP_TRY(hipMemsetAsync(&d_sc->heavy, 0, sizeof(uint32_t), s));
     HIP_TRY(hipMemsetAsync(&d_sc->total, 0, sizeof(unsigned long long), s));
-    FST_TRY(count(nstates));
+    rc = with_room(c, [&]() { return count(nstates); });
+    if (rc == FST_ERR_NOMEM && by_state) {  // the list's room may do for the chunks
+      bool held;
+      FST_TRY(release_all(c, {&c->keys}, &held));
+      by_state = false;
+      rc = count(nstates);
+    }
+    FST_TRY(rc);
     FST_TRY(readback(c, s));
     FST_TRY(add_time(c, FST_KERNEL_COUNT, by_state ? 3 : 2));
   }
@@ -1322,6 +1375,23 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   *V_C = nstates;
   *E_C = (int64_t)narcs;
   return FST_OK;
+}
+
+// run_impl, once more without what earlier calls have left in the buffers of a
+// composition where it finds no room.
+int run_room(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, int64_t *V_C,
+             int64_t *E_C) {
+  const int rc = run_impl(c, A, B, s, V_C, E_C);
+  if (rc != FST_ERR_NOMEM) return rc;
+  bool searched, held;
+  FST_TRY(release_search(c, &searched));
+  FST_TRY(release_all(
+      c, {&c->scal, &c->keys, &c->scan_tmp, &c->aOutPerm, &c->aOutArc, &c->aOutRec, &c->aOutLut,
+          &c->bOutPerm, &c->bOutArc, &c->bOutRec, &c->bOutLut, &c->aOutLab, &c->aOutW,
+          &c->bOutLab, &c->bOutW, &c->trim, &c->wbase, &c->fq, &c->bq, &c->cnt, &c->btot},
+      &held));
+  c->list_hint = 0;
+  return run_impl(c, A, B, s, V_C, E_C);
 }
 
 // ---------------------------------------------------------------------------
@@ -1705,8 +1775,8 @@ int run_items(fst_ctx *c, const fst_graph *A, int32_t i0, int32_t i1, const fst_
               hipStream_t s, int64_t *V_C, int64_t *E_C, long long *st, long long *ar) {
   const int32_t n = i1 - i0;
   fst_graph U;
-  FST_TRY(build_union(c, A + i0, n, s, &U));
-  FST_TRY(run_impl(c, &U, B, s, V_C, E_C));
+  FST_TRY(with_room(c, [&]() { return build_union(c, A + i0, n, s, &U); }));
+  FST_TRY(run_room(c, &U, B, s, V_C, E_C));
   if (c->nstates == 0) {
     for (int32_t i = 0; i <= n; ++i) st[i] = ar[i] = 0;
     return FST_OK;
@@ -2063,7 +2133,7 @@ int fst_compose_run(fst_ctx *c, const fst_graph *A, const fst_graph *B, void *st
   c->parts.clear();
   *num_states = 0;
   *num_arcs = 0;
-  int rc = run_impl(c, A, B, reinterpret_cast<hipStream_t>(stream), num_states, num_arcs);
+  int rc = run_room(c, A, B, reinterpret_cast<hipStream_t>(stream), num_states, num_arcs);
   if (rc != FST_OK) {
     c->ready = false;
     *num_states = 0;
@@ -2176,8 +2246,9 @@ int fst_compose3_run(fst_ctx *c, const fst_graph *A, const fst_graph *B, const f
   c->have_times3 = false;
   *num_states = 0;
   *num_arcs = 0;
-  int rc = compose3_impl(c, A, B, D, reinterpret_cast<hipStream_t>(stream), num_states,
-                         num_arcs);
+  int rc = with_room(c, [&]() {
+    return compose3_impl(c, A, B, D, reinterpret_cast<hipStream_t>(stream), num_states, num_arcs);
+  });
   if (rc != FST_OK) {
     c->c3.ready = false;
     *num_states = 0;
@@ -2288,7 +2359,9 @@ int fst_score(fst_ctx *c, const fst_graph *G, double *alpha, double *beta, doubl
   DeviceGuard g(c->device);
   if (!g.ok) return FST_ERR_HIP;
   c->have_score_times = false;
-  int rc = score_impl(c, G, alpha, beta, total, reinterpret_cast<hipStream_t>(stream));
+  int rc = with_room(c, [&]() {
+    return score_impl(c, G, alpha, beta, total, reinterpret_cast<hipStream_t>(stream));
+  });
   if (rc != FST_OK) (void)hipGetLastError();
   return rc;
 }
@@ -2300,8 +2373,10 @@ int fst_score_cyclic(fst_ctx *c, const fst_graph *G, double *alpha, double *beta
   DeviceGuard g(c->device);
   if (!g.ok) return FST_ERR_HIP;
   c->have_score_times = false;
-  int rc = score_cyclic_impl(c, G, alpha, beta, total, max_sweeps, tol, sweeps,
+  int rc = with_room(c, [&]() {
+    return score_cyclic_impl(c, G, alpha, beta, total, max_sweeps, tol, sweeps,
                              reinterpret_cast<hipStream_t>(stream));
+  });
   if (rc != FST_OK && rc != FST_ERR_NOT_CONVERGED) (void)hipGetLastError();
   return rc;
 }
@@ -2315,7 +2390,7 @@ int fst_score_posterior(fst_ctx *c, const fst_graph *G, const double *alpha, con
   if (!g.ok) return FST_ERR_HIP;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const DevGraph d = dev_graph(G);
-  FST_TRY(ensure(c, c->s_sc, sizeof(ScoreScalars)));
+  FST_TRY(with_room(c, [&]() { return ensure(c, c->s_sc, sizeof(ScoreScalars)); }));
   FST_TRY(score_validate(c, d, s));
   if (launch_posterior(plain_score_graph(d), alpha, beta, total, scale, grad, s) != hipSuccess) {
     (void)hipGetLastError();
@@ -2331,8 +2406,10 @@ int fst_grad_scatter(fst_ctx *c, int64_t n, const float *grad, const int32_t *id
   DeviceGuard g(c->device);
   if (!g.ok) return FST_ERR_HIP;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  FST_TRY(ensure(c, c->s_sc, sizeof(ScoreScalars)));
-  FST_TRY(ensure(c, c->s_acc, (size_t)m * 4 * sizeof(unsigned long long)));
+  FST_TRY(with_room(c, [&]() { return ensure(c, c->s_sc, sizeof(ScoreScalars)); }));
+  FST_TRY(with_room(c, [&]() {
+    return ensure(c, c->s_acc, (size_t)m * 4 * sizeof(unsigned long long));
+  }));
   ScoreScalars *dsc = as<ScoreScalars>(c->s_sc);
   HIP_TRY(hipMemsetAsync(dsc, 0, SCORE_SCALARS, s));
   if (m > 0) HIP_TRY(hipMemsetAsync(c->s_acc.p, 0, (size_t)m * 4 * sizeof(unsigned long long), s));
@@ -2396,8 +2473,10 @@ int fst_segment_logsum(fst_ctx *c, const double *val, const uint8_t *flag, int32
   DeviceGuard g(c->device);
   if (!g.ok) return FST_ERR_HIP;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  FST_TRY(ensure(c, c->seg, ((size_t)n + 1) * sizeof(long long) +
-                                3 * (size_t)n * sizeof(unsigned long long)));
+  FST_TRY(with_room(c, [&]() {
+    return ensure(c, c->seg, ((size_t)n + 1) * sizeof(long long) +
+                                 3 * (size_t)n * sizeof(unsigned long long));
+  }));
   long long *db = as<long long>(c->seg);
   unsigned long long *z = reinterpret_cast<unsigned long long *>(db + n + 1);
   HIP_TRY(hipMemcpyAsync(db, bounds, ((size_t)n + 1) * sizeof(long long), hipMemcpyHostToDevice,

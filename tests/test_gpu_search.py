@@ -427,6 +427,83 @@ def test_compaction_without_room():
         assert fits(hi + more * (1 << 16)), more
 
 
+# ---- workspace caps ----
+
+def _least_cap(order, A, B, ref):
+    """The least workspace cap (to 64 KB) that a fresh context composes in."""
+    from paper_2110_02848_amd import gpu
+
+    def fits(cap):
+        c = _composer(order)
+        c.set_option(gpu.FST_OPT_MAX_WORKSPACE, cap)
+        try:
+            check_pair(c, A, B, f"cap {cap}", ref=ref)
+            return True
+        except gpu.FstError as e:
+            assert e.code == gpu.FST_ERR_NOMEM
+            return False
+        finally:
+            c.close()
+
+    lo, hi = 1 << 16, 1 << 27
+    while hi - lo > 1 << 16:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if fits(mid) else (mid, hi)
+    return hi
+
+
+@pytest.mark.parametrize("order", ORDERS)
+@pytest.mark.parametrize("kind", ("level", "linear", "chain"))
+def test_workspace_of_earlier_calls(order, kind):
+    """A call fits the cap that it fits in a fresh context also after larger
+    calls, of every form of search, that left their buffers behind, and after
+    calls that the cap refuses."""
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(21)
+    words = _words(rng, rng.integers(1, 9, size=120), 4)
+    A, B = {"level": lambda: [synth.random_fst(rng, 200, 4, 5, 0.1, 0.3, start=range(9))
+                              for _ in range(2)],
+            "linear": lambda: (_frames(rng, 250, 4), words),
+            "chain": lambda: (synth.random_fst(rng, 150, 5, 4, 0.1, 0.2, start=range(5)), words),
+            }[kind]()
+    ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
+    # (half as much again: how many keys a chain search hands on varies by run)
+    cap = _least_cap(order, A, B, ref) * 3 // 2
+    large = [[synth.random_fst(rng, 1500, 4, 6, 0.1, 0.3, start=range(9)) for _ in range(2)],
+             [_frames(rng, 900, 4), _words(rng, rng.integers(1, 9, size=400), 4)]]
+    refs = [oracle.compose(X, Y, oracle.ORDER_FORWARD) for X, Y in large]
+    for (X, Y), r in zip(large, refs):
+        c = _composer(order)
+        check_pair(c, X, Y, f"large before {kind} {order}", ref=r)
+        c.set_option(gpu.FST_OPT_MAX_WORKSPACE, cap)
+        check_pair(c, A, B, f"{kind} {order} at {cap} after it", ref=ref)
+        c.close()
+        c = _composer(order)
+        c.set_option(gpu.FST_OPT_MAX_WORKSPACE, cap)
+        for k in range(2):
+            with pytest.raises(gpu.FstError) as e:
+                c.compose(gpu.to_device(X), gpu.to_device(Y))
+            assert e.value.code == gpu.FST_ERR_NOMEM
+            check_pair(c, A, B, f"{kind} {order} at {cap} after a refused call", ref=ref)
+        c.close()
+
+
+@pytest.mark.parametrize("order", ORDERS)
+def test_lists_between_two_sizes(order):
+    """A cap whose room for the work lists lies between a size that overflows
+    and the next one that does not fit: every cap above the least one does."""
+    from paper_2110_02848_amd import gpu
+    rng = np.random.default_rng(5)
+    A, B = (synth.random_fst(rng, 700, 4, 4, 0.1, 0.3, start=range(700)) for _ in range(2))
+    ref = oracle.compose(A, B, oracle.ORDER_FORWARD)
+    least = _least_cap(order, A, B, ref)
+    for cap in [least + k * (least // 16) for k in range(16)]:
+        c = _composer(order)
+        c.set_option(gpu.FST_OPT_MAX_WORKSPACE, cap)
+        check_pair(c, A, B, f"{order} lists in {cap}", ref=ref)
+        c.close()
+
+
 # ---- small search ----
 
 def _search_launches(c):
