@@ -95,6 +95,7 @@ struct fst_ctx {
   bool have_times3 = false;
   Scalars *h_sc = nullptr;
   ScoreScalars *h_ssc = nullptr;
+  SweepScalars *h_sw = nullptr;
   ScoreBufs score_f, score_b;  // forward / backward recursion
   bool have_score_times = false;
   hipEvent_t ev[NEV] = {};
@@ -367,11 +368,8 @@ int search(fst_ctx *c, const SearchArgs &S, bool forward, int64_t *levels, hipSt
 // scores
 // ---------------------------------------------------------------------------
 
-// The scalars without the sweeps' notes at their end.
-constexpr size_t SCORE_SCALARS = offsetof(ScoreScalars, part);
-
 int score_readback(fst_ctx *c, hipStream_t s) {
-  HIP_TRY(hipMemcpyAsync(c->h_ssc, c->s_sc.p, SCORE_SCALARS, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(c->h_ssc, c->s_sc.p, sizeof(ScoreScalars), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   return FST_OK;
 }
@@ -379,7 +377,7 @@ int score_readback(fst_ctx *c, hipStream_t s) {
 // Validates G (one readback): FST_ERR_INVALID_GRAPH on a violation.
 int score_validate(fst_ctx *c, const DevGraph &d, hipStream_t s) {
   ScoreScalars *dsc = as<ScoreScalars>(c->s_sc);
-  HIP_TRY(hipMemsetAsync(dsc, 0, SCORE_SCALARS, s));
+  HIP_TRY(hipMemsetAsync(dsc, 0, sizeof(ScoreScalars), s));
   // scores read no label: the structure alone is checked (or nothing, for
   // a caller that vouches for it)
   if (!c->validate) return FST_OK;
@@ -427,7 +425,7 @@ int score_generations(fst_ctx *c, const ScoreArgs *F, const ScoreArgs *B, ScoreB
   ScoreBufs *bufs[2] = {bf, bb};
   for (int i = 0; i < 2; ++i) {
     if (!dirs[i]) continue;
-    HIP_TRY(hipMemsetAsync(dirs[i]->sc, 0, SCORE_SCALARS, s));
+    HIP_TRY(hipMemsetAsync(dirs[i]->sc, 0, sizeof(ScoreScalars), s));
     HIP_TRY(launch_score_seed(*dirs[i], i == 0, s));
   }
   const KernelTimer t = timer(c, FST_KERNEL_SCORE_GEN);
@@ -441,7 +439,7 @@ int score_generations(fst_ctx *c, const ScoreArgs *F, const ScoreArgs *B, ScoreB
     t.end(s);
     for (int i = 0; i < 2; ++i)
       if (dirs[i])
-        HIP_TRY(hipMemcpyAsync(bufs[i]->host, dirs[i]->sc, SCORE_SCALARS,
+        HIP_TRY(hipMemcpyAsync(bufs[i]->host, dirs[i]->sc, sizeof(ScoreScalars),
                                hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     FST_TRY(add_time(c, FST_KERNEL_SCORE_GEN, batch));
@@ -587,23 +585,30 @@ int score_cyclic_impl(fst_ctx *c, const fst_graph *G, double *alpha, double *bet
   ScoreGraph SG = plain_score_graph(d);
   FST_TRY(ensure(c, c->s_ioff, ((size_t)V + 1) * 4));
   FST_TRY(ensure(c, c->s_iarc, (size_t)d.E * 8));
-  FST_TRY(ensure(c, c->s_mpos, (size_t)d.E * 4));  // the arcs' ranks
   FST_TRY(ensure(c, c->scan_tmp, scan_temp_bytes((size_t)V + 1)));
+  FST_TRY(ensure(c, c->s_chg, sizeof(SweepScalars) + 4 * (((size_t)V + 63) / 64) * 8));
+  // the values of both directions, two buffers each; before them, the arcs'
+  // ranks in the same room, or a cursor per state where that is too small
+  const size_t values = (size_t)V * 4 * sizeof(double), ranks = (size_t)d.E * 4;
+  int rc = ensure(c, c->s_sweep, values > ranks ? values : ranks);
+  const bool ranked = rc == FST_OK;
+  if (rc == FST_ERR_NOMEM && ranks > values) rc = ensure(c, c->s_sweep, values);
+  FST_TRY(rc);
   SG.ioff = as<int32_t>(c->s_ioff);
   SG.iarc = as<int2>(c->s_iarc);
-  HIP_TRY(launch_in_csr(SG, as<int32_t>(c->s_ioff), as<int2>(c->s_iarc), as<int32_t>(c->s_mpos),
+  HIP_TRY(launch_in_csr(SG, as<int32_t>(c->s_ioff), as<int2>(c->s_iarc),
+                        ranked ? as<int32_t>(c->s_sweep) : nullptr, as<int32_t>(c->s_sweep),
                         c->scan_tmp.p, &dsc->mtotal, s));
-  FST_TRY(ensure(c, c->s_sweep, (size_t)V * 4 * sizeof(double)));
   double *a[2] = {as<double>(c->s_sweep), as<double>(c->s_sweep) + V};
   double *b[2] = {a[1] + V, a[1] + 2 * (size_t)V};
   if (fwd) HIP_TRY(launch_fill_f64(a[0], V, -INFINITY, s));
   if (bwd) HIP_TRY(launch_fill_f64(b[0], V, -INFINITY, s));
   tp.end(s);
   const KernelTimer t = timer(c, FST_KERNEL_SCORE_GEN);
-  FST_TRY(ensure(c, c->s_chg, 4 * (((size_t)V + 63) / 64) * 8));
-  const SweepNote note = {dsc->part, as<unsigned long long>(c->s_chg), &dsc->sweep_done, tol};
-  const size_t off = offsetof(ScoreScalars, part);
-  HIP_TRY(hipMemsetAsync(dsc->part, 0, sizeof(ScoreScalars) - off, s));
+  SweepScalars *dsw = as<SweepScalars>(c->s_chg);
+  const SweepNote note = {dsw->part, reinterpret_cast<unsigned long long *>(dsw + 1), &dsw->done,
+                          tol};
+  HIP_TRY(hipMemsetAsync(dsw, 0, sizeof(SweepScalars), s));
   int k = 0, settled = 0;
   while (!settled && k < max_sweeps) {
     const int batch = k / 4 < 16 ? 16 : (k / 4 > SWEEP_BATCH ? SWEEP_BATCH : k / 4);
@@ -615,16 +620,15 @@ int score_cyclic_impl(fst_ctx *c, const fst_graph *G, double *alpha, double *bet
                            s));
     }
     t.end(s);
-    HIP_TRY(hipMemcpyAsync(c->h_ssc->part, dsc->part, sizeof(ScoreScalars) - off,
-                           hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(c->h_sw, dsw, sizeof(SweepScalars), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     FST_TRY(add_time(c, FST_KERNEL_SCORE_GEN, n));
-    settled = (int)c->h_ssc->sweep_done;
+    settled = (int)c->h_sw->done;
     if (!settled) {  // no sweep has looked at the last one's rise yet
       unsigned long long key = 0;
       for (unsigned i = 0; i < SWEEP_PARTS; ++i) {
         const unsigned long long p =
-            c->h_ssc->part[((size_t)((k - 1) % 3) * 3 * SWEEP_PARTS + i) * SWEEP_STRIDE];
+            c->h_sw->part[((size_t)((k - 1) % 3) * 3 * SWEEP_PARTS + i) * SWEEP_STRIDE];
         key = p > key ? p : key;
       }
       // the order key of a rise >= +0.0 is its bit pattern with the top bit set
@@ -2002,6 +2006,10 @@ int fst_ctx_create(int device, fst_ctx **ctx) {
     return FST_ERR_NOMEM;
   }
   memset(c->h_ssc, 0, sizeof(ScoreScalars));
+  if (hipHostMalloc(reinterpret_cast<void **>(&c->h_sw), sizeof(SweepScalars), 0) != hipSuccess) {
+    fst_ctx_destroy(c);
+    return FST_ERR_NOMEM;
+  }
   if (hipHostMalloc(reinterpret_cast<void **>(&c->h_s3), sizeof(Scal3), 0) != hipSuccess) {
     fst_ctx_destroy(c);
     return FST_ERR_NOMEM;
@@ -2078,6 +2086,7 @@ void fst_ctx_destroy(fst_ctx *c) {
     if (c->kev[i]) (void)hipEventDestroy(c->kev[i]);
   if (c->h_sc) (void)hipHostFree(c->h_sc);
   if (c->h_ssc) (void)hipHostFree(c->h_ssc);
+  if (c->h_sw) (void)hipHostFree(c->h_sw);
   if (c->h_s3) (void)hipHostFree(c->h_s3);
   delete c;
 }
@@ -2411,7 +2420,7 @@ int fst_grad_scatter(fst_ctx *c, int64_t n, const float *grad, const int32_t *id
     return ensure(c, c->s_acc, (size_t)m * 4 * sizeof(unsigned long long));
   }));
   ScoreScalars *dsc = as<ScoreScalars>(c->s_sc);
-  HIP_TRY(hipMemsetAsync(dsc, 0, SCORE_SCALARS, s));
+  HIP_TRY(hipMemsetAsync(dsc, 0, sizeof(ScoreScalars), s));
   if (m > 0) HIP_TRY(hipMemsetAsync(c->s_acc.p, 0, (size_t)m * 4 * sizeof(unsigned long long), s));
   // grouping the terms by target range needs 8 bytes per term of workspace;
   // without it (workspace cap) every term goes to the plain scatter

@@ -365,6 +365,10 @@ struct SweepNote {
   uint32_t *done;
   double tol;
 };
+struct SweepScalars {  // read back after every batch
+  unsigned long long part[9 * SWEEP_PARTS * SWEEP_STRIDE];
+  uint32_t done, pad;
+};
 
 constexpr unsigned FIN_PARTS = 32, FIN_STRIDE = 16;
 // Device scalars of a score computation, read back by the host.
@@ -379,8 +383,6 @@ struct ScoreScalars {
   unsigned long long zmax, zlo, zhi;  // total: order key of the maximum, 128-bit sum
   uint32_t absmax, pad;         // scatter: bits of the largest |gradient|
   GenSlot G[3];
-  unsigned long long part[9 * SWEEP_PARTS * SWEEP_STRIDE];  // sweeps: see SweepNote
-  uint32_t sweep_done, pad1;
 };
 
 // One direction of the score recursion (forward: alpha from in-arcs;
@@ -778,9 +780,11 @@ hipError_t launch_sweep(const ScoreGraph &G, const double *xa, double *ya, const
 hipError_t launch_fill_f64(double *p, long long n, double x, hipStream_t s);
 // The in-arc CSR of G for the sweeps (counting by target, a scan, then each
 // arc placed at its rank): ioff (V + 1 words), iarc (E), rank (E words of
-// scratch); scan_temp of scan_temp_bytes(V) bytes.
+// scratch, or null: arcs are placed at cursors cur, V words of scratch);
+// scan_temp of scan_temp_bytes(V) bytes.
 hipError_t launch_in_csr(const ScoreGraph &G, int32_t *ioff, int2 *iarc, int32_t *rank,
-                         void *scan_temp, unsigned long long *total_dev, hipStream_t s);
+                         int32_t *cur, void *scan_temp, unsigned long long *total_dev,
+                         hipStream_t s);
 // *total = log-add of val[v] over the states with flag[v] (sc->zmax, zlo,
 // zhi zeroed).
 hipError_t launch_score_total(const double *val, const uint8_t *flag, int32_t V,

@@ -1032,14 +1032,15 @@ __global__ __launch_bounds__(NT) void k_in_count(ScoreGraph G, int32_t *cnt, int
 #pragma unroll
     for (int k = 0; k < ST_ITEMS; ++k) {
       const long long e = e0 + (long long)k * NT;
-      if (e < G.E) rank[e] = d[k];
+      if (e < G.E && rank) rank[e] = d[k];
     }
   }
 }
 
-// (Source and weight go side by side, one scattered store per arc.)
+// (Source and weight go side by side, one scattered store per arc.  Without
+// room for the ranks the arcs take turns at their target's cursor.)
 __global__ __launch_bounds__(NT) void k_in_place(ScoreGraph G, const int32_t *ioff,
-                                                 const int32_t *rank, int2 *iarc) {
+                                                 const int32_t *rank, int32_t *cur, int2 *iarc) {
   const long long stride = (long long)gridDim.x * NT * ST_ITEMS;
   for (long long e0 = (long long)blockIdx.x * NT * ST_ITEMS + threadIdx.x; e0 < G.E;
        e0 += stride) {
@@ -1050,7 +1051,8 @@ __global__ __launch_bounds__(NT) void k_in_place(ScoreGraph G, const int32_t *io
       const long long e = e0 + (long long)k * NT;
       p[k] = -1;
       if (e < G.E) {
-        p[k] = rank[e] + ioff[G.dst[e]];
+        const int32_t d = G.dst[e];
+        p[k] = ioff[d] + (rank ? rank[e] : atomicAdd(cur + d, 1));
         a[k] = make_int2(G.src[e], __float_as_int(G.w[e]));
       }
     }
@@ -1750,9 +1752,11 @@ hipError_t launch_sweep(const ScoreGraph &G, const double *xa, double *ya, const
 }
 
 hipError_t launch_in_csr(const ScoreGraph &G, int32_t *ioff, int2 *iarc, int32_t *rank,
-                         void *scan_temp, unsigned long long *total_dev, hipStream_t s) {
+                         int32_t *cur, void *scan_temp, unsigned long long *total_dev,
+                         hipStream_t s) {
   hipError_t e = hipMemsetAsync(ioff, 0, ((size_t)G.V + 1) * 4, s);
   if (e != hipSuccess) return e;
+  if (!rank && (e = hipMemsetAsync(cur, 0, (size_t)G.V * 4, s)) != hipSuccess) return e;
   const unsigned grid = grid_for((G.E + ST_ITEMS - 1) / ST_ITEMS);
   if (G.E) {
     k_in_count<<<grid, NT, 0, s>>>(G, ioff, rank);
@@ -1762,7 +1766,7 @@ hipError_t launch_in_csr(const ScoreGraph &G, int32_t *ioff, int2 *iarc, int32_t
   e = scan_u32(reinterpret_cast<const uint32_t *>(ioff), reinterpret_cast<uint32_t *>(ioff),
                (size_t)G.V, true, total_dev, scan_temp, s);
   if (e != hipSuccess || G.E == 0) return e;
-  k_in_place<<<grid, NT, 0, s>>>(G, ioff, rank, iarc);
+  k_in_place<<<grid, NT, 0, s>>>(G, ioff, rank, cur, iarc);
   return hipGetLastError();
 }
 

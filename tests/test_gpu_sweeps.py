@@ -66,3 +66,37 @@ def test_the_sweep_that_settled(comp, V, dirs):  # noqa: F811
     with pytest.raises(gpu.FstError) as e:
         _run(comp, G, alpha=dirs[0], beta=dirs[1], max_sweeps=V)
     assert e.value.code == gpu.FST_ERR_NOT_CONVERGED
+
+
+@pytest.mark.parametrize("degree", (1, 3, 8, 9, 20))
+def test_without_room_for_ranks(comp, degree):  # noqa: F811
+    """The least workspace cap that fits: the arcs' ranks share the values'
+    room (8 arcs a state and fewer) or are done without; the same bits."""
+    from paper_2110_02848_amd import gpu
+    V = 3000
+    G = synth.random_cyclic(degree, V, degree=degree, mass=0.5)
+    want = _run(comp, G)
+
+    def at(cap):
+        c = gpu.Composer(0)
+        c.set_option(gpu.FST_OPT_MAX_WORKSPACE, cap)
+        try:
+            return _run(c, G)
+        except gpu.FstError as e:
+            assert e.code == gpu.FST_ERR_NOMEM
+            return None
+        finally:
+            c.close()
+
+    lo, hi = 1 << 12, 1 << 24
+    while hi - lo > 1 << 12:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if at(mid) else (mid, hi)
+    # in-arcs 8 bytes an arc and 4 a state, values 32, bits 1/2, notes 41 KB and
+    # at most 12 KB of scan and rounding
+    assert hi < 8 * degree * V + 36.5 * V + (56 << 10), hi
+    for cap in (hi, hi + degree * V * 2, hi + degree * V * 4 + 4096):
+        got = at(cap)
+        assert got["sweeps"] == want["sweeps"]
+        for k in ("alpha", "beta"):
+            assert np.array_equal(got[k].view(np.int64), want[k].view(np.int64)), (k, cap)
