@@ -49,13 +49,13 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 
 
 def algorithmic_bytes(A, B, st, provenance=False):
-    """Bytes the method itself must move per composition (inputs read once,
-    one dedupe probe per examined move, each kept key written to and read
-    from a frontier once, the output CSR written once)."""
+    """Bytes that a composition cannot do without: inputs read once, a bit per
+    reached key and direction written once and read once, the output CSR
+    written once."""
     EA, EB = len(A["src"]), len(B["src"])
     VA, VB = A["num_states"], B["num_states"]
     b_in = 16 * (EA + EB) + 4 * (VA + VB + 2) + 2 * (VA + VB)
-    b_search = 4 * st["generated"] + 16 * st["accessible"]
+    b_search = (st["accessible"] + st["coaccessible"]) // 4
     V, E = st["num_states"], st["num_arcs"]
     b_out = 20 * E + 4 * (V + 1) + 2 * V
     if provenance:
@@ -65,18 +65,15 @@ def algorithmic_bytes(A, B, st, provenance=False):
 
 def kernel_bytes(st):
     """Algorithmic bytes per composition of each timed kernel group.
-    search (both searches, whose launches the default order shares): 4 B
-    probe per move out of an accessible key + 16 B per accessible key
-    (frontier write and read), and the same over the predecessor moves of
-    the co-accessible keys and those keys; count: 1 B per state of C (its
-    count out; keys come from the trim bitmap, 1 bit each) + 4 B per kept
-    arc (the probe of its target); fill: the output CSR (20 B per arc, 6 B
-    per state + 4 B) and each state's count (1 B)."""
+    search (both searches, whose launches the default order shares): a bit
+    per reached key and direction, written once and read once (a search that
+    follows 64 keys at a time probes and lists no single ones); count: the
+    trim bitmap and 1 B per state of C (its count); fill: the output CSR (20
+    B per arc, 6 B per state + 4 B) and each state's count (1 B)."""
     V, E = st["num_states"], st["num_arcs"]
     return {
-        "search": (4 * st["generated"] + 16 * st["accessible"]
-                   + 4 * st["generated_backward"] + 16 * st["coaccessible"]),
-        "count": V + 4 * E,
+        "search": (st["accessible"] + st["coaccessible"]) // 4,
+        "count": V + st["key_space"] // 8,
         "fill": 20 * E + 4 * (V + 1) + 2 * V + V,
     }
 

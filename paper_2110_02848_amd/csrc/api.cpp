@@ -968,9 +968,8 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
   const size_t nwords = (size_t)((nkeys + 31) / 32);  // key-order bitmaps
   const size_t snwords = (size_t)(nsbits / 32);          // search bitmaps
   // Every list holds at most one entry per key, so 2 V_A V_B (f = 1 only
-  // where epsOutA) bounds them; what a search pushes (frontier and heavy
-  // keys, the accepting keys it meets) is far less when its threads follow
-  // keys depth-first.  The lists start at FST_OPT_LIST_CAPACITY entries
+  // where epsOutA) bounds them; what a search pushes (the frontier of a
+  // generation, all heavy keys) is far less.  The lists start at FST_OPT_LIST_CAPACITY entries
   // (2^22 by default), or the size the last call needed, and the searches
   // run again with four times as much when one overflows.
   const unsigned long long capll = 2ull * (unsigned long long)VA * (unsigned long long)VB;
@@ -1133,14 +1132,13 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       HIP_TRY(launch_trim(P, (uint32_t)VA, as<uint32_t>(c->trim), wbase, s));
       phase_end(c, PH_BWD, s);
     } else if (c->order == FST_ORDER_CONCURRENT) {
-      // The forward search's first generations run alone (listing accepting
-      // keys as in the forward-first order).  If it has ended by then, the
-      // backward search follows as in that order; otherwise a backward search
-      // from every accepting pair runs beside the rest of it.
+      // The forward search's first generations run alone.  If it has ended by
+      // then, the backward search follows as in the forward-first order, from
+      // the accessible accepting keys; otherwise one from every accepting pair
+      // runs beside the rest of it.
       // With few accepting pairs the backward search starts at once (its
       // seeds cannot outnumber much of the forward work).
-      const int FIRST =
-          pairs <= FEW_ACCEPTING_PAIRS ? 0 : 4;
+      const int FIRST = pairs <= FEW_ACCEPTING_PAIRS ? 0 : 4;
       P.restrict_fwd = 0;
       P.restrict_bwd = 0;
       phase_begin(c, PH_FWD, s);
@@ -1173,7 +1171,8 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
         phase_end(c, PH_BWD, s);
       } else {
         SearchArgs SB = S;
-        SB.Q = Frontier{as<uint32_t>(c->bq), rc, S.Q.stride, P.chains ? d_sc->front[1] : S.Q.cnt + FRONT_WORDS};
+        SB.Q = Frontier{as<uint32_t>(c->bq), rc, S.Q.stride,
+                        P.chains ? d_sc->front[1] : S.Q.cnt + FRONT_WORDS};
         SB.heavy = as<uint32_t>(c->heavy2);
         SB.hoff = as<uint32_t>(c->hoff2);
         SB.G = d_sc->G2;

@@ -3523,6 +3523,11 @@ hipError_t launch_linear_seed(const LinearArgs &F, const LinearArgs &B, const De
 }
 
 hipError_t launch_linear(const LinearArgs &F, const LinearArgs &B, int g, hipStream_t s) {
+  // Workgroups per direction: most generations are a few thousand items, whose
+  // walks one round takes, and every workgroup reads the counters and clears
+  // its table.  Search of 1,000 frames o 30,000 words, ms: 64 1.58, 128 1.05, 256
+  // 1.19, 1,024 1.16; 4,000 o 2,000: 4.21, 4.22, 4.81, 4.90; only of the largest
+  // lexicons are more faster (300 o 100,000: 1.47, 1.01, 0.81, 0.86).
   constexpr unsigned GRID = 128;
   k_linear<<<2 * GRID, NT, 0, s>>>(F, B, g);
   return hipGetLastError();

@@ -743,18 +743,17 @@ __device__ __forceinline__ Jump3 jump3(const Problem3 &P, const Search3 &S, uint
 // A thread's depth-first walk from `key` (in `slot`): a key with at most
 // WALK3 units is expanded at once (a chain of one-move keys by a jump) and
 // the walk goes on with the first new key it reached (up to CHAIN3 keys); a
-// heavier key is cut into chunks for the chunk list `heavy_to`.  Every
+// heavier key is cut into chunks of the next level (`next`, ring slot nx).  Every
 // other new key joins the next frontier.  Returns the number of keys the
 // walk inserted and did not put in a frontier.
 __device__ __forceinline__ uint32_t walk_fwd(const Problem3 &P, const Search3 &S, uint32_t slot,
-                                             ull key, Lvl3 *nx, uint32_t nbase, Lvl3 *heavy_to,
-                                             int heavy_l) {
+                                             ull key, Lvl3 *nx, uint32_t nbase, int next) {
   uint32_t went = 0;
   for (int depth = 0; depth < CHAIN3; ++depth) {
     const Units3 u = units_of(P, key);
     const uint32_t n = nunits(u);
     if (n > WALK3) {
-      push_chunks(S, heavy_to, heavy_l, slot, n);
+      push_chunks(S, nx, next, slot, n);
       return went;
     }
     // the key reached last must still be expanded within the budget
@@ -914,7 +913,7 @@ __global__ __launch_bounds__(NT) void k3_fwd(Problem3 P, Search3 S, int l) {
     const uint32_t n = ovf ? 0 : cur.fcount;
     for (ull i = (ull)blockIdx.x * NT + threadIdx.x; i < n; i += (ull)half * NT) {
       const uint32_t slot = S.F[cur.fbase + i];
-      went += walk_fwd(P, S, slot, P.tab[slot], nx, nbase, nx, l + 1);
+      went += walk_fwd(P, S, slot, P.tab[slot], nx, nbase, l + 1);
     }
   } else {
     const uint32_t nch = ovf ? 0 : (cur.ccount < S.ccap ? cur.ccount : S.ccap);
@@ -928,7 +927,7 @@ __global__ __launch_bounds__(NT) void k3_fwd(Problem3 P, Search3 S, int l) {
       ull cont_key = 0;
       if (!expand_beps(P, S, c.x, u, c.y, u1, nx, nbase, &cont, &cont_key))
         expand_units(P, S, c.x, u, c.y, u1, nx, nbase, &cont, &cont_key);
-      if (cont != NO_SLOT) went += 1 + walk_fwd(P, S, cont, cont_key, nx, nbase, nx, l + 1);
+      if (cont != NO_SLOT) went += 1 + walk_fwd(P, S, cont, cont_key, nx, nbase, l + 1);
     }
   }
   wave_add(went, &S.sc->ncont);
@@ -1053,8 +1052,7 @@ __device__ __forceinline__ uint32_t claim_segment(const Problem3 &P, const Searc
 // Depth-first backward walk from slot v (as walk_fwd, over in-arcs; a key
 // that ends a chain segment has the segment's keys claimed first).
 __device__ __forceinline__ uint32_t walk_bwd(const Problem3 &P, const Search3 &S, uint32_t v,
-                                             Lvl3 *nx, uint32_t nbase, Lvl3 *heavy_to,
-                                             int heavy_l) {
+                                             Lvl3 *nx, uint32_t nbase, int next) {
   uint32_t went = 0;
   for (int depth = 0; depth < CHAIN3; ++depth) {
     const uint32_t p0 = P.in_off[v], p1 = P.in_off[v + 1];
@@ -1063,7 +1061,7 @@ __device__ __forceinline__ uint32_t walk_bwd(const Problem3 &P, const Search3 &S
     if (sg != NO_SLOT) cont = claim_segment(P, S, sg, nx, nbase, depth + 1 < CHAIN3, &went);
     if (p1 - p0 > WALK3) {
       if (cont != NO_SLOT) push_one(S, nx, nbase, cont);
-      push_chunks(S, heavy_to, heavy_l, v, p1 - p0);
+      push_chunks(S, nx, next, v, p1 - p0);
       return went;
     }
     bwd_range(P, S, p0, p1, nx, nbase, depth + 1 < CHAIN3 ? &cont : nullptr);
@@ -1087,7 +1085,7 @@ __global__ __launch_bounds__(NT) void k3_bwd(Problem3 P, Search3 S, int l) {
   if (blockIdx.x < half) {
     const uint32_t n = ovf ? 0 : cur.fcount;
     for (ull i = (ull)blockIdx.x * NT + threadIdx.x; i < n; i += (ull)half * NT)
-      went += walk_bwd(P, S, S.F[cur.fbase + i], nx, nbase, nx, l + 1);
+      went += walk_bwd(P, S, S.F[cur.fbase + i], nx, nbase, l + 1);
   } else {
     const uint32_t nch = ovf ? 0 : (cur.ccount < S.ccap ? cur.ccount : S.ccap);
     const uint2 *list = chunks_of(S, l);
@@ -1097,7 +1095,7 @@ __global__ __launch_bounds__(NT) void k3_bwd(Problem3 P, Search3 S, int l) {
       const uint32_t p1 = p0 + CHUNK3 < pe ? p0 + CHUNK3 : pe;
       uint32_t cont = NO_SLOT;
       bwd_range(P, S, p0, p1, nx, nbase, &cont);
-      if (cont != NO_SLOT) went += 1 + walk_bwd(P, S, cont, nx, nbase, nx, l + 1);
+      if (cont != NO_SLOT) went += 1 + walk_bwd(P, S, cont, nx, nbase, l + 1);
     }
   }
   wave_add(went, &S.sc->ncont);
