@@ -164,8 +164,7 @@ FST_API void fst_ctx_destroy(fst_ctx *ctx);
  * a pair and 4,096), unless B is mostly chains (most of its states have one
  * out-arc).  Where B is and every arc of A leads from a state to the next one
  * with an output other than epsilon, it follows 64 keys of a state of B at a
- * time (generations then advance both directions).  Where B is not, deep and
- * narrow searches run many generations in a launch, in every order.
+ * time (generations then advance both directions).
  * FST_OPT_VALIDATE (default 1) checks every input graph's
  * structure as described at fst_graph; 0 is for callers that vouch for
  * their graphs: the checks are skipped (the composition still reads the

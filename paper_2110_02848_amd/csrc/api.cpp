@@ -307,58 +307,35 @@ bool search_over(const fst_ctx *c, bool second, int g) {
   return any == 0;
 }
 
-// How a search goes on after `gens` generations, the last of them with `width`
-// items.  A level search that is deep by then (DEEP: most that are not, random
-// graphs of 1,000 states among them, have ended) runs narrow levels up to
-// NARROW_KEYS / 4 items (500 frames aligned to 300 states with loops 4.1 -> 2.4 ms a
-// call, 1 o 10,000 states with two arcs each 37 -> 15; up to NARROW_KEYS / 2, 300
-// frames o 100 words with loops take 3.3 ms instead of 3.0), and launches a
-// quarter of the workgroups up to FEW_ITEMS (4,000 frames aligned to 3,900 states
-// 35 -> 29 ms).  Others launch GENERATION_GRID workgroups per direction.
-constexpr int DEEP = 32;
-constexpr unsigned long long FEW_ITEMS = 8192;
-constexpr unsigned GENERATION_GRID = 1024;
+// Hops of a level search's wavefronts after `gens` generations: LEVEL_HOPS once
+// it is deep.  Random graphs of 1,000 states have ended by then; with hops from
+// the start they take 1.05 instead of 1.00 ms, since most of their levels are
+// wide and a launch waits for the wavefront that hops longest.  With 8, 16 and
+// 32 hops 8,000 o 8,000 states of two arcs take 25.2, 23.3 and 21.4 ms, a deep
+// random graph (3,000 states of three arcs, 1.1 moves a key) 1.46, 1.44 and 1.55.
+constexpr int DEEP = 32, LEVEL_HOPS = 16;
 
-bool narrow(const fst_ctx *c, int gens, unsigned long long width) {
-  return !c->P.chains && gens >= DEEP && width <= NARROW_KEYS / 4;
-}
-
-unsigned generation_grid(const fst_ctx *c, int gens, unsigned long long width) {
-  return !c->P.chains && gens >= DEEP && width <= FEW_ITEMS ? GENERATION_GRID / 4
-                                                            : GENERATION_GRID;
-}
+int hops_after(int gens) { return gens >= DEEP ? LEVEL_HOPS : 0; }
 
 // Generations are queued in batches (4, 16, 32, 64, 64, ...) with no host
 // round trip; after each batch the host checks whether the search is over
 // (generations queued after that do nothing).
-int search(fst_ctx *c, const SearchArgs &S, bool forward, int64_t *levels, hipStream_t s) {
+int search(fst_ctx *c, SearchArgs S, bool forward, int64_t *levels, hipStream_t s) {
   const int kernel = forward ? FST_KERNEL_SEARCH_FORWARD : FST_KERNEL_SEARCH_BACKWARD;
   const KernelTimer t = timer(c, kernel);
   int g = 0, batch = 4;
-  unsigned grid = GENERATION_GRID;
   for (;;) {
     t.begin(s);
-    for (int b = 0; b < batch; ++b, ++g) HIP_TRY(launch_generation(c->P, S, forward, g, grid, s));
+    for (int b = 0; b < batch; ++b, ++g) {
+      S.hops = hops_after(g);
+      HIP_TRY(launch_generation(c->P, S, forward, g, s));
+    }
     t.end(s);
     FST_TRY(readback(c, s));
     FST_TRY(add_time(c, kernel, batch));
     if (c->h_sc->overflow) return FST_ERR_TOO_LARGE;
     if (search_over(c, false, g)) break;
     batch = batch == 4 ? 16 : (batch < 64 ? 2 * batch : 64);
-    bool over = false;
-    while (!over && narrow(c, g, c->h_sc->note.width)) {
-      t.begin(s);
-      HIP_TRY(launch_narrow(c->P, S, S, g, g, forward ? 1 : 2, s));
-      t.end(s);
-      FST_TRY(readback(c, s));
-      FST_TRY(add_time(c, kernel, 1));
-      if (c->h_sc->overflow) return FST_ERR_TOO_LARGE;
-      g = (int)c->h_sc->note.gen;
-      over = c->h_sc->note.width == 0;
-      batch = 16;
-    }
-    if (over) break;
-    grid = generation_grid(c, g, c->h_sc->note.width);
   }
   *levels = c->h_sc->gens;
   return FST_OK;
@@ -679,69 +656,47 @@ ScoreGraph plain_score_graph(const DevGraph &d) {
 // once.
 constexpr unsigned long long FEW_ACCEPTING_PAIRS = 1024;
 
-int search_concurrent(fst_ctx *c, Problem P, const SearchArgs &SF, const SearchArgs &SB, int g0,
+int search_concurrent(fst_ctx *c, Problem P, SearchArgs SF, SearchArgs SB, int g0,
                       hipStream_t s) {
   const KernelTimer t = timer(c, FST_KERNEL_SEARCH_FORWARD);
   int gf = g0, gb = 0;  // each search numbers its own generations
-  bool fdone = false, bdone = false, pause = false, first = true, levels = false;
-  int launches = 0;  // before the first narrow levels
-  bool any_levels = false;
-  unsigned grid = GENERATION_GRID;
+  bool fdone = false, bdone = false, pause = false, first = true;
   for (;;) {
-    const bool both = !fdone && !bdone && !pause;
     // the one search left after the other ends is usually near its end too;
     // the first batch covers as many launches as the last search took
-    int batch = levels ? 1 : (fdone || bdone ? 8 : 16);
+    int batch = fdone || bdone ? 8 : 16;
     // (a level search: and one that finds nothing)
     const int hint = c->gen_hint + 1;
     if (first && c->gen_hint) batch = hint < 256 ? hint : 256;
     first = false;
     t.begin(s);
-    if (levels) {
-      HIP_TRY(launch_narrow(P, SF, SB, gf, gb, both ? 3 : (fdone ? 2 : 1), s));
-    } else {
-      for (int b = 0; b < batch; ++b) {
-        if (both) HIP_TRY(launch_generation2(P, SF, SB, gf++, gb++, grid, s));
-        else if (!fdone) HIP_TRY(launch_generation(P, SF, true, gf++, grid, s));
-        else HIP_TRY(launch_generation(P, SB, false, gb++, grid, s));
-      }
+    for (int b = 0; b < batch; ++b) {
+      SF.hops = SB.hops = hops_after(gf > gb ? gf : gb);
+      if (!fdone && !bdone && !pause) HIP_TRY(launch_generation2(P, SF, SB, gf++, gb++, s));
+      else if (!fdone) HIP_TRY(launch_generation(P, SF, true, gf++, s));
+      else HIP_TRY(launch_generation(P, SB, false, gb++, s));
     }
     t.end(s);
     FST_TRY(readback(c, s));
     FST_TRY(add_time(c, FST_KERNEL_SEARCH_FORWARD, batch));
-    const Scalars &h = *c->h_sc;
-    if (h.overflow) return FST_ERR_TOO_LARGE;
-    const bool ranf = !fdone, ranb = both || fdone;
-    if (levels) {
-      if (ranf) gf = (int)h.note.gen;
-      if (ranb) gb = (int)h.note2.gen;
-    }
-    fdone = fdone || (levels ? h.note.width == 0 : search_over(c, false, gf));
-    bdone = bdone || (ranb && (levels ? h.note2.width == 0 : search_over(c, true, gb)));
+    if (c->h_sc->overflow) return FST_ERR_TOO_LARGE;
+    fdone = fdone || search_over(c, false, gf);
+    bdone = bdone || search_over(c, true, gb);
     if (fdone) P.restrict_bwd = 1;  // the accessible set is complete
     // an unrestricted backward frontier far wider than the forward one is
     // mostly keys that are not accessible: the backward search waits (its
     // frontier stays in its slot) until the forward search has ended
-    const unsigned long long wf = h.note.width, wb = h.note2.width;
+    const unsigned long long wf = c->h_sc->note.width, wb = c->h_sc->note2.width;
     pause = pause || (!fdone && wb > 4 * wf + 65536);
     if (fdone && bdone) break;
-    if (!any_levels) launches += batch;
-    // items of the direction that goes on, or of the wider one
-    const bool runf = !fdone, runb = fdone || (!bdone && !pause);
-    const unsigned long long width = runf && runb ? (wf > wb ? wf : wb) : (runf ? wf : wb);
-    const int gens = gf > gb ? gf : gb;
-    levels = narrow(c, gens, width);
-    grid = generation_grid(c, gens, width);
-    any_levels = any_levels || levels;
     // (no growth: a read-back every 16 generations costs less than the
     // empty launches a larger batch leaves after the searches end)
   }
   c->stats.fwd_levels = c->h_sc->gens;
   c->stats.bwd_levels = c->h_sc->gens2;
-  // launches that found work (both searches side by side from g0 on), up to
-  // the first narrow levels
+  // launches that found work (both searches side by side from g0 on)
   const int fl = (int)c->h_sc->gens - g0, bl = (int)c->h_sc->gens2;
-  c->gen_hint = any_levels ? launches - 1 : (fl > bl ? fl : bl);
+  c->gen_hint = fl > bl ? fl : bl;
   return FST_OK;
 }
 
@@ -1058,7 +1013,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
     int32_t *la = as<int32_t>(c->lists), *lb = la + VA;
     const unsigned long long pairs = (unsigned long long)c->h_sc->naccA * c->h_sc->naccB;
     uint32_t *ns = d_sc->lists, *na = ns + 2;  // start, accepting states listed
-    SearchArgs S;
+    SearchArgs S = {};
     S.Q = P.chains ? Frontier{as<uint32_t>(c->fq), rc, 1, d_sc->front[0]}
                    : Frontier{as<uint32_t>(c->fq), rc, SUBQ_STRIDE, as<uint32_t>(c->fcnt)};
     S.heavy = as<uint32_t>(c->heavy);
@@ -1146,7 +1101,7 @@ int run_impl(fst_ctx *c, const fst_graph *A, const fst_graph *B, hipStream_t s, 
       HIP_TRY(launch_seed_forward(P, S, la, ns, lb, ns + 1, s));
       const KernelTimer tf = timer(c, FST_KERNEL_SEARCH_FORWARD);
       tf.begin(s);
-      for (int g = 0; g < FIRST; ++g) HIP_TRY(launch_generation(P, S, true, g, GENERATION_GRID, s));
+      for (int g = 0; g < FIRST; ++g) HIP_TRY(launch_generation(P, S, true, g, s));
       tf.end(s);
       // with no generation run alone there is nothing to read back yet (an
       // empty forward search ends in the concurrent loop as well)

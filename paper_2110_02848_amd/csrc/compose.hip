@@ -1444,13 +1444,22 @@ __device__ __forceinline__ bool reach(const Problem &P, const Target &t) {
   return (atomicOr(mine + w, bit) & bit) == 0;
 }
 
+// After its batches a wavefront goes on for up to S.hops hops with the keys that
+// it has reached and not yet handed on, while they are at most 64 and have few
+// units: a hop takes its dependent loads (about 2.5 us) where a level takes a
+// launch (7).  Deep searches do so (LEVEL_HOPS; 300 frames o 100 words with loops
+// 3.9 -> 1.3 ms a call, 2,000 frames aligned to 1,000 states with loops 16.7 -> 5.8, 500
+// o 5,000 words 158 -> 12); more units than HOP_UNITS a hop are left to the whole
+// grid (200 o 200 states of 100 arcs: 2.24 ms without that, 2.04 with it).
+constexpr uint32_t HOP_UNITS = 256;
+
 // Generation g of a level search (one kernel).  Its items are the unit slots
 // of its heavy keys (one per thread) and its frontier keys, which a
 // wavefront takes in batches (see spread_units).  A batch is the frontier divided by the
 // wavefronts, at most 64 keys: a narrow frontier is spread over more
 // wavefronts, a wide one fills the lanes.  nb is a multiple of 8 (slots of
 // heavy keys are spread over the XCDs as in gen_body).
-template <bool FWD>
+template <bool FWD, bool HOPS>
 __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S, int g,
                                            unsigned bid, unsigned nb, LevelLds &L) {
   const unsigned lane = __lane_id(), wid = threadIdx.x / WAVE;
@@ -1482,6 +1491,8 @@ __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S
   uint32_t K = (nq + 8 * nl - 1) / (8 * nl);
   if (K < 1) K = 1;
   if (K > WAVE) K = WAVE;
+  PushBuf &buf = *nx.buf;
+  int hop = 0;
   for (ull j = lw;; j += nl) {
     const bool hv = j < hb;
     uint32_t key = 0, u0 = 0, units = 0;
@@ -1503,17 +1514,35 @@ __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S
       }
     } else {
       const ull fb = (j - hb) * 8 + xcd;  // this batch of the frontier
-      if (fb * K >= nq) break;
-      const uint32_t i = (uint32_t)(fb * K) + lane;
-      have = lane < K && i < nq;
-      if (have) key = front_key(S.Q, g, L.pre, i);
+      if (fb * K < nq) {
+        const uint32_t i = (uint32_t)(fb * K) + lane;
+        have = lane < K && i < nq;
+        if (have) key = front_key(S.Q, g, L.pre, i);
+      } else if (!HOPS) {
+        break;
+      } else {  // a hop
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t n = buf.n;
+        if (hop == S.hops || n == 0 || n > WAVE) break;
+        ++hop;
+        have = lane < n;
+        if (have) key = buf.key[lane];
+      }
     }
     if (have) {
       A = load_rec(Dir<FWD>::viewA(P), key_qa(key, P.shiftB));
       B = load_rec(Dir<FWD>::viewB(P), key_qb(key, P.shiftB));
       units = Dir<FWD>::units(Dir<FWD>::make(key, P.shiftB, A, B));
     }
-    auto take = [&](const Target &t) { buf_push(reach<FWD>(P, t), t.key, *nx.buf, nx.q); };
+    if (HOPS && hop) {
+      if (wave_sum(units > LEVEL_UNITS ? 0u : units) > HOP_UNITS) break;
+      __builtin_amdgcn_wave_barrier();
+      if (lane == 0) buf.n = 0;  // its keys are the lanes' now
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    auto take = [&](const Target &t) { buf_push(reach<FWD>(P, t), t.key, buf, nx.q); };
     if (hv) {  // a unit per lane (a slot past the key's units has none)
       UnitRange x = {};
       if (u0 < units) x = Dir<FWD>::range(P, Dir<FWD>::make(key, P.shiftB, A, B), u0);
@@ -1528,144 +1557,23 @@ __device__ __forceinline__ void level_body(const Problem &P, const SearchArgs &S
     }
     spread_units<FWD>(P, L.spread[wid], key, A, B, units, take);
   }
-  push_flush(*nx.buf, nx.q);
+  push_flush(buf, nx.q);
 }
 
-template <bool FWD>
+template <bool FWD, bool HOPS>
 __global__ __launch_bounds__(NT) void k_level(Problem P, SearchArgs S, int g) {
   __shared__ LevelLds L;
-  level_body<FWD>(P, S, g, blockIdx.x, gridDim.x, L);
+  level_body<FWD, HOPS>(P, S, g, blockIdx.x, gridDim.x, L);
 }
 
 // Both searches side by side, half of the workgroups each.
+template <bool HOPS>
 __global__ __launch_bounds__(NT) void k_level2(Problem P, SearchArgs SF, SearchArgs SB, int gf,
                                                int gb) {
   __shared__ LevelLds L;
   const unsigned half = gridDim.x / 2;
-  if (blockIdx.x < half) level_body<true>(P, SF, gf, blockIdx.x, half, L);
-  else level_body<false>(P, SB, gb, blockIdx.x - half, half, L);
-}
-
-// Narrow levels: while a frontier has few keys, one workgroup per direction runs
-// level after level, the frontier in LDS and a barrier between levels (about 2
-// to 3 us; a launch of k_level2 takes 7).  It stops before generation note->gen:
-// after NARROW_LEVELS levels, or with a heavy key listed, more than
-// NARROW_UNITS units in a level or more keys than the list holds; what waits
-// (note->width) is then in that generation's frontier, as if each level had
-// been a launch.
-constexpr uint32_t NARROW_UNITS = 16384;
-constexpr int NARROW_LEVELS = 128, NARROW_NT = 1024, NARROW_WAVES = NARROW_NT / WAVE;
-struct NarrowLds {
-  uint32_t list[2][NARROW_KEYS];
-  SpreadLds spread[NARROW_WAVES];
-  uint32_t pre[SUBQ + 1];
-  uint32_t n[2];
-  uint32_t units, heavy, ovf;
-};
-
-template <bool FWD>
-__device__ __forceinline__ void narrow_body(const Problem &P, const SearchArgs &S, int g0,
-                                            NarrowLds &L) {
-  const uint32_t tid = threadIdx.x, lane = __lane_id(), wid = tid / WAVE;
-  const GenSlot first = S.G[g0 % 3];
-  load_front(S.Q, g0, L.pre);
-  if (tid == 0) {
-    L.ovf = S.sc->overflow;
-    L.units = L.heavy = L.n[1] = 0;
-  }
-  __syncthreads();
-  const uint32_t nq = L.pre[SUBQ];
-  const ull U = first.hpack >> 32;
-  if (L.ovf || U || nq == 0 || nq > NARROW_KEYS) {  // nothing for it here
-    if (tid == 0) {
-      S.note->gen = (uint32_t)g0;
-      S.note->width = U ? NARROW_KEYS + 1 : nq;
-    }
-    return;
-  }
-  for (uint32_t i = tid; i < nq; i += NARROW_NT) L.list[0][i] = front_key(S.Q, g0, L.pre, i);
-  if (tid == 0) L.n[0] = nq;
-  // no launch has anything left in the lists: all three generations' counters
-  // and slots start again
-  __syncthreads();
-  for (uint32_t i = tid; i < 3 * SUBQ; i += NARROW_NT) S.Q.cnt[(size_t)i * S.Q.stride] = 0;
-  if (tid < 3) {
-    S.G[tid].hpack = 0;
-    S.G[tid].hbase = first.hbase;
-  }
-  __threadfence();
-  __syncthreads();
-  int g = g0;
-  for (int cur = 0;; cur ^= 1, ++g) {
-    const uint32_t n = L.n[cur];  // the same for all threads (a barrier before)
-    const bool wide = n > NARROW_KEYS || L.heavy || (n && L.units > NARROW_UNITS);
-    const bool stop = n == 0 || wide || g - g0 == NARROW_LEVELS;
-    __syncthreads();
-    if (stop) {
-      // what waits goes to generation g's frontier (keys past the list's end
-      // are there already)
-      const NextFront q = next_front(S.Q, g - 1, wid, S.sc);
-      const uint32_t m = n < NARROW_KEYS ? n : NARROW_KEYS;
-      for (uint32_t i = wid * WAVE; i < m; i += NARROW_NT)
-        front_push(i + lane < m, i + lane < m ? L.list[cur][i + lane] : 0u, q);
-      if (tid == 0) {
-        S.note->gen = (uint32_t)g;
-        S.note->width = wide ? NARROW_KEYS + 1 : n;
-        *S.gens = (uint32_t)g;
-      }
-      return;
-    }
-    if (tid == 0) L.units = 0;
-    __syncthreads();
-    NextGen nx;
-    nx.slot = &S.G[(g + 1) % 3];
-    nx.hbase = first.hbase;
-    nx.q = next_front(S.Q, g, wid, S.sc);
-    nx.buf = nullptr;
-    uint32_t K = (n + NARROW_WAVES - 1) / NARROW_WAVES;
-    if (K > WAVE) K = WAVE;
-    for (uint32_t k0 = wid * K; k0 < n; k0 += NARROW_WAVES * K) {
-      const bool have = lane < K && k0 + lane < n;
-      uint32_t key = 0, units = 0;
-      Rec A = {}, B = {};
-      if (have) {
-        key = L.list[cur][k0 + lane];
-        A = load_rec(Dir<FWD>::viewA(P), key_qa(key, P.shiftB));
-        B = load_rec(Dir<FWD>::viewB(P), key_qb(key, P.shiftB));
-        units = Dir<FWD>::units(Dir<FWD>::make(key, P.shiftB, A, B));
-      }
-      if (units > LEVEL_UNITS) {
-        list_heavy(S, nx, key, units);
-        L.heavy = 1;
-        units = 0;
-      }
-      spread_units<FWD>(P, L.spread[wid], key, A, B, units, [&](const Target &t) {
-        const bool fresh = reach<FWD>(P, t);
-        const ull m = __ballot(fresh);
-        if (m == 0) return;
-        const int leader = __ffsll(m) - 1;
-        uint32_t base = 0;
-        if ((int)lane == leader) base = atomicAdd(&L.n[cur ^ 1], (uint32_t)__popcll(m));
-        base = __shfl(base, leader, WAVE);
-        const uint32_t pos = base + (uint32_t)__popcll(m & __lanemask_lt());
-        if (fresh && pos < NARROW_KEYS) L.list[cur ^ 1][pos] = t.key;
-        front_push(fresh && pos >= NARROW_KEYS, t.key, nx.q);
-      });
-      const uint32_t all = wave_sum(units);
-      if (lane == 0) atomicAdd(&L.units, all);
-    }
-    __syncthreads();  // the next level is listed
-    if (tid == 0) L.n[cur] = 0;
-    __syncthreads();
-  }
-}
-
-// Both directions, or (dirs: 1 forward, 2 backward) one.
-__global__ __launch_bounds__(NARROW_NT) void k_narrow(Problem P, SearchArgs SF, SearchArgs SB,
-                                                      int gf, int gb, int dirs) {
-  __shared__ NarrowLds L;
-  if ((dirs & 1) && blockIdx.x == 0) narrow_body<true>(P, SF, gf, L);
-  else narrow_body<false>(P, SB, gb, L);
+  if (blockIdx.x < half) level_body<true, HOPS>(P, SF, gf, blockIdx.x, half, L);
+  else level_body<false, HOPS>(P, SB, gb, blockIdx.x - half, half, L);
 }
 
 // ---------------------------------------------------------------------------
@@ -3480,27 +3388,27 @@ hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, int32_t *
 }
 
 hipError_t launch_generation(const Problem &P, const SearchArgs &S, bool forward, int g,
-                             unsigned grid, hipStream_t s) {
-  if (!P.chains) {
-    if (forward) k_level<true><<<grid, NT, 0, s>>>(P, S, g);
-    else k_level<false><<<grid, NT, 0, s>>>(P, S, g);
+                             hipStream_t s) {
+  constexpr unsigned GRID = 1024;
+  if (!P.chains && S.hops) {
+    if (forward) k_level<true, true><<<GRID, NT, 0, s>>>(P, S, g);
+    else k_level<false, true><<<GRID, NT, 0, s>>>(P, S, g);
+  } else if (!P.chains) {
+    if (forward) k_level<true, false><<<GRID, NT, 0, s>>>(P, S, g);
+    else k_level<false, false><<<GRID, NT, 0, s>>>(P, S, g);
   } else {
-    if (forward) k_gen<true><<<grid, NT, 0, s>>>(P, S, g);
-    else k_gen<false><<<grid, NT, 0, s>>>(P, S, g);
+    if (forward) k_gen<true><<<GRID, NT, 0, s>>>(P, S, g);
+    else k_gen<false><<<GRID, NT, 0, s>>>(P, S, g);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_generation2(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
-                              int gb, unsigned grid, hipStream_t s) {
-  if (!P.chains) k_level2<<<2 * grid, NT, 0, s>>>(P, SF, SB, gf, gb);
-  else k_gen2<<<2 * grid, NT, 0, s>>>(P, SF, SB, gf, gb);
-  return hipGetLastError();
-}
-
-hipError_t launch_narrow(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
-                         int gb, int dirs, hipStream_t s) {
-  k_narrow<<<dirs == 3 ? 2 : 1, NARROW_NT, 0, s>>>(P, SF, SB, gf, gb, dirs);
+                              int gb, hipStream_t s) {
+  constexpr unsigned GRID = 1024;
+  if (!P.chains && SF.hops) k_level2<true><<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
+  else if (!P.chains) k_level2<false><<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
+  else k_gen2<<<2 * GRID, NT, 0, s>>>(P, SF, SB, gf, gb);
   return hipGetLastError();
 }
 

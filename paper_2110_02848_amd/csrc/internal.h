@@ -185,11 +185,9 @@ struct GenSlot {
   unsigned long long hpack;
 };
 
-// What the last generation of a search that ran found: its work items; after
-// narrow levels the items that wait, and the generation they wait for.
+// What the last generation of a search that ran found: its work items.
 struct SearchNote {
   unsigned long long width;
-  uint32_t gen, pad;
 };
 
 // Device scalars read back by the host (one pinned mirror).
@@ -246,6 +244,7 @@ struct SearchArgs {
   uint32_t *heavy;  // heavy keys, generation after generation (up to cap)
   uint32_t *hoff;   // unit offset of each heavy key inside its generation
   uint32_t cap;
+  int hops;         // level search: hops of a wavefront beyond its generation
   Scalars *sc;
   GenSlot *G;       // this search's three generation slots
   uint32_t *gens;   // this search's count of generations that had work
@@ -633,20 +632,14 @@ hipError_t launch_seed_forward(const Problem &P, const SearchArgs &S, int32_t *l
 hipError_t launch_seed_backward(const Problem &P, const SearchArgs &S, int32_t *la,
                                 uint32_t *na, int32_t *lb, uint32_t *nb,
                                 unsigned long long pairs, size_t nwords, hipStream_t s);
-// Generation g of the forward (or backward) search: one kernel of `grid`
-// workgroups per direction (a multiple of 8).
+// Generation g of the forward (or backward) search: one kernel.
 hipError_t launch_generation(const Problem &P, const SearchArgs &S, bool forward, int g,
-                             unsigned grid, hipStream_t s);
+                             hipStream_t s);
 // Generation gf of a forward search (SF) and generation gb of a backward
 // search (SB) running side by side in one kernel (half of the workgroups
 // each).
 hipError_t launch_generation2(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
-                              int gb, unsigned grid, hipStream_t s);
-// Narrow levels of a level search, many in one launch (dirs: 1 forward from
-// generation gf, 2 backward from gb, 3 both); see SearchNote.
-constexpr uint32_t NARROW_KEYS = 2048;
-hipError_t launch_narrow(const Problem &P, const SearchArgs &SF, const SearchArgs &SB, int gf,
-                         int gb, int dirs, hipStream_t s);
+                              int gb, hipStream_t s);
 // Small search: both directions in one launch, for at most SMALL_PAIRS pairs of
 // states whose search bitmaps have at most SMALL_SEARCH_BITS bits; writes the
 // whole bitmaps, gens, gens2 and naccessible, and overflow if it gave up.

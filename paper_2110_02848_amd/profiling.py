@@ -46,8 +46,8 @@ CSRC = os.path.join(_HERE, "csrc")
 # Kernel groups.  The search groups every launch of a search generation, in
 # whichever of its forms.
 FAMILIES = {
-    "search": ("k_gen<true>", "k_gen<false>", "k_gen2(", "k_level<true>", "k_level<false>",
-               "k_level2(", "k_narrow(", "k_linear(", "k_small("),
+    "search": ("k_gen<true>", "k_gen<false>", "k_gen2(", "k_level<",
+               "k_level2<", "k_linear(", "k_small("),
     "count": ("k_count(", "k_count_heavy(", "k_count_states(", "k_state_keys("),
     "fill": ("k_fill<true>", "k_fill<false>"),
     # scores of the composed graph (bench.py --task score)

@@ -172,15 +172,15 @@ def _deep(rng, parts, VA):
 
 @pytest.mark.parametrize("order", ORDERS)
 @pytest.mark.parametrize("VA,parts", [
-    (9, [1000]),                        # narrow all the way: more than 128 levels a launch
+    (9, [1000]),                        # a few keys a wavefront all the way
     (16, [300, -200, 300]),             # a key of 200 units
-    (3, [300, (20, 150), 400, (4, 200), 300]),  # levels past a narrow list's end (2,048)
+    (3, [300, (20, 150), 400, (4, 200), 300]),  # hops that reach more than 64 keys
     (3, [1500, -254, 700, -255, 700, -256, 40, -257, 300, -600, 300]),  # heavy keys or just not
     (16, [300, -30, 20, -120, 60, -119, 100, -25, 25])])
-def test_narrow_levels(order, VA, parts):
-    """Deep products with few keys a level: many levels in one launch, handed
-    back to the grid where a level has many keys, many units or a heavy key;
-    and with work lists that overflow."""
+def test_hops(order, VA, parts):
+    """Deep products: wavefronts that go on with the keys they reached, until
+    those are many, have many units or are heavy; and with work lists that
+    overflow."""
     from paper_2110_02848_amd import gpu
     rng = np.random.default_rng(len(parts) + VA)
     A, B = _deep(rng, parts, VA)
@@ -189,11 +189,12 @@ def test_narrow_levels(order, VA, parts):
     assert ref["num_states"] > 2000
     c = _composer(order)
     for k in range(2):
-        check_pair(c, A, B, f"narrow {VA} {parts} {order} call {k}", ref=ref)
-    assert c.stats()["fwd_levels"] > 64
+        check_pair(c, A, B, f"hops {VA} {parts} {order} call {k}", ref=ref)
+    # generations past the 32nd reach many levels each
+    assert 32 < c.stats()["fwd_levels"] < 32 + sum(p for p in parts if isinstance(p, int) and p > 0) // 4
     for cap in (64, 1):
         c.set_option(gpu.FST_OPT_LIST_CAPACITY, cap)
-        check_pair(c, A, B, f"narrow {VA} {parts} {order} lists from {cap}", ref=ref)
+        check_pair(c, A, B, f"hops {VA} {parts} {order} lists from {cap}", ref=ref)
     c.close()
 
 
