@@ -1444,13 +1444,14 @@ __device__ __forceinline__ bool reach(const Problem &P, const Target &t) {
   return (atomicOr(mine + w, bit) & bit) == 0;
 }
 
-// After its batches a wavefront goes on for up to S.hops hops with the keys that
-// it has reached and not yet handed on, while they are at most 64 and have few
-// units: a hop takes its dependent loads (about 2.5 us) where a level takes a
-// launch (7).  Deep searches do so (LEVEL_HOPS; 300 frames o 100 words with loops
-// 3.9 -> 1.3 ms a call, 2,000 frames aligned to 1,000 states with loops 16.7 -> 5.8, 500
-// o 5,000 words 158 -> 12); more units than HOP_UNITS a hop are left to the whole
-// grid (200 o 200 states of 100 arcs: 2.24 ms without that, 2.04 with it).
+// With HOPS a wavefront goes on after its batches, for up to S.hops hops, with
+// the keys that it has reached and not yet handed on, while they are at most 64
+// and have few units: a hop takes its dependent loads (about 2.5 us) where a
+// level takes a launch (7).  Deep searches do so (300 frames o 100 words with
+// loops 3.2 -> 1.4 ms a call, 2,000 frames aligned to 1,000 states with loops 15.6 ->
+// 5.9, 500 o 5,000 words 69 -> 15); more units than HOP_UNITS a hop are left to the
+// whole grid (200 o 200 states of 100 arcs, hops from the start: 2.24 ms without
+// that, 2.04 with it, 2.00 without hops).
 constexpr uint32_t HOP_UNITS = 256;
 
 // Generation g of a level search (one kernel).  Its items are the unit slots
