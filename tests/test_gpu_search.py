@@ -1,8 +1,9 @@
-"""The two kinds of search, level and chain, at the sizes where they change:
-keys with as many moves as a wavefront takes, a workgroup's list holds and a
-generation hands on; B with half of its states single-arc (level search) and
-one more (chain search); frontiers of a few keys and of many.  Every array
-of C and the statistics against the oracle."""
+"""The forms of the search and of the compaction at the sizes where they
+change: keys and units with as many moves as a lane, a wavefront or a
+workgroup's list takes, lists that overflow, B with half of its states
+single-arc (level search) and one more (chain search), few and many accepting
+pairs, deep products, rows of a linear search, the limits of a small one, and
+workspace caps.  Every array of C and the statistics against the oracle."""
 import numpy as np
 import pytest
 
