@@ -139,8 +139,8 @@ FST_API void fst_ctx_destroy(fst_ctx *ctx);
  * arc records (8 bytes per arc); 0 = binary search only) and
  * FST_OPT_CHAIN_DEPTH (default 64: how many newly found keys one search
  * thread may expand depth-first before handing keys to the next frontier,
- * where B is mostly chains; 0 = plain frontier-by-frontier search, as
- * elsewhere).  FST_OPT_COUNT_MOVES = 1 makes
+ * where B is mostly chains; 0 = a search by levels, as elsewhere,
+ * whose deep searches go on inside a launch for 16 levels at most).  FST_OPT_COUNT_MOVES = 1 makes
  * each run also count the moves out of all accessible keys and the
  * predecessor moves of all co-accessible keys (extra passes, reported in
  * fst_stats.generated and fst_stats.generated_backward).
